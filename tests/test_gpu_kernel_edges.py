@@ -32,3 +32,30 @@ def test_token_weight_columns_and_row_slots(bd, tokens, anchors):
     _, ref = oracle.anchor_aggregate(x32, a32, 1.0, want_col_sum=True)
     got = to_host(tw).astype(np.float64)
     assert (np.abs(got - ref) <= 2.0 ** -6 * ref).all(), float((np.abs(got - ref) / ref).max())
+
+
+@pytest.mark.parametrize("inv_tau", [0.0, 5.0, 60.0, 60.5])
+@pytest.mark.parametrize("tokens,anchors,dim", [(1, 1, 64), (63, 127, 64), (64, 128, 128), (65, 129, 64), (129, 130, 192), (700, 260, 128)])
+def test_anchor_softmax_routes(bd, inv_tau, tokens, anchors, dim):
+    """Both routes of the softmax (exponentials straight out of the first product up to inv_tau = 60, logits and a row pass
+    above), with logits over the whole range [-inv_tau, inv_tau]: tokens that are an anchor or its negative, and tokens with a
+    mean ten times their spread.  Rounding Q_A to bf16 moves a logit by inv_tau * 2^-9 / sqrt(3 dim) on average (independent
+    errors against unit rows); four of those and the rounding of weights and results (2^-8) times the largest |x|."""
+    log("softmax routes", inv_tau, tokens, anchors, dim)
+    rng = np.random.default_rng(int(inv_tau) + tokens + anchors)
+    a = rng.standard_normal((anchors, dim)).astype(np.float32)
+    x = rng.standard_normal((2, tokens, dim)).astype(np.float32)
+    x[0, ::3] = a[np.arange(0, tokens, 3) % anchors]
+    x[0, 1::3] = -a[np.arange(1, tokens, 3) % anchors]
+    x[1, ::2] += 10.0
+    x[1, -1] = 0.5                                               # no variance: logit zero
+    x, x32 = wl.quantize(x, "bf16")
+    a, a32 = wl.quantize(a, "bf16")
+    z, tw = bd.civic_anchor_aggregate(to_dev(x), to_dev(a), inv_tau, want_token_weight=True)
+    ref, ref_tw = oracle.anchor_aggregate(x32, a32, inv_tau, want_col_sum=True)
+    rel = 2.0 ** -8 + 4 * inv_tau * 2.0 ** -9 / np.sqrt(3 * dim)
+    got = widen(to_host(z)).astype(np.float64)
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= rel * np.abs(x32).max(), float(np.abs(got - ref).max())
+    # a token's weight is a sum over the anchors of weights that are off by `rel` of themselves, plus their rows' share
+    got_tw = to_host(tw).astype(np.float64)
+    assert (np.abs(got_tw - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all(), float(np.abs(got_tw - ref_tw).max())
