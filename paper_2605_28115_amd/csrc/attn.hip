@@ -28,8 +28,8 @@
 //   - civic_prefill_attn_kv: the workgroup of a KV head's first head block also copies the K/V rows of its
 //     own query rows into the caches (8 threads per row, same address for K and V).
 //
-// fp32 path and head sizes the MFMA path does not cover: a plain fp32 kernel, one wavefront per
-// query row (lanes over keys for Q K^T, lanes over channels for P V).
+// fp32 path and head sizes the bf16 MFMA path does not cover: fp32 matrix instructions, the keys of a 16-row tile split over a
+// workgroup's wavefronts.
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -76,126 +76,235 @@ struct AttnArgs {
     int32_t kv_packed;                    // ragged: keys and values are packed along the token axis like the queries
 };
 
-// ------------------------------------------------------------------------------------ fp32 ALU path
+// ---------------------------------------------------------------------------------- fp32 matrix-core path
+// fp32 inputs, and head sizes the bf16 kernel does not cover: all arithmetic in fp32 on v_mfma_f32_16x16x4f32.  A workgroup of
+// four wavefronts owns 16 query rows of one head and its wavefronts take every fourth tile of 32 keys, each with an online
+// softmax of its own; the four states meet in LDS at the end.  Splitting the keys is what fills the chip: these shapes have few
+// rows (469 rows x 16 heads are 480 workgroups of 16 rows), and one wavefront needs 64 clocks for 16 x 16 x 16 multiply-adds.
+// No operand goes through LDS on its way to the matrix cores.  The contraction of Q K^T may run over the channels in any order
+// that both operands share, and the rows of V^T may be any permutation of the channels, so a lane takes the 16-byte pieces that
+// lie there: channels 16 t + 4 (lane / 16) .. + 3 of key lane % 16 serve four consecutive MFMAs, channels 64 T + 4 (lane % 16) ..
+// + 3 of one key are four rows of V^T.  S^T leaves a lane with four consecutive keys of one query, which is the B operand of
+// O^T += V^T P^T as it stands.  L1 delivers 16 KB per 16 x 16 tile and wavefront, 32 bytes a clock and unit at full MFMA rate.
+// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), REPLACED_US us here.
 template <bool BF16>
-__device__ __forceinline__ float load_elem(const void* p, int64_t i)
+__device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 {
-    if constexpr (BF16) return bf16_bits_to_float(static_cast<const uint16_t*>(p)[i]);
-    else return static_cast<const float*>(p)[i];
+    if constexpr (BF16) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p) + i);
+        return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16),
+                           __uint_as_float(w.y & 0xFFFF0000u));
+    } else {
+        return *reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
+    }
 }
 
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-    return v;
-}
+constexpr int kF32Rows = 16, kF32Keys = 32, kF32Waves = 4;
+static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * kF32Waves * kF32Rows * (64 * nt + 4 + 2); }
 
-template <bool BF16>
-__global__ __launch_bounds__(256) void attn_plain_kernel(AttnArgs a)
+// NT: head_dim rounded up to 64, over 64.
+template <bool BF16, int NT>
+__global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_kernel(AttnArgs a)
 {
-    __shared__ float q_s[4][CIVIC_MAX_HEAD_DIM];
-    __shared__ float p_s[4][kWave];
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
-    const int i = blockIdx.x * 4 + w, h = blockIdx.y, b = blockIdx.z;
-    if (i >= a.seq) return;                                   // no workgroup barrier below
-    const int g = h / (a.n_q_heads / a.n_kv_heads), d = a.head_dim;
-    const int64_t q_off = b * a.qs[0] + i * a.qs[1] + h * a.qs[2];
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+    constexpr int PITCH = 64 * NT + 4;                         // floats per staged row (padded against bank conflicts)
+    float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int row_tile = gridDim.x - 1 - blockIdx.x;           // the heaviest causal tiles first
+    const int h = blockIdx.y, b = blockIdx.z, group = a.n_q_heads / a.n_kv_heads;
+    const int g = h / group, d = a.head_dim, i0 = row_tile * kF32Rows;
+    const int rows = min(kF32Rows, a.seq - i0);
     const int64_t kv_off = b * a.ks[0] + g * a.ks[2];
-    // KV-cache write of this query row's K and V row (the first head of every KV group does it; 16-byte pieces, loads
-    // and stores fly under everything below), so that this path needs no second launch either
-    if (a.k_cache != nullptr && h == g * (a.n_q_heads / a.n_kv_heads)) {
-        constexpr int EPP = BF16 ? 8 : 4;                     // elements per piece
-        const int64_t src = kv_off + static_cast<int64_t>(i) * a.ks[1];
-        const int64_t dst = ((static_cast<int64_t>(b) * a.n_kv_heads + g) * a.s_max + a.pos0 + i) * d;
-        for (int c = lane * EPP; c < d; c += kWave * EPP) {
-            if constexpr (BF16) {
-                *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.k_cache) + dst + c) = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.k) + src + c);
-                *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.v_cache) + dst + c) = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.v) + src + c);
-            } else {
-                *reinterpret_cast<float4*>(static_cast<float*>(a.k_cache) + dst + c) = *reinterpret_cast<const float4*>(static_cast<const float*>(a.k) + src + c);
-                *reinterpret_cast<float4*>(static_cast<float*>(a.v_cache) + dst + c) = *reinterpret_cast<const float4*>(static_cast<const float*>(a.v) + src + c);
-            }
-        }
-    }
-    for (int c = lane; c < d; c += kWave) q_s[w][c] = load_elem<BF16>(a.q, q_off + c) * a.scale;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (a.q_cs) {                                             // rotary embedding: pairs (c, c + d/2) of the query row
-        const float2* cs = a.q_cs + (static_cast<int64_t>(b) * a.seq + i) * (d / 2);
-        for (int c = lane; c < d / 2; c += kWave) {
-            const float x0 = q_s[w][c], x1 = q_s[w][c + d / 2];
-            const float2 t = cs[c];
-            rope_pair(x0, x1, t.x, t.y, q_s[w][c], q_s[w][c + d / 2]);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
 
-    float acc[CIVIC_MAX_HEAD_DIM / kWave];
+    // Q: scaled, rotated if asked, staged as fp32 (rows past the sequence repeat the last one; never written)
+    for (int idx = tid; idx < kF32Rows * (d / 4); idx += kF32Waves * kWave) {
+        const int r = idx / (d / 4), c = (idx - r * (d / 4)) * 4;
+        float4 x = load_quad<BF16>(a.q, b * a.qs[0] + (i0 + min(r, rows - 1)) * a.qs[1] + h * a.qs[2] + c);
+        x.x *= a.scale; x.y *= a.scale; x.z *= a.scale; x.w *= a.scale;
+        *reinterpret_cast<float4*>(f32_lds + r * PITCH + c) = x;
+    }
+    // KV-cache write of the tile's own K and V rows (the first head of every KV group does it)
+    if (a.k_cache != nullptr && h == g * group) {
+        constexpr int EPP = BF16 ? 8 : 4, ESZ = BF16 ? 2 : 4;  // elements per 16-byte piece
+        const int pieces = d / EPP;
+        for (int idx = tid; idx < rows * pieces; idx += kF32Waves * kWave) {
+            const int r = idx / pieces, c = (idx - r * pieces) * EPP;
+            const int64_t src = (kv_off + (i0 + r) * a.ks[1] + c) * ESZ;
+            const int64_t dst = (((static_cast<int64_t>(b) * a.n_kv_heads + g) * a.s_max + a.pos0 + i0 + r) * d + c) * ESZ;
+            *reinterpret_cast<u32x4*>(static_cast<char*>(a.k_cache) + dst) = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.k) + src);
+            *reinterpret_cast<u32x4*>(static_cast<char*>(a.v_cache) + dst) = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.v) + src);
+        }
+    }
+    __syncthreads();
+    if (a.q_cs != nullptr) {                                   // rotary embedding: pairs (c, c + d/2) of a query row
+        for (int idx = tid; idx < kF32Rows * (d / 2); idx += kF32Waves * kWave) {
+            const int r = idx / (d / 2), c = idx - r * (d / 2);
+            const float2 t = a.q_cs[(static_cast<int64_t>(b) * a.seq + i0 + min(r, rows - 1)) * (d / 2) + c];
+            float* q = f32_lds + r * PITCH + c;
+            rope_pair(q[0], q[d / 2], t.x, t.y, q[0], q[d / 2]);
+        }
+        __syncthreads();
+    }
+    float4 qf[4 * NT];                                         // B operand: channels 16 t + 4 kq .. + 3 of query l16
 #pragma unroll
-    for (int t = 0; t < CIVIC_MAX_HEAD_DIM / kWave; ++t) acc[t] = 0.f;
-    float m = -INFINITY, l = 0.f;
-    const int last = a.causal ? i : a.kv_seq - 1;
-    for (int j0 = 0; j0 <= last; j0 += kWave) {
-        const int j = j0 + lane;
-        float z = -INFINITY;
-        if (j <= last) {
-            const int64_t base = kv_off + j * a.ks[1];
-            float dot = 0.f;
-            for (int c = 0; c < d; c += 8) {
-                if constexpr (BF16) {
-                    const uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.k) + base + c);
-                    const uint32_t wds[4] = {raw.x, raw.y, raw.z, raw.w};
+    for (int t = 0; t < 4 * NT; ++t) {
+        const int c = 16 * t + 4 * kq;
+        qf[t] = c < d ? *reinterpret_cast<const float4*>(f32_lds + l16 * PITCH + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();                                           // the area becomes the wavefronts' results
+
+    f32x4 o[NT][4];                                            // O^T: register r of (T, e): channel 64 T + 16 kq + 4 r + e, query l16
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        dot = fmaf(q_s[w][c + 2 * e], __uint_as_float(wds[e] << 16), dot);
-                        dot = fmaf(q_s[w][c + 2 * e + 1], __uint_as_float(wds[e] & 0xFFFF0000u), dot);
+    for (int T = 0; T < NT; ++T)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[T][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;                              // l: the lane's own keys only
+    const int n_keys = a.causal ? i0 + rows : a.kv_seq;        // keys some row of the tile sees
+    const int qi = i0 + l16;
+    // (a key past the last one re-reads it: its score is masked)
+    auto k_row = [&](int key) { return kv_off + static_cast<int64_t>(min(key, n_keys - 1)) * a.ks[1]; };
+    float4 kf[2][4 * NT];
+    auto fetch_k = [&](int key0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int64_t base = k_row(key0 + 16 * s + l16) + 4 * kq;
+#pragma unroll
+            for (int t = 0; t < 4 * NT; ++t)
+                if (16 * t < d) kf[s][t] = load_quad<BF16>(a.k, base + (16 * t + 4 * kq < d ? 16 * t : 0));
+        }
+    };
+    int key0 = w * kF32Keys;
+    if (key0 < n_keys) fetch_k(key0);
+    for (; key0 < n_keys; key0 += kF32Waves * kF32Keys) {
+        // S^T of 32 keys: two sub-tiles of 16, two partial sums each (four independent MFMA chains)
+        f32x4 sc[2][2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) sc[s][0] = sc[s][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4 * NT; ++t)
+            if (16 * t < d) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        const float kv[4] = {kf[s][t].x, kf[s][t].y, kf[s][t].z, kf[s][t].w};
+                        const float qv[4] = {qf[t].x, qf[t].y, qf[t].z, qf[t].w};
+                        sc[s][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], sc[s][e & 1], 0, 0, 0);
                     }
-                } else {
-                    const float4 lo = *reinterpret_cast<const float4*>(static_cast<const float*>(a.k) + base + c);
-                    const float4 hi = *reinterpret_cast<const float4*>(static_cast<const float*>(a.k) + base + c + 4);
-                    dot = fmaf(q_s[w][c], lo.x, dot); dot = fmaf(q_s[w][c + 1], lo.y, dot);
-                    dot = fmaf(q_s[w][c + 2], lo.z, dot); dot = fmaf(q_s[w][c + 3], lo.w, dot);
-                    dot = fmaf(q_s[w][c + 4], hi.x, dot); dot = fmaf(q_s[w][c + 5], hi.y, dot);
-                    dot = fmaf(q_s[w][c + 6], hi.z, dot); dot = fmaf(q_s[w][c + 7], hi.w, dot);
+            }
+        // V rows of this tile, in flight under the softmax: step e of sub-tile s multiplies keys 16 s + 4 kq + e
+        float4 vf[2][4][NT];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t base = k_row(key0 + 16 * s + 4 * kq + e);
+#pragma unroll
+                for (int T = 0; T < NT; ++T) {
+                    const int c = 64 * T + 4 * l16;
+                    vf[s][e][T] = load_quad<BF16>(a.v, base + (c < d ? c : 0));
                 }
             }
-            z = dot;
-        }
-        const float m_new = fmaxf(m, wave_max(z));           // finite: key j0 is always visible
-        const float p = expf(z - m_new);
-        const float alpha = expf(m - m_new);
-        l = l * alpha + wave_sum(p);
-        m = m_new;
-        p_s[w][lane] = p;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int nk = min(kWave, last - j0 + 1);
+        const bool more = key0 + kF32Waves * kF32Keys < n_keys;
+        const int lim = a.causal ? min(qi + 1, n_keys) : n_keys;   // the lane sees keys below lim
+        float p[2][4], m_new = m;
 #pragma unroll
-        for (int t = 0; t < CIVIC_MAX_HEAD_DIM / kWave; ++t) {
-            const int c = lane + t * kWave;
-            if (c < d) {
-                float s = acc[t] * alpha;
-                for (int jj = 0; jj < nk; ++jj)
-                    s = fmaf(p_s[w][jj], load_elem<BF16>(a.v, kv_off + (j0 + jj) * a.ks[1] + c), s);
-                acc[t] = s;
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float z = sc[s][0][r] + sc[s][1][r];
+                p[s][r] = key0 + 16 * s + 4 * kq + r < lim ? z : -INFINITY;
+                m_new = fmaxf(m_new, p[s][r]);
             }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-    const float inv = 1.f / l;
-    const int64_t o_off = b * a.os[0] + i * a.os[1] + h * a.os[2];
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 16, kWave));
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 32, kWave));
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;  // a query that has met no key of this wavefront yet
+        const float alpha = expf(m - m_use);
+        float sum = 0.f;
 #pragma unroll
-    for (int t = 0; t < CIVIC_MAX_HEAD_DIM / kWave; ++t) {
-        const int c = lane + t * kWave;
-        if (c < d) {
-            const float o = acc[t] * inv;
-            if constexpr (BF16) static_cast<__bf16*>(a.out)[o_off + c] = static_cast<__bf16>(o);
-            else static_cast<float*>(a.out)[o_off + c] = o;
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { p[s][r] = expf(p[s][r] - m_use); sum += p[s][r]; }
+        l = fmaf(l, alpha, sum);
+        m = m_new;
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[T][e] *= alpha;
+        if (more) fetch_k(key0 + kF32Waves * kF32Keys);        // the next tile's K rows fly under the second product
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int T = 0; T < NT; ++T) {
+                    const float vv[4] = {vf[s][e][T].x, vf[s][e][T].y, vf[s][e][T].z, vf[s][e][T].w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) o[T][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[c], p[s][e], o[T][c], 0, 0, 0);
+                }
+    }
+    l += __shfl_xor(l, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+
+    // the four states of the tile meet: out = sum_w f_w o_w / sum_w f_w l_w, f_w = exp(m_w - max m)
+    if (kq == 0) { st_m[w * kF32Rows + l16] = m; st_l[w * kF32Rows + l16] = l; }
+#pragma unroll
+    for (int T = 0; T < NT; ++T)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<float4*>(f32_lds + (w * kF32Rows + l16) * PITCH + 64 * T + 16 * kq + 4 * r) =
+                make_float4(o[T][0][r], o[T][1][r], o[T][2][r], o[T][3][r]);
+    __syncthreads();
+    for (int idx = tid; idx < rows * (d / 4); idx += kF32Waves * kWave) {
+        const int r = idx / (d / 4), c = (idx - r * (d / 4)) * 4;
+        float mx = st_m[r];
+#pragma unroll
+        for (int x = 1; x < kF32Waves; ++x) mx = fmaxf(mx, st_m[x * kF32Rows + r]);   // finite: every row sees a key
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        float lt = 0.f;
+#pragma unroll
+        for (int x = 0; x < kF32Waves; ++x) {
+            const float f = expf(st_m[x * kF32Rows + r] - mx);
+            const float4 t = *reinterpret_cast<const float4*>(f32_lds + (x * kF32Rows + r) * PITCH + c);
+            lt = fmaf(f, st_l[x * kF32Rows + r], lt);
+            acc.x = fmaf(f, t.x, acc.x); acc.y = fmaf(f, t.y, acc.y); acc.z = fmaf(f, t.z, acc.z); acc.w = fmaf(f, t.w, acc.w);
+        }
+        const float inv = 1.f / lt;
+        const int64_t at = b * a.os[0] + (i0 + r) * a.os[1] + h * a.os[2] + c;
+        if constexpr (BF16) {
+            const bf16x4 v = {static_cast<__bf16>(acc.x * inv), static_cast<__bf16>(acc.y * inv), static_cast<__bf16>(acc.z * inv),
+                              static_cast<__bf16>(acc.w * inv)};
+            *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(a.out) + at) = v;
+        } else {
+            *reinterpret_cast<float4*>(static_cast<float*>(a.out) + at) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
         }
     }
+}
+
+template <bool BF16, int NT>
+static int launch_f32(const AttnArgs& a, hipStream_t s)
+{
+    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(a.seq) + kF32Rows - 1) / kF32Rows), static_cast<unsigned>(a.n_q_heads),
+                    static_cast<unsigned>(a.batch));
+    constexpr size_t lds = f32_lds_bytes(NT);
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> allowed{0};
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<BF16, NT>), lds, &allowed);
+        if (rc != CIVIC_OK) return rc;
+    }
+    civic::launch((attn_f32_kernel<BF16, NT>), grid, dim3(kF32Waves * kWave), lds, s, a);
+    return check_launch();
+}
+
+template <bool BF16>
+static int launch_f32_for(const AttnArgs& a, hipStream_t s)
+{
+    if (a.head_dim <= 64) return launch_f32<BF16, 1>(a, s);
+    if (a.head_dim <= 128) return launch_f32<BF16, 2>(a, s);
+    if (a.head_dim <= 192) return launch_f32<BF16, 3>(a, s);
+    return launch_f32<BF16, 4>(a, s);
 }
 
 // --------------------------------------------------------------------------------------- MFMA path
@@ -1131,10 +1240,7 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
                 ai.v_cache = static_cast<char*>(v_cache) + cache_at;
             }
         }
-        const dim3 grid(static_cast<unsigned>((ai.seq + 3) / 4), static_cast<unsigned>(n_q_heads), static_cast<unsigned>(ai.batch));
-        if (dtype == CIVIC_BF16) civic::launch((attn_plain_kernel<true>), grid, dim3(256), 0, s, ai);
-        else civic::launch((attn_plain_kernel<false>), grid, dim3(256), 0, s, ai);
-        const int rc = check_launch();
+        const int rc = dtype == CIVIC_BF16 ? launch_f32_for<true>(ai, s) : launch_f32_for<false>(ai, s);
         if (rc != CIVIC_OK) return rc;
     }
     return CIVIC_OK;

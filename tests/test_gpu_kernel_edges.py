@@ -59,3 +59,28 @@ def test_anchor_softmax_routes(bd, inv_tau, tokens, anchors, dim):
     # a token's weight is a sum over the anchors of weights that are off by `rel` of themselves, plus their rows' share
     got_tw = to_host(tw).astype(np.float64)
     assert (np.abs(got_tw - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all(), float(np.abs(got_tw - ref_tw).max())
+
+
+@pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 161])
+@pytest.mark.parametrize("dtype,head_dim", [("fp32", 8), ("fp32", 64), ("fp32", 72), ("fp32", 128), ("fp32", 136), ("fp32", 192),
+                                            ("fp32", 256), ("bf16", 136), ("bf16", 192), ("bf16", 256)])
+def test_fp32_attention_tiles(bd, seq, dtype, head_dim):
+    """The fp32 matrix-core kernel around its 16 rows, 32 keys and four key streams, over its four head sizes and their
+    remainders, with the cache write, masked and unmasked.  fp32 bar of the parity tests (products over 256 channels and sums
+    over a few hundred keys stay at 1e-6); bf16: the output's rounding."""
+    log("fp32 attention", seq, dtype, head_dim)
+    rng = np.random.default_rng(seq * 1000 + head_dim)
+    q, q32 = wl.quantize(rng.standard_normal((2, seq, 4, head_dim)).astype(np.float32), dtype)
+    k, k32 = wl.quantize(rng.standard_normal((2, seq, 2, head_dim)).astype(np.float32), dtype)
+    v, v32 = wl.quantize(rng.standard_normal((2, seq, 2, head_dim)).astype(np.float32), dtype)
+    for causal in (True, False):
+        kc = torch.full((2, 2, seq + 3, head_dim), 7.0, dtype=torch.float32 if dtype == "fp32" else torch.bfloat16, device="cuda")
+        vc = kc.clone()
+        out = bd.civic_prefill_attn_kv(to_dev(q), to_dev(k), to_dev(v), kc, vc, 2, causal)
+        ref = oracle.attention(q32, k32, v32, causal)
+        err = float(np.abs(widen(to_host(out)).astype(np.float64) - ref).max())
+        assert err <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(np.abs(ref).max())), err
+        for cache, x in ((kc, k), (vc, v)):
+            c = to_host(cache)
+            assert (c[:, :, 2:2 + seq] == x.transpose(0, 2, 1, 3)).all()
+            assert (widen(c[:, :, :2]) == 7.0).all() and (widen(c[:, :, 2 + seq:]) == 7.0).all()
