@@ -86,7 +86,7 @@ struct AttnArgs {
 // lie there: channels 16 t + 4 (lane / 16) .. + 3 of key lane % 16 serve four consecutive MFMAs, channels 64 T + 4 (lane % 16) ..
 // + 3 of one key are four rows of V^T.  S^T leaves a lane with four consecutive keys of one query, which is the B operand of
 // O^T += V^T P^T as it stands.  L1 delivers 16 KB per 16 x 16 tile and wavefront, 32 bytes a clock and unit at full MFMA rate.
-// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), REPLACED_US us here.
+// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), 28.8 us here.
 template <bool BF16>
 __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 {
