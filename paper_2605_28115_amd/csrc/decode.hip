@@ -16,6 +16,7 @@
 //   - At the end the 4 * 64 / LPR partial states of the workgroup meet in LDS; the workgroup writes the final
 //     rows (one split) or its (max, sum, unnormalised output) into the workspace, which a second small launch
 //     combines.
+#include <algorithm>
 #include <cmath>
 
 #include "civic_internal.h"
@@ -26,6 +27,9 @@ constexpr int kDecThreads = 256;
 constexpr int kDecWaves = kDecThreads / kWave;
 constexpr int kDecU = 4;                 // cache rows per lane and round
 
+constexpr int kDecFullUnits = 384;       // (sample, KV head, head block) triples that keep the chip busy without a split
+
+constexpr int kDecRaggedRounds = 8;       // rounds per piece of a ragged launch that fills the chip
 constexpr int kDecRaggedItems = 256;     // samples of one launch when every sample has its own context length
 
 struct DecodeArgs {
@@ -35,11 +39,15 @@ struct DecodeArgs {
     int32_t n_ctx, splits, keys_per_split;
     int32_t cpr;                          // 16-byte chunks per cache row
     float scale_log2;                     // softmax scale * log2(e)
-    // civic_decode_attn_ragged: sample b attends to its cache rows [0, ctx_of[b]) (n_ctx is then the longest, which the
-    // splits are laid out for; a split that starts past a sample's rows contributes an empty partial result)
-    int32_t per_item;
-    int32_t ctx_of[kDecRaggedItems];
 };
+
+// civic_decode_attn_ragged: sample b attends to its cache rows [0, ctx[b]), cut into pieces of keys_per_split rows.  (The grid
+// covers the longest sample, workgroups past a sample's pieces leave at once: finding a piece's sample in a table of first
+// pieces instead was 1.3 us slower on 5 samples of 27..216 rows, two dependent reads of the kernel arguments.)
+struct DecodeTable {
+    int32_t ctx[kDecRaggedItems];
+};
+struct NoTable {};
 
 typedef __bf16 dec_bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -73,10 +81,12 @@ __device__ __forceinline__ float row_sum(float v)
     return v;
 }
 
-template <bool BF16, int HG, int LPR>
-__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs a)
+template <bool BF16, int HG, int LPR, typename TABLE>
+__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
+    constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
     constexpr int E = BF16 ? 8 : 4;       // elements per 16-byte chunk
+    constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int RPS = kWave / LPR;      // cache rows per wavefront instruction
     constexpr int SLOTS = kDecWaves * RPS;   // independent softmax streams per workgroup
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
@@ -88,12 +98,16 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
     const bool chunk_live = c < a.cpr;
-    const int split = blockIdx.x;
     const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
-    const int b = blockIdx.z;
     const int d = a.head_dim;
+    const int b = blockIdx.z, split = blockIdx.x;
+    int n_ctx = a.n_ctx, n_splits = a.splits;
+    if constexpr (RAGGED) {
+        n_ctx = t.ctx[b];
+        if (split * a.keys_per_split >= n_ctx) return;
+        n_splits = (n_ctx + a.keys_per_split - 1) / a.keys_per_split;
+    }
     const int k0 = split * a.keys_per_split;
-    const int n_ctx = a.per_item ? a.ctx_of[b] : a.n_ctx;
     const int k1 = min(k0 + a.keys_per_split, n_ctx);
 
     // the lane's chunk of every query head of the pass (heads past the group repeat the last one; never written)
@@ -103,12 +117,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         const int hg = min(hb * HG + hh, a.group - 1);
         const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hg;
         qw[hh] = u32x4{0u, 0u, 0u, 0u};
-        if (chunk_live) qw[hh] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.q) + (row * d + c * E) * (BF16 ? 2 : 4));
+        if (chunk_live) qw[hh] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.q) + (row * d + c * E) * ESZ);
     }
     const int64_t head_row0 = (static_cast<int64_t>(b) * a.n_kv_heads + g) * a.s_max;
-    const char* kbase = static_cast<const char*>(a.kc) + (head_row0 * d + c * E) * (BF16 ? 2 : 4);
-    const char* vbase = static_cast<const char*>(a.vc) + (head_row0 * d + c * E) * (BF16 ? 2 : 4);
-    const int64_t row_bytes = static_cast<int64_t>(d) * (BF16 ? 2 : 4);
+    const char* kbase = static_cast<const char*>(a.kc) + (head_row0 * d + c * E) * ESZ;
+    const char* vbase = static_cast<const char*>(a.vc) + (head_row0 * d + c * E) * ESZ;
+    const int64_t row_bytes = static_cast<int64_t>(d) * ESZ;
 
     float m[HG], l[HG], acc[HG][E];
 #pragma unroll
@@ -210,12 +224,13 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
             o = fmaf(wgt, sm_o[(static_cast<size_t>(sidx) * HG + hh) * d + ch], o);
             lt = fmaf(wgt, sm_l[sidx * HG + hh], lt);
         }
-        const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hg;
-        if (a.splits == 1) {
+        if (n_splits == 1) {
+            const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hg;
             const float val = o / lt;                              // n_ctx >= 1: at least one row was met
             if constexpr (BF16) static_cast<__bf16*>(a.out)[row * d + ch] = static_cast<__bf16>(val);
             else static_cast<float*>(a.out)[row * d + ch] = val;
         } else {
+            const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hg;
             float* dst = a.ws + (row * a.splits + split) * (d + 2);
             if (ch == 0) { dst[0] = mx; dst[1] = lt; }
             dst[2 + ch] = o;
@@ -224,69 +239,105 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 }
 
 // Combines the splits of one (batch item, query head): out = sum_s w_s o_s / sum_s w_s l_s, w_s = 2^(m_s - max m).
-// The weights are prepared once per block (one thread per split, through LDS); the channel sums then run over
-// independent loads, eight splits at a time.
+// Latency-bound (a few KB per workgroup), so everything that can be asked for at once is: a thread's first 8 partial outputs are
+// requested together with the (max, sum) pairs, later ones 8 at a time whether or not 8 are left; beyond 8 splits two groups of
+// threads take every other one.  (With what a division by 8 leaves fetched one by one, 4 x 938 rows took 12.6 us in 15 splits,
+// 10.3 us in 8 of twice the length.)
 constexpr int kDecMaxSplits = 1024;
-template <bool BF16>
-__global__ __launch_bounds__(128) void decode_merge_kernel(const float* __restrict__ ws, void* __restrict__ out, int32_t splits,
-                                                           int32_t d)
+template <bool BF16, int THREADS, int GROUPS, typename TABLE>
+__global__ __launch_bounds__(THREADS) void decode_merge_kernel(const float* __restrict__ ws, void* __restrict__ out, int32_t splits,
+                                                               int32_t d, int32_t n_q_heads, int32_t keys_per_split, TABLE t)
 {
+    constexpr int kWaves = THREADS / kWave, COLS = THREADS / GROUPS;
     __shared__ float wgt[kDecMaxSplits];
-    __shared__ float red[4];
+    __shared__ float red[2 * kWaves];
+    __shared__ float meet[GROUPS > 1 ? THREADS : 1];
     const int64_t row = blockIdx.x;
     const float* src = ws + row * splits * (d + 2);
+    if constexpr (std::is_same<TABLE, DecodeTable>::value) {   // a sample of one piece has its result already
+        splits = (t.ctx[row / n_q_heads] + keys_per_split - 1) / keys_per_split;
+        if (splits == 1) return;
+    }
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
-    // everything the first eight splits contribute is requested at once: the thread's (max, sum) pair and its
-    // channel of their outputs; the weights then need no further trip to memory
-    float o_pre[8];
+    const int x = tid % COLS, y = tid / COLS;                  // the thread's channel and group
+    constexpr int kBatch = 8;
+    float o_pre[kBatch];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) o_pre[j] = (j < splits && tid < d) ? src[j * (d + 2) + 2 + tid] : 0.f;
-    float mloc = -INFINITY;
-    for (int s = tid; s < splits; s += 128) mloc = fmaxf(mloc, src[s * (d + 2)]);
+    for (int j = 0; j < kBatch; ++j) {
+        const int s = y + j * GROUPS;
+        o_pre[j] = (s < splits && x < d) ? src[s * (d + 2) + 2 + x] : 0.f;
+    }
     const float m_own = tid < splits ? src[tid * (d + 2)] : -INFINITY, l_own = tid < splits ? src[tid * (d + 2) + 1] : 0.f;
+    float mloc = m_own;
+    for (int s = tid + THREADS; s < splits; s += THREADS) mloc = fmaxf(mloc, src[s * (d + 2)]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, off, kWave));
     if (lane == 0) red[wv] = mloc;
     __syncthreads();
-    const float mx = fmaxf(red[0], red[1]);
+    float mx = red[0];
+#pragma unroll
+    for (int i = 1; i < kWaves; ++i) mx = fmaxf(mx, red[i]);
     float lsum = 0.f;
-    for (int s = tid; s < splits; s += 128) {
+    for (int s = tid; s < splits; s += THREADS) {
         const float ms = s == tid ? m_own : src[s * (d + 2)];
         const float wt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - mx);
         wgt[s] = wt;
         lsum = fmaf(wt, s == tid ? l_own : src[s * (d + 2) + 1], lsum);
     }
     lsum = wave_sum(lsum);
-    if (lane == 0) red[2 + wv] = lsum;
+    if (lane == 0) red[kWaves + wv] = lsum;
     __syncthreads();
-    const float inv = 1.0f / (red[2] + red[3]);
-    for (int ch = tid; ch < d; ch += 128) {
-        float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        int s = 0;
-        if (ch == tid) {                                           // the first eight are in registers already
+    float l_all = red[kWaves];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = j < splits ? wgt[j] * o_pre[j] : 0.f;
-            s = splits < 8 ? splits : 8;
-        }
-        for (; s + 8 <= splits; s += 8) {
+    for (int i = 1; i < kWaves; ++i) l_all += red[kWaves + i];
+    const float inv = 1.0f / l_all;
+    for (int c0 = 0; c0 < d; c0 += COLS) {
+        const int ch = c0 + x;
+        float o[kBatch];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = fmaf(wgt[s + j], src[(s + j) * (d + 2) + 2 + ch], o[j]);
+        for (int j = 0; j < kBatch; ++j) {
+            const int s = y + j * GROUPS;
+            const float v = c0 == 0 ? o_pre[j] : (s < splits && ch < d) ? src[s * (d + 2) + 2 + ch] : 0.f;
+            o[j] = s < splits ? wgt[s] * v : 0.f;
         }
-        for (; s < splits; ++s) o[0] = fmaf(wgt[s], src[s * (d + 2) + 2 + ch], o[0]);
-        const float val = (((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]))) * inv;
-        if constexpr (BF16) static_cast<__bf16*>(out)[row * d + ch] = static_cast<__bf16>(val);
-        else static_cast<float*>(out)[row * d + ch] = val;
+        for (int s0 = kBatch * GROUPS; s0 < splits; s0 += kBatch * GROUPS) {
+            float v[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int s = s0 + y + j * GROUPS;
+                v[j] = (s < splits && ch < d) ? src[s * (d + 2) + 2 + ch] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int s = s0 + y + j * GROUPS;
+                if (s < splits) o[j] = fmaf(wgt[s], v[j], o[j]);
+            }
+        }
+        float val = ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
+        if constexpr (GROUPS > 1) {                            // (one pass over the channels then: d <= COLS)
+            meet[tid] = val;
+            __syncthreads();
+            if (y > 0) return;
+#pragma unroll
+            for (int i = 1; i < GROUPS; ++i) val += meet[i * COLS + x];
+        }
+        if (ch < d) {
+            if constexpr (BF16) static_cast<__bf16*>(out)[row * d + ch] = static_cast<__bf16>(val * inv);
+            else static_cast<float*>(out)[row * d + ch] = val * inv;
+        }
     }
 }
 
 // Block shape and split count for these sizes (shared by the launch and the workspace query).
 struct DecodePlan {
-    int hg, lpr, head_blocks, splits, keys_per_split;
+    int hg, lpr, head_blocks, round_keys;
+    int32_t splits, keys_per_split;      // of one context length for all samples
+    int32_t max_splits;                  // per sample, at most: what the workspace is sized for
     size_t ws_bytes, lds_bytes;
 };
 
 static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t n_ctx,
-                       DecodePlan* p)
+                       DecodePlan* p, bool ragged = false)
 {
     const int esz = dtype_size(dtype);
     if (!esz || batch < 0 || n_q_heads <= 0 || n_kv_heads <= 0 || head_dim <= 0 || n_ctx < 0) return CIVIC_ERR_INVALID_ARG;
@@ -300,57 +351,103 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     if (static_cast<int64_t>(n_kv_heads) * p->head_blocks > 65535) return CIVIC_ERR_UNSUPPORTED;
     p->lpr = 8;
     while (p->lpr < cpr) p->lpr *= 2;
-    // About four workgroups per compute unit, and no split shorter than one round of the workgroup.
     const int64_t units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * p->head_blocks;
     const int64_t round_keys = static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU;
-    int64_t splits = (1024 + units - 1) / units;
-    const int64_t max_splits = (n_ctx + round_keys - 1) / round_keys;
-    if (splits > max_splits) splits = max_splits;
-    if (splits < 1) splits = 1;
-    if (splits > kDecMaxSplits) splits = kDecMaxSplits;
-    int64_t kps = (n_ctx + splits - 1) / splits;
-    kps = (kps + round_keys - 1) / round_keys * round_keys;     // whole rounds
-    if (kps < round_keys) kps = round_keys;
-    splits = n_ctx > 0 ? (n_ctx + kps - 1) / kps : 1;
-    p->splits = static_cast<int>(splits);
-    p->keys_per_split = static_cast<int>(kps);
-    p->ws_bytes = splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * splits * (head_dim + 2) : 0;
+    p->round_keys = static_cast<int>(round_keys);
+    // whole rounds per split, no split shorter than one round of the workgroup
+    auto cut = [&](int64_t splits, int32_t* n, int32_t* keys) {
+        const int64_t max_splits = (n_ctx + round_keys - 1) / round_keys;
+        splits = std::max<int64_t>(std::min(std::min(splits, max_splits), static_cast<int64_t>(kDecMaxSplits)), 1);
+        int64_t kps = (n_ctx + splits - 1) / splits;
+        kps = std::max((kps + round_keys - 1) / round_keys * round_keys, round_keys);
+        *n = static_cast<int32_t>(n_ctx > 0 ? (n_ctx + kps - 1) / kps : 1);
+        *keys = static_cast<int32_t>(kps);
+    };
+    // what the workspace has room for: about four workgroups per compute unit, and the pieces of a ragged launch
+    int32_t unused;
+    cut((1024 + units - 1) / units, &p->max_splits, &unused);
+    const int64_t ragged_keys = kDecRaggedRounds * round_keys;
+    if (ragged) p->max_splits = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p->max_splits, (n_ctx + ragged_keys - 1) / ragged_keys), kDecMaxSplits));
+    // What is launched: nothing to combine once the (item, KV head) pairs fill the chip by themselves (64 x 938 rows, 8 KV
+    // heads: one split 45.5 us, two 52; 64 x 3584: 153 against 172); otherwise two workgroups per unit in at most 8 splits, which
+    // one trip of the combining launch reads (16 x 938: 4 splits 18.7 us, 8 splits 20.8; 4 x 938: 8 splits 10.3 us, 15 splits
+    // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).
+    cut(units >= kDecFullUnits ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), &p->splits, &p->keys_per_split);
+    p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
     const int slots = kDecWaves * (kWave / p->lpr);
     p->lds_bytes = sizeof(float) * static_cast<size_t>(slots) * p->hg * (head_dim + 2);
     return CIVIC_OK;
 }
 
-template <bool BF16, int HG>
-static int launch_decode_lpr(const DecodeArgs& a, const DecodePlan& p, hipStream_t s)
+// How samples of different context lengths are cut into pieces of one length (the last piece of a sample is what is left):
+//   - not at all when the pairs fill the chip and the longest context is within 7 rounds of the average: its workgroups then
+//     outlast the others by less than a second launch costs (96 samples of 100..800 rows: 41 us, 45-50 us cut)
+//   - else into the shortest pieces that make at most 512 workgroups, or pieces of 8 rounds if that takes longer ones
+//     (64 samples of 117..3584 rows, 8 KV heads: 97 us; 118 us in pieces of 2 rounds, 103 of 16, 129 uncut; the same grid for
+//     every sample, laid out for the longest context, took 133 us, half of its workgroups with nothing to do)
+// Never more pieces per sample than the workspace holds, max_splits.
+static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, DecodePlan* p)
+{
+    int64_t rows = 0;
+    int32_t longest = 0;
+    for (int32_t i = 0; i < batch; ++i) { rows += ctx_of[i]; longest = std::max(longest, ctx_of[i]); }
+    const int64_t per_sample = units / batch;
+    int64_t kps = p->round_keys;
+    if (units >= kDecFullUnits && longest - rows / batch <= 7 * p->round_keys) kps = longest;
+    for (;; kps += p->round_keys) {                           // (ends: a piece as long as the longest context is one per sample)
+        const int64_t most = (longest + kps - 1) / kps;
+        if (most > p->max_splits) continue;
+        int64_t pieces = 0;
+        for (int32_t i = 0; i < batch; ++i) pieces += (ctx_of[i] + kps - 1) / kps;
+        if (pieces * per_sample <= 512 || kps >= kDecRaggedRounds * p->round_keys) break;
+    }
+    p->keys_per_split = static_cast<int32_t>(kps);
+    p->splits = static_cast<int32_t>((longest + kps - 1) / kps);
+}
+
+template <bool BF16, int HG, int LPR, typename TABLE>
+static int launch_decode_kernel(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
     const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
-#define CIVIC_DEC_CASE(L)                                                                                              \
-    case L: {                                                                                                          \
-        if (p.lds_bytes > 64 * 1024) {                                                                                 \
-            static std::atomic<uint64_t> allowed{0};                                                                   \
-            const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(decode_partial_kernel<BF16, HG, L>), p.lds_bytes, &allowed); \
-            if (rc != CIVIC_OK) return rc;                                                                             \
-        }                                                                                                              \
-        civic::launch((decode_partial_kernel<BF16, HG, L>), grid, dim3(kDecThreads), p.lds_bytes, s, a);          \
-        break;                                                                                                         \
+    if (p.lds_bytes > 64 * 1024) {
+        static std::atomic<uint64_t> allowed{0};
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(decode_partial_kernel<BF16, HG, LPR, TABLE>), p.lds_bytes, &allowed);
+        if (rc != CIVIC_OK) return rc;
     }
-    switch (p.lpr) {
-        CIVIC_DEC_CASE(8) CIVIC_DEC_CASE(16) CIVIC_DEC_CASE(32) CIVIC_DEC_CASE(64)
-        default: return CIVIC_ERR_UNSUPPORTED;
-    }
-#undef CIVIC_DEC_CASE
+    civic::launch((decode_partial_kernel<BF16, HG, LPR, TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
     return check_launch();
 }
 
-template <bool BF16>
-static int launch_decode(const DecodeArgs& a, const DecodePlan& p, hipStream_t s)
+template <bool BF16, int HG, typename TABLE>
+static int launch_decode_lpr(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
-    switch (p.hg) {
-        case 1: return launch_decode_lpr<BF16, 1>(a, p, s);
-        case 2: return launch_decode_lpr<BF16, 2>(a, p, s);
-        case 4: return launch_decode_lpr<BF16, 4>(a, p, s);
-        default: return launch_decode_lpr<BF16, 8>(a, p, s);
+    switch (p.lpr) {
+        case 8: return launch_decode_kernel<BF16, HG, 8>(a, t, p, s);
+        case 16: return launch_decode_kernel<BF16, HG, 16>(a, t, p, s);
+        case 32: return launch_decode_kernel<BF16, HG, 32>(a, t, p, s);
+        default: return launch_decode_kernel<BF16, HG, 64>(a, t, p, s);
     }
+}
+
+template <bool BF16, typename TABLE>
+static int launch_decode(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
+{
+    int rc;
+    switch (p.hg) {
+        case 1: rc = launch_decode_lpr<BF16, 1>(a, t, p, s); break;
+        case 2: rc = launch_decode_lpr<BF16, 2>(a, t, p, s); break;
+        case 4: rc = launch_decode_lpr<BF16, 4>(a, t, p, s); break;
+        default: rc = launch_decode_lpr<BF16, 8>(a, t, p, s);
+    }
+    if (rc != CIVIC_OK || p.splits == 1) return rc;
+    const dim3 rows(static_cast<unsigned>(a.batch) * static_cast<unsigned>(a.n_q_heads));
+#define CIVIC_DEC_MERGE(T, G) civic::launch((decode_merge_kernel<BF16, T, G, TABLE>), rows, dim3(T), 0, s, a.ws, a.out, p.splits, a.head_dim, \
+                                            a.n_q_heads, p.keys_per_split, t)
+    if (p.splits <= 8) CIVIC_DEC_MERGE(128, 1);
+    else if (a.head_dim <= 128) CIVIC_DEC_MERGE(256, 2);
+    else CIVIC_DEC_MERGE(256, 1);
+#undef CIVIC_DEC_MERGE
+    return check_launch();
 }
 
 // Everything but the choice of the workspace: `ws` holds at least plan.ws_bytes when the plan splits.
@@ -359,8 +456,6 @@ static int decode_attn(const void* q, const void* k_cache, const void* v_cache, 
                        float softmax_scale, const DecodePlan& p, float* ws, void* stream, const int32_t* ctx_of = nullptr)
 {
     DecodeArgs a;
-    a.per_item = ctx_of ? 1 : 0;
-    for (int i = 0; i < kDecRaggedItems; ++i) a.ctx_of[i] = ctx_of && i < batch ? ctx_of[i] : 0;
     a.q = q; a.kc = k_cache; a.vc = v_cache; a.out = out; a.ws = ws;
     a.s_max = s_max;
     a.batch = batch; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
@@ -370,22 +465,24 @@ static int decode_attn(const void* q, const void* k_cache, const void* v_cache, 
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt(static_cast<float>(head_dim));
     a.scale_log2 = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = dtype == CIVIC_BF16 ? launch_decode<true>(a, p, s) : launch_decode<false>(a, p, s);
-    if (rc != CIVIC_OK || p.splits == 1) return rc;
-    const unsigned rows = static_cast<unsigned>(batch) * static_cast<unsigned>(n_q_heads);
-    if (dtype == CIVIC_BF16) civic::launch((decode_merge_kernel<true>), dim3(rows), dim3(128), 0, s, ws, out, p.splits, head_dim);
-    else civic::launch((decode_merge_kernel<false>), dim3(rows), dim3(128), 0, s, ws, out, p.splits, head_dim);
-    return check_launch();
+    if (!ctx_of) return dtype == CIVIC_BF16 ? launch_decode<true>(a, NoTable{}, p, s) : launch_decode<false>(a, NoTable{}, p, s);
+    DecodePlan pr = p;
+    cut_ragged(ctx_of, batch, static_cast<int64_t>(batch) * n_kv_heads * p.head_blocks, &pr);
+    a.keys_per_split = pr.keys_per_split;
+    a.splits = pr.splits;
+    DecodeTable t;
+    for (int i = 0; i < kDecRaggedItems; ++i) t.ctx[i] = i < batch ? ctx_of[i] : 0;
+    return dtype == CIVIC_BF16 ? launch_decode<true>(a, t, pr, s) : launch_decode<false>(a, t, pr, s);
 }
 
 // Argument checks shared by the two entry points (all before any HIP call).  CIVIC_OK with *nothing = true when
 // there is no row to compute.
 static int decode_check(const void* q, const void* k_cache, const void* v_cache, void* out, int dtype, int32_t batch,
                         int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t s_max, int64_t n_ctx,
-                        float softmax_scale, DecodePlan* p, bool* nothing)
+                        float softmax_scale, DecodePlan* p, bool* nothing, bool ragged = false)
 {
     *nothing = false;
-    const int rc = decode_plan(dtype, batch, n_q_heads, n_kv_heads, head_dim, n_ctx, p);
+    const int rc = decode_plan(dtype, batch, n_q_heads, n_kv_heads, head_dim, n_ctx, p, ragged);
     if (rc != CIVIC_OK) return rc;
     if (s_max < 0 || n_ctx > s_max) return CIVIC_ERR_INVALID_ARG;
     if (!(softmax_scale >= 0.f) || std::isinf(softmax_scale)) return CIVIC_ERR_INVALID_ARG;
@@ -498,7 +595,7 @@ extern "C" size_t civic_decode_attn_ragged_workspace_bytes(int dtype, int32_t ba
         const int32_t nb = batch - b0 < kDecRaggedItems ? batch - b0 : kDecRaggedItems;
         const int64_t longest = longest_ctx(n_ctx, b0, nb, INT32_MAX);
         DecodePlan p;
-        if (longest < 0 || decode_plan(dtype, nb, n_q_heads, n_kv_heads, head_dim, longest, &p) != CIVIC_OK) return 0;
+        if (longest < 0 || decode_plan(dtype, nb, n_q_heads, n_kv_heads, head_dim, longest, &p, true) != CIVIC_OK) return 0;
         need = p.ws_bytes > need ? p.ws_bytes : need;
     }
     return need;
@@ -513,8 +610,8 @@ extern "C" int civic_decode_attn_ragged(const void* q, const void* k_cache, cons
     const int esz = dtype_size(dtype);
     if (!esz || batch < 0) return CIVIC_ERR_INVALID_ARG;
     if (batch > 0 && !n_ctx) return CIVIC_ERR_INVALID_ARG;
-    // Groups of up to kDecRaggedItems samples, each the two launches of civic_decode_attn laid out for the group's
-    // longest context; every group is checked before the first launch.
+    // Groups of up to kDecRaggedItems samples, each the launch or two of civic_decode_attn over pieces of one length; every
+    // group is checked before the first launch.
     for (int pass = 0; pass < 2; ++pass)
         for (int32_t b0 = 0; b0 < batch; b0 += kDecRaggedItems) {
             const int32_t nb = batch - b0 < kDecRaggedItems ? batch - b0 : kDecRaggedItems;
@@ -528,7 +625,7 @@ extern "C" int civic_decode_attn_ragged(const void* q, const void* k_cache, cons
             DecodePlan p;
             bool nothing = false;
             int rc = decode_check(q ? qb : nullptr, k_cache ? kb : nullptr, v_cache ? vb : nullptr, out ? ob : nullptr, dtype, nb, n_q_heads,
-                                  n_kv_heads, head_dim, s_max, longest, softmax_scale, &p, &nothing);
+                                  n_kv_heads, head_dim, s_max, longest, softmax_scale, &p, &nothing, true);
             if (rc != CIVIC_OK) return rc;
             if (p.ws_bytes > 0 && (!workspace || workspace_bytes < p.ws_bytes || !aligned16(workspace))) return CIVIC_ERR_WORKSPACE;
             if (pass == 0 || nothing) continue;

@@ -84,3 +84,28 @@ def test_fp32_attention_tiles(bd, seq, dtype, head_dim):
             c = to_host(cache)
             assert (c[:, :, 2:2 + seq] == x.transpose(0, 2, 1, 3)).all()
             assert (widen(c[:, :, :2]) == 7.0).all() and (widen(c[:, :, 2 + seq:]) == 7.0).all()
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx", [
+    (1, 8, 8, 128, [1]), (1, 4, 1, 128, [64]), (1, 4, 1, 128, [65]), (3, 4, 2, 128, [1, 700, 64]), (2, 8, 1, 64, [9000, 3]),
+    (60, 8, 8, 64, [40 + 7 * i for i in range(60)]), (52, 8, 8, 32, [1 + 97 * i for i in range(52)]), (48, 16, 8, 128, [300] * 48),
+    (260, 2, 2, 64, [1 + i % 130 for i in range(260)])])
+def test_decode_cuts(bd, batch, hq, hkv, d, ctx):
+    """How a decode launch is cut: one piece per sample and several, samples of one piece beside samples of many, pieces that
+    end on a round and one row past it, more than one group of samples, up to 8 splits and more.  Rows past a context are NaN.
+    bf16 rounds the result once (2^-9 of it; weighted means of values that are bf16 already)."""
+    log("decode cuts", batch, hq, hkv, d, max(ctx))
+    rng = np.random.default_rng(sum(ctx))
+    q = wl.quantize(rng.standard_normal((batch, hq, d)).astype(np.float32), "bf16")[0]
+    kc, vc = (wl.quantize(rng.standard_normal((batch, hkv, max(ctx) + 1, d)).astype(np.float32), "bf16")[0] for _ in range(2))
+    for b, n in enumerate(ctx):
+        kc[b, :, n:] = 0x7FC0
+        vc[b, :, n:] = 0x7FC0
+    outs = [bd.civic_decode_attn_ragged(to_dev(q), to_dev(kc), to_dev(vc), ctx)]
+    if len(set(ctx)) == 1:
+        outs.append(bd.civic_decode_attn(to_dev(q), to_dev(kc), to_dev(vc), ctx[0]))
+    for out in outs:
+        got = widen(to_host(out)).astype(np.float64)
+        for b, n in enumerate(ctx):
+            ref = oracle.decode_attention(widen(q[b:b + 1]), widen(kc[b:b + 1]), widen(vc[b:b + 1]), n)
+            assert np.abs(got[b] - ref[0]).max() <= 2.0 ** -8 * max(1.0, float(np.abs(ref).max())), (b, n)
