@@ -445,9 +445,9 @@ int civic_decode_attn_noalloc(const void* q, const void* k_cache, const void* v_
                               int64_t n_ctx, float softmax_scale, void* stream);
 
 /* civic_decode_attn over caches that hold a different number of rows per sample (what civic_prefill_attn_ragged
- * leaves): sample b attends to rows [0, n_ctx[b]) of k_cache[b], v_cache[b].  Groups of up to 256 samples, each the two
- * launches of civic_decode_attn laid out for the group's longest context (a split that starts past a sample's rows
- * contributes nothing); results equal civic_decode_attn on every sample alone up to the order of the partial sums.
+ * leaves): sample b attends to rows [0, n_ctx[b]) of k_cache[b], v_cache[b].  Groups of up to 256 samples, each one or two
+ * launches over pieces of the contexts (all samples cut at the same length, workgroups past a sample's rows do
+ * nothing); results equal civic_decode_attn on every sample alone up to the order of the partial sums.
  *   n_ctx      host [batch] int32, every entry in [1, s_max]
  *   workspace  civic_decode_attn_ragged_workspace_bytes(same sizes), 16-byte aligned (shared by the groups in turn)
  * Everything else as civic_decode_attn; every group is checked before the first launch. */

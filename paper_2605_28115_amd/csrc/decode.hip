@@ -13,7 +13,7 @@
 //     summed over the row's lanes; every lane of the row then holds the row's logits.
 //   - Each (wavefront, row slot) runs its own online softmax over the rows it meets: no barrier and no LDS in
 //     the loop.  The lane keeps the 8 output channels of its chunk for every head in fp32.
-//   - At the end the 4 * 64 / LPR partial states of the workgroup meet in LDS; the workgroup writes the final
+//   - At the end the partial states of a wavefront meet in registers and those of the workgroup in LDS; it writes the final
 //     rows (one split) or its (max, sum, unnormalised output) into the workspace, which a second small launch
 //     combines.
 #include <algorithm>
@@ -29,7 +29,8 @@ constexpr int kDecU = 4;                 // cache rows per lane and round
 
 constexpr int kDecFullUnits = 384;       // (sample, KV head, head block) triples that keep the chip busy without a split
 
-constexpr int kDecRaggedRounds = 8;       // rounds per piece of a ragged launch that fills the chip
+constexpr int kDecRaggedKeys = 512;       // rows per piece of a ragged launch that fills the chip
+constexpr int kDecTailKeys = 448;         // rows by which the longest context may exceed the average before it is cut
 constexpr int kDecRaggedItems = 256;     // samples of one launch when every sample has its own context length
 
 struct DecodeArgs {
@@ -50,6 +51,8 @@ struct DecodeTable {
 struct NoTable {};
 
 typedef __bf16 dec_bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 dec_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float dec_f32x4 __attribute__((ext_vector_type(4)));
 
 // acc + a.lo * b.lo + a.hi * b.hi for two words of packed bf16 pairs.  (The words come in as scalars on purpose:
 // a bit cast applied directly to an element of a vector variable reads the vector's first element.)
@@ -81,6 +84,25 @@ __device__ __forceinline__ float row_sum(float v)
     return v;
 }
 
+// Sum and maximum over the 64 / LPR row slots of a wavefront (lanes LPR apart), in every lane: a rotation inside rows of 16
+// lanes, then swaps of rows and of half-waves (v_permlane16_swap, v_permlane32_swap).  No LDS.
+template <int LPR, typename OP>
+__device__ __forceinline__ float over_slots(float v, OP op)
+{
+    if constexpr (LPR <= 8) v = op(v, dpp_moved<0x128>(v));    // row_ror:8
+    if constexpr (LPR <= 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    }
+    if constexpr (LPR <= 32) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    }
+    return v;
+}
+template <int LPR> __device__ __forceinline__ float slots_sum(float v) { return over_slots<LPR>(v, [](float x, float y) { return x + y; }); }
+template <int LPR> __device__ __forceinline__ float slots_max(float v) { return over_slots<LPR>(v, [](float x, float y) { return fmaxf(x, y); }); }
+
 template <bool BF16, int HG, int LPR, typename TABLE>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
@@ -90,10 +112,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     constexpr int RPS = kWave / LPR;      // cache rows per wavefront instruction
     constexpr int SLOTS = kDecWaves * RPS;   // independent softmax streams per workgroup
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
-    // [SLOTS][HG] maxima, [SLOTS][HG] sums, [SLOTS][HG][d] outputs
-    float* sm_m = dec_lds;
-    float* sm_l = dec_lds + SLOTS * HG;
-    float* sm_o = dec_lds + 2 * SLOTS * HG;
+    // of every wavefront: [HG][d] outputs, [HG] maxima, [HG] sums
+    float* sm_o = dec_lds;
+    float* sm_m = dec_lds + kDecWaves * HG * a.head_dim;
+    float* sm_l = sm_m + kDecWaves * HG;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
@@ -197,32 +219,42 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         }
     }
 
-    // the workgroup's SLOTS states meet in LDS
-    const int slot = w * RPS + r;
+    // The row slots of a wavefront meet in registers (every lane of a chunk then holds the wavefront's state) ...
 #pragma unroll
     for (int hh = 0; hh < HG; ++hh) {
-        if (c == 0) { sm_m[slot * HG + hh] = m[hh]; sm_l[slot * HG + hh] = l[hh]; }
-        if (chunk_live) {
-            float* dst = sm_o + (static_cast<size_t>(slot) * HG + hh) * d + c * E;
+        const float mw = slots_max<LPR>(m[hh]);
+        const float f = m[hh] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[hh] - mw);
+        m[hh] = mw;
+        l[hh] = slots_sum<LPR>(l[hh] * f);
 #pragma unroll
-            for (int e = 0; e < E; ++e) dst[e] = acc[hh][e];
-        }
+        for (int e = 0; e < E; ++e) acc[hh][e] = slots_sum<LPR>(acc[hh][e] * f);
     }
+    // ... and the wavefronts in LDS; slot r writes the heads r, r + RPS, ...
+#pragma unroll
+    for (int hh = 0; hh < HG; ++hh)
+        if (hh % RPS == r) {
+            if (c == 0) { sm_m[w * HG + hh] = m[hh]; sm_l[w * HG + hh] = l[hh]; }
+            if (chunk_live) {
+                float4* dst = reinterpret_cast<float4*>(sm_o + (w * HG + hh) * d + c * E);
+#pragma unroll
+                for (int e = 0; e < E; e += 4) dst[e / 4] = make_float4(acc[hh][e], acc[hh][e + 1], acc[hh][e + 2], acc[hh][e + 3]);
+            }
+        }
     __syncthreads();
     for (int i = tid; i < HG * d; i += kDecThreads) {
         const int hh = i / d, ch = i - hh * d;
         const int hg = hb * HG + hh;
         if (hg >= a.group) continue;
-        float mx = -INFINITY;
+        float mx = sm_m[hh];
 #pragma unroll
-        for (int sidx = 0; sidx < SLOTS; ++sidx) mx = fmaxf(mx, sm_m[sidx * HG + hh]);
+        for (int x = 1; x < kDecWaves; ++x) mx = fmaxf(mx, sm_m[x * HG + hh]);
         float o = 0.f, lt = 0.f;
 #pragma unroll
-        for (int sidx = 0; sidx < SLOTS; ++sidx) {
-            const float ms = sm_m[sidx * HG + hh];
+        for (int x = 0; x < kDecWaves; ++x) {
+            const float ms = sm_m[x * HG + hh];
             const float wgt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - mx);
-            o = fmaf(wgt, sm_o[(static_cast<size_t>(sidx) * HG + hh) * d + ch], o);
-            lt = fmaf(wgt, sm_l[sidx * HG + hh], lt);
+            o = fmaf(wgt, sm_o[(x * HG + hh) * d + ch], o);
+            lt = fmaf(wgt, sm_l[x * HG + hh], lt);
         }
         if (n_splits == 1) {
             const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hg;
@@ -234,6 +266,191 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
             float* dst = a.ws + (row * a.splits + split) * (d + 2);
             if (ch == 0) { dst[0] = mx; dst[1] = lt; }
             dst[2 + ch] = o;
+        }
+    }
+}
+
+// The same for bf16 caches with head_dim <= 128 and at least three query heads per KV head, on the matrix cores: all query heads of a KV head (up to 16 per pass) are the
+// columns of one MFMA tile, so the vector work per cache row no longer grows with the heads, and a workgroup that has little
+// context gets through it in a few memory latencies.  (Per 64 rows of 128 channels and four heads the kernel above needs about
+// 450 vector instructions a wavefront and 1.4 us; bound by that, not by memory, whenever a workgroup runs alone.)
+//   - A wavefront takes 32 keys a step.  K rows are read as they lie (lane = key, 16-byte chunks of the row in any order that Q
+//     shares) and are the first operand of v_mfma_f32_16x16x32_bf16.  The two 16-key tiles of a step hold keys 8 a + r and
+//     8 a + 4 + r in row 4 a + r: a lane then owns the logits of 8 consecutive keys of one head, which is the second operand
+//     of O^T += V^T P^T as it stands.
+//   - V^T rows may be any permutation of the channels: a lane reads channels 8 i .. 8 i + 7 of its 8 keys, 16 bytes each, and
+//     v_perm gathers 8 operands (channel 8 i + j of the 8 keys) out of them: no LDS, no transposed copy.
+//   - Weights enter as two bf16 terms (16 mantissa bits): rounding them to one would cost precision the fp32 sums have.
+//   - Each wavefront runs its own online softmax; the states meet in LDS at the end.
+// Against the kernel above (us): 64 x 938 rows, 32 / 8 heads 45.5 -> 42.3 (5.8 TB/s); 64 x 3584 154 -> 142 (6.6 TB/s); 4 x 938
+// 10.6 -> 9.1; 16 x 2000 with 64 / 8 heads 43.8 -> 28.6.  With one or two heads the vector work is less than the gathering here
+// (32 x 1000, 16 / 16 heads of 64: 22.5 there, 26.0 here; 8 x 1280, 16 / 8 heads 12.8, 13.8), so those stay there.
+template <typename TABLE>
+__global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs a, TABLE tab)
+{
+    constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
+    constexpr int WAVES = kDecWaves, THREADS = kDecThreads, KT = 4;      // K chunks of 32 channels
+    extern __shared__ __attribute__((aligned(16))) float dec_lds[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
+    const int b = blockIdx.z, split = blockIdx.x, d = a.head_dim;
+    int n_ctx = a.n_ctx, n_splits = a.splits;
+    if constexpr (RAGGED) {
+        n_ctx = tab.ctx[b];
+        if (split * a.keys_per_split >= n_ctx) return;
+        n_splits = (n_ctx + a.keys_per_split - 1) / a.keys_per_split;
+    }
+    const int k0 = split * a.keys_per_split;
+    const int k1 = min(k0 + a.keys_per_split, n_ctx);
+    const int heads = min(16, a.group - 16 * hb);              // query heads of this pass
+    // of every wavefront: [heads][d] outputs, [heads] maxima, [heads] sums
+    float* const sm_o = dec_lds;
+    float* const sm_m = dec_lds + WAVES * heads * d;
+    float* const sm_l = sm_m + WAVES * heads;
+
+    const uint32_t row_bytes = static_cast<uint32_t>(d) * 2;
+    const int64_t first_row = (static_cast<int64_t>(b) * a.n_kv_heads + g) * a.s_max + k0;
+    const char* const kbase = static_cast<const char*>(a.kc) + first_row * row_bytes;
+    const char* const vbase = static_cast<const char*>(a.vc) + first_row * row_bytes;
+    const int n_keys = k1 - k0;
+
+    // Loads of the 32 keys from `key` on (relative to k0); keys past the end re-read the last one (their logits are masked)
+    auto fetch = [&](int key, u32x4 (&kf)[2][KT], u32x4 (&vf)[8]) __attribute__((always_inline)) {
+        const int last = n_keys - 1 - key;
+        const char* const kb = kbase + static_cast<int64_t>(key) * row_bytes;
+        const char* const vb = vbase + static_cast<int64_t>(key) * row_bytes;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t off = static_cast<uint32_t>(min(8 * (l16 >> 2) + 4 * s + (l16 & 3), last)) * row_bytes;
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+                if (32 * t < d) kf[s][t] = load_streaming(reinterpret_cast<const u32x4*>(kb + (off + (32 * t + 8 * kq < d ? 64 * t + 16 * kq : 0))));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t off = static_cast<uint32_t>(min(8 * kq + e, last)) * row_bytes + (8 * l16 < d ? l16 * 16 : 0);
+            vf[e] = load_streaming(reinterpret_cast<const u32x4*>(vb + off));
+        }
+    };
+    u32x4 kf[2][2][KT], vf[2][8];
+    const int step = 32 * WAVES;
+    int key = 32 * w;
+    if (key < n_keys) fetch(key, kf[0], vf[0]);
+    // Q^T: channels 32 t + 8 kq .. + 7 of head l16
+    dec_bf16x8 qf[KT];
+    {
+        const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hb * 16 + min(l16, heads - 1);
+        const char* qb = static_cast<const char*>(a.q) + row * row_bytes + kq * 16;
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            u32x4 x = u32x4{0u, 0u, 0u, 0u};
+            if (32 * t + 8 * kq < d) x = *reinterpret_cast<const u32x4*>(qb + 64 * t);
+            qf[t] = __builtin_bit_cast(dec_bf16x8, x);
+        }
+    }
+    dec_f32x4 o[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;                              // of head l16; l: the lane's own keys
+
+    auto compute = [&](int at, u32x4 (&ck)[2][KT], u32x4 (&cv)[8]) __attribute__((always_inline)) {
+        dec_f32x4 s[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            s[x] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+                if (32 * t < d) s[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, ck[x][t]), qf[t], s[x], 0, 0, 0);
+        }
+        const int lim = n_keys - at - 8 * kq;                   // the lane's keys below this exist
+        float p[8], m_new = m;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            p[e] = e < lim ? s[e >> 2][e & 3] * a.scale_log2 : -INFINITY;
+            m_new = fmaxf(m_new, p[e]);
+        }
+        m_new = slots_max<16>(m_new);                           // finite: the step's first key exists
+        if (__any(m_new != m)) {
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);   // exp2(-inf) = 0 on the first step
+            l *= alpha;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[j][r] *= alpha;
+            m = m_new;
+        }
+        u32x4 ph, pl;                                           // the weights' leading and trailing bf16 terms
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p0 = __builtin_amdgcn_exp2f(p[2 * e] - m), p1 = __builtin_amdgcn_exp2f(p[2 * e + 1] - m);
+            l += p0 + p1;
+            const dec_bf16x2 hi = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
+            const uint32_t hw = __builtin_bit_cast(uint32_t, hi);
+            const dec_bf16x2 lo = {static_cast<__bf16>(p0 - __uint_as_float(hw << 16)), static_cast<__bf16>(p1 - __uint_as_float(hw & 0xFFFF0000u))};
+            ph[e] = hw;
+            pl[e] = __builtin_bit_cast(uint32_t, lo);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            u32x4 v;                                            // channel 8 l16 + j of keys 8 kq .. + 7
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w0 = cv[2 * e][j >> 1], w1 = cv[2 * e + 1][j >> 1];
+                v[e] = __builtin_amdgcn_perm(w1, w0, (j & 1) ? 0x07060302u : 0x05040100u);
+            }
+            o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, v), __builtin_bit_cast(dec_bf16x8, ph), o[j], 0, 0, 0);
+            o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, v), __builtin_bit_cast(dec_bf16x8, pl), o[j], 0, 0, 0);
+        }
+    };
+    // two steps per pass of the loop: the other buffer is in flight while one is computed
+    while (key < n_keys) {
+        if (key + step < n_keys) fetch(key + step, kf[1], vf[1]);
+        compute(key, kf[0], vf[0]);
+        key += step;
+        if (key >= n_keys) break;
+        if (key + step < n_keys) fetch(key + step, kf[0], vf[0]);
+        compute(key, kf[1], vf[1]);
+        key += step;
+    }
+    l = slots_sum<16>(l);
+
+    if (l16 < heads) {                                          // register r of o[j]: channel 8 (4 kq + r) + j
+        if (kq == 0) { sm_m[w * heads + l16] = m; sm_l[w * heads + l16] = l; }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int ch = 8 * (4 * kq + r);
+            if (ch < d) {
+                float4* dst = reinterpret_cast<float4*>(sm_o + (w * heads + l16) * d + ch);
+                dst[0] = make_float4(o[0][r], o[1][r], o[2][r], o[3][r]);
+                dst[1] = make_float4(o[4][r], o[5][r], o[6][r], o[7][r]);
+            }
+        }
+    }
+    __syncthreads();
+    const int half_d = d / 2;
+    for (int i = tid; i < heads * half_d; i += THREADS) {
+        const int hh = i / half_d, ch = (i - hh * half_d) * 2;
+        float mx = sm_m[hh];
+#pragma unroll
+        for (int x = 1; x < WAVES; ++x) mx = fmaxf(mx, sm_m[x * heads + hh]);
+        float o0 = 0.f, o1 = 0.f, lt = 0.f;
+#pragma unroll
+        for (int x = 0; x < WAVES; ++x) {                       // (a wavefront without keys: m = -inf, weight 0)
+            const float f = __builtin_amdgcn_exp2f(sm_m[x * heads + hh] - mx);
+            const float2 v = *reinterpret_cast<const float2*>(sm_o + (x * heads + hh) * d + ch);
+            o0 = fmaf(f, v.x, o0); o1 = fmaf(f, v.y, o1);
+            lt = fmaf(f, sm_l[x * heads + hh], lt);
+        }
+        const int64_t row = static_cast<int64_t>(b) * a.n_q_heads + g * a.group + hb * 16 + hh;
+        if (n_splits == 1) {
+            const float inv = 1.0f / lt;
+            const dec_bf16x2 val = {static_cast<__bf16>(o0 * inv), static_cast<__bf16>(o1 * inv)};
+            *reinterpret_cast<dec_bf16x2*>(static_cast<__bf16*>(a.out) + row * d + ch) = val;
+        } else {
+            float* dst = a.ws + (row * a.splits + split) * (d + 2);
+            if (ch == 0) *reinterpret_cast<float2*>(dst) = make_float2(mx, lt);
+            *reinterpret_cast<float2*>(dst + 2 + ch) = make_float2(o0, o1);
         }
     }
 }
@@ -330,7 +547,9 @@ __global__ __launch_bounds__(THREADS) void decode_merge_kernel(const float* __re
 
 // Block shape and split count for these sizes (shared by the launch and the workspace query).
 struct DecodePlan {
+    bool mfma;
     int hg, lpr, head_blocks, round_keys;
+    int whole_keys;                      // contexts up to this are not cut
     int32_t splits, keys_per_split;      // of one context length for all samples
     int32_t max_splits;                  // per sample, at most: what the workspace is sized for
     size_t ws_bytes, lds_bytes;
@@ -346,13 +565,15 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     const int cpr = head_dim * esz / 16;
     if (cpr > kWave || n_ctx > INT32_MAX || batch > 65535) return CIVIC_ERR_UNSUPPORTED;
     const int group = n_q_heads / n_kv_heads;
-    p->hg = group >= 8 ? 8 : group > 2 ? 4 : group;             // 1, 2, 4 or 8 query heads per pass
+    p->mfma = dtype == CIVIC_BF16 && head_dim <= 128 && group > 2;
+    p->hg = p->mfma ? std::min(group, 16) : group >= 8 ? 8 : group > 2 ? 4 : group;   // query heads per pass (1, 2, 4 or 8 without MFMA)
     p->head_blocks = (group + p->hg - 1) / p->hg;
     if (static_cast<int64_t>(n_kv_heads) * p->head_blocks > 65535) return CIVIC_ERR_UNSUPPORTED;
     p->lpr = 8;
     while (p->lpr < cpr) p->lpr *= 2;
     const int64_t units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * p->head_blocks;
-    const int64_t round_keys = static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU;
+    const int64_t round_keys = p->mfma ? 32 * kDecWaves : static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU;
+    const int64_t whole_keys = round_keys * (p->mfma ? 2 : 4);
     p->round_keys = static_cast<int>(round_keys);
     // whole rounds per split, no split shorter than one round of the workgroup
     auto cut = [&](int64_t splits, int32_t* n, int32_t* keys) {
@@ -363,16 +584,19 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
         *n = static_cast<int32_t>(n_ctx > 0 ? (n_ctx + kps - 1) / kps : 1);
         *keys = static_cast<int32_t>(kps);
     };
-    // what the workspace has room for: about four workgroups per compute unit, and the pieces of a ragged launch
+    // what the workspace has room for: about four workgroups per compute unit with at most 8 heads in each, and the pieces of a
+    // ragged launch
     int32_t unused;
-    cut((1024 + units - 1) / units, &p->max_splits, &unused);
-    const int64_t ragged_keys = kDecRaggedRounds * round_keys;
-    if (ragged) p->max_splits = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p->max_splits, (n_ctx + ragged_keys - 1) / ragged_keys), kDecMaxSplits));
+    const int64_t room_units = p->hg > 8 ? 2 * units : units;
+    cut((1024 + room_units - 1) / room_units, &p->max_splits, &unused);
+    if (ragged) p->max_splits = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p->max_splits, (n_ctx + kDecRaggedKeys - 1) / kDecRaggedKeys), kDecMaxSplits));
     // What is launched: nothing to combine once the (item, KV head) pairs fill the chip by themselves (64 x 938 rows, 8 KV
     // heads: one split 45.5 us, two 52; 64 x 3584: 153 against 172); otherwise two workgroups per unit in at most 8 splits, which
     // one trip of the combining launch reads (16 x 938: 4 splits 18.7 us, 8 splits 20.8; 4 x 938: 8 splits 10.3 us, 15 splits
-    // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).
-    cut(units >= kDecFullUnits ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), &p->splits, &p->keys_per_split);
+    // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).  Nor is a context cut that one
+    // workgroup gets through before a second launch would have started (1 x 256 rows, 32 / 8 heads: 7.0 us whole, 7.8 in two).
+    p->whole_keys = static_cast<int>(whole_keys);
+    cut(units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
     const int slots = kDecWaves * (kWave / p->lpr);
     p->lds_bytes = sizeof(float) * static_cast<size_t>(slots) * p->hg * (head_dim + 2);
@@ -380,10 +604,10 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
 }
 
 // How samples of different context lengths are cut into pieces of one length (the last piece of a sample is what is left):
-//   - not at all when the pairs fill the chip and the longest context is within 7 rounds of the average: its workgroups then
+//   - not at all when the pairs fill the chip and the longest context is within 448 rows of the average: its workgroups then
 //     outlast the others by less than a second launch costs (96 samples of 100..800 rows: 41 us, 45-50 us cut)
-//   - else into the shortest pieces that make at most 512 workgroups, or pieces of 8 rounds if that takes longer ones
-//     (64 samples of 117..3584 rows, 8 KV heads: 97 us; 118 us in pieces of 2 rounds, 103 of 16, 129 uncut; the same grid for
+//   - else into the shortest pieces that make at most 512 workgroups, or pieces of 512 rows if that takes longer ones
+//     (64 samples of 117..3584 rows, 8 KV heads: 97 us; 118 us in pieces of 128, 103 of 1024, 129 uncut; the same grid for
 //     every sample, laid out for the longest context, took 133 us, half of its workgroups with nothing to do)
 // Never more pieces per sample than the workspace holds, max_splits.
 static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, DecodePlan* p)
@@ -393,13 +617,13 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, Deco
     for (int32_t i = 0; i < batch; ++i) { rows += ctx_of[i]; longest = std::max(longest, ctx_of[i]); }
     const int64_t per_sample = units / batch;
     int64_t kps = p->round_keys;
-    if (units >= kDecFullUnits && longest - rows / batch <= 7 * p->round_keys) kps = longest;
+    if (longest <= p->whole_keys || (units >= kDecFullUnits && longest - rows / batch <= kDecTailKeys)) kps = longest;
     for (;; kps += p->round_keys) {                           // (ends: a piece as long as the longest context is one per sample)
         const int64_t most = (longest + kps - 1) / kps;
         if (most > p->max_splits) continue;
         int64_t pieces = 0;
         for (int32_t i = 0; i < batch; ++i) pieces += (ctx_of[i] + kps - 1) / kps;
-        if (pieces * per_sample <= 512 || kps >= kDecRaggedRounds * p->round_keys) break;
+        if (pieces * per_sample <= 512 || kps >= kDecRaggedKeys) break;
     }
     p->keys_per_split = static_cast<int32_t>(kps);
     p->splits = static_cast<int32_t>((longest + kps - 1) / kps);
@@ -433,7 +657,11 @@ template <bool BF16, typename TABLE>
 static int launch_decode(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
     int rc;
-    switch (p.hg) {
+    if (p.mfma) {
+        const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
+        civic::launch((decode_mfma_kernel<TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
+        rc = check_launch();
+    } else switch (p.hg) {
         case 1: rc = launch_decode_lpr<BF16, 1>(a, t, p, s); break;
         case 2: rc = launch_decode_lpr<BF16, 2>(a, t, p, s); break;
         case 4: rc = launch_decode_lpr<BF16, 4>(a, t, p, s); break;

@@ -89,7 +89,10 @@ def test_fp32_attention_tiles(bd, seq, dtype, head_dim):
 @pytest.mark.parametrize("batch,hq,hkv,d,ctx", [
     (1, 8, 8, 128, [1]), (1, 4, 1, 128, [64]), (1, 4, 1, 128, [65]), (3, 4, 2, 128, [1, 700, 64]), (2, 8, 1, 64, [9000, 3]),
     (60, 8, 8, 64, [40 + 7 * i for i in range(60)]), (52, 8, 8, 32, [1 + 97 * i for i in range(52)]), (48, 16, 8, 128, [300] * 48),
-    (260, 2, 2, 64, [1 + i % 130 for i in range(260)])])
+    (260, 2, 2, 64, [1 + i % 130 for i in range(260)]),
+    # the matrix-core kernel: 3 to 17 heads per KV head, channels that are not whole chunks, steps of 32 and rounds of 128
+    (2, 6, 2, 40, [31, 33]), (1, 16, 1, 128, [257]), (1, 17, 1, 128, [129]), (2, 33, 1, 72, [127, 600]), (3, 12, 4, 96, [1, 128, 385]),
+    (70, 18, 6, 8, [20 * i + 1 for i in range(70)])])
 def test_decode_cuts(bd, batch, hq, hkv, d, ctx):
     """How a decode launch is cut: one piece per sample and several, samples of one piece beside samples of many, pieces that
     end on a round and one row past it, more than one group of samples, up to 8 splits and more.  Rows past a context are NaN.
