@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -62,8 +63,7 @@ lib.civic_ragged_offsets.argtypes = [C.c_int32, _P, C.POINTER(Grid), _P, _P, _P]
 lib.civic_compact_prefill_ragged.restype = C.c_int
 lib.civic_compact_prefill_ragged.argtypes = [_P, C.c_int, C.c_int32, _P, C.c_int32, _P, C.POINTER(Grid), _P, _P, C.c_float, _P, _P, _P, _P, _P, _P]
 lib.civic_prefill_attn_ragged.restype = C.c_int
-lib.civic_prefill_attn_ragged.argtypes = [_P, _P, _P, _P, C.c_int, C.c_int32, _P, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int64),
-                                          C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.c_int32, C.c_float, _P, _P, C.c_int64, C.c_int64, _P]
+lib.civic_prefill_attn_ragged.argtypes = [_P, _P, _P, _P, C.c_int, C.c_int32, _P, C.c_int32, C.c_int32, C.c_int32, _P, _P, _P, C.c_int32, C.c_float, _P, _P, C.c_int64, C.c_int64, _P]
 lib.civic_decode_attn_ragged_workspace_bytes.restype = C.c_size_t
 lib.civic_decode_attn_ragged_workspace_bytes.argtypes = [C.c_int, C.c_int32, _P, C.c_int32, C.c_int32, C.c_int32]
 lib.civic_decode_attn_ragged.restype = C.c_int
@@ -140,6 +140,8 @@ lib.civic_prefill_attn_rope.argtypes = [_P, _P, _P, _P, C.c_int, C.c_int32, C.c_
                                         _P, _P, _P, C.c_int32, C.c_float, _P, _P]
 
 
+# Marshalling costs as much as a short kernel (a step of the path makes two or three calls of 5-20 arguments), so these helpers
+# do as little as they can: plain integers for pointers (the argument types convert them), no stream object.
 def _check(call: str, rc: int) -> None:
     if rc != CIVIC_OK:
         raise CivicError(call, rc, lib.civic_last_hip_error() if rc == ERR_HIP else 0)
@@ -149,32 +151,56 @@ def make_grid(grid) -> Grid:
     return grid if isinstance(grid, Grid) else Grid(*[int(x) for x in grid])
 
 
+_DTYPE_CODES = {torch.float32: CIVIC_F32, torch.bfloat16: CIVIC_BF16}
+_DTYPE_BYTES = {torch.float32: 4, torch.bfloat16: 2}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return CIVIC_F32
-    if t.dtype == torch.bfloat16:
-        return CIVIC_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
-def _stream(stream) -> C.c_void_p:
+_current_device = torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # the handle alone, without a Stream object around it
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _dev(t: Optional[torch.Tensor]) -> C.c_void_p:
+def _dev(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
-        return C.c_void_p(0)
+        return None
     if not t.is_cuda:
         raise ValueError("device tensor expected")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _strides3(t: torch.Tensor):
-    if t.dim() != 4 or t.stride(3) != 1:
+def _host(a: np.ndarray) -> int:
+    """Address of a host array that the caller keeps alive over the call."""
+    return a.__array_interface__["data"][0]
+
+
+def _host_i64(values) -> np.ndarray:
+    if isinstance(values, np.ndarray) and values.dtype == np.int64 and values.flags.c_contiguous:
+        return values
+    return np.ascontiguousarray(np.asarray(values, dtype=np.int64))
+
+
+_pack_i64x3 = struct.Struct("3q").pack       # three int64 as bytes, which a pointer argument takes as they are
+
+
+def _strides3(t: torch.Tensor) -> bytes:
+    s = t.stride()
+    if len(s) != 4 or s[3] != 1:
         raise ValueError("expected [batch, seq, heads, head_dim] with contiguous head_dim")
-    return (C.c_int64 * 3)(t.stride(0), t.stride(1), t.stride(2))
+    return _pack_i64x3(s[0], s[1], s[2])
 
 
 # ------------------------------------------------------------------------------ host functions
@@ -203,7 +229,7 @@ def civic_compact_workspace_bytes(batch: int, seq_len: int) -> int:
 def civic_anchor_normalize(anchor: np.ndarray) -> np.ndarray:
     a = np.ascontiguousarray(anchor, dtype=np.float32)
     q = np.empty_like(a)
-    _check("civic_anchor_normalize", lib.civic_anchor_normalize(C.c_void_p(a.ctypes.data), a.shape[0], C.c_void_p(q.ctypes.data)))
+    _check("civic_anchor_normalize", lib.civic_anchor_normalize(_host(a), a.shape[0], _host(q)))
     return q
 
 
@@ -229,13 +255,13 @@ def civic_score_visual(hidden: torch.Tensor, grid, frame_start: Sequence[int], a
     if hidden.dim() != 3 or not hidden.is_contiguous():
         raise ValueError("hidden must be contiguous [batch, S, dim]")
     batch, seq_len, dim = hidden.shape
-    fs = np.ascontiguousarray(np.asarray(frame_start, dtype=np.int64))
+    fs = _host_i64(frame_start)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     if scores is None:
         scores = torch.empty((batch, g.n_visual), dtype=torch.float32, device=hidden.device)
     _check("civic_score_visual", lib.civic_score_visual(_dev(hidden), _dtype_code(hidden), batch, seq_len, dim, C.byref(g),
-                                                        C.c_void_p(fs.ctypes.data), _dev(anchor_q), float(inv_tau),
+                                                        _host(fs), _dev(anchor_q), float(inv_tau),
                                                         _dev(scores), _stream(stream)))
     return scores
 
@@ -252,7 +278,7 @@ def civic_select(scores: torch.Tensor, grid, kept_idx: Optional[torch.Tensor] = 
         kept_idx = torch.empty((batch, k), dtype=torch.int32, device=scores.device)
     if keep_flags is None and want_flags:
         keep_flags = torch.empty((batch, g.n_visual), dtype=torch.uint8, device=scores.device)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check("civic_select", lib.civic_select(_dev(scores), batch, C.byref(g), _dev(kept_idx), _dev(keep_flags),
                                             _dev(workspace), ws_bytes, _stream(stream)))
     return kept_idx, keep_flags
@@ -270,7 +296,7 @@ def civic_compact(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, frame_start
         raise ValueError("pos_ids must be int32 [3, batch, S] and kept_idx int32")
     n_kept = kept_idx.shape[1]
     seq_c = seq_len - g.n_visual + n_kept
-    fs = np.ascontiguousarray(np.asarray(frame_start, dtype=np.int64))
+    fs = _host_i64(frame_start)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     if hidden_c is None:
@@ -279,9 +305,9 @@ def civic_compact(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, frame_start
         pos_c = torch.empty((3, batch, seq_c), dtype=torch.int32, device=hidden.device)
     if src_idx is None:
         src_idx = torch.empty((batch, seq_c), dtype=torch.int32, device=hidden.device)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check("civic_compact", lib.civic_compact(_dev(hidden), _dtype_code(hidden), dim, _dev(pos_ids), batch, seq_len,
-                                              C.byref(g), C.c_void_p(fs.ctypes.data), _dev(kept_idx), n_kept,
+                                              C.byref(g), _host(fs), _dev(kept_idx), n_kept,
                                               _dev(hidden_c), _dev(pos_c), _dev(src_idx), _dev(workspace), ws_bytes,
                                               _stream(stream)))
     return hidden_c, pos_c, src_idx
@@ -300,7 +326,7 @@ def civic_compact_prefill(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, fra
         raise ValueError("pos_ids must be int32 [3, batch, S]")
     n_kept = civic_kept_count(grid)
     seq_c = seq_len - g.n_visual + n_kept
-    fs = np.ascontiguousarray(np.asarray(frame_start, dtype=np.int64))
+    fs = _host_i64(frame_start)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     dev = hidden.device
@@ -315,7 +341,7 @@ def civic_compact_prefill(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, fra
     if src_idx is None:
         src_idx = torch.empty((batch, seq_c), dtype=torch.int32, device=dev)
     _check("civic_compact_prefill", lib.civic_compact_prefill(
-        _dev(hidden), _dtype_code(hidden), batch, seq_len, dim, _dev(pos_ids), C.byref(g), C.c_void_p(fs.ctypes.data),
+        _dev(hidden), _dtype_code(hidden), batch, seq_len, dim, _dev(pos_ids), C.byref(g), _host(fs),
         _dev(anchor_q), float(inv_tau), _dev(scores), _dev(kept_idx), _dev(hidden_c), _dev(pos_c), _dev(src_idx),
         None, 0, _stream(stream)))
     return scores, kept_idx, hidden_c, pos_c, src_idx
@@ -326,8 +352,8 @@ def civic_ragged_offsets(seq_lens: Sequence[int], grids):
     gs = (Grid * len(grids))(*[make_grid(g) for g in grids])
     seq = np.concatenate([[0], np.cumsum(np.asarray(seq_lens, dtype=np.int64))]).astype(np.int64)
     vis, kept, comp = (np.zeros(len(grids) + 1, dtype=np.int64) for _ in range(3))
-    _check("civic_ragged_offsets", lib.civic_ragged_offsets(len(grids), C.c_void_p(seq.ctypes.data), gs, C.c_void_p(vis.ctypes.data),
-                                                            C.c_void_p(kept.ctypes.data), C.c_void_p(comp.ctypes.data)))
+    _check("civic_ragged_offsets", lib.civic_ragged_offsets(len(grids), _host(seq), gs, _host(vis),
+                                                            _host(kept), _host(comp)))
     return seq, vis, kept, comp
 
 
@@ -353,7 +379,7 @@ def civic_compact_prefill_ragged(hidden: torch.Tensor, pos_ids: torch.Tensor, se
     pos_c = torch.empty((3, int(comp[-1])), dtype=torch.int32, device=dev)
     src_idx = torch.empty(int(comp[-1]), dtype=torch.int32, device=dev)
     _check("civic_compact_prefill_ragged", lib.civic_compact_prefill_ragged(
-        _dev(hidden), _dtype_code(hidden), len(grids), C.c_void_p(seq.ctypes.data), dim, _dev(pos_ids), gs, C.c_void_p(fs.ctypes.data),
+        _dev(hidden), _dtype_code(hidden), len(grids), _host(seq), dim, _dev(pos_ids), gs, _host(fs),
         _dev(anchor_q), float(inv_tau), _dev(scores), _dev(kept_idx), _dev(hidden_c), _dev(pos_c), _dev(src_idx), _stream(stream)))
     return scores, kept_idx, hidden_c, pos_c, src_idx
 
@@ -366,7 +392,7 @@ def civic_prefill_attn_ragged(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
     caches [batch, H_kv, s_max, d] every sample's K and V rows are written to its own cache rows from pos0."""
     if k.shape != v.shape or k.stride() != v.stride() or q.dtype != k.dtype or q.dim() != 3 or k.dim() != 3 or q.stride(2) != 1 or k.stride(2) != 1:
         raise ValueError("q [total, H_q, d]; k and v [total, H_kv, d] of one shape, strides and dtype")
-    off = np.ascontiguousarray(np.asarray(row_offsets, dtype=np.int64))
+    off = _host_i64(row_offsets)
     batch = off.size - 1
     total, hq, d = q.shape
     if out is None:
@@ -377,11 +403,11 @@ def civic_prefill_attn_ragged(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
                 tuple(k_cache.shape[:2]) != (batch, k.shape[1]) or k_cache.shape[3] != d:
             raise ValueError("k_cache and v_cache must be contiguous [batch, H_kv, s_max, d]")
         s_max = k_cache.shape[2]
-    qs = (C.c_int64 * 3)(0, q.stride(0), q.stride(1))
-    ks = (C.c_int64 * 3)(0, k.stride(0), k.stride(1))
-    os_ = (C.c_int64 * 3)(0, out.stride(0), out.stride(1))
+    qs = _pack_i64x3(0, q.stride(0), q.stride(1))
+    ks = _pack_i64x3(0, k.stride(0), k.stride(1))
+    os_ = _pack_i64x3(0, out.stride(0), out.stride(1))
     _check("civic_prefill_attn_ragged", lib.civic_prefill_attn_ragged(
-        _dev(q), _dev(k), _dev(v), _dev(out), _dtype_code(q), batch, C.c_void_p(off.ctypes.data), hq, k.shape[1], d, qs, ks, os_,
+        _dev(q), _dev(k), _dev(v), _dev(out), _dtype_code(q), batch, _host(off), hq, k.shape[1], d, qs, ks, os_,
         int(bool(causal)), float(softmax_scale), _dev(k_cache), _dev(v_cache), s_max, int(pos0), _stream(stream)))
     return out
 
@@ -461,7 +487,7 @@ def civic_decode_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Ten
     if workspace is None:
         need = civic_decode_attn_workspace_bytes(q.dtype, batch, hq, hkv, d, n_ctx)
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device) if need else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check("civic_decode_attn", lib.civic_decode_attn(_dev(q), _dev(k_cache), _dev(v_cache), _dev(out), _dtype_code(q), batch,
                                                       hq, hkv, d, s_max, int(n_ctx), float(softmax_scale), _dev(workspace),
                                                       ws_bytes, _stream(stream)))
@@ -472,16 +498,17 @@ def civic_decode_attn_ragged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: to
                              out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """The decode step with one context length per sample: q [batch, H_q, d] over rows [0, n_ctx[b]) of the caches."""
     batch, hq, hkv, d, s_max = _decode_shapes(q, k_cache, v_cache)
-    ctx = np.ascontiguousarray(np.asarray(n_ctx, dtype=np.int32))
+    ctx = n_ctx if isinstance(n_ctx, np.ndarray) and n_ctx.dtype == np.int32 and n_ctx.flags.c_contiguous else \
+        np.ascontiguousarray(np.asarray(n_ctx, dtype=np.int32))
     if ctx.shape != (batch,):
         raise ValueError("one context length per sample")
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:
-        need = int(lib.civic_decode_attn_ragged_workspace_bytes(_dtype_code(q), batch, C.c_void_p(ctx.ctypes.data), hq, hkv, d))
+        need = int(lib.civic_decode_attn_ragged_workspace_bytes(_dtype_code(q), batch, _host(ctx), hq, hkv, d))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     _check("civic_decode_attn_ragged", lib.civic_decode_attn_ragged(
-        _dev(q), _dev(k_cache), _dev(v_cache), _dev(out), _dtype_code(q), batch, C.c_void_p(ctx.ctypes.data), hq, hkv, d, s_max,
+        _dev(q), _dev(k_cache), _dev(v_cache), _dev(out), _dtype_code(q), batch, _host(ctx), hq, hkv, d, s_max,
         float(softmax_scale), _dev(workspace), workspace.numel(), _stream(stream)))
     return out
 
@@ -508,8 +535,8 @@ def civic_mrope_table(pos_ids: torch.Tensor, axis_of_pair, inv_freq, cos_sin: Op
     _, batch, seq = pos_ids.shape
     if cos_sin is None:
         cos_sin = torch.empty((batch, seq, ax.shape[0], 2), dtype=torch.float32, device=pos_ids.device)
-    _check("civic_mrope_table", lib.civic_mrope_table(_dev(pos_ids), batch, seq, ax.shape[0], C.c_void_p(ax.ctypes.data),
-                                                      C.c_void_p(fr.ctypes.data), _dev(cos_sin), _stream(stream)))
+    _check("civic_mrope_table", lib.civic_mrope_table(_dev(pos_ids), batch, seq, ax.shape[0], _host(ax),
+                                                      _host(fr), _dev(cos_sin), _stream(stream)))
     return cos_sin
 
 
@@ -621,7 +648,7 @@ def civic_kv_compress_ragged(k: torch.Tensor, v: torch.Tensor, r: torch.Tensor, 
     rows [row_offsets[b], row_offsets[b+1]) -> k_c, v_c [batch, S, ...]."""
     if k.shape != v.shape or not k.is_contiguous() or not v.is_contiguous() or not r.is_contiguous() or r.dtype != torch.float32:
         raise ValueError("k and v must be contiguous of one shape, r contiguous fp32 [total, S]")
-    off = np.ascontiguousarray(np.asarray(row_offsets, dtype=np.int64))
+    off = _host_i64(row_offsets)
     batch = off.size - 1
     width = int(np.prod(k.shape[1:]))
     s_mem = r.shape[1]
@@ -632,10 +659,10 @@ def civic_kv_compress_ragged(k: torch.Tensor, v: torch.Tensor, r: torch.Tensor, 
     if v_c is None:
         v_c = torch.empty_like(k_c)
     if workspace is None:
-        need = int(lib.civic_kv_compress_ragged_workspace_bytes(batch, C.c_void_p(off.ctypes.data), s_mem, width))
+        need = int(lib.civic_kv_compress_ragged_workspace_bytes(batch, _host(off), s_mem, width))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=k.device)
     _check("civic_kv_compress_ragged", lib.civic_kv_compress_ragged(
-        _dev(k), _dev(v), _dtype_code(k), _dev(r), batch, C.c_void_p(off.ctypes.data), s_mem, width, _dev(k_c), _dev(v_c),
+        _dev(k), _dev(v), _dtype_code(k), _dev(r), batch, _host(off), s_mem, width, _dev(k_c), _dev(v_c),
         _dev(workspace), workspace.numel(), _stream(stream)))
     return k_c, v_c
 
@@ -645,14 +672,14 @@ def civic_cross_attn_ragged(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, q
     """q [total, H_q, d] packed (item b owning rows [q_offsets[b], q_offsets[b+1])) over k, v [batch, n_kv, H_kv, d]."""
     if k.shape != v.shape or k.stride() != v.stride() or q.dtype != k.dtype or q.dim() != 3 or q.stride(2) != 1:
         raise ValueError("q [total, H_q, d]; k and v [batch, n_kv, H_kv, d] of one shape, strides and dtype")
-    off = np.ascontiguousarray(np.asarray(q_offsets, dtype=np.int64))
+    off = _host_i64(q_offsets)
     batch = off.size - 1
     total, hq, d = q.shape
     if out is None:
         out = torch.empty((total, hq, d), dtype=q.dtype, device=q.device)
-    qs = (C.c_int64 * 3)(0, q.stride(0), q.stride(1))
-    os_ = (C.c_int64 * 3)(0, out.stride(0), out.stride(1))
+    qs = _pack_i64x3(0, q.stride(0), q.stride(1))
+    os_ = _pack_i64x3(0, out.stride(0), out.stride(1))
     _check("civic_cross_attn_ragged", lib.civic_cross_attn_ragged(
-        _dev(q), _dev(k), _dev(v), _dev(out), _dtype_code(q), batch, C.c_void_p(off.ctypes.data), k.shape[1], hq, k.shape[2], d,
+        _dev(q), _dev(k), _dev(v), _dev(out), _dtype_code(q), batch, _host(off), k.shape[1], hq, k.shape[2], d,
         qs, _strides3(k), os_, float(softmax_scale), _stream(stream)))
     return out
