@@ -100,7 +100,7 @@ __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 }
 
 constexpr int kF32Rows = 16, kF32Keys = 32, kF32Waves = 4;
-static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * kF32Waves * kF32Rows * (64 * nt + 4 + 2); }
+static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * (kF32Waves * kF32Rows * (64 * nt + 4 + 2) + kF32Waves); }
 
 // NT: head_dim rounded up to 64, over 64.
 template <bool BF16, int NT>
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
     constexpr int PITCH = 64 * NT + 4;                         // floats per staged row (padded against bank conflicts)
-    float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows;
+    float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows, * const st_odd = st_l + kF32Waves * kF32Rows;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int l16 = lane & 15, kq = lane >> 4;
     const int row_tile = gridDim.x - 1 - blockIdx.x;           // the heaviest causal tiles first
@@ -163,6 +163,11 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
     float m = -INFINITY, l = 0.f;                              // l: the lane's own keys only
     const int n_keys = a.causal ? i0 + rows : a.kv_seq;        // keys some row of the tile sees
     const int qi = i0 + l16;
+    // From the tile of this key on some query does not see every key of a tile.  A hidden key's weight is 0, and 0 x V has to
+    // stay 0 whatever that row of V holds: infinities and NaN are taken out there, and put back at the end for the rows that see
+    // them (in the loop that would cost the registers it runs in).
+    const int mixed0 = (a.causal ? i0 + 1 : n_keys) / kF32Keys * kF32Keys;
+    bool odd = false;
     // (a key past the last one re-reads it: its score is masked)
     auto k_row = [&](int key) { return kv_off + static_cast<int64_t>(min(key, n_keys - 1)) * a.ks[1]; };
     float4 kf[2][4 * NT];
@@ -234,6 +239,17 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[T][e] *= alpha;
         if (more) fetch_k(key0 + kF32Waves * kF32Keys);        // the next tile's K rows fly under the second product
+        if (key0 >= mixed0) {
+            auto finite = [&](float& x) __attribute__((always_inline)) {
+                if (!(fabsf(x) < INFINITY)) { x = 0.f; odd = true; }
+            };
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int T = 0; T < NT; ++T) { finite(vf[s][e][T].x); finite(vf[s][e][T].y); finite(vf[s][e][T].z); finite(vf[s][e][T].w); }
+        }
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -250,6 +266,8 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
 
     // the four states of the tile meet: out = sum_w f_w o_w / sum_w f_w l_w, f_w = exp(m_w - max m)
     if (kq == 0) { st_m[w * kF32Rows + l16] = m; st_l[w * kF32Rows + l16] = l; }
+    odd = __any(odd);
+    if (lane == 0) st_odd[w] = odd ? 1.f : 0.f;
 #pragma unroll
     for (int T = 0; T < NT; ++T)
 #pragma unroll
@@ -270,6 +288,14 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
             const float4 t = *reinterpret_cast<const float4*>(f32_lds + (x * kF32Rows + r) * PITCH + c);
             lt = fmaf(f, st_l[x * kF32Rows + r], lt);
             acc.x = fmaf(f, t.x, acc.x); acc.y = fmaf(f, t.y, acc.y); acc.z = fmaf(f, t.z, acc.z); acc.w = fmaf(f, t.w, acc.w);
+        }
+        if (__builtin_expect(st_odd[0] + st_odd[1] + st_odd[2] + st_odd[3] != 0.f, 0)) {
+            const int lim = a.causal ? i0 + r + 1 : n_keys;    // an infinity or NaN that the row sees is the result, whatever its weight
+            for (int key = mixed0; key < lim; ++key) {
+                const float4 v = load_quad<BF16>(a.v, k_row(key) + c);
+                acc.x += fabsf(v.x) < INFINITY ? 0.f : v.x; acc.y += fabsf(v.y) < INFINITY ? 0.f : v.y;
+                acc.z += fabsf(v.z) < INFINITY ? 0.f : v.z; acc.w += fabsf(v.w) < INFINITY ? 0.f : v.w;
+            }
         }
         const float inv = 1.f / lt;
         const int64_t at = b * a.os[0] + (i0 + r) * a.os[1] + h * a.os[2] + c;

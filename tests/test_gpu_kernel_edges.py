@@ -86,6 +86,24 @@ def test_fp32_attention_tiles(bd, seq, dtype, head_dim):
             assert (widen(c[:, :, :2]) == 7.0).all() and (widen(c[:, :, 2 + seq:]) == 7.0).all()
 
 
+@pytest.mark.parametrize("seq,at", [(17, 16), (40, 33), (64, 50), (150, 149)])
+@pytest.mark.parametrize("head_dim", [64, 72, 256])
+def test_fp32_attention_hidden_rows_hold_anything(bd, seq, at, head_dim):
+    """Under the causal mask a row's result does not depend on later rows of V, whatever they hold: the rows before `at` are
+    bit for bit what finite rows give, and the rows that see an infinity or NaN in a channel return it there."""
+    log("fp32 attention, odd values", seq, at, head_dim)
+    g = torch.Generator().manual_seed(seq + head_dim)
+    q, k, v = (torch.randn((1, seq, n, head_dim), generator=g).cuda() for n in (4, 2, 2))
+    clean = bd.civic_prefill_attn(q, k, v, True)
+    v[:, at, :, 3], v[:, at, :, 6], v[:, at, :, head_dim - 1] = float("nan"), float("inf"), float("-inf")
+    got = bd.civic_prefill_attn(q, k, v, True)
+    assert torch.equal(got[:, :at], clean[:, :at])
+    seen = got[:, at]
+    assert torch.isnan(seen[..., 3]).all() and (seen[..., 6] == float("inf")).all() and (seen[..., head_dim - 1] == float("-inf")).all()
+    keep = [c for c in range(head_dim) if c not in (3, 6, head_dim - 1)]
+    assert torch.equal(got[..., keep], clean[..., keep])
+
+
 @pytest.mark.parametrize("batch,hq,hkv,d,ctx", [
     (1, 8, 8, 128, [1]), (1, 4, 1, 128, [64]), (1, 4, 1, 128, [65]), (3, 4, 2, 128, [1, 700, 64]), (2, 8, 1, 64, [9000, 3]),
     (60, 8, 8, 64, [40 + 7 * i for i in range(60)]), (52, 8, 8, 32, [1 + 97 * i for i in range(52)]), (48, 16, 8, 128, [300] * 48),
