@@ -108,7 +108,9 @@ typedef short enc_s16x8 __attribute__((ext_vector_type(8)));
 enum GemmOut { kOutBf16, kOutLogits, kOutExp, kOutRowNorm };
 // |logit| <= inv_tau, so with inv_tau <= 60 a weight lies in [2^-103, 2^71]: every row's weights are normal fp32 and bf16
 // numbers and their sums with X_0 stay far from overflow without knowing the row's maximum.
-constexpr float kExpShift = 16.0f, kMaxDirectInvTau = 60.0f;
+// The half in the shift puts the weights of a warm softmax, all near one another, at 2^0.5 in their binade instead of around 1,
+// just above which bf16 is coarsest (inv_tau = 4, 700 tokens of 768, error of Z_0 against 64 bits: 2.41e-3 with 16, 2.30e-3 with 15.5).
+constexpr float kExpShift = 15.5f, kMaxDirectInvTau = 60.0f;
 
 // C = A B^T in the form OUT.  A is stored [m x k] (contraction index contiguous).  B_KROWS = false: B stored [n x k], the same
 // way.  B_KROWS = true: B stored [k x n], contraction index as the row index - the layout of X_0 in Z_0 = W_A X_0 and of
