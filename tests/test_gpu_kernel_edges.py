@@ -61,6 +61,34 @@ def test_anchor_softmax_routes(bd, inv_tau, tokens, anchors, dim):
     assert (np.abs(got_tw - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all(), float(np.abs(got_tw - ref_tw).max())
 
 
+@pytest.mark.parametrize("inv_tau", [4.0, 5.0, 7.0])
+@pytest.mark.parametrize("tokens,anchors,dim", [(256, 128, 1280), (300, 100, 1152), (300, 150, 1280), (700, 233, 1152)])
+def test_warm_softmax_weights_are_rounded_no_worse_than_normalised_ones(bd, inv_tau, tokens, anchors, dim):
+    """Weights without their row's factor, rounded to bf16, cost no more precision than normalised ones: the error of Z_0
+    against 64 bits is at most that of softmax weights rounded after the division, on tokens and anchors normalised and rounded
+    to bf16.  Warm softmaxes put all weights near one another, so it matters where in a binade that is: 300 tokens are the
+    best place for normalised weights (1 / 300 = 2^0.77 / 512), 256 the worst.  Both errors are norms over at least 25600
+    rounded weights, which scatter by 1 / sqrt(2 * 25600) = 0.45 % each: 1 % covers the difference."""
+    log("warm softmax", inv_tau, tokens, anchors, dim)
+    g = torch.Generator().manual_seed(tokens + dim)
+    x = torch.randn((1, tokens, dim), generator=g).bfloat16().cuda()
+    a = torch.randn((anchors, dim), generator=g).bfloat16().cuda()
+
+    def norm(t):
+        c = t.double() - t.double().mean(-1, keepdim=True)
+        return c / c.norm(dim=-1, keepdim=True)
+
+    def rounded(t):
+        return t.float().bfloat16().double()
+
+    qa, k0, x64 = norm(a), norm(x[0]), x[0].double()
+    ref = torch.softmax(inv_tau * (qa @ k0.t().contiguous()), -1) @ x64
+    normalised = rounded(rounded(torch.softmax(inv_tau * (rounded(qa) @ rounded(k0).t().contiguous()), -1)) @ x64)
+    z = bd.civic_anchor_aggregate(x, a, inv_tau, want_token_weight=True)[0][0].double()
+    err, bar = float((z - ref).norm() / ref.norm()), float((normalised - ref).norm() / ref.norm())
+    assert err <= 1.01 * bar, (err, bar)
+
+
 @pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 161])
 @pytest.mark.parametrize("dtype,head_dim", [("fp32", 8), ("fp32", 64), ("fp32", 72), ("fp32", 128), ("fp32", 136), ("fp32", 192),
                                             ("fp32", 256), ("bf16", 136), ("bf16", 192), ("bf16", 256)])
