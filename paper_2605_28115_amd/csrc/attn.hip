@@ -174,15 +174,24 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
     auto fetch_k = [&](int key0) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int64_t base = k_row(key0 + 16 * s + l16) + 4 * kq;
+            const int64_t base = k_row(key0 + 16 * s + l16);
 #pragma unroll
             for (int t = 0; t < 4 * NT; ++t)
-                if (16 * t < d) kf[s][t] = load_quad<BF16>(a.k, base + (16 * t + 4 * kq < d ? 16 * t : 0));
+                if (16 * t < d) kf[s][t] = load_quad<BF16>(a.k, base + (16 * t + 4 * kq < d ? 16 * t + 4 * kq : 0));
         }
     };
     int key0 = w * kF32Keys;
     if (key0 < n_keys) fetch_k(key0);
     for (; key0 < n_keys; key0 += kF32Waves * kF32Keys) {
+        if ((d & 8) != 0) {                                    // lanes past the row hold a piece of its front: 0 x it has to be 0
+#pragma unroll
+            for (int t = 0; t < 4 * NT; ++t)
+                if (16 * t < d && 16 * t + 16 > d) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+                        if (16 * t + 4 * kq >= d) kf[s][t] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+        }
         // S^T of 32 keys: two sub-tiles of 16, two partial sums each (four independent MFMA chains)
         f32x4 sc[2][2];
 #pragma unroll

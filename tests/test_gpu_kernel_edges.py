@@ -132,6 +132,64 @@ def test_fp32_attention_hidden_rows_hold_anything(bd, seq, at, head_dim):
     assert torch.equal(got[..., keep], clean[..., keep])
 
 
+@pytest.mark.parametrize("seq", [1, 16, 45])
+@pytest.mark.parametrize("dtype,head_dim", [(torch.float32, 8), (torch.float32, 24), (torch.float32, 72), (torch.float32, 136),
+                                            (torch.float32, 256), (torch.bfloat16, 8), (torch.bfloat16, 136)])
+def test_fp32_attention_reads_its_own_rows_only(bd, dtype, head_dim, seq):
+    """The fp32 matrix-core kernel where a row is shorter than, or ends inside, the 16 channels of a matrix step: Q, K, V and
+    the output are parts of larger tensors whose other elements (the channels after a row, which are the next head's or the next
+    key's front in a dense tensor, and whatever follows the last row) are NaN, so a read past a row that reaches a product, and a
+    write past one, shows.  bf16 at 8 channels comes here with rotary positions (the bf16 kernel has no such head).  The result
+    is bit for bit that of dense tensors."""
+    log("fp32 attention, own rows", dtype, head_dim, seq)
+    g = torch.Generator().manual_seed(seq + head_dim)
+    q, k, v = (torch.randn((1, seq, n, head_dim), generator=g).cuda().to(dtype) for n in (4, 2, 2))
+    angle = torch.rand((1, seq, head_dim // 2), generator=g)
+    cs = torch.stack([torch.cos(angle), torch.sin(angle)], -1).cuda().contiguous()
+
+    def inside(t):
+        wide = torch.full((1, seq + 1, t.shape[2] + 1, head_dim + 8), float("nan"), dtype=dtype, device="cuda")
+        part = wide[:, :seq, :t.shape[2], :head_dim]
+        part.copy_(t)
+        return wide, part
+
+    def run(q, k, v, causal, out):
+        if dtype == torch.bfloat16 and head_dim == 8:
+            return bd.civic_prefill_attn_rope(q, k, v, cs, causal, out=out)
+        return bd.civic_prefill_attn(q, k, v, causal, out=out)
+
+    for causal in (True, False):
+        dense = run(q, k, v, causal, torch.empty_like(q))
+        wide, out = inside(q)
+        got = run(inside(q)[1], inside(k)[1], inside(v)[1], causal, out)
+        assert torch.isfinite(dense).all() and torch.equal(got, dense)
+        out.fill_(float("nan"))
+        assert torch.isnan(wide).all()
+    # a key that a row does not see changes nothing, and an infinite channel that the query weighs with zero keeps to its own key
+    clean = run(q, k, v, True, torch.empty_like(q))
+    k[:, seq - 1, :, :] = float("nan")
+    odd = run(q, k, v, True, torch.empty_like(q))
+    assert torch.equal(odd[:, :seq - 1], clean[:, :seq - 1]) and torch.isnan(odd[:, seq - 1]).all()
+
+
+@pytest.mark.parametrize("seq", [17, 40, 70])
+@pytest.mark.parametrize("head_dim", [8, 24, 72, 128, 136])
+def test_fp32_attention_key_of_minus_infinity_weighs_nothing(bd, head_dim, seq):
+    """A logit of minus infinity is a weight of zero, at every head size: a K row holds -infinity in a channel where all queries
+    are positive (the first one, which steps past the end of a row used to read again).  Against the same call without that key:
+    the sums over the other keys run in another order, fp32 bar of the parity tests."""
+    log("fp32 attention, minus infinity", head_dim, seq)
+    g = torch.Generator().manual_seed(seq * 3 + head_dim)
+    q, k, v = (torch.randn((1, seq, n, head_dim), generator=g).cuda() for n in (4, 2, 2))
+    q[..., 0] = q[..., 0].abs() + 0.1
+    at = seq // 2
+    k[:, at, :, 0] = float("-inf")
+    got = bd.civic_prefill_attn(q, k, v, False)
+    keep = [i for i in range(seq) if i != at]
+    ref = bd.civic_cross_attn(q, k[:, keep].contiguous(), v[:, keep].contiguous())
+    assert torch.isfinite(got).all() and float((got - ref).abs().max()) <= 1e-5 * max(1.0, float(ref.abs().max()))
+
+
 @pytest.mark.parametrize("batch,hq,hkv,d,ctx", [
     (1, 8, 8, 128, [1]), (1, 4, 1, 128, [64]), (1, 4, 1, 128, [65]), (3, 4, 2, 128, [1, 700, 64]), (2, 8, 1, 64, [9000, 3]),
     (60, 8, 8, 64, [40 + 7 * i for i in range(60)]), (52, 8, 8, 32, [1 + 97 * i for i in range(52)]), (48, 16, 8, 128, [300] * 48),
