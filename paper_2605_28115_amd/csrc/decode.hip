@@ -355,6 +355,15 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
     float m = -INFINITY, l = 0.f;                              // of head l16; l: the lane's own keys
 
     auto compute = [&](int at, u32x4 (&ck)[2][KT], u32x4 (&cv)[8]) __attribute__((always_inline)) {
+        if ((d & 31) != 0) {                                    // lanes past the row hold a piece of its front: 0 x it has to be 0
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+                if (32 * t < d && 32 * t + 32 > d) {
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        if (32 * t + 8 * kq >= d) ck[x][t] = u32x4{0u, 0u, 0u, 0u};
+                }
+        }
         dec_f32x4 s[2];
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
@@ -370,9 +379,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
             p[e] = e < lim ? s[e >> 2][e & 3] * a.scale_log2 : -INFINITY;
             m_new = fmaxf(m_new, p[e]);
         }
-        m_new = slots_max<16>(m_new);                           // finite: the step's first key exists
+        m_new = slots_max<16>(m_new);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;   // every key so far has a logit of -infinity: weight 0
         if (__any(m_new != m)) {
-            const float alpha = __builtin_amdgcn_exp2f(m - m_new);   // exp2(-inf) = 0 on the first step
+            const float alpha = __builtin_amdgcn_exp2f(m - m_use);   // exp2(-inf) = 0 on the first step
             l *= alpha;
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -383,7 +393,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
         u32x4 ph, pl;                                           // the weights' leading and trailing bf16 terms
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float p0 = __builtin_amdgcn_exp2f(p[2 * e] - m), p1 = __builtin_amdgcn_exp2f(p[2 * e + 1] - m);
+            const float p0 = __builtin_amdgcn_exp2f(p[2 * e] - m_use), p1 = __builtin_amdgcn_exp2f(p[2 * e + 1] - m_use);
             l += p0 + p1;
             const dec_bf16x2 hi = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
             const uint32_t hw = __builtin_bit_cast(uint32_t, hi);
@@ -436,8 +446,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
         for (int x = 1; x < WAVES; ++x) mx = fmaxf(mx, sm_m[x * heads + hh]);
         float o0 = 0.f, o1 = 0.f, lt = 0.f;
 #pragma unroll
-        for (int x = 0; x < WAVES; ++x) {                       // (a wavefront without keys: m = -inf, weight 0)
-            const float f = __builtin_amdgcn_exp2f(sm_m[x * heads + hh] - mx);
+        for (int x = 0; x < WAVES; ++x) {                       // (a wavefront without a key of any weight: m = -inf)
+            const float mw = sm_m[x * heads + hh], f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
             const float2 v = *reinterpret_cast<const float2*>(sm_o + (x * heads + hh) * d + ch);
             o0 = fmaf(f, v.x, o0); o1 = fmaf(f, v.y, o1);
             lt = fmaf(f, sm_l[x * heads + hh], lt);

@@ -216,3 +216,37 @@ def test_decode_cuts(bd, batch, hq, hkv, d, ctx):
         for b, n in enumerate(ctx):
             ref = oracle.decode_attention(widen(q[b:b + 1]), widen(kc[b:b + 1]), widen(vc[b:b + 1]), n)
             assert np.abs(got[b] - ref[0]).max() <= 2.0 ** -8 * max(1.0, float(np.abs(ref).max())), (b, n)
+
+
+def _decode_reference(q, k, v, n):
+    """Softmax attention of one query per head over the first n rows, in 64 bits; an infinite logit and an infinity in V are
+    what the formula makes of them."""
+    hq, hkv = q.shape[1], k.shape[1]
+    qg, kk, vv = q.double().view(q.shape[0], hkv, hq // hkv, -1), k[:, :, :n].double(), v[:, :, :n].double()
+    logits = (qg[:, :, :, None, :] * kk[:, :, None]).sum(-1) / q.shape[-1] ** 0.5
+    p = torch.softmax(logits, -1)
+    return (p[..., None] * vv[:, :, None]).sum(-2).view(q.shape)
+
+
+DECODE_GROUPS = [(2, 1), (4, 1), (4, 2), (16, 1), (17, 1), (6, 2)]
+
+
+@pytest.mark.parametrize("hq,hkv", DECODE_GROUPS)
+@pytest.mark.parametrize("d,n", [(8, 40), (40, 33), (64, 200), (72, 300), (128, 64), (128, 1500)])
+def test_decode_keys_of_minus_infinity_weigh_nothing(bd, hq, hkv, d, n):
+    """Logits of minus infinity, with one and two heads per KV head (vector kernel) and more (matrix cores), in one piece and in
+    several: a single key, the whole first 32 keys (a wavefront that has met no weight yet) and a whole piece weigh nothing, at
+    head sizes that are not whole steps of 32 channels too; no key with a weight at all is 0 / 0.  bf16 rounds the result once."""
+    log("decode, minus infinity", hq, hkv, d, n)
+    g = torch.Generator().manual_seed(hq + 10 * d + n)
+    q, k, v = (torch.randn((2, h, *s, d), generator=g).bfloat16() for h, s in ((hq, ()), (hkv, (n,)), (hkv, (n,))))
+    q[..., 0] = q[..., 0].abs() + 0.25
+    for hidden in ((5,), tuple(range(32)), tuple(range(n - 1)), tuple(range(n))):
+        kk = k.clone()
+        kk[:, :, list(hidden), 0] = float("-inf")
+        got = bd.civic_decode_attn(q.cuda(), kk.cuda(), v.cuda(), n).cpu().double()
+        if len(hidden) == n:
+            assert torch.isnan(got).all()
+            continue
+        ref = _decode_reference(q, kk, v, n)
+        assert torch.isfinite(got).all() and float((got - ref).abs().max()) <= 2.0 ** -8 * max(1.0, float(ref.abs().max()))
