@@ -354,7 +354,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
     for (int j = 0; j < 8; ++j) o[j] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;                              // of head l16; l: the lane's own keys
 
-    auto compute = [&](int at, u32x4 (&ck)[2][KT], u32x4 (&cv)[8]) __attribute__((always_inline)) {
+    // logits (times log2 e) of the lane's keys 8 kq .. + 7 of the step at `at`, head l16; keys past the end -infinity
+    auto logits = [&](int at, u32x4 (&ck)[2][KT], float (&z)[8]) __attribute__((always_inline)) {
         if ((d & 31) != 0) {                                    // lanes past the row hold a piece of its front: 0 x it has to be 0
 #pragma unroll
             for (int t = 0; t < KT; ++t)
@@ -373,12 +374,14 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
                 if (32 * t < d) s[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, ck[x][t]), qf[t], s[x], 0, 0, 0);
         }
         const int lim = n_keys - at - 8 * kq;                   // the lane's keys below this exist
-        float p[8], m_new = m;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            p[e] = e < lim ? s[e >> 2][e & 3] * a.scale_log2 : -INFINITY;
-            m_new = fmaxf(m_new, p[e]);
-        }
+        for (int e = 0; e < 8; ++e) z[e] = e < lim ? s[e >> 2][e & 3] * a.scale_log2 : -INFINITY;
+    };
+    auto compute = [&](int at, u32x4 (&ck)[2][KT], u32x4 (&cv)[8]) __attribute__((always_inline)) {
+        float p[8], m_new = m;
+        logits(at, ck, p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m_new = fmaxf(m_new, p[e]);
         m_new = slots_max<16>(m_new);
         const float m_use = m_new == -INFINITY ? 0.f : m_new;   // every key so far has a logit of -infinity: weight 0
         if (__any(m_new != m)) {
@@ -424,6 +427,44 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
         key += step;
     }
     l = slots_sum<16>(l);
+    // An infinity of V has met the trailing terms of its weight, or the weight of a key past the end (0 x infinity, infinity -
+    // infinity): the wavefront's results are made again from the final maximum, one fp32 multiply-add per key that exists.
+    float odd = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) odd = fmaf(o[j][r], 0.f, odd);
+    if (__builtin_expect(__any(odd != 0.f), 0)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = dec_f32x4{0.f, 0.f, 0.f, 0.f};
+        const float m_use = m == -INFINITY ? 0.f : m;
+#pragma unroll 1
+        for (int at = 32 * w; at < n_keys; at += step) {
+            float p[8];
+            fetch(at, kf[0], vf[0]);
+            logits(at, kf[0], p);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(p[e] - m_use);
+#pragma unroll 1
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float wgt = __shfl(p[e], 16 * x + l16, kWave);
+                    const int key_at = at + 8 * x + e;
+                    if (key_at < n_keys) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int ch = 8 * (4 * kq + r);
+                            if (ch >= d) continue;
+                            const u32x4 v = *reinterpret_cast<const u32x4*>(vbase + static_cast<int64_t>(key_at) * row_bytes + ch * 2);
+#pragma unroll
+                            for (int j = 0; j < 8; ++j)
+                                o[j][r] = fmaf(wgt, (j & 1) ? __uint_as_float(v[j >> 1] & 0xFFFF0000u) : __uint_as_float(v[j >> 1] << 16), o[j][r]);
+                        }
+                    }
+                }
+        }
+    }
 
     if (l16 < heads) {                                          // register r of o[j]: channel 8 (4 kq + r) + j
         if (kq == 0) { sm_m[w * heads + l16] = m; sm_l[w * heads + l16] = l; }

@@ -250,3 +250,23 @@ def test_decode_keys_of_minus_infinity_weigh_nothing(bd, hq, hkv, d, n):
             continue
         ref = _decode_reference(q, kk, v, n)
         assert torch.isfinite(got).all() and float((got - ref).abs().max()) <= 2.0 ** -8 * max(1.0, float(ref.abs().max()))
+
+
+@pytest.mark.parametrize("hq,hkv", DECODE_GROUPS)
+@pytest.mark.parametrize("d,n,at", [(8, 40, 39), (40, 33, 32), (64, 200, 0), (72, 300, 150), (128, 64, 63), (128, 1500, 700), (128, 1500, 1499)])
+def test_decode_infinities_of_v_stay_what_they_are(bd, hq, hkv, d, n, at):
+    """An infinity or NaN in a row of V is the result in its channel (every weight here is far from zero), at one and two heads
+    per KV head and at more alike, in the last row too (which keys past the end read again); all other channels, and rows past
+    the context, whatever they hold, change nothing.  bf16 rounds the result once; 16 bits are what a weight's terms must hold."""
+    log("decode, infinities of V", hq, hkv, d, n, at)
+    g = torch.Generator().manual_seed(hq + 10 * d + n)
+    q, k, v = (torch.randn((2, h, *s, d), generator=g).bfloat16() for h, s in ((hq, ()), (hkv, (n + 2,)), (hkv, (n + 2,))))
+    k[:, :, n:], v[:, :, n:] = float("nan"), float("inf")
+    v[:, :, at, 3], v[:, :, at, 6], v[:, :, at, d - 1] = float("nan"), float("inf"), float("-inf")
+    ref = _decode_reference(q, k, v, n)
+    outs = [bd.civic_decode_attn(q.cuda(), k.cuda(), v.cuda(), n), bd.civic_decode_attn_ragged(q.cuda(), k.cuda(), v.cuda(), [n, n])]
+    for got in (o.cpu().double() for o in outs):
+        assert torch.isnan(got[..., 3]).all() and (got[..., 6] == float("inf")).all() and (got[..., d - 1] == float("-inf")).all()
+        keep = [c for c in range(d) if c not in (3, 6, d - 1)]
+        diff = (got[..., keep] - ref[..., keep]).abs().max()
+        assert float(diff) <= 2.0 ** -8 * max(1.0, float(ref[..., keep].abs().max()))
