@@ -649,8 +649,7 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     p->whole_keys = static_cast<int>(whole_keys);
     cut(units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
-    const int slots = kDecWaves * (kWave / p->lpr);
-    p->lds_bytes = sizeof(float) * static_cast<size_t>(slots) * p->hg * (head_dim + 2);
+    p->lds_bytes = sizeof(float) * kDecWaves * static_cast<size_t>(p->hg) * (head_dim + 2);   // one state per wavefront and head
     return CIVIC_OK;
 }
 
@@ -709,6 +708,7 @@ static int launch_decode(const DecodeArgs& a, const TABLE& t, const DecodePlan& 
 {
     int rc;
     if (p.mfma) {
+        static_assert(sizeof(float) * kDecWaves * 16 * (128 + 2) <= 64 * 1024, "no launch needs more LDS than every launch may have");
         const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
         civic::launch((decode_mfma_kernel<TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
         rc = check_launch();

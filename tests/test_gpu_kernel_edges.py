@@ -196,7 +196,9 @@ def test_fp32_attention_key_of_minus_infinity_weighs_nothing(bd, head_dim, seq):
     (260, 2, 2, 64, [1 + i % 130 for i in range(260)]),
     # the matrix-core kernel: 3 to 17 heads per KV head, channels that are not whole chunks, steps of 32 and rounds of 128
     (2, 6, 2, 40, [31, 33]), (1, 16, 1, 128, [257]), (1, 17, 1, 128, [129]), (2, 33, 1, 72, [127, 600]), (3, 12, 4, 96, [1, 128, 385]),
-    (70, 18, 6, 8, [20 * i + 1 for i in range(70)])])
+    (70, 18, 6, 8, [20 * i + 1 for i in range(70)]),
+    # the most LDS: eight heads of 512 channels on the vector kernel, sixteen of 128 on the matrix cores
+    (1, 8, 1, 512, [70]), (2, 24, 3, 256, [300, 45]), (1, 32, 2, 128, [700])])
 def test_decode_cuts(bd, batch, hq, hkv, d, ctx):
     """How a decode launch is cut: one piece per sample and several, samples of one piece beside samples of many, pieces that
     end on a round and one row past it, more than one group of samples, up to 8 splits and more.  Rows past a context are NaN.
