@@ -280,7 +280,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 //     of O^T += V^T P^T as it stands.
 //   - V^T rows may be any permutation of the channels: a lane reads channels 8 i .. 8 i + 7 of its 8 keys, 16 bytes each, and
 //     v_perm gathers 8 operands (channel 8 i + j of the 8 keys) out of them: no LDS, no transposed copy.
-//   - Weights enter as two bf16 terms (16 mantissa bits): rounding them to one would cost precision the fp32 sums have.
+//   - Weights enter as sums of three bf16 terms, which hold every bit of the fp32 weight (two hold 16: the results then differ
+//     from the rounded exact ones four times as often as with fp32 weights).  The third costs 8 MFMAs a step, which memory hides,
+//     and registers, which scalar base addresses gave back (with vector ones 20 were spilled: 64 samples of 117..3584 rows 99 us).
 //   - Each wavefront runs its own online softmax; the states meet in LDS at the end.
 // Against the kernel above (us): 64 x 938 rows, 32 / 8 heads 45.5 -> 42.3 (5.8 TB/s); 64 x 3584 154 -> 142 (6.6 TB/s); 4 x 938
 // 10.6 -> 9.1; 16 x 2000 with 64 / 8 heads 43.8 -> 28.6.  With one or two heads the vector work is less than the gathering here
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
     constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
     constexpr int WAVES = kDecWaves, THREADS = kDecThreads, KT = 4;      // K chunks of 32 channels
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid >> 6);   // (w uniform: loads from scalar bases)
     const int l16 = lane & 15, kq = lane >> 4;
     const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
     const int b = blockIdx.z, split = blockIdx.x, d = a.head_dim;
@@ -316,7 +318,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
     const int n_keys = k1 - k0;
 
     // Loads of the 32 keys from `key` on (relative to k0); keys past the end re-read the last one (their logits are masked)
-    auto fetch = [&](int key, u32x4 (&kf)[2][KT], u32x4 (&vf)[8]) __attribute__((always_inline)) {
+    auto fetch = [&](int key_v, u32x4 (&kf)[2][KT], u32x4 (&vf)[8]) __attribute__((always_inline)) {
+        const int key = __builtin_amdgcn_readfirstlane(key_v);
         const int last = n_keys - 1 - key;
         const char* const kb = kbase + static_cast<int64_t>(key) * row_bytes;
         const char* const vb = vbase + static_cast<int64_t>(key) * row_bytes;
@@ -393,15 +396,17 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
                 for (int r = 0; r < 4; ++r) o[j][r] *= alpha;
             m = m_new;
         }
-        u32x4 ph, pl;                                           // the weights' leading and trailing bf16 terms
+        u32x4 ph, pm, pl;                                       // the weights as sums of three bf16 terms: 24 bits, all of fp32's
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float p0 = __builtin_amdgcn_exp2f(p[2 * e] - m_use), p1 = __builtin_amdgcn_exp2f(p[2 * e + 1] - m_use);
             l += p0 + p1;
             const dec_bf16x2 hi = {static_cast<__bf16>(p0), static_cast<__bf16>(p1)};
-            const uint32_t hw = __builtin_bit_cast(uint32_t, hi);
-            const dec_bf16x2 lo = {static_cast<__bf16>(p0 - __uint_as_float(hw << 16)), static_cast<__bf16>(p1 - __uint_as_float(hw & 0xFFFF0000u))};
-            ph[e] = hw;
+            ph[e] = __builtin_bit_cast(uint32_t, hi);
+            const float r0 = p0 - __uint_as_float(ph[e] << 16), r1 = p1 - __uint_as_float(ph[e] & 0xFFFF0000u);
+            const dec_bf16x2 mid = {static_cast<__bf16>(r0), static_cast<__bf16>(r1)};
+            pm[e] = __builtin_bit_cast(uint32_t, mid);
+            const dec_bf16x2 lo = {static_cast<__bf16>(r0 - __uint_as_float(pm[e] << 16)), static_cast<__bf16>(r1 - __uint_as_float(pm[e] & 0xFFFF0000u))};
             pl[e] = __builtin_bit_cast(uint32_t, lo);
         }
 #pragma unroll
@@ -413,6 +418,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
                 v[e] = __builtin_amdgcn_perm(w1, w0, (j & 1) ? 0x07060302u : 0x05040100u);
             }
             o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, v), __builtin_bit_cast(dec_bf16x8, ph), o[j], 0, 0, 0);
+            o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, v), __builtin_bit_cast(dec_bf16x8, pm), o[j], 0, 0, 0);
             o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8, v), __builtin_bit_cast(dec_bf16x8, pl), o[j], 0, 0, 0);
         }
     };

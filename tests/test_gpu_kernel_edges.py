@@ -259,7 +259,7 @@ def test_decode_keys_of_minus_infinity_weigh_nothing(bd, hq, hkv, d, n):
 def test_decode_infinities_of_v_stay_what_they_are(bd, hq, hkv, d, n, at):
     """An infinity or NaN in a row of V is the result in its channel (every weight here is far from zero), at one and two heads
     per KV head and at more alike, in the last row too (which keys past the end read again); all other channels, and rows past
-    the context, whatever they hold, change nothing.  bf16 rounds the result once; 16 bits are what a weight's terms must hold."""
+    the context, whatever they hold, change nothing.  bf16 rounds the result once."""
     log("decode, infinities of V", hq, hkv, d, n, at)
     g = torch.Generator().manual_seed(hq + 10 * d + n)
     q, k, v = (torch.randn((2, h, *s, d), generator=g).bfloat16() for h, s in ((hq, ()), (hkv, (n + 2,)), (hkv, (n + 2,))))
@@ -272,3 +272,32 @@ def test_decode_infinities_of_v_stay_what_they_are(bd, hq, hkv, d, n, at):
         keep = [c for c in range(d) if c not in (3, 6, d - 1)]
         diff = (got[..., keep] - ref[..., keep]).abs().max()
         assert float(diff) <= 2.0 ** -8 * max(1.0, float(ref[..., keep].abs().max()))
+
+
+@pytest.mark.parametrize("group", [2, 4, 16])
+@pytest.mark.parametrize("n", [3, 300, 2000])
+def test_decode_weights_are_fp32(bd, group, n):
+    """The softmax weights meet V with all bits of fp32: three rows of V cancel to about 2^-18 of themselves, so the error of the
+    weights is what is left.  Against 64 bits, relative to sum p |v|: the logit's two roundings, exp2 and the factors of the merges
+    (2^-23 each at logits of at most 1) and a few sums stay below 2^-20; a weight of 16 bits is off by up to 2^-18.  The output's
+    rounding is 2^-9 of the small result."""
+    log("decode weights", group, n)
+    batch, hkv, d = 8, 4, 64
+    g = torch.Generator().manual_seed(group + n)
+    q = torch.zeros(batch, hkv, d)
+    q[..., 0] = 1.0 + torch.rand((batch, hkv), generator=g)
+    k = torch.zeros(batch, hkv, n, d)
+    k[..., 0] = 4.0 * torch.rand((batch, hkv, n), generator=g)
+    q, k = q.bfloat16(), k.bfloat16()
+    p = torch.softmax((q[:, :, None, :1].double() * k[..., :1].double()).sum(-1) / 8.0, -1)
+    at = [0, n // 2, n - 1]
+    v = torch.zeros(batch, hkv, n, d, dtype=torch.float64)
+    v[:, :, at[0]] = (1.0 + torch.rand((batch, hkv, d), generator=g)).bfloat16().double()
+    left = p[:, :, at[0], None] * v[:, :, at[0]]
+    for i in at[1:]:
+        v[:, :, i] = (-left / p[:, :, i, None]).float().bfloat16().double()
+        left = left + p[:, :, i, None] * v[:, :, i]
+    bar = 2.0 ** -20 * (p[..., None] * v.abs()).sum(-2) + 2.0 ** -8 * left.abs()
+    out = bd.civic_decode_attn(q.repeat_interleave(group, 1).cuda(), k.cuda(), v.bfloat16().cuda(), n)
+    err = (out.cpu().double().view(batch, hkv, group, d) - left[:, :, None]).abs() / bar[:, :, None]
+    assert float(err.max()) <= 1.0, float(err.max())
