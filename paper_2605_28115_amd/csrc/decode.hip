@@ -623,29 +623,32 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     if (cpr > kWave || n_ctx > INT32_MAX || batch > 65535) return CIVIC_ERR_UNSUPPORTED;
     const int group = n_q_heads / n_kv_heads;
     p->mfma = dtype == CIVIC_BF16 && head_dim <= 128 && group > 2;
-    p->hg = p->mfma ? std::min(group, 16) : group >= 8 ? 8 : group > 2 ? 4 : group;   // query heads per pass (1, 2, 4 or 8 without MFMA)
+    // blocks of the vector kernel's 1, 2, 4 or 8 heads: the limit on the sizes and the workspace go by them, whichever kernel runs
+    const int vec_heads = group >= 8 ? 8 : group > 2 ? 4 : group, vec_blocks = (group + vec_heads - 1) / vec_heads;
+    if (static_cast<int64_t>(n_kv_heads) * vec_blocks > 65535) return CIVIC_ERR_UNSUPPORTED;
+    p->hg = p->mfma ? std::min(group, 16) : vec_heads;          // query heads per pass
     p->head_blocks = (group + p->hg - 1) / p->hg;
-    if (static_cast<int64_t>(n_kv_heads) * p->head_blocks > 65535) return CIVIC_ERR_UNSUPPORTED;
     p->lpr = 8;
     while (p->lpr < cpr) p->lpr *= 2;
     const int64_t units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * p->head_blocks;
     const int64_t round_keys = p->mfma ? 32 * kDecWaves : static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU;
     const int64_t whole_keys = round_keys * (p->mfma ? 2 : 4);
     p->round_keys = static_cast<int>(round_keys);
-    // whole rounds per split, no split shorter than one round of the workgroup
-    auto cut = [&](int64_t splits, int32_t* n, int32_t* keys) {
-        const int64_t max_splits = (n_ctx + round_keys - 1) / round_keys;
+    // whole rounds per split, no split shorter than one round
+    auto cut = [&](int64_t splits, int64_t round, int32_t* n, int32_t* keys) {
+        const int64_t max_splits = (n_ctx + round - 1) / round;
         splits = std::max<int64_t>(std::min(std::min(splits, max_splits), static_cast<int64_t>(kDecMaxSplits)), 1);
         int64_t kps = (n_ctx + splits - 1) / splits;
-        kps = std::max((kps + round_keys - 1) / round_keys * round_keys, round_keys);
+        kps = std::max((kps + round - 1) / round * round, round);
         *n = static_cast<int32_t>(n_ctx > 0 ? (n_ctx + kps - 1) / kps : 1);
         *keys = static_cast<int32_t>(kps);
     };
-    // what the workspace has room for: about four workgroups per compute unit with at most 8 heads in each, and the pieces of a
-    // ragged launch
+    // What the workspace has room for: about four workgroups per compute unit, in rounds of the vector kernel (the size decides
+    // which calls civic_decode_attn_noalloc takes).  What is launched below is never more: at most 512 or 256 workgroups, of at
+    // most twice the heads, in rounds as long or longer.  And the pieces of a ragged launch.
     int32_t unused;
-    const int64_t room_units = p->hg > 8 ? 2 * units : units;
-    cut((1024 + room_units - 1) / room_units, &p->max_splits, &unused);
+    const int64_t room_units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * vec_blocks;
+    cut((1024 + room_units - 1) / room_units, static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU, &p->max_splits, &unused);
     if (ragged) p->max_splits = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p->max_splits, (n_ctx + kDecRaggedKeys - 1) / kDecRaggedKeys), kDecMaxSplits));
     // What is launched: nothing to combine once the (item, KV head) pairs fill the chip by themselves (64 x 938 rows, 8 KV
     // heads: one split 45.5 us, two 52; 64 x 3584: 153 against 172); otherwise two workgroups per unit in at most 8 splits, which
@@ -653,7 +656,7 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).  Nor is a context cut that one
     // workgroup gets through before a second launch would have started (1 x 256 rows, 32 / 8 heads: 7.0 us whole, 7.8 in two).
     p->whole_keys = static_cast<int>(whole_keys);
-    cut(units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), &p->splits, &p->keys_per_split);
+    cut(units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), round_keys, &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
     p->lds_bytes = sizeof(float) * kDecWaves * static_cast<size_t>(p->hg) * (head_dim + 2);   // one state per wavefront and head
     return CIVIC_OK;

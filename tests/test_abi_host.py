@@ -355,3 +355,16 @@ def test_header_is_plain_c(tmp_path):
     for cmd in (["gcc", "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror"], ["g++", "-std=c++17", "-x", "c++", "-Wall", "-Wextra", "-pedantic"]):
         r = subprocess.run(cmd + ["-I", inc, "-fsyntax-only", str(src)], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def test_decode_workspace_holds_four_workgroups_per_unit(bd):
+    """The decode workspace has room for 1024 workgroups of up to 8 query heads (4 from 3 to 7 heads per KV head) and no more,
+    whichever kernel a head grouping takes: fewer calls would fit the array of civic_decode_attn_noalloc otherwise."""
+    bf16 = __import__("torch").bfloat16
+    for group in range(1, 34):
+        block = 8 if group >= 8 else 4 if group > 2 else group
+        for batch, hkv, d, n in ((1, 1, 128, 4000), (7, 4, 128, 900), (60, 16, 32, 3315), (100, 8, 128, 268), (228, 4, 128, 8460)):
+            pairs = batch * hkv * -(-group // block)
+            splits = -(-1024 // pairs)
+            need = bd.civic_decode_attn_workspace_bytes(bf16, batch, group * hkv, hkv, d, n)
+            assert need <= (4 * batch * group * hkv * (d + 2) * splits if splits > 1 else 0), (group, batch, hkv, d, n)

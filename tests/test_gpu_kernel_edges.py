@@ -301,3 +301,16 @@ def test_decode_weights_are_fp32(bd, group, n):
     out = bd.civic_decode_attn(q.repeat_interleave(group, 1).cuda(), k.cuda(), v.bfloat16().cuda(), n)
     err = (out.cpu().double().view(batch, hkv, group, d) - left[:, :, None]).abs() / bar[:, :, None]
     assert float(err.max()) <= 1.0, float(err.max())
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,n", [(228, 24, 4, 128, 600), (50, 112, 16, 96, 320), (100, 48, 8, 128, 268)])
+def test_noalloc_takes_groups_of_five_to_seven_heads(bd, batch, hq, hkv, d, n):
+    """Head groupings whose blocks of heads differ between the two decode kernels: the call without a workspace is taken where
+    its array held the splits before there was a second kernel, and returns the same bits as the call with one."""
+    log("noalloc", batch, hq, hkv, d, n)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn((batch, hq, d), generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn((batch, hkv, n, d), generator=g, device="cuda").bfloat16() for _ in range(2))
+    out = torch.empty_like(q)
+    bd.civic_decode_attn_noalloc(q, k, v, n, out)
+    assert torch.equal(out, bd.civic_decode_attn(q, k, v, n))
