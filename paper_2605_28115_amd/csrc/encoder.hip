@@ -107,12 +107,16 @@ typedef short enc_s16x8 __attribute__((ext_vector_type(8)));
 //                1365 x 4096 weights with 4096 x 1152 tokens 47.8 us instead of 40.)
 enum GemmOut { kOutBf16, kOutLogits, kOutExp, kOutRowNorm };
 // |logit| <= inv_tau up to the rounding of Q_A, so with inv_tau <= 60 (86.6 binades) a weight lies in [2^-103, 2^72]: every row's
-// weights are normal fp32 and bf16 numbers and their sums with X_0 stay far from overflow without knowing the row's maximum.
+// weights are normal fp32 and bf16 numbers without knowing the row's maximum, and so are their sums.  (Their products with X_0
+// are, but for tokens beyond 2^40 or rows without a weight above 2^-40, which the second product looks for.)
 // The fraction of the shift puts the weights of a warm softmax, all near one another, high in their binade (2^0.7 of it), where
 // bf16 is finest against the weight and the upper tail still does not spill into the next one.  Normalised weights lie around
 // 1 / n_tokens instead, wherever in its binade that is; 300 tokens happen to be the best place, so the error of Z_0 is compared
 // there (1152 wide, 100 anchors, inv_tau = 4, against 64 bits): 2.21e-3 normalised, 2.28e-3 with 15.5, 2.20e-3 with 15.3.
 constexpr float kExpShift = 15.3f, kMaxDirectInvTau = 60.0f;
+// One over a row's sum beyond which its product with the tokens is not left to fp32's range (the row's largest weights are below
+// 2^-40 then; never at inv_tau <= 17, and above only for an anchor that every token points away from).
+constexpr float kMaxRowFactor = 1.0995116e12f;
 
 // C = A B^T in the form OUT.  A is stored [m x k] (contraction index contiguous).  B_KROWS = false: B stored [n x k], the same
 // way.  B_KROWS = true: B stored [k x n], contraction index as the row index - the layout of X_0 in Z_0 = W_A X_0 and of
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
         sums[tid] = t;
         __syncthreads();
     }
-    float scale[2], part_sum[2] = {0.f, 0.f};
+    float scale[2], part_sum[2] = {0.f, 0.f}, odd[2] = {0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int row = row_q + 32 * i + col;
@@ -394,6 +398,10 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
             for (int i = 0; i < 2; ++i) {
                 float v[4];
                 value(i, j, rq, mean, inv, v);
+                if constexpr (OUT == kOutRowNorm) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd[i] = fmaf(v[e], 0.f, odd[i]);
+                }
                 enc_bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -410,6 +418,37 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
                 }
             }
         }
+    if constexpr (OUT == kOutRowNorm) {
+        // Weights without their row's factor reach from 2^-103 to 2^72, so a product with tokens beyond 2^40 may have overflowed, and
+        // one of a row of small weights with small tokens vanished.  Such a wavefront makes its results again with the factor
+        // applied to the weight first, one fp32 multiply-add each, four columns at a time.
+        // (A row whose factor is NaN has met a NaN among the tokens: that is its result.)
+        bool again = false;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            again |= row_q + 32 * i + col < g.m && (scale[i] > kMaxRowFactor || (odd[i] != 0.f && scale[i] == scale[i]));
+        if (__builtin_expect(__any(again), 0)) {
+#pragma unroll 1
+            for (int c4 = 4 * half; c4 < 64; c4 += 8)
+#pragma unroll 1
+                for (int row = row_q + col, i = 0; i < 2; row += 32, ++i) {
+                    if (row >= g.m || col_q + c4 >= g.n) continue;
+                    const float factor = i == 0 ? scale[0] : scale[1];
+                    const __bf16* wgt = g.a + a_first + row * lda;
+                    const __bf16* x = b_mat + b_first + col_q + c4;
+                    float t[4] = {0.f, 0.f, 0.f, 0.f};
+                    for (int k = 0; k < kb_rows; ++k) {
+                        const enc_bf16x4 xk = *reinterpret_cast<const enc_bf16x4*>(x + k * g.ldb);
+                        const float wk = static_cast<float>(wgt[k]) * factor;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
+                    }
+                    const enc_bf16x4 o = {static_cast<__bf16>(t[0]), static_cast<__bf16>(t[1]), static_cast<__bf16>(t[2]), static_cast<__bf16>(t[3])};
+                    *reinterpret_cast<enc_bf16x4*>(reinterpret_cast<__bf16*>(c_base) + static_cast<int64_t>(row) * g.ldc + col_q + c4) = o;
+                }
+            return;
+        }
+    }
     if constexpr (OUT == kOutExp) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {

@@ -89,6 +89,31 @@ def test_warm_softmax_weights_are_rounded_no_worse_than_normalised_ones(bd, inv_
     assert err <= 1.01 * bar, (err, bar)
 
 
+@pytest.mark.parametrize("inv_tau", [4.0, 30.0, 60.0, 61.0])
+@pytest.mark.parametrize("binades", [-55, 0, 40, 58])
+@pytest.mark.parametrize("tokens,anchors,dim", [(70, 3, 64), (200, 130, 192)])
+def test_anchor_aggregate_over_the_range_of_the_tokens(bd, tokens, anchors, dim, binades, inv_tau):
+    """Z_0 is as good for tokens of any size whose squares fp32 holds: tokens times 2^binades give the result times 2^binades, for
+    rows whose softmax is warm, for anchors that are a token (the largest weights) and for anchors that every token points away
+    from (logits of -inv_tau throughout: the smallest).  Bound of the routes' test: the logits' errors from rounding Q_A, weights
+    and results rounded to bf16, per anchor against the largest token; once more 2^-8 between two such results."""
+    log("token range", tokens, anchors, dim, binades, inv_tau)
+    rng = np.random.default_rng(tokens + dim)
+    a = rng.standard_normal((anchors, dim)).astype(np.float32)
+    x = rng.standard_normal((2, tokens, dim)).astype(np.float32)
+    x[0, ::7] = a[np.arange(0, tokens, 7) % anchors]
+    x[1] = -a[0] + 0.01 * x[1]
+    x, x32 = wl.quantize(x, "bf16")
+    a, a32 = wl.quantize(a, "bf16")
+    scaled = torch.from_numpy(x32 * np.float32(2.0) ** binades).bfloat16().cuda()
+    z, tw = bd.civic_anchor_aggregate(scaled, to_dev(a), inv_tau, want_token_weight=True)
+    ref, ref_tw = oracle.anchor_aggregate(x32, a32, inv_tau, want_col_sum=True)
+    rel = 2.0 ** -8 + 4 * inv_tau * 2.0 ** -9 / np.sqrt(3 * dim)
+    got = z.float().cpu().numpy().astype(np.float64) * 2.0 ** -binades
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= rel * np.abs(x32).max(), float(np.abs(got - ref).max())
+    assert (np.abs(to_host(tw).astype(np.float64) - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all()
+
+
 @pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 161])
 @pytest.mark.parametrize("dtype,head_dim", [("fp32", 8), ("fp32", 64), ("fp32", 72), ("fp32", 128), ("fp32", 136), ("fp32", 192),
                                             ("fp32", 256), ("bf16", 136), ("bf16", 192), ("bf16", 256)])
