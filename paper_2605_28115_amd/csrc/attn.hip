@@ -78,7 +78,7 @@ struct AttnArgs {
 
 // ---------------------------------------------------------------------------------- fp32 matrix-core path
 // fp32 inputs, and head sizes the bf16 kernel does not cover: all arithmetic in fp32 on v_mfma_f32_16x16x4f32.  A workgroup of
-// four wavefronts owns 16 query rows of one head and its wavefronts take every fourth tile of 32 keys, each with an online
+// four wavefronts owns 16 query rows of one head and its wavefronts take every fourth tile of keys, each with an online
 // softmax of its own; the four states meet in LDS at the end.  Splitting the keys is what fills the chip: these shapes have few
 // rows (469 rows x 16 heads are 480 workgroups of 16 rows), and one wavefront needs 64 clocks for 16 x 16 x 16 multiply-adds.
 // No operand goes through LDS on its way to the matrix cores.  The contraction of Q K^T may run over the channels in any order
@@ -99,15 +99,18 @@ __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
     }
 }
 
-constexpr int kF32Rows = 16, kF32Keys = 32, kF32Waves = 4;
+constexpr int kF32Rows = 16, kF32Waves = 4;
 static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * (kF32Waves * kF32Rows * (64 * nt + 4 + 2) + kF32Waves); }
 
-// NT: head_dim rounded up to 64, over 64.
+// NT: head_dim rounded up to 64, over 64.  Heads wider than 192 take 16 keys a tile: the operands of 32 do not fit the registers
+// (2 x 1024 rows, 8 heads of 256, fp32 / bf16: 1468 / 930 us on the vector units, 418 / 483 with 32 keys and 100 to 160 registers
+// spilled, 243 / 381 with 16).
 template <bool BF16, int NT>
 __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_kernel(AttnArgs a)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+    constexpr int SUB = NT <= 3 ? 2 : 1, KEYS = 16 * SUB;      // sub-tiles and keys of a tile
     constexpr int PITCH = 64 * NT + 4;                         // floats per staged row (padded against bank conflicts)
     float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows, * const st_odd = st_l + kF32Waves * kF32Rows;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
@@ -166,52 +169,52 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
     // From the tile of this key on some query does not see every key of a tile.  A hidden key's weight is 0, and 0 x V has to
     // stay 0 whatever that row of V holds: infinities and NaN are taken out there, and put back at the end for the rows that see
     // them (in the loop that would cost the registers it runs in).
-    const int mixed0 = (a.causal ? i0 + 1 : n_keys) / kF32Keys * kF32Keys;
+    const int mixed0 = (a.causal ? i0 + 1 : n_keys) / KEYS * KEYS;
     bool odd = false;
     // (a key past the last one re-reads it: its score is masked)
     auto k_row = [&](int key) { return kv_off + static_cast<int64_t>(min(key, n_keys - 1)) * a.ks[1]; };
-    float4 kf[2][4 * NT];
+    float4 kf[SUB][4 * NT];
     auto fetch_k = [&](int key0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < SUB; ++s) {
             const int64_t base = k_row(key0 + 16 * s + l16);
 #pragma unroll
             for (int t = 0; t < 4 * NT; ++t)
                 if (16 * t < d) kf[s][t] = load_quad<BF16>(a.k, base + (16 * t + 4 * kq < d ? 16 * t + 4 * kq : 0));
         }
     };
-    int key0 = w * kF32Keys;
+    int key0 = w * KEYS;
     if (key0 < n_keys) fetch_k(key0);
-    for (; key0 < n_keys; key0 += kF32Waves * kF32Keys) {
+    for (; key0 < n_keys; key0 += kF32Waves * KEYS) {
         if ((d & 8) != 0) {                                    // lanes past the row hold a piece of its front: 0 x it has to be 0
 #pragma unroll
             for (int t = 0; t < 4 * NT; ++t)
                 if (16 * t < d && 16 * t + 16 > d) {
 #pragma unroll
-                    for (int s = 0; s < 2; ++s)
+                    for (int s = 0; s < SUB; ++s)
                         if (16 * t + 4 * kq >= d) kf[s][t] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
         }
-        // S^T of 32 keys: two sub-tiles of 16, two partial sums each (four independent MFMA chains)
-        f32x4 sc[2][2];
+        // S^T: sub-tiles of 16 keys, two partial sums each (independent MFMA chains)
+        f32x4 sc[SUB][2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) sc[s][0] = sc[s][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < SUB; ++s) sc[s][0] = sc[s][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 4 * NT; ++t)
             if (16 * t < d) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int s = 0; s < 2; ++s) {
+                    for (int s = 0; s < SUB; ++s) {
                         const float kv[4] = {kf[s][t].x, kf[s][t].y, kf[s][t].z, kf[s][t].w};
                         const float qv[4] = {qf[t].x, qf[t].y, qf[t].z, qf[t].w};
                         sc[s][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[e], qv[e], sc[s][e & 1], 0, 0, 0);
                     }
             }
         // V rows of this tile, in flight under the softmax: step e of sub-tile s multiplies keys 16 s + 4 kq + e
-        float4 vf[2][4][NT];
+        float4 vf[SUB][4][NT];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < SUB; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int64_t base = k_row(key0 + 16 * s + 4 * kq + e);
@@ -221,11 +224,11 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
                     vf[s][e][T] = load_quad<BF16>(a.v, base + (c < d ? c : 0));
                 }
             }
-        const bool more = key0 + kF32Waves * kF32Keys < n_keys;
+        const bool more = key0 + kF32Waves * KEYS < n_keys;
         const int lim = a.causal ? min(qi + 1, n_keys) : n_keys;   // the lane sees keys below lim
-        float p[2][4], m_new = m;
+        float p[SUB][4], m_new = m;
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < SUB; ++s)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float z = sc[s][0][r] + sc[s][1][r];
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
         const float alpha = expf(m - m_use);
         float sum = 0.f;
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < SUB; ++s)
 #pragma unroll
             for (int r = 0; r < 4; ++r) { p[s][r] = expf(p[s][r] - m_use); sum += p[s][r]; }
         l = fmaf(l, alpha, sum);
@@ -247,20 +250,20 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
         for (int T = 0; T < NT; ++T)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[T][e] *= alpha;
-        if (more) fetch_k(key0 + kF32Waves * kF32Keys);        // the next tile's K rows fly under the second product
+        if (more) fetch_k(key0 + kF32Waves * KEYS);        // the next tile's K rows fly under the second product
         if (key0 >= mixed0) {
             auto finite = [&](float& x) __attribute__((always_inline)) {
                 if (!(fabsf(x) < INFINITY)) { x = 0.f; odd = true; }
             };
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+            for (int s = 0; s < SUB; ++s)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int T = 0; T < NT; ++T) { finite(vf[s][e][T].x); finite(vf[s][e][T].y); finite(vf[s][e][T].z); finite(vf[s][e][T].w); }
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < SUB; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
