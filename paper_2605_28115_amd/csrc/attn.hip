@@ -102,15 +102,13 @@ __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 constexpr int kF32Rows = 16, kF32Waves = 4;
 static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * (kF32Waves * kF32Rows * (64 * nt + 4 + 2) + kF32Waves); }
 
-// NT: head_dim rounded up to 64, over 64.  Heads wider than 192 take 16 keys a tile: the operands of 32 do not fit the registers
-// (2 x 1024 rows, 8 heads of 256, fp32 / bf16: 1468 / 930 us on the vector units, 418 / 483 with 32 keys and 100 to 160 registers
-// spilled, 243 / 381 with 16).
-template <bool BF16, int NT>
-__global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_kernel(AttnArgs a)
+// NT: head_dim rounded up to 64, over 64.  SUB: sub-tiles of 16 keys a tile (launch_f32_for says which).
+template <bool BF16, int NT, int SUB>
+__global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_kernel(AttnArgs a)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
-    constexpr int SUB = NT <= 3 ? 2 : 1, KEYS = 16 * SUB;      // sub-tiles and keys of a tile
+    constexpr int KEYS = 16 * SUB;                             // SUB sub-tiles of 16 keys a tile
     constexpr int PITCH = 64 * NT + 4;                         // floats per staged row (padded against bank conflicts)
     float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows, * const st_odd = st_l + kF32Waves * kF32Rows;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
@@ -321,7 +319,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 2 ? 2 : 1) void attn_f32_k
     }
 }
 
-template <bool BF16, int NT>
+template <bool BF16, int NT, int SUB>
 static int launch_f32(const AttnArgs& a, hipStream_t s)
 {
     const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(a.seq) + kF32Rows - 1) / kF32Rows), static_cast<unsigned>(a.n_q_heads),
@@ -329,20 +327,27 @@ static int launch_f32(const AttnArgs& a, hipStream_t s)
     constexpr size_t lds = f32_lds_bytes(NT);
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
-        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<BF16, NT>), lds, &allowed);
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<BF16, NT, SUB>), lds, &allowed);
         if (rc != CIVIC_OK) return rc;
     }
-    civic::launch((attn_f32_kernel<BF16, NT>), grid, dim3(kF32Waves * kWave), lds, s, a);
+    civic::launch((attn_f32_kernel<BF16, NT, SUB>), grid, dim3(kF32Waves * kWave), lds, s, a);
     return check_launch();
 }
 
 template <bool BF16>
 static int launch_f32_for(const AttnArgs& a, hipStream_t s)
 {
-    if (a.head_dim <= 64) return launch_f32<BF16, 1>(a, s);
-    if (a.head_dim <= 128) return launch_f32<BF16, 2>(a, s);
-    if (a.head_dim <= 192) return launch_f32<BF16, 3>(a, s);
-    return launch_f32<BF16, 4>(a, s);
+    // 32 keys a tile for long contexts, but 16
+    //   - up to 64 keys, one tile for each wavefront, where the instructions of the longer tile are most of the time (17 rows,
+    //     4 / 2 fp32 heads of 64 / 128: 4.4 / 6.0 us, 5.3 / 7.7 in tiles of 32, 4.2 / 5.8 with one row per wavefront on the vector
+    //     units; 32 x 64 rows, 16 / 8 heads of 128: 33.1, 41.2 and 172.8)
+    //   - for heads wider than 128, where two workgroups then fit a unit (up to 192) and nothing is spilled (beyond): 469
+    //     rows, 16 / 8 fp32 heads of 192 / 256: 36.0 / 72.4 us, 56.6 / 120.7 in tiles of 32; bf16 45.8 / 102, 69.7 / 144
+    const bool few = a.kv_seq <= 64;
+    if (a.head_dim <= 64) return few ? launch_f32<BF16, 1, 1>(a, s) : launch_f32<BF16, 1, 2>(a, s);
+    if (a.head_dim <= 128) return few ? launch_f32<BF16, 2, 1>(a, s) : launch_f32<BF16, 2, 2>(a, s);
+    if (a.head_dim <= 192) return launch_f32<BF16, 3, 1>(a, s);
+    return launch_f32<BF16, 4, 1>(a, s);
 }
 
 // --------------------------------------------------------------------------------------- MFMA path

@@ -139,6 +139,23 @@ def test_fp32_attention_tiles(bd, seq, dtype, head_dim):
             assert (widen(c[:, :, :2]) == 7.0).all() and (widen(c[:, :, 2 + seq:]) == 7.0).all()
 
 
+@pytest.mark.parametrize("n_kv", [1, 16, 48, 63, 64, 65, 80, 128, 193])
+@pytest.mark.parametrize("dtype,head_dim", [("fp32", 64), ("fp32", 128), ("fp32", 192), ("fp32", 256), ("bf16", 192), ("bf16", 256)])
+def test_fp32_attention_tile_lengths(bd, n_kv, dtype, head_dim):
+    """Tiles of 16 and of 32 keys on both sides of the rule between them (64 keys, 128 channels), over key counts that end on a
+    tile and beside one, with another number of queries.  Bars of test_fp32_attention_tiles."""
+    log("fp32 attention tiles", n_kv, dtype, head_dim)
+    rng = np.random.default_rng(n_kv + head_dim)
+    q, q32 = wl.quantize(rng.standard_normal((2, 19, 4, head_dim)).astype(np.float32), dtype)
+    k, k32 = wl.quantize(rng.standard_normal((2, n_kv, 2, head_dim)).astype(np.float32), dtype)
+    v, v32 = wl.quantize(rng.standard_normal((2, n_kv, 2, head_dim)).astype(np.float32), dtype)
+    out = widen(to_host(bd.civic_cross_attn(to_dev(q), to_dev(k), to_dev(v)))).astype(np.float64)
+    qq, kk, vv = (torch.from_numpy(x).double().transpose(1, 2) for x in (q32, k32, v32))
+    kk, vv = kk.repeat_interleave(2, 1), vv.repeat_interleave(2, 1)
+    ref = (torch.softmax((qq[:, :, :, None] * kk[:, :, None]).sum(-1) / head_dim ** 0.5, -1)[..., None] * vv[:, :, None]).sum(-2).transpose(1, 2).numpy()
+    assert np.abs(out - ref).max() <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(np.abs(ref).max()))
+
+
 @pytest.mark.parametrize("seq,at", [(17, 16), (40, 33), (64, 50), (150, 149)])
 @pytest.mark.parametrize("head_dim", [64, 72, 256])
 def test_fp32_attention_hidden_rows_hold_anything(bd, seq, at, head_dim):
