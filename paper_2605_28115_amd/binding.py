@@ -187,10 +187,11 @@ def _host(a: np.ndarray) -> int:
     return a.__array_interface__["data"][0]
 
 
-def _host_i64(values) -> np.ndarray:
-    if isinstance(values, np.ndarray) and values.dtype == np.int64 and values.flags.c_contiguous:
+def _host_array(values, dtype) -> np.ndarray:
+    """A contiguous host array of at least one dimension (a single number counts as one entry)."""
+    if isinstance(values, np.ndarray) and values.dtype == dtype and values.ndim and values.flags.c_contiguous:
         return values
-    return np.ascontiguousarray(np.asarray(values, dtype=np.int64))
+    return np.ascontiguousarray(np.asarray(values, dtype=dtype))
 
 
 _pack_i64x3 = struct.Struct("3q").pack       # three int64 as bytes, which a pointer argument takes as they are
@@ -255,7 +256,7 @@ def civic_score_visual(hidden: torch.Tensor, grid, frame_start: Sequence[int], a
     if hidden.dim() != 3 or not hidden.is_contiguous():
         raise ValueError("hidden must be contiguous [batch, S, dim]")
     batch, seq_len, dim = hidden.shape
-    fs = _host_i64(frame_start)
+    fs = _host_array(frame_start, np.int64)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     if scores is None:
@@ -296,7 +297,7 @@ def civic_compact(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, frame_start
         raise ValueError("pos_ids must be int32 [3, batch, S] and kept_idx int32")
     n_kept = kept_idx.shape[1]
     seq_c = seq_len - g.n_visual + n_kept
-    fs = _host_i64(frame_start)
+    fs = _host_array(frame_start, np.int64)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     if hidden_c is None:
@@ -326,7 +327,7 @@ def civic_compact_prefill(hidden: torch.Tensor, pos_ids: torch.Tensor, grid, fra
         raise ValueError("pos_ids must be int32 [3, batch, S]")
     n_kept = civic_kept_count(grid)
     seq_c = seq_len - g.n_visual + n_kept
-    fs = _host_i64(frame_start)
+    fs = _host_array(frame_start, np.int64)
     if fs.shape != (g.frames,):
         raise ValueError("frame_start must have one entry per frame")
     dev = hidden.device
@@ -392,7 +393,7 @@ def civic_prefill_attn_ragged(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
     caches [batch, H_kv, s_max, d] every sample's K and V rows are written to its own cache rows from pos0."""
     if k.shape != v.shape or k.stride() != v.stride() or q.dtype != k.dtype or q.dim() != 3 or k.dim() != 3 or q.stride(2) != 1 or k.stride(2) != 1:
         raise ValueError("q [total, H_q, d]; k and v [total, H_kv, d] of one shape, strides and dtype")
-    off = _host_i64(row_offsets)
+    off = _host_array(row_offsets, np.int64)
     batch = off.size - 1
     total, hq, d = q.shape
     if out is None:
@@ -498,8 +499,7 @@ def civic_decode_attn_ragged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: to
                              out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """The decode step with one context length per sample: q [batch, H_q, d] over rows [0, n_ctx[b]) of the caches."""
     batch, hq, hkv, d, s_max = _decode_shapes(q, k_cache, v_cache)
-    ctx = n_ctx if isinstance(n_ctx, np.ndarray) and n_ctx.dtype == np.int32 and n_ctx.flags.c_contiguous else \
-        np.ascontiguousarray(np.asarray(n_ctx, dtype=np.int32))
+    ctx = _host_array(n_ctx, np.int32)
     if ctx.shape != (batch,):
         raise ValueError("one context length per sample")
     if out is None:
@@ -648,7 +648,7 @@ def civic_kv_compress_ragged(k: torch.Tensor, v: torch.Tensor, r: torch.Tensor, 
     rows [row_offsets[b], row_offsets[b+1]) -> k_c, v_c [batch, S, ...]."""
     if k.shape != v.shape or not k.is_contiguous() or not v.is_contiguous() or not r.is_contiguous() or r.dtype != torch.float32:
         raise ValueError("k and v must be contiguous of one shape, r contiguous fp32 [total, S]")
-    off = _host_i64(row_offsets)
+    off = _host_array(row_offsets, np.int64)
     batch = off.size - 1
     width = int(np.prod(k.shape[1:]))
     s_mem = r.shape[1]
@@ -672,7 +672,7 @@ def civic_cross_attn_ragged(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, q
     """q [total, H_q, d] packed (item b owning rows [q_offsets[b], q_offsets[b+1])) over k, v [batch, n_kv, H_kv, d]."""
     if k.shape != v.shape or k.stride() != v.stride() or q.dtype != k.dtype or q.dim() != 3 or q.stride(2) != 1:
         raise ValueError("q [total, H_q, d]; k and v [batch, n_kv, H_kv, d] of one shape, strides and dtype")
-    off = _host_i64(q_offsets)
+    off = _host_array(q_offsets, np.int64)
     batch = off.size - 1
     total, hq, d = q.shape
     if out is None:

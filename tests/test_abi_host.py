@@ -368,3 +368,18 @@ def test_decode_workspace_holds_four_workgroups_per_unit(bd):
             splits = -(-1024 // pairs)
             need = bd.civic_decode_attn_workspace_bytes(bf16, batch, group * hkv, hkv, d, n)
             assert need <= (4 * batch * group * hkv * (d + 2) * splits if splits > 1 else 0), (group, batch, hkv, d, n)
+
+
+def test_a_single_number_is_an_array_of_one_entry(bd):
+    """Frame starts of one frame and the context of one sample may come as a plain number or a 0-d array: such a call gets past
+    the shape check, to the tensors (which are on the CPU here)."""
+    torch = __import__("torch")
+    hidden = torch.zeros((1, 20, 8), dtype=torch.bfloat16)
+    q, cache = torch.zeros((1, 2, 8), dtype=torch.bfloat16), torch.zeros((1, 2, 4, 8), dtype=torch.bfloat16)
+    for kind in (int, lambda v: np.array(v, dtype=np.int64), lambda v: np.array(v, dtype=np.int32), lambda v: np.array([v], dtype=np.int64)):
+        with pytest.raises(ValueError, match="device tensor"):
+            bd.civic_score_visual(hidden, (1, 4, 4, 2, 2, 1, 0, 5), kind(2), torch.zeros(8), 1.0)
+        with pytest.raises(ValueError, match="device tensor"):
+            bd.civic_decode_attn_ragged(q, cache, cache, kind(3))
+    with pytest.raises(ValueError, match="one entry per frame"):
+        bd.civic_score_visual(hidden, (1, 4, 4, 2, 2, 1, 0, 5), np.zeros((1, 1), dtype=np.int64), torch.zeros(8), 1.0)
