@@ -343,15 +343,17 @@ int civic_prefill_attn_rope(const void* q, const void* k, const void* v, void* o
 /* Soft anchor aggregation, Eq. 8 in full - the paper's own, learned route from T_e dense patch embeddings to M_e
  * compact tokens, before the visual encoder:
  *   K_0 = Norm(LN(X_0)),  Q_A = Norm(LN(A)),  W_A = softmax(Q_A K_0^T / tau) over the dense tokens,  Z_0 = W_A X_0.
- * LN without affine (its epsilon cancels under Norm); a row without variance normalises to zero.  K_0, Q_A and
- * W_A are rounded to bf16 for the two contractions (bf16 MFMA, fp32 accumulation); the softmax is fp32.
+ * LN without affine (its epsilon cancels under Norm); a row without variance normalises to zero.  Q_A and the
+ * softmax weights are rounded to bf16 for the two contractions (bf16 MFMA, fp32 accumulation), K_0 enters as X_0
+ * with each row's mean and norm applied to the fp32 product; the softmax is fp32.
  *   x0            device [batch, n_tokens, dim] bf16, dense
  *   anchors       device [n_anchors, dim] bf16: A itself, not normalised (shared by the batch)
  *   z0            device [batch, n_anchors, dim] bf16
  *   token_weight  device [batch, n_tokens] fp32 or NULL: sum over the anchors of W_A[a, i], the weight each dense
  *                 token receives (a multi-anchor importance score that civic_select accepts)
  *   workspace     device, 16-byte aligned, civic_anchor_aggregate_workspace_bytes(same sizes) bytes: normalised
- *                 rows, logits, weights, X_0 transposed; no initialisation needed
+ *                 anchors, the tokens' statistics, row sums, weights, and room for fp32 logits, which are written
+ *                 above inv_tau = 60 only (the size does not depend on inv_tau); no initialisation needed
  * dtype must be CIVIC_BF16 and dim a multiple of 64 (else CIVIC_ERR_UNSUPPORTED); inv_tau >= 0, finite. */
 size_t civic_anchor_aggregate_workspace_bytes(int32_t batch, int32_t n_tokens, int32_t n_anchors, int32_t dim);
 int civic_anchor_aggregate(const void* x0, const void* anchors, int dtype, int32_t batch, int32_t n_tokens,

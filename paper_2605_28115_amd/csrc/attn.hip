@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
         for (int T = 0; T < NT; ++T)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[T][e] *= alpha;
-        if (more) fetch_k(key0 + kF32Waves * KEYS);        // the next tile's K rows fly under the second product
+        if (more) fetch_k(key0 + kF32Waves * KEYS);            // the next tile's K rows fly under the second product
         if (key0 >= mixed0) {
             auto finite = [&](float& x) __attribute__((always_inline)) {
                 if (!(fabsf(x) < INFINITY)) { x = 0.f; odd = true; }

@@ -5,7 +5,8 @@
 //
 // The context of a (batch item, KV head) is split over several workgroups so that a launch of a few dozen
 // (item, head) pairs still covers the chip; a workgroup serves all query heads of its KV head at once (up to 8
-// per pass), so K and V are read once per group, not once per query head.
+// per pass, 16 on the matrix cores), so K and V are read once per group, not once per query head.
+// The vector kernel (fp32, one or two bf16 heads per KV head, head_dim above 128):
 //   - A cache row is read by LPR adjacent lanes, 16 bytes each (LPR = row bytes / 16 rounded up to a power of two),
 //     64 / LPR rows per wavefront instruction; a lane's loads of a round (U rows of K and the same rows of V) are
 //     issued before anything is computed, so a workgroup whose share is one round makes a single trip to memory.
@@ -270,9 +271,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     }
 }
 
-// The same for bf16 caches with head_dim <= 128 and at least three query heads per KV head, on the matrix cores: all query heads of a KV head (up to 16 per pass) are the
-// columns of one MFMA tile, so the vector work per cache row no longer grows with the heads, and a workgroup that has little
-// context gets through it in a few memory latencies.  (Per 64 rows of 128 channels and four heads the kernel above needs about
+// The same for bf16 caches with head_dim <= 128 and at least three query heads per KV head, on the matrix cores: all query heads
+// of a KV head (up to 16 per pass) are the columns of one MFMA tile, so the vector work per cache row no longer grows with the
+// heads, and a workgroup that has little context gets through it in a few memory latencies.  (Per 64 rows of 128 channels and four heads the kernel above needs about
 // 450 vector instructions a wavefront and 1.4 us; bound by that, not by memory, whenever a workgroup runs alone.)
 //   - A wavefront takes 32 keys a step.  K rows are read as they lie (lane = key, 16-byte chunks of the row in any order that Q
 //     shares) and are the first operand of v_mfma_f32_16x16x32_bf16.  The two 16-key tiles of a step hold keys 8 a + r and
@@ -284,16 +285,18 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 //     from the rounded exact ones four times as often as with fp32 weights).  The third costs 8 MFMAs a step, which memory hides,
 //     and registers, which scalar base addresses gave back (with vector ones 20 were spilled: 64 samples of 117..3584 rows 99 us).
 //   - Each wavefront runs its own online softmax; the states meet in LDS at the end.
-// Against the kernel above (us): 64 x 938 rows, 32 / 8 heads 45.5 -> 42.3 (5.8 TB/s); 64 x 3584 154 -> 142 (6.6 TB/s); 4 x 938
-// 10.6 -> 9.1; 16 x 2000 with 64 / 8 heads 43.8 -> 28.6.  With one or two heads the vector work is less than the gathering here
-// (32 x 1000, 16 / 16 heads of 64: 22.5 there, 26.0 here; 8 x 1280, 16 / 8 heads 12.8, 13.8), so those stay there.
+// Against the kernel above (us): 64 x 938 rows, 32 / 8 heads 45.5 -> 40.9 (6.0 TB/s); 64 x 3584 154 -> 140 (6.7 TB/s); 4 x 938
+// 10.6 -> 9.0; 16 x 2000 with 64 / 8 heads 43.8 -> 27.7, 32 x 2000 with 32 / 2 43.8 -> 19.6.  With one or two heads the vector
+// work is less than the gathering here (32 x 1000, 16 / 16 heads of 64: 22.5 there, 26.0 here; 8 x 1280, 16 / 8 heads 12.8, 13.8),
+// so those stay there.
 template <typename TABLE>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs a, TABLE tab)
 {
     constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
     constexpr int WAVES = kDecWaves, THREADS = kDecThreads, KT = 4;      // K chunks of 32 channels
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid >> 6);   // (w uniform: loads from scalar bases)
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform for the compiler: loads take scalar base addresses)
     const int l16 = lane & 15, kq = lane >> 4;
     const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
     const int b = blockIdx.z, split = blockIdx.x, d = a.head_dim;
@@ -406,7 +409,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs 
             const float r0 = p0 - __uint_as_float(ph[e] << 16), r1 = p1 - __uint_as_float(ph[e] & 0xFFFF0000u);
             const dec_bf16x2 mid = {static_cast<__bf16>(r0), static_cast<__bf16>(r1)};
             pm[e] = __builtin_bit_cast(uint32_t, mid);
-            const dec_bf16x2 lo = {static_cast<__bf16>(r0 - __uint_as_float(pm[e] << 16)), static_cast<__bf16>(r1 - __uint_as_float(pm[e] & 0xFFFF0000u))};
+            const dec_bf16x2 lo = {static_cast<__bf16>(r0 - __uint_as_float(pm[e] << 16)),
+                                   static_cast<__bf16>(r1 - __uint_as_float(pm[e] & 0xFFFF0000u))};
             pl[e] = __builtin_bit_cast(uint32_t, lo);
         }
 #pragma unroll
@@ -649,14 +653,18 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     int32_t unused;
     const int64_t room_units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * vec_blocks;
     cut((1024 + room_units - 1) / room_units, static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU, &p->max_splits, &unused);
-    if (ragged) p->max_splits = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(p->max_splits, (n_ctx + kDecRaggedKeys - 1) / kDecRaggedKeys), kDecMaxSplits));
+    if (ragged) {
+        const int64_t pieces = std::max<int64_t>(p->max_splits, (n_ctx + kDecRaggedKeys - 1) / kDecRaggedKeys);
+        p->max_splits = static_cast<int32_t>(std::min<int64_t>(pieces, kDecMaxSplits));
+    }
     // What is launched: nothing to combine once the (item, KV head) pairs fill the chip by themselves (64 x 938 rows, 8 KV
     // heads: one split 45.5 us, two 52; 64 x 3584: 153 against 172); otherwise two workgroups per unit in at most 8 splits, which
     // one trip of the combining launch reads (16 x 938: 4 splits 18.7 us, 8 splits 20.8; 4 x 938: 8 splits 10.3 us, 15 splits
     // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).  Nor is a context cut that one
     // workgroup gets through before a second launch would have started (1 x 256 rows, 32 / 8 heads: 7.0 us whole, 7.8 in two).
     p->whole_keys = static_cast<int>(whole_keys);
-    cut(units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units), round_keys, &p->splits, &p->keys_per_split);
+    const int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
+    cut(wanted, round_keys, &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
     p->lds_bytes = sizeof(float) * kDecWaves * static_cast<size_t>(p->hg) * (head_dim + 2);   // one state per wavefront and head
     return CIVIC_OK;
@@ -704,11 +712,14 @@ static int launch_decode_kernel(const DecodeArgs& a, const TABLE& t, const Decod
 template <bool BF16, int HG, typename TABLE>
 static int launch_decode_lpr(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
+    if constexpr (!BF16 || HG <= 2) {                           // (bf16 rows of up to 16 chunks with more heads: the matrix cores)
+        if (p.lpr == 8) return launch_decode_kernel<BF16, HG, 8>(a, t, p, s);
+        if (p.lpr == 16) return launch_decode_kernel<BF16, HG, 16>(a, t, p, s);
+    }
     switch (p.lpr) {
-        case 8: return launch_decode_kernel<BF16, HG, 8>(a, t, p, s);
-        case 16: return launch_decode_kernel<BF16, HG, 16>(a, t, p, s);
         case 32: return launch_decode_kernel<BF16, HG, 32>(a, t, p, s);
-        default: return launch_decode_kernel<BF16, HG, 64>(a, t, p, s);
+        case 64: return launch_decode_kernel<BF16, HG, 64>(a, t, p, s);
+        default: return CIVIC_ERR_UNSUPPORTED;
     }
 }
 

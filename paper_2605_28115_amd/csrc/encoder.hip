@@ -5,7 +5,7 @@
 // (the attention over the compressed keys, softmax(Q K_c^T / sqrt(d)) V_c, is civic_cross_attn in attn.hip).
 //
 // Both are dense contractions and run on the bf16 MFMA pipe through one kernel, C = alpha * A B^T, whose B operand
-// may be stored either way round: like A, with the contraction index contiguous (the logits Q_A K_0^T), or with the
+// may be stored either way round: like A, with the contraction index contiguous (the products Q_A X_0^T behind the logits), or with the
 // contraction index as the row index, which is how X_0 lies in Z_0 = W_A X_0 and how K and V lie in Eq. 9; those are
 // read where they are (transposing LDS reads), no transposed copy is made.  A is always contraction-contiguous and
 // zero-padded to a multiple of 64 in that direction (W_A and Rbar^T are written that way), so the GEMM has no tail
@@ -20,8 +20,9 @@
 //     slower, 46.6 against 35.3 us on the 1365 x 4096 x 1152 logits), four stages for grids that leave units without a
 //     second workgroup anyway, where the latency of a tile is what a workgroup waits for.
 //   - K_c and V_c of Eq. 9 come from one launch (grid z = batch item x tensor).
-// The softmax of Eq. 8 runs over rows of 4096 logits and more, too long for a fused epilogue: the logits go to
-// scratch in fp32, a row kernel turns them into bf16 weights, the second GEMM consumes those.
+// The softmax of Eq. 8 has two routes.  A logit never exceeds inv_tau in size, so up to 60 the first product's epilogue writes
+// exponentials in bf16 and their partial row sums, and the second product divides by those: no logits in memory, no softmax
+// launch.  A colder softmax needs its row's maximum: logits in fp32 to scratch, a row kernel into bf16 weights, the second product.
 #include <algorithm>
 #include <cmath>
 
@@ -443,7 +444,9 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
 #pragma unroll
                         for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
                     }
-                    const enc_bf16x4 o = {static_cast<__bf16>(t[0]), static_cast<__bf16>(t[1]), static_cast<__bf16>(t[2]), static_cast<__bf16>(t[3])};
+                    enc_bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(t[e]);
                     *reinterpret_cast<enc_bf16x4*>(reinterpret_cast<__bf16*>(c_base) + static_cast<int64_t>(row) * g.ldc + col_q + c4) = o;
                 }
             return;
@@ -640,11 +643,11 @@ __global__ __launch_bounds__(256) void row_softmax_kernel(const float* __restric
     }
 }
 
-// out[b, j] = sum over rows of p[b, row, j] * row_scale[b, row] (1 where row_scale is null): the weight a dense token receives from all anchors together.  One pass over
-// the weights, so memory-bound: a workgroup owns 64 columns (one 128-byte line of every row) and its 1024 threads are 8
-// column chunks x 128 row slots, 16 bytes a load, four rows in flight per thread; the slots meet in a fixed order (shuffles,
-// then LDS), so the sums are the same every time.  1365 x 4096 weights, two items: 313 us as one thread per column walking
-// all rows (32 workgroups, one 2-byte load in flight each), 6.8 us so.
+// out[b, j] = sum over rows of p[b, row, j] * row_scale[b, row] (1 where row_scale is null): the weight a dense token receives
+// from all anchors together.  One pass over the weights, so memory-bound: a workgroup owns 64 columns (one 128-byte line of
+// every row) and its 1024 threads are 8 column chunks x 128 row slots, 16 bytes a load, four rows in flight per thread; the
+// slots meet in a fixed order (shuffles, then LDS), so the sums are the same every time.  1365 x 4096 weights, two items: 313 us
+// as one thread per column walking all rows (32 workgroups, one 2-byte load in flight each), 6.8 us so.
 constexpr int kColSumThreads = 1024, kColSumCols = 64;
 __global__ __launch_bounds__(kColSumThreads) void col_sum_kernel(const __bf16* __restrict__ p, int32_t rows, int32_t cols, int64_t ld_p,
                                                                  int64_t batch_stride, const float* __restrict__ row_scale,
