@@ -14,7 +14,7 @@
 //     summed over the row's lanes; every lane of the row then holds the row's logits.
 //   - Each (wavefront, row slot) runs its own online softmax over the rows it meets: no barrier and no LDS in
 //     the loop.  The lane keeps the 8 output channels of its chunk for every head in fp32.
-//   - At the end the partial states of a wavefront meet in registers and those of the workgroup in LDS; it writes the final
+//   - At the end the 4 * 64 / LPR partial states of the workgroup meet, in registers and LDS; it writes the final
 //     rows (one split) or its (max, sum, unnormalised output) into the workspace, which a second small launch
 //     combines.
 #include <algorithm>
@@ -104,6 +104,11 @@ __device__ __forceinline__ float over_slots(float v, OP op)
 template <int LPR> __device__ __forceinline__ float slots_sum(float v) { return over_slots<LPR>(v, [](float x, float y) { return x + y; }); }
 template <int LPR> __device__ __forceinline__ float slots_max(float v) { return over_slots<LPR>(v, [](float x, float y) { return fmaxf(x, y); }); }
 
+// States of the vector kernel's workgroup that meet in LDS: one per wavefront where a wavefront holds 8 row slots, one per slot
+// elsewhere.  Sums in registers take two lane swaps a value and halving of the slots, LDS one round trip a slot (21 x 16 rows, 8 / 8
+// bf16 heads of 64, 8 slots: 3.7 us in registers, 4.1 in LDS; 85 x 23 rows, 28 / 4 fp32 heads of 64, 4 slots: 7.7 and 6.9).
+constexpr int decode_states(int lpr) { return lpr == 8 ? kDecWaves : kDecWaves * (kWave / lpr); }
+
 template <bool BF16, int HG, int LPR, typename TABLE>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
@@ -113,10 +118,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     constexpr int RPS = kWave / LPR;      // cache rows per wavefront instruction
     constexpr int SLOTS = kDecWaves * RPS;   // independent softmax streams per workgroup
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
-    // of every wavefront: [HG][d] outputs, [HG] maxima, [HG] sums
+    constexpr int STATES = decode_states(LPR);
+    // of every state that meets in LDS: [HG][d] outputs, [HG] maxima, [HG] sums
     float* sm_o = dec_lds;
-    float* sm_m = dec_lds + kDecWaves * HG * a.head_dim;
-    float* sm_l = sm_m + kDecWaves * HG;
+    float* sm_m = dec_lds + STATES * HG * a.head_dim;
+    float* sm_l = sm_m + STATES * HG;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
@@ -220,27 +226,31 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         }
     }
 
-    // The row slots of a wavefront meet in registers (every lane of a chunk then holds the wavefront's state) ...
+    int state = w * RPS + r;
+    bool writes = true;
+    if constexpr (STATES == kDecWaves) {                       // a wavefront's slots meet in registers first
+#pragma unroll
+        for (int hh = 0; hh < HG; ++hh) {
+            const float mw = slots_max<LPR>(m[hh]);
+            const float f = m[hh] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[hh] - mw);
+            m[hh] = mw;
+            l[hh] = slots_sum<LPR>(l[hh] * f);
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[hh][e] = slots_sum<LPR>(acc[hh][e] * f);
+        }
+        state = w;
+    }
+    // the workgroup's states meet in LDS
 #pragma unroll
     for (int hh = 0; hh < HG; ++hh) {
-        const float mw = slots_max<LPR>(m[hh]);
-        const float f = m[hh] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[hh] - mw);
-        m[hh] = mw;
-        l[hh] = slots_sum<LPR>(l[hh] * f);
+        if constexpr (STATES == kDecWaves) writes = hh % RPS == r;   // (every slot holds the sums: slot r writes heads r, r + RPS, ...)
+        if (writes && c == 0) { sm_m[state * HG + hh] = m[hh]; sm_l[state * HG + hh] = l[hh]; }
+        if (writes && chunk_live) {
+            float4* dst = reinterpret_cast<float4*>(sm_o + (state * HG + hh) * d + c * E);
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[hh][e] = slots_sum<LPR>(acc[hh][e] * f);
-    }
-    // ... and the wavefronts in LDS; slot r writes the heads r, r + RPS, ...
-#pragma unroll
-    for (int hh = 0; hh < HG; ++hh)
-        if (hh % RPS == r) {
-            if (c == 0) { sm_m[w * HG + hh] = m[hh]; sm_l[w * HG + hh] = l[hh]; }
-            if (chunk_live) {
-                float4* dst = reinterpret_cast<float4*>(sm_o + (w * HG + hh) * d + c * E);
-#pragma unroll
-                for (int e = 0; e < E; e += 4) dst[e / 4] = make_float4(acc[hh][e], acc[hh][e + 1], acc[hh][e + 2], acc[hh][e + 3]);
-            }
+            for (int e = 0; e < E; e += 4) dst[e / 4] = make_float4(acc[hh][e], acc[hh][e + 1], acc[hh][e + 2], acc[hh][e + 3]);
         }
+    }
     __syncthreads();
     for (int i = tid; i < HG * d; i += kDecThreads) {
         const int hh = i / d, ch = i - hh * d;
@@ -248,10 +258,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         if (hg >= a.group) continue;
         float mx = sm_m[hh];
 #pragma unroll
-        for (int x = 1; x < kDecWaves; ++x) mx = fmaxf(mx, sm_m[x * HG + hh]);
+        for (int x = 1; x < STATES; ++x) mx = fmaxf(mx, sm_m[x * HG + hh]);
         float o = 0.f, lt = 0.f;
 #pragma unroll
-        for (int x = 0; x < kDecWaves; ++x) {
+        for (int x = 0; x < STATES; ++x) {
             const float ms = sm_m[x * HG + hh];
             const float wgt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - mx);
             o = fmaf(wgt, sm_o[(x * HG + hh) * d + ch], o);
@@ -666,7 +676,7 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     const int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
     cut(wanted, round_keys, &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
-    p->lds_bytes = sizeof(float) * kDecWaves * static_cast<size_t>(p->hg) * (head_dim + 2);   // one state per wavefront and head
+    p->lds_bytes = sizeof(float) * (p->mfma ? kDecWaves : decode_states(p->lpr)) * static_cast<size_t>(p->hg) * (head_dim + 2);
     return CIVIC_OK;
 }
 
