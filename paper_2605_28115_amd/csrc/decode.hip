@@ -30,7 +30,8 @@ constexpr int kDecU = 4;                 // cache rows per lane and round
 
 constexpr int kDecFullUnits = 384;       // (sample, KV head, head block) triples that keep the chip busy without a split
 
-constexpr int kDecRaggedKeys = 512;       // rows per piece of a ragged launch that fills the chip
+constexpr int kDecRaggedUnits = 256;     // the same where every sample has its own context length
+constexpr int kDecRaggedKeys = 512, kDecVecRaggedKeys = 256;   // rows per piece of a ragged launch that fills the chip
 constexpr int kDecTailKeys = 448;         // rows by which the longest context may exceed the average before it is cut
 constexpr int kDecRaggedItems = 256;     // samples of one launch when every sample has its own context length
 
@@ -283,8 +284,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 
 // The same for bf16 caches with head_dim <= 128 and at least three query heads per KV head, on the matrix cores: all query heads
 // of a KV head (up to 16 per pass) are the columns of one MFMA tile, so the vector work per cache row no longer grows with the
-// heads, and a workgroup that has little context gets through it in a few memory latencies.  (Per 64 rows of 128 channels and four heads the kernel above needs about
-// 450 vector instructions a wavefront and 1.4 us; bound by that, not by memory, whenever a workgroup runs alone.)
+// heads, and a workgroup that has little context gets through it in a few memory latencies.  (Per 64 rows of 128 channels and
+// four heads the kernel above needs about 450 vector instructions a wavefront and 1.4 us; bound by that, not by memory, whenever
+// a workgroup runs alone.)
 //   - A wavefront takes 32 keys a step.  K rows are read as they lie (lane = key, 16-byte chunks of the row in any order that Q
 //     shares) and are the first operand of v_mfma_f32_16x16x32_bf16.  The two 16-key tiles of a step hold keys 8 a + r and
 //     8 a + 4 + r in row 4 a + r: a lane then owns the logits of 8 consecutive keys of one head, which is the second operand
@@ -621,6 +623,8 @@ struct DecodePlan {
     bool mfma;
     int hg, lpr, head_blocks, round_keys;
     int whole_keys;                      // contexts up to this are not cut
+    // pieces of different contexts: whole samples from ragged_units pairs on; else no more than ragged_groups, or of ragged_keys rows
+    int ragged_units, ragged_keys, ragged_groups;
     int32_t splits, keys_per_split;      // of one context length for all samples
     int32_t max_splits;                  // per sample, at most: what the workspace is sized for
     size_t ws_bytes, lds_bytes;
@@ -646,7 +650,8 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     while (p->lpr < cpr) p->lpr *= 2;
     const int64_t units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * p->head_blocks;
     const int64_t round_keys = p->mfma ? 32 * kDecWaves : static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU;
-    const int64_t whole_keys = round_keys * (p->mfma ? 2 : 4);
+    const bool heavy = !p->mfma && p->hg > 4;                  // 8 heads on the vector units: a round is long, two workgroups fill a unit
+    const int64_t whole_keys = round_keys * (p->mfma || heavy ? 2 : 4);
     p->round_keys = static_cast<int>(round_keys);
     // whole rounds per split, no split shorter than one round
     auto cut = [&](int64_t splits, int64_t round, int32_t* n, int32_t* keys) {
@@ -663,8 +668,11 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     int32_t unused;
     const int64_t room_units = static_cast<int64_t>(batch > 0 ? batch : 1) * n_kv_heads * vec_blocks;
     cut((1024 + room_units - 1) / room_units, static_cast<int64_t>(kDecWaves) * (kWave / p->lpr) * kDecU, &p->max_splits, &unused);
+    p->ragged_keys = p->mfma || heavy ? kDecRaggedKeys : kDecVecRaggedKeys;
+    p->ragged_groups = p->mfma || heavy ? 512 : 1024;
+    p->ragged_units = heavy ? kDecFullUnits : kDecRaggedUnits;
     if (ragged) {
-        const int64_t pieces = std::max<int64_t>(p->max_splits, (n_ctx + kDecRaggedKeys - 1) / kDecRaggedKeys);
+        const int64_t pieces = std::max<int64_t>(p->max_splits, (n_ctx + p->ragged_keys - 1) / p->ragged_keys);
         p->max_splits = static_cast<int32_t>(std::min<int64_t>(pieces, kDecMaxSplits));
     }
     // What is launched: nothing to combine once the (item, KV head) pairs fill the chip by themselves (64 x 938 rows, 8 KV
@@ -673,7 +681,17 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     // 12.6), or one per unit in more (1 x 3584: 28 splits 11.9 us, 57 splits 13.0, 8 splits 16).  Nor is a context cut that one
     // workgroup gets through before a second launch would have started (1 x 256 rows, 32 / 8 heads: 7.0 us whole, 7.8 in two).
     p->whole_keys = static_cast<int>(whole_keys);
-    const int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
+    // The vector kernel with 4 or 8 heads a pass is bound by its instructions and takes more workgroups per unit: 4 splits (74 x 968
+    // rows, 16 / 4 fp32 heads of 96: 63 us in one, 49 in four; 22 x 392, 32 / 8 of 128: 22.5 in two, 21.3 in four), or 8 where
+    // several passes read the same rows, which then run on one XCD (grid x a multiple of 8) and share its L2 (24 x 2500, 28 / 4
+    // of 128: 93 us in two, 65 in eight).  As long as a split is two rounds, and the workspace has the room.
+    int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
+    // The same 4 where the matrix cores would run one workgroup on most units and two on some through a long context (80 x 2918
+    // rows, 16 / 4 heads of 72, 320 pairs: 87 us in one, 74 in four).
+    const int64_t busy = !p->mfma && p->head_blocks > 1 ? 8 : 4, shortest = (p->mfma ? 8 : 2 * busy) * round_keys;
+    const bool more = p->mfma ? units > 256 : p->hg > 2;
+    if (more && wanted < busy && units < kDecFullUnits && n_ctx > whole_keys && n_ctx >= shortest)
+        wanted = std::min<int64_t>(busy, (1024 + room_units - 1) / room_units);
     cut(wanted, round_keys, &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
     p->lds_bytes = sizeof(float) * (p->mfma ? kDecWaves : decode_states(p->lpr)) * static_cast<size_t>(p->hg) * (head_dim + 2);
@@ -682,10 +700,15 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
 
 // How samples of different context lengths are cut into pieces of one length (the last piece of a sample is what is left):
 //   - not at all when the pairs fill the chip and the longest context is within 448 rows of the average: its workgroups then
-//     outlast the others by less than a second launch costs (96 samples of 100..800 rows: 41 us, 45-50 us cut)
+//     outlast the others by less than a second launch costs (96 samples of 100..800 rows: 41 us, 45-50 us cut; from 256
+//     pairs on: 40 samples of 152..300, 32 / 8 heads 13.2 us, 16.2-19.3 cut; 40 of 85..600, 16 / 8 heads 16.3, 17.7-24.5 cut)
 //   - else into the shortest pieces that make at most 512 workgroups, or pieces of 512 rows if that takes longer ones
 //     (64 samples of 117..3584 rows, 8 KV heads: 97 us; 118 us in pieces of 128, 103 of 1024, 129 uncut; the same grid for
 //     every sample, laid out for the longest context, took 133 us, half of its workgroups with nothing to do)
+//   - the vector kernel with up to 4 heads a pass into at most 1024 workgroups, or pieces of 256 rows (64 samples of 345..2500,
+//     16 / 4 fp32 heads of 96: 63 us, 69 in pieces of 512; 24 of 345..2500, 16 / 8 bf16 heads of 128: 28.0, 30.5; 17 of 57..457:
+//     10.1, 11.2), but no more than 512 of a single round of 32 rows.  (With 8 heads a pass 512 as well, and whole samples from
+//     384 pairs on only: 80 of 694..1388, 32 / 4 fp32 heads of 64 58 us, 69 in 1024 or whole.)
 // Never more pieces per sample than the workspace holds, max_splits.
 static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, DecodePlan* p)
 {
@@ -694,13 +717,13 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, Deco
     for (int32_t i = 0; i < batch; ++i) { rows += ctx_of[i]; longest = std::max(longest, ctx_of[i]); }
     const int64_t per_sample = units / batch;
     int64_t kps = p->round_keys;
-    if (longest <= p->whole_keys || (units >= kDecFullUnits && longest - rows / batch <= kDecTailKeys)) kps = longest;
+    if (longest <= p->whole_keys || (units >= p->ragged_units && longest - rows / batch <= kDecTailKeys)) kps = longest;
     for (;; kps += p->round_keys) {                           // (ends: a piece as long as the longest context is one per sample)
         const int64_t most = (longest + kps - 1) / kps;
         if (most > p->max_splits) continue;
         int64_t pieces = 0;
         for (int32_t i = 0; i < batch; ++i) pieces += (ctx_of[i] + kps - 1) / kps;
-        if (pieces * per_sample <= 512 || kps >= kDecRaggedKeys) break;
+        if (pieces * per_sample <= (kps < 64 ? 512 : p->ragged_groups) || kps >= p->ragged_keys) break;
     }
     p->keys_per_split = static_cast<int32_t>(kps);
     p->splits = static_cast<int32_t>((longest + kps - 1) / kps);

@@ -384,3 +384,29 @@ def test_noalloc_takes_groups_of_five_to_seven_heads(bd, batch, hq, hkv, d, n):
     out = torch.empty_like(q)
     bd.civic_decode_attn_noalloc(q, k, v, n, out)
     assert torch.equal(out, bd.civic_decode_attn(q, k, v, n))
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", [
+    (70, 16, 4, 96, [600] * 70, "fp32"), (20, 28, 4, 64, [1100] * 20, "fp32"), (12, 14, 2, 64, [511] * 12, "fp32"),   # 4 and 8 splits, and not
+    (3, 16, 2, 64, [128, 129, 300], "fp32"), (2, 8, 1, 128, [64, 65], "fp32"), (1, 9, 1, 256, [200], "fp32"),         # eight heads a pass
+    (2, 4, 1, 32, [257, 40], "fp32"), (2, 4, 1, 36, [33, 500], "fp32"), (3, 2, 2, 64, [90, 1, 400], "bf16"),          # 8 and 4 row slots
+    (3, 4, 2, 128, [90, 64, 400], "bf16"), (2, 2, 1, 512, [70, 9], "bf16"),                                          # 4 and 1
+    (30, 8, 4, 128, [1 + 17 * i for i in range(30)], "fp32"), (64, 8, 4, 64, [250 + 7 * i for i in range(64)], "fp32"),  # pieces, whole
+    (66, 16, 4, 72, [1100] * 66, "bf16"), (33, 32, 8, 64, [200 + i for i in range(33)], "bf16")])
+def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
+    """The rules of the cuts that go by the kernel and its heads a pass, and both ways a workgroup's states meet.  Rows past a
+    context are NaN.  fp32: bar of the parity tests; bf16 rounds the result once."""
+    log("decode cuts", dtype, batch, hq, hkv, d, max(ctx))
+    g = torch.Generator().manual_seed(sum(ctx))
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    q, k, v = (torch.randn((batch, h, *n, d), generator=g).to(dt) for h, n in ((hq, ()), (hkv, (max(ctx) + 1,)), (hkv, (max(ctx) + 1,))))
+    ref = torch.empty((batch, hq, d), dtype=torch.float64)
+    for b, n in enumerate(ctx):
+        ref[b] = _decode_reference(q[b:b + 1], k[b:b + 1], v[b:b + 1], n)[0]
+        k[b, :, n:], v[b, :, n:] = float("nan"), float("nan")
+    outs = [bd.civic_decode_attn_ragged(q.cuda(), k.cuda(), v.cuda(), ctx)]
+    if len(set(ctx)) == 1:
+        outs.append(bd.civic_decode_attn(q.cuda(), k.cuda(), v.cuda(), ctx[0]))
+    for out in outs:
+        err = float((out.cpu().double() - ref).abs().max())
+        assert err <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(ref.abs().max())), err
