@@ -179,9 +179,9 @@ int civic_compact(const void* hidden, int dtype, int32_t dim, const int32_t* pos
                   void* workspace, size_t workspace_bytes, void* stream);
 
 /* The front of the path in one call: civic_score_visual (Eq. 8), civic_select (budget and
- * floors) and civic_compact (Eq. 13) enqueued back to back on `stream`, with n_kept =
- * civic_kept_count(grid).  The results are those of the three calls, bit for bit; what the
- * call saves is host time (one crossing from the caller's language instead of three).
+ * floors) and civic_compact (Eq. 13) on `stream`, with n_kept = civic_kept_count(grid).  The
+ * results are those of the three calls, bit for bit; selection and merge are one launch, and
+ * there is one crossing from the caller's language instead of three.
  * Arguments as in the three calls; scores [batch, N_v] and kept_idx [batch, K] are outputs
  * here (intermediate results the caller may want).  Every check of every stage runs before
  * the first launch. */
@@ -205,9 +205,9 @@ int civic_compact_prefill(const void* hidden, int dtype, int32_t batch, int64_t 
  * CIVIC_ERR_INVALID_ARG on a bad grid or a sample shorter than its visual tokens.
  *
  * civic_compact_prefill_ragged: the three stages of civic_compact_prefill for all samples - the scores of up to 64
- * frame spans per launch, the selection of up to 16 samples per launch (a workgroup per sample, each with its own
- * grid), the merge of up to 24 samples per launch (a sample of more than 8 frames by a launch of its own, together
- * with the samples of the same shape that follow it) - with every check of every sample before the first launch.  seq_offsets[batch] and the visual tokens together <= INT32_MAX, else
+ * frame spans per launch, selection and merge of up to 16 samples per launch (each with its own grid; a sample of
+ * more than 8 frames by a launch of its own, together with the samples of the same shape that follow it) - with every
+ * check of every sample before the first launch.  seq_offsets[batch] and the visual tokens together <= INT32_MAX, else
  * CIVIC_ERR_UNSUPPORTED.
  *   hidden      device [seq_offsets[batch], dim];  pos_ids  device [3, seq_offsets[batch]] int32
  *   frame_start host, the samples' frame starts one after the other (grids[b].frames entries each), each

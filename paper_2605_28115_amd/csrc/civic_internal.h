@@ -76,31 +76,28 @@ int compact_check(const void* hidden, int dtype, int32_t dim, const int32_t* pos
                   const civic_grid* grid, const int64_t* frame_start, const int32_t* kept_idx, int64_t n_kept,
                   const void* hidden_c, const int32_t* pos_c, const int32_t* src_idx);
 
-// The launch of civic_compact for arguments that compact_check has passed; pos_axis_in / pos_axis_out are the element
-// distances between the three id axes of pos_ids and of pos_c.
-int compact_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, int32_t batch, int64_t seq_len,
-                   const civic_grid* grid, const int64_t* frame_start, const int32_t* kept_idx, int64_t n_kept, void* hidden_c,
-                   int32_t* pos_c, int32_t* src_idx, int64_t pos_axis_in, int64_t pos_axis_out, void* stream);
-
 // Up to 64 spans of rows of a packed tensor scored in one launch (the ragged front); arguments checked by the caller.
 int score_slices_launch(const void* hidden, int dtype, int32_t dim, const float* anchor_q, float inv_tau, float* scores,
                         const int32_t* first, const int32_t* count, const int32_t* out, int32_t n_slices, int32_t longest, void* stream);
 
-// Up to 16 samples of different grids selected in one launch (the ragged front); every sample checked by the caller.
-int select_samples_launch(const float* const* scores, int32_t* const* kept_idx, const civic_grid* const* grids, int32_t n, void* stream);
+// Selection and compact merge in one launch (merge.hip), arguments checked by the caller.  pos_axis_in / pos_axis_out: element
+// distances between the three id axes of pos_ids and of pos_c.
+int merge_batch_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, int32_t batch, int64_t seq_len,
+                       const civic_grid* grid, const int64_t* frame_start, const float* scores, int32_t* kept_idx, void* hidden_c,
+                       int32_t* pos_c, int32_t* src_idx, int64_t pos_axis_in, int64_t pos_axis_out, void* stream);
 
-// One sample of a ragged batch for compact_samples_launch: where its rows, kept indices and compact rows begin in the
-// packed tensors, its kept count, length, grid and (sample-local) frame starts.
+// One sample of a ragged batch for merge_samples_launch: where its rows, scores, kept indices and compact rows begin in the
+// packed tensors, its length, grid and (sample-local) frame starts.
 struct RaggedSample {
-    int64_t row0, comp0, kept0, n_kept, seq_len;
+    int64_t row0, vis0, kept0, comp0, seq_len;
     const civic_grid* grid;
     const int64_t* frame_start;
 };
-constexpr int kCompactRaggedItems = 24, kCompactRaggedFrames = 8;
-// Up to kCompactRaggedItems samples (each checked by the caller, at most kCompactRaggedFrames frames) merged by one launch.
-int compact_samples_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, const int32_t* kept_idx, void* hidden_c,
-                           int32_t* pos_c, int32_t* src_idx, const RaggedSample* samples, int32_t n, int64_t pos_axis_in,
-                           int64_t pos_axis_out, void* stream);
+constexpr int kMergeItems = 16, kMergeItemFrames = 8;
+// Up to kMergeItems samples of at most kMergeItemFrames frames each; row numbers fit 32 bits.
+int merge_samples_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, const float* scores, int32_t* kept_idx,
+                         void* hidden_c, int32_t* pos_c, int32_t* src_idx, const RaggedSample* samples, int32_t n, int64_t pos_axis_in,
+                         int64_t pos_axis_out, void* stream);
 
 constexpr int kWave = 64;
 

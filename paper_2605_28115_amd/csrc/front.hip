@@ -1,8 +1,7 @@
 // civic_compact_prefill: the front of the path in one call - anchor scores of the visual rows (Eq. 8), token
-// selection under the budget and the floors, compact merge (Eq. 13).  No arithmetic of its own: the three
-// stages' kernels are enqueued back to back on the caller's stream.  What it saves is host time: one crossing
-// of the language boundary instead of three, which is most of a step on shapes whose kernels take a few
-// microseconds each.
+// selection under the budget and the floors, compact merge (Eq. 13) - in two launches on the caller's stream: the
+// scores, then selection and merge (merge.hip).  One crossing of the language boundary and two launches are most of what
+// the call costs on shapes whose kernels take a few microseconds each.
 #include "civic_internal.h"
 
 #include <cstring>
@@ -27,10 +26,9 @@ extern "C" int civic_compact_prefill(const void* hidden, int dtype, int32_t batc
 
     rc = civic_score_visual(hidden, dtype, batch, seq_len, dim, grid, frame_start, anchor_q, inv_tau, scores, stream);
     if (rc != CIVIC_OK) return rc;
-    rc = civic_select(scores, batch, grid, kept_idx, nullptr, workspace, workspace_bytes, stream);
-    if (rc != CIVIC_OK) return rc;
-    return civic_compact(hidden, dtype, dim, pos_ids, batch, seq_len, grid, frame_start, kept_idx, n_kept, hidden_c, pos_c,
-                         src_idx, workspace, workspace_bytes, stream);
+    const int64_t seq_c = seq_len - static_cast<int64_t>(grid->frames) * grid->height * grid->width + n_kept;
+    return merge_batch_launch(hidden, dtype, dim, pos_ids, batch, seq_len, grid, frame_start, scores, kept_idx, hidden_c, pos_c, src_idx,
+                              batch * seq_len, batch * seq_c, stream);
 }
 
 // ------------------------------------------------------------------------------------------------ ragged batches
@@ -126,10 +124,9 @@ extern "C" int civic_compact_prefill_ragged(const void* hidden, int dtype, int32
         }
         if (total > INT32_MAX || vis > INT32_MAX) return CIVIC_ERR_UNSUPPORTED;     // (row numbers travel as 32-bit kernel arguments)
     }
-    // Scores: the frames of all samples, 64 spans per launch.  Selection: 16 samples per launch, each workgroup with its
-    // own sample's grid.  Merge: run by run.
+    // Scores: the frames of all samples, 64 spans per launch.
     {
-        constexpr int kSlices = 64, kSamples = 16;
+        constexpr int kSlices = 64;
         int32_t first[kSlices], count[kSlices], out[kSlices], n_sl = 0, longest = 0;
         auto flush_scores = [&]() {
             const int r = n_sl ? score_slices_launch(hidden, dtype, dim, anchor_q, inv_tau, scores, first, count, out, n_sl, longest, stream) : CIVIC_OK;
@@ -151,31 +148,15 @@ extern "C" int civic_compact_prefill_ragged(const void* hidden, int dtype, int32
             frames_before += g.frames;
         }
         if ((rc = flush_scores()) != CIVIC_OK) return rc;
-
-        const float* sc[kSamples];
-        int32_t* kp[kSamples];
-        const civic_grid* gp[kSamples];
-        int32_t n_sm = 0;
-        int64_t kept = 0;
-        vis = 0;
-        for (int32_t b = 0; b < batch; ++b) {
-            sc[n_sm] = scores + vis; kp[n_sm] = kept_idx + kept; gp[n_sm] = &grids[b];
-            vis += static_cast<int64_t>(grids[b].frames) * grids[b].height * grids[b].width;
-            kept += civic_kept_count(&grids[b]);
-            if (++n_sm == kSamples || b + 1 == batch) {
-                if ((rc = select_samples_launch(sc, kp, gp, n_sm, stream)) != CIVIC_OK) return rc;
-                n_sm = 0;
-            }
-        }
     }
-    // Merge: samples with few frames 24 per launch (a table of sample descriptions in the kernel arguments); a sample
+    // Selection and merge: samples with few frames 16 per launch (a table of sample descriptions in the kernel arguments); a sample
     // with more frames than the table holds per sample goes out by itself, together with its run of equal samples.
     {
-        RaggedSample rs[kCompactRaggedItems];
+        RaggedSample rs[kMergeItems];
         int32_t n_rs = 0;
         auto flush_merge = [&]() {
-            const int r = n_rs ? compact_samples_launch(hidden, dtype, dim, pos_ids, kept_idx, hidden_c, pos_c, src_idx, rs, n_rs, total,
-                                                        total_c, stream)
+            const int r = n_rs ? merge_samples_launch(hidden, dtype, dim, pos_ids, scores, kept_idx, hidden_c, pos_c, src_idx, rs, n_rs, total,
+                                                      total_c, stream)
                                : CIVIC_OK;
             n_rs = 0;
             return r;
@@ -186,14 +167,14 @@ extern "C" int civic_compact_prefill_ragged(const void* hidden, int dtype, int32
             const Sample x = sample(b, vis, kept, comp, frames_before);
             const int64_t nv = static_cast<int64_t>(g->frames) * g->height * g->width;
             int32_t n = 1;
-            if (g->frames > kCompactRaggedFrames) {
+            if (g->frames > kMergeItemFrames) {
                 n = run_length(b, frames_before);
-                rc = compact_launch(x.hidden, dtype, dim, x.pos, n, x.len, g, x.frames, x.kept, x.n_kept, x.hidden_c, x.pos_c, x.src, total,
-                                    total_c, stream);
+                rc = merge_batch_launch(x.hidden, dtype, dim, x.pos, n, x.len, g, x.frames, x.scores, x.kept, x.hidden_c, x.pos_c, x.src,
+                                        total, total_c, stream);
                 if (rc != CIVIC_OK) return rc;
             } else {
-                rs[n_rs++] = RaggedSample{seq_offsets[b], comp, kept, x.n_kept, x.len, g, x.frames};
-                if (n_rs == kCompactRaggedItems && (rc = flush_merge()) != CIVIC_OK) return rc;
+                rs[n_rs++] = RaggedSample{seq_offsets[b], vis, kept, comp, x.len, g, x.frames};
+                if (n_rs == kMergeItems && (rc = flush_merge()) != CIVIC_OK) return rc;
             }
             vis += n * nv; kept += n * x.n_kept; comp += n * (x.len - nv + x.n_kept); frames_before += static_cast<int64_t>(n) * g->frames;
             b += n;

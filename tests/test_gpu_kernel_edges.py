@@ -410,3 +410,57 @@ def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
     for out in outs:
         err = float((out.cpu().double() - ref).abs().max())
         assert err <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(ref.abs().max())), err
+
+
+@pytest.mark.parametrize("case", [
+    # batch, grid (frames, height, width, cell, cell, cell floor, frame floor, budget), text before / between / behind, dim, rows
+    (1, (1, 1, 1, 4, 4, 1, 0, 1), 0, 0, 0, 8, "random"),          # one token, one vector a row
+    (2, (1, 32, 64, 4, 4, 1, 0, 700), 3, 0, 5, 64, "random"),     # 2048 tokens: the last size of 512 threads
+    (2, (1, 3, 683, 4, 4, 1, 0, 700), 3, 0, 5, 64, "random"),     # 2049: the first of 1024, rows of keys that are not aligned
+    (1, (2, 64, 32, 3, 2, 2, 5, 1300), 7, 9, 0, 128, "random"),   # 4096: mark words in lanes; text placed by the selection
+    (1, (3, 35, 39, 4, 3, 20, 0, 4000), 0, 1, 2, 128, "random"),  # 4095, cells kept whole
+    (1, (1, 17, 241, 8, 8, 1, 0, 1300), 2, 0, 0, 8, "random"),    # 4097: mark words through LDS
+    (1, (2, 128, 128, 8, 8, 1, 7, 9000), 40, 30, 20, 8, "random"),  # 32768: no room for text workgroups on the same unit
+    (1, (128, 2, 2, 2, 2, 1, 0, 200), 1, 1, 1, 16, "random"),     # as many frames as there can be
+    (1, (1, 16, 16, 4, 4, 0, 0, 0), 4, 0, 3, 64, "random"),       # nothing kept: text only
+    (1, (2, 8, 8, 4, 4, 0, 0, 1), 0, 6, 0, 64, "random"),         # one kept token among text
+    (128, (1, 8, 8, 4, 4, 1, 0, 20), 3, 0, 2, 64, "random"),      # the last batch with text workgroups, the first without
+    (129, (1, 8, 8, 4, 4, 1, 0, 20), 3, 0, 2, 64, "random"),
+    (300, (1, 40, 60, 4, 4, 1, 0, 2300), 9, 0, 100, 8, "random"),  # more samples than units: 2409 rows a workgroup, in two runs
+    (1, (1, 32, 64, 4, 4, 1, 0, 700), 3, 0, 5, 64, "equal"),      # every score 0: ties by index
+    (1, (1, 64, 64, 4, 4, 1, 9, 1500), 3, 0, 5, 64, "few"),       # eight distinct scores
+    (1, (1, 32, 64, 4, 4, 2, 0, 700), 3, 0, 5, 64, "outlier"),    # all but two scores in one bucket
+])
+def test_selection_and_merge_in_one_launch(bd, case):
+    """civic_compact_prefill's second launch, where every workgroup that moves rows selects for itself, against civic_select and
+    civic_compact on the same scores and against the oracle's selection: whole numbers and copied rows, no tolerance."""
+    batch, grid, before, between, behind, dim, rows = case
+    log("selection and merge", case)
+    frames, hw = grid[0], grid[1] * grid[2]
+    fs = np.asarray([before + f * (hw + between) for f in range(frames)], dtype=np.int64)
+    s_len = int(fs[-1]) + hw + behind
+    rng = np.random.default_rng(batch + frames * hw + dim)
+    hid = rng.standard_normal((batch, s_len, dim)).astype(np.float32)
+    anchor = rng.standard_normal(dim).astype(np.float32) + 0.25
+    if rows == "equal":
+        hid[:] = 1.0
+    elif rows == "few":
+        hid = hid[:, rng.integers(0, 8, s_len)]
+    elif rows == "outlier":
+        hid = hid[:, :1] + 1e-2 * hid
+        hid[:, before + 77], hid[:, before + 1000] = anchor, -anchor
+    hid, _ = wl.quantize(hid, "bf16")
+    d_hid = to_dev(hid)
+    d_pos = torch.from_numpy(rng.integers(0, 9000, (3, batch, s_len)).astype(np.int32)).cuda()
+    d_anchor = torch.from_numpy(bd.civic_anchor_normalize(anchor)).cuda()
+    k = bd.civic_kept_count(grid)
+    kept = torch.full((batch, k), -1, dtype=torch.int32, device="cuda")
+    scores, kept, hc, pc, si = bd.civic_compact_prefill(d_hid, d_pos, grid, fs, d_anchor, 1.0, kept_idx=kept)
+    kept3, _ = bd.civic_select(scores, grid)
+    hc3, pc3, si3 = bd.civic_compact(d_hid, d_pos, grid, fs, kept3)
+    torch.cuda.synchronize()
+    assert torch.equal(kept, kept3) and torch.equal(si, si3) and torch.equal(pc, pc3)
+    assert torch.equal(hc.view(torch.int16), hc3.view(torch.int16))
+    some = sorted({0, batch // 2, batch - 1})
+    ref, _ = oracle.select(to_host(scores)[some], grid)
+    assert np.array_equal(to_host(kept)[some], ref)
