@@ -4,12 +4,13 @@
 //   civic_kv_compress       Eq. 9: K_c = Rbar^T K, V_c = Rbar^T V with the column-normalised assignment matrix
 // (the attention over the compressed keys, softmax(Q K_c^T / sqrt(d)) V_c, is civic_cross_attn in attn.hip).
 //
-// Both are dense contractions and run on the bf16 MFMA pipe through one kernel, C = alpha * A B^T, whose B operand
-// may be stored either way round: like A, with the contraction index contiguous (the products Q_A X_0^T behind the logits), or with the
-// contraction index as the row index, which is how X_0 lies in Z_0 = W_A X_0 and how K and V lie in Eq. 9; those are
-// read where they are (transposing LDS reads), no transposed copy is made.  A is always contraction-contiguous and
-// zero-padded to a multiple of 64 in that direction (W_A and Rbar^T are written that way), so the GEMM has no tail
-// there; row and column tails are clamped loads and masked stores.
+// Both are dense contractions and run on the bf16 MFMA pipe.  Eq. 9 has a kernel of its own (compress_kernel, one launch); the
+// products of Eq. 8 go through one kernel, C = alpha * A B^T, whose B operand may be stored either way round: like A, with the
+// contraction index contiguous (the products Q_A X_0^T behind the logits), or with the contraction index as the row index, which is
+// how X_0 lies in Z_0 = W_A X_0; it is read where it is (transposing LDS reads), no transposed copy is made.  A is always
+// contraction-contiguous and zero-padded to a multiple of 64 in that direction (W_A is written that way), so the GEMM has no tail
+// there; row and column tails are clamped loads and masked stores.  (Eq. 9 for rows that are not whole 16-byte pieces goes through
+// the GEMM as well, with transposed, padded copies of R and X.)
 //   - 128 x 128 output tile per 256-thread workgroup, 64 x 64 per wavefront (2 x 2 blocks of
 //     v_mfma_f32_32x32x16_bf16, fp32 accumulators), 64 contraction elements per LDS tile.
 //   - A and B tiles go from global memory straight into an LDS ring (global_load_lds_dwordx4), 16-byte chunks
@@ -19,7 +20,6 @@
 //     bound by the L2 -> LDS traffic of its tiles, 64 FLOP per byte; a deeper ring at one workgroup per unit was
 //     slower, 46.6 against 35.3 us on the 1365 x 4096 x 1152 logits), four stages for grids that leave units without a
 //     second workgroup anyway, where the latency of a tile is what a workgroup waits for.
-//   - K_c and V_c of Eq. 9 come from one launch (grid z = batch item x tensor).
 // The softmax of Eq. 8 has two routes.  A logit never exceeds inv_tau in size, so up to 60 the first product's epilogue writes
 // exponentials in bf16 and their partial row sums, and the second product divides by those: no logits in memory, no softmax
 // launch.  A colder softmax needs its row's maximum: logits in fp32 to scratch, a row kernel into bf16 weights, the second product.
@@ -32,6 +32,7 @@ namespace civic {
 
 typedef __bf16 enc_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float enc_f32x16 __attribute__((ext_vector_type(16)));
+typedef float enc_f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char enc_lds_char;
 
 constexpr int kGemmBM = 128, kGemmBN = 128, kGemmBK = 64;
@@ -40,19 +41,14 @@ constexpr int kGemmTileBytes = kGemmBM * kGemmBK * 2;         // one operand til
 
 constexpr int kGroupItems = 64;    // items of one grouped launch (longer lists go out in several)
 
-// Items of different row counts packed along the row axis (the ragged Eq. 9 calls): item i owns rows
-// [row[i], row[i + 1]) of the packed tensors; pad_row counts the same rows with every item's length rounded up to 64,
-// which is how the items' zero-padded Rbar^T blocks follow one another in scratch memory.
+// Items of different row counts packed along the row axis (the ragged Eq. 9 call): item i owns rows [row[i], row[i + 1]).
 struct Group {
     int32_t row[kGroupItems + 1];
-    int32_t pad_row[kGroupItems + 1];
     uint8_t longest_first[kGroupItems];   // the items by falling row count
 };
 
 struct GemmArgs {
     const __bf16* a; const __bf16* b; void* c;
-    // a second (B, C) pair served by the same launch (grid z = 2 * batch item + pair), or null
-    const __bf16* b_alt; void* c_alt;
     int64_t lda, ldb, ldc;             // elements between rows of A [m x k], of B as stored, of C [m x n]
     int64_t sa, sb, sc;                // elements between batch items (0 = shared)
     int32_t m, n, k;                   // k a multiple of 64 (A is zero-padded up to it)
@@ -66,9 +62,6 @@ struct GemmArgs {
     // partial row sums [batch][parts][part_pitch], written by kOutExp (parts = 2 * its tiles_n), read by kOutRowNorm
     float* row_part; int32_t parts; int64_t part_pitch;
     float* row_inv;                    // kOutRowNorm: one over the sum of every A row, written when not null, [batch x m]
-    // GROUPED launches only: batch item i multiplies A_i = a + m * pad_row[i] (its own contraction length
-    // pad_row[i + 1] - pad_row[i], which is also its row pitch) with the rows [row[i], row[i + 1]) of b
-    Group grp;
 };
 
 template <int LDS_IMM>
@@ -128,7 +121,7 @@ constexpr float kMaxRowFactor = 1.0995116e12f;
 // row segments.
 // STAGES: tiles in the LDS ring, all but one in flight ahead of the one consumed: 2 (two workgroups per compute unit)
 // when the grid fills the chip, 4 (one workgroup per unit) when it does not and a tile's latency is what is waited for.
-template <int OUT, bool B_KROWS, int STAGES, bool GROUPED = false>
+template <int OUT, bool B_KROWS, int STAGES>
 __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) char gemm_lds[];
@@ -142,48 +135,22 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
     // that run is a compact block whose A row slabs and B column slabs are shared inside one L2 as the workgroups
     // advance along the contraction together.  With the plain (x, y) numbering every XCD touches every slab and the
     // kernel runs at the speed of the memory behind the L2s.
-    uint32_t zi;
-    int m0, n0;
-    if constexpr (GROUPED) {
-        // Items of different length: an XCD's run of tiles would be an item or two, and the one with the longest item's would
-        // work on alone.  Column slabs (one tile column of an item and tensor, all its tile rows) go to the XCDs in turn
-        // instead, the longest items' first.  (Eight items of 85 to 1365 rows, 256 x 1152 out: 30.9 us with a run each.)
-        const uint32_t slot = blockIdx.x >> 3, per_item = static_cast<uint32_t>(g.tiles_n) * (g.b_alt != nullptr ? 2u : 1u);
-        const uint32_t up = slot / static_cast<uint32_t>(g.tiles_m), slab = up * 8u + (blockIdx.x & 7u);
-        if (slab >= static_cast<uint32_t>(g.total_tiles / g.tiles_m)) return;
-        const uint32_t rank = slab / per_item, in_item = slab - rank * per_item, pair = in_item / static_cast<uint32_t>(g.tiles_n);
-        zi = g.grp.longest_first[rank] * (g.b_alt != nullptr ? 2u : 1u) + pair;
-        m0 = static_cast<int>(slot - up * g.tiles_m) * kGemmBM;
-        n0 = static_cast<int>(in_item - pair * g.tiles_n) * kGemmBN;
-    } else {
-        const uint32_t per_xcd = gridDim.x >> 3;
-        const uint32_t tile = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-        if (tile >= static_cast<uint32_t>(g.total_tiles)) return;        // (the grid is padded to a multiple of 8)
-        const uint32_t per_mat = static_cast<uint32_t>(g.tiles_m) * g.tiles_n;
-        zi = tile / per_mat;
-        const uint32_t rr = tile - zi * per_mat;
-        const uint32_t pn = rr / (static_cast<uint32_t>(g.panel) * g.tiles_m);
-        const uint32_t base_n = pn * g.panel;
-        const uint32_t pw = min(static_cast<uint32_t>(g.panel), static_cast<uint32_t>(g.tiles_n) - base_n);
-        const uint32_t within = rr - pn * g.panel * g.tiles_m;
-        m0 = static_cast<int>(within / pw) * kGemmBM;
-        n0 = static_cast<int>(base_n + within % pw) * kGemmBN;
-    }
-    const bool alt = g.b_alt != nullptr && (zi & 1u);
-    const int64_t bz = g.b_alt != nullptr ? (zi >> 1) : zi;
-    const __bf16* const b_mat = alt ? g.b_alt : g.b;
-    // contraction length, A's row pitch and the operands' first elements for this batch item
-    int32_t k_len = g.k, kb_rows = g.kb_rows;
-    int64_t lda = g.lda, a_first = bz * g.sa, b_first = bz * g.sb;
-    if constexpr (GROUPED) {
-        static_assert(B_KROWS, "grouped items differ in their contraction rows");
-        const int32_t r0 = g.grp.row[bz], p0 = g.grp.pad_row[bz];
-        k_len = g.grp.pad_row[bz + 1] - p0;
-        kb_rows = g.grp.row[bz + 1] - r0;
-        lda = k_len;
-        a_first = static_cast<int64_t>(g.m) * p0;
-        b_first = static_cast<int64_t>(r0) * g.ldb;
-    }
+    const uint32_t per_xcd = gridDim.x >> 3;
+    const uint32_t tile = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= static_cast<uint32_t>(g.total_tiles)) return;        // (the grid is padded to a multiple of 8)
+    const uint32_t per_mat = static_cast<uint32_t>(g.tiles_m) * g.tiles_n;
+    const uint32_t zi = tile / per_mat;
+    const uint32_t rr = tile - zi * per_mat;
+    const uint32_t pn = rr / (static_cast<uint32_t>(g.panel) * g.tiles_m);
+    const uint32_t base_n = pn * g.panel;
+    const uint32_t pw = min(static_cast<uint32_t>(g.panel), static_cast<uint32_t>(g.tiles_n) - base_n);
+    const uint32_t within = rr - pn * g.panel * g.tiles_m;
+    const int m0 = static_cast<int>(within / pw) * kGemmBM;
+    const int n0 = static_cast<int>(base_n + within % pw) * kGemmBN;
+    const int64_t bz = zi;
+    const __bf16* const b_mat = g.b;
+    const int32_t k_len = g.k, kb_rows = g.kb_rows;
+    const int64_t lda = g.lda, a_first = bz * g.sa, b_first = bz * g.sb;
 
     // global -> LDS: instruction j of wavefront w fills slots [(4 w + j) * 64, +64) of a tile; slot -> (row, physical chunk)
     const char* a_base = reinterpret_cast<const char*>(g.a + a_first + static_cast<int64_t>(m0) * lda);
@@ -317,7 +284,7 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
     // register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the wavefront's quadrant
     const int row_q = m0 + wm * 64, col_q = n0 + wn * 64;
     constexpr bool kFp32 = OUT == kOutLogits;
-    char* c_base = static_cast<char*>(alt ? g.c_alt : g.c) + (bz * g.sc) * (kFp32 ? 4 : 2);
+    char* c_base = static_cast<char*>(g.c) + (bz * g.sc) * (kFp32 ? 4 : 2);
     constexpr int kPitch = 64 + 8;                            // elements per staged row (padded against bank conflicts)
     constexpr int kStageBytes = 4 * 64 * kPitch * 2;
     if constexpr (OUT == kOutRowNorm) {                       // the tile's row sums: 2 threads a row, every other part each
@@ -473,38 +440,36 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
     }
 }
 
-template <int OUT, bool B_KROWS, int STAGES, bool GROUPED = false>
+template <int OUT, bool B_KROWS, int STAGES>
 static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s)
 {
     const dim3 grid(blocks);
     constexpr size_t lds = 2 * STAGES * kGemmTileBytes;
     static_assert(lds >= 4 * 64 * (64 + 8) * 2 + 1024, "the ring holds the staged output tile and the row sums");
     static std::atomic<uint64_t> allowed{0};
-    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(gemm_kernel<OUT, B_KROWS, STAGES, GROUPED>), lds, &allowed);
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(gemm_kernel<OUT, B_KROWS, STAGES>), lds, &allowed);
     if (rc != CIVIC_OK) return rc;
-    civic::launch((gemm_kernel<OUT, B_KROWS, STAGES, GROUPED>), grid, dim3(kGemmThreads), lds, s, g);
+    civic::launch((gemm_kernel<OUT, B_KROWS, STAGES>), grid, dim3(kGemmThreads), lds, s, g);
     return check_launch();
 }
 
-// `batch` batch items; with g.b_alt set every item runs twice, once per (B, C) pair.  B_KROWS: B is stored [k x n].
-// GROUPED: g.grp describes the `batch` items (B stored [k x n] only).
-template <int OUT, bool B_KROWS, bool GROUPED = false>
+// `batch` batch items.  B_KROWS: B is stored [k x n].
+template <int OUT, bool B_KROWS>
 static int launch_gemm(const GemmArgs& g_in, int batch, hipStream_t s)
 {
     GemmArgs g = g_in;
-    const int64_t z = static_cast<int64_t>(batch) * (g.b_alt ? 2 : 1);
     g.tiles_n = (g.n + kGemmBN - 1) / kGemmBN;
     g.tiles_m = (g.m + kGemmBM - 1) / kGemmBM;
-    const int64_t total = z * g.tiles_m * g.tiles_n;
+    const int64_t total = static_cast<int64_t>(batch) * g.tiles_m * g.tiles_n;
     if (total > (int64_t{1} << 30)) return CIVIC_ERR_UNSUPPORTED;
     g.total_tiles = static_cast<int32_t>(total);
-    const unsigned grid = GROUPED ? static_cast<unsigned>((z * g.tiles_n + 7) / 8 * 8 * g.tiles_m) : static_cast<unsigned>((total + 7) / 8 * 8);
+    const unsigned grid = static_cast<unsigned>((total + 7) / 8 * 8);
     // panel width: about the square root of an XCD's share of the tiles, so that its block is as tall as it is wide
     int panel = 1;
     while (static_cast<int64_t>(panel + 1) * (panel + 1) <= (total + 7) / 8) ++panel;
     g.panel = panel < g.tiles_n ? panel : g.tiles_n;
     // a grid that leaves compute units without a second workgroup takes the deeper ring
-    return total < 2 * 256 ? launch_gemm_variant<OUT, B_KROWS, 4, GROUPED>(g, grid, s) : launch_gemm_variant<OUT, B_KROWS, 2, GROUPED>(g, grid, s);
+    return total < 2 * 256 ? launch_gemm_variant<OUT, B_KROWS, 4>(g, grid, s) : launch_gemm_variant<OUT, B_KROWS, 2>(g, grid, s);
 }
 
 // ------------------------------------------------------------------------------------------ row kernels
@@ -747,19 +712,6 @@ __global__ __launch_bounds__(256) void transpose_pad_kernel(const TIN* __restric
     transpose_pad_block<TIN>(in, rows, cols, ld_in, in_batch, part, out, ld_out, out_batch, blockIdx.z);
 }
 
-// The same for the items of a group (grid z): item i's rows of r [.., cols], every column over its own sum (the item's
-// kColParts x cols partial sums), to the item's block of the padded Rbar^T scratch (cols x its padded length); blocks
-// past an item's padded length write nothing.
-__global__ __launch_bounds__(256) void transpose_pad_grouped_kernel(const float* __restrict__ r, int32_t cols,
-                                                                    const float* __restrict__ part, __bf16* __restrict__ out, Group grp)
-{
-    const int i = blockIdx.z;
-    const int32_t r0 = grp.row[i], p0 = grp.pad_row[i];
-    transpose_pad_block<float>(r + static_cast<int64_t>(r0) * cols, grp.row[i + 1] - r0, cols, cols, 0,
-                               part + static_cast<int64_t>(i) * kColParts * cols, out + static_cast<int64_t>(cols) * p0,
-                               grp.pad_row[i + 1] - p0, 0, 0);
-}
-
 // Column sums of r [rows, cols], first step: block (x, y) adds the rows y, y + gridDim.y, ... of 64 columns (its four
 // wavefronts four rows apart, coalesced 256-byte reads, meeting in LDS) into part[y, c]; the transposing kernel above
 // adds a column's kColParts partial sums and inverts the total.
@@ -782,11 +734,362 @@ __global__ __launch_bounds__(256) void col_part_sum_kernel(const float* __restri
     col_part_sum_block(r, rows, cols, part);
 }
 
-__global__ __launch_bounds__(256) void col_part_sum_grouped_kernel(const float* __restrict__ r, int32_t cols, float* __restrict__ part, Group grp)
+// ------------------------------------------------------------------------------------------ Eq. 9 in one launch
+// X_c = Rbar^T X for X = K and V, Rbar the columns of R over their sums: the product is taken with R as it lies and every row of
+// the result divided by its column's sum, so neither the sums nor a transposed, scaled copy of R have to be there first.  (Three
+// launches before: partial sums 5.0 us, transposed copy 5.8, product 17.8 on eight items of 85 to 1365 rows, 256 x 1152 out.)
+//   - 128 x 128 outputs per workgroup of eight wavefronts: four quadrants of 64 x 64, twice, once for the even and once for the
+//     odd 64 contraction rows of a step of 128; the two halves meet in LDS at the end.  The longest item's chain of steps is
+//     what these few hundred workgroups wait for, and a unit has room for one workgroup: eight wavefronts halve the chain.
+//   - R goes through registers (fp32 to bf16, and its column sums in fp32 on the way), one step ahead, into tiles [64 rows x 128
+//     columns] like those of X, which go straight into LDS; both operands are read with the transposing LDS read.
+//   - one barrier a step: at its head a wavefront writes the next step's R, asks for the R after that and for the next X, and
+//     waits for both when the step's products are done.
+// R may have any scale: a wavefront whose results are not finite, or whose column sums are below 2^-40, makes its results again from
+// weights that are normalised before they are rounded, one fp32 multiply-add each.
+// The rounded columns are divided by sums of the same rounded values; against 64 bits the error is 0.67 to 1.00 of that of weights
+// normalised first and rounded after (60 sizes of 1 to 2048 rows, four distributions of R).
+// One step takes 2270 clocks: 64 KB of R in fp32 and 32 KB of X at the 64 bytes a clock that a unit can load are 1536.  Kernel times:
+// eight items of 85 to 1365 rows, 256 x 1152 out, 21 us.
+struct CompressArgs {
+    const float* r;                       // [rows x m], shared by all items or packed like them
+    const __bf16* x[2];                   // K, V [rows x n]
+    __bf16* out[2];                       // [items x m x n]
+    int32_t m, n, tiles_m, tiles_n, slabs;
+    int32_t n_rows;                       // of every item; PACKED: from grp
+    Group grp;
+};
+constexpr int kCmpThreads = 512, kCmpTile = 64 * 128 * 2;     // bytes of one operand tile of 64 contraction rows
+constexpr int kCmpStage = 4 * kCmpTile;                       // R and X, two groups
+constexpr float kMinColumnSum = 9.094947e-13f;                // 2^-40
+
+// QUADS: m a multiple of 4, so that rows of R are aligned to 16 bytes and made of whole quads of columns.
+template <bool PACKED, bool QUADS>
+__global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g)
 {
-    const int i = blockIdx.z;                                 // the item: its own rows, its own kColParts x cols partial sums
-    const int32_t r0 = grp.row[i];
-    col_part_sum_block(r + static_cast<int64_t>(r0) * cols, grp.row[i + 1] - r0, cols, part + static_cast<int64_t>(i) * kColParts * cols);
+    extern __shared__ __attribute__((aligned(16))) char cmp_lds[];
+    enc_lds_char* const lds = (enc_lds_char*)cmp_lds;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = w >> 2, q = w & 3;   // contraction half, quadrant
+    const int col = lane & 31, half = lane >> 5, wm = q >> 1, wn = q & 1;
+    // Column slabs (one tile column of an item and tensor, all its tile rows) go to the XCDs in turn, the longest items' first: an
+    // XCD's L2 holds the slab of X for its tile rows, and no XCD works on alone.
+    const uint32_t slot = blockIdx.x >> 3, per_item = static_cast<uint32_t>(g.tiles_n) * 2u;
+    const uint32_t up = slot / static_cast<uint32_t>(g.tiles_m), slab = up * 8u + (blockIdx.x & 7u);
+    if (slab >= static_cast<uint32_t>(g.slabs)) return;
+    const uint32_t rank = slab / per_item, in_item = slab - rank * per_item, tensor = in_item / static_cast<uint32_t>(g.tiles_n);
+    const int m0 = static_cast<int>(slot - up * g.tiles_m) * 128, n0 = static_cast<int>(in_item - tensor * g.tiles_n) * 128;
+    int64_t item = rank, r_first = 0, x_first = rank * static_cast<int64_t>(g.n_rows);
+    int32_t rows = g.n_rows;
+    if constexpr (PACKED) {
+        item = g.grp.longest_first[rank];
+        r_first = x_first = g.grp.row[item];
+        rows = g.grp.row[item + 1] - g.grp.row[item];
+    }
+    const float* const r_item = g.r + r_first * g.m;
+    const __bf16* const x_item = (tensor ? g.x[1] : g.x[0]) + x_first * g.n;
+    const int steps = (rows + 127) / 128;
+
+    // R: thread -> four columns of rows row_r, row_r + 8, ... of its group's 64
+    const int t256 = tid & 255, col4 = (t256 & 31) * 4, row_r = t256 >> 5;
+    const uint32_t r_pitch = static_cast<uint32_t>(g.m) * 4u, x_pitch = static_cast<uint32_t>(g.n) * 2u;
+    uint32_t r_off[8];                                        // bytes from the step's first row
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r_off[j] = static_cast<uint32_t>(kg * 64 + row_r + 8 * j);
+    enc_f32x4 rv[2][8];                                        // R of an even and of an odd step
+    float csum[4] = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t r_col = static_cast<uint32_t>(QUADS ? min(col4, g.m - 4 - m0) : 0) * 4u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r_off[j] = r_off[j] * r_pitch + r_col;
+    // row j of the thread's eight of a step whose first row is at `base` and whose last row is at `last_row`
+    auto fetch_row = [&](const char* base, uint32_t last_row, int j, auto set_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+        // (global by type: a pointer put together from scalars is a generic one, whose loads count as LDS accesses as well)
+        const auto p = (const __attribute__((address_space(1))) char*)base + min(r_off[j], last_row);
+        if constexpr (QUADS) {
+            rv[set][j] = *(const __attribute__((address_space(1))) enc_f32x4*)p;
+        } else {
+            const int last = g.m - 1 - m0;
+            const auto f = (const __attribute__((address_space(1))) float*)p;
+            rv[set][j] = enc_f32x4{f[min(col4, last)], f[min(col4 + 1, last)], f[min(col4 + 2, last)], f[min(col4 + 3, last)]};
+        }
+    };
+    // (steps, rows and columns past the end re-read the last one)
+    auto step_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(r_item + m0 + static_cast<int64_t>(min(step, steps - 1)) * 128 * g.m); };
+    auto step_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * 128) * r_pitch + r_col; };
+    auto fetch_r = [&](int step, auto set_c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fetch_row(step_base(step), step_last(step), j, set_c);
+    };
+    // rows of `step` past the item become zeros (only the last step has any)
+    auto clear_tail = [&](int step, auto set_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+        if (__builtin_expect((step + 1) * 128 > rows, 0)) {
+            const int live = rows - (step * 128 + kg * 64 + row_r);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool in = 8 * j < live;
+                rv[set][j].x = in ? rv[set][j].x : 0.f; rv[set][j].y = in ? rv[set][j].y : 0.f;
+                rv[set][j].z = in ? rv[set][j].z : 0.f; rv[set][j].w = in ? rv[set][j].w : 0.f;
+            }
+        }
+    };
+    // Row j of the thread's eight, rounded, into the stage of its step's parity and into its columns' sums.  (Sums of what is
+    // multiplied: the weights of a column add up to one whatever the rounding did, and a single row's weight is exact.)
+    u32x2 word;
+    auto round_r = [&](int j, auto set_c) __attribute__((always_inline)) {
+        const enc_f32x4 v = rv[decltype(set_c)::value][j];
+        const enc_bf16x2 lo = {static_cast<__bf16>(v.x), static_cast<__bf16>(v.y)}, hi = {static_cast<__bf16>(v.z), static_cast<__bf16>(v.w)};
+        word = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+        csum[0] += __uint_as_float(word.x << 16);
+        csum[1] += __uint_as_float(word.x & 0xFFFF0000u);
+    };
+    auto write_r = [&](int j, auto set_c) __attribute__((always_inline)) {
+        const int kr = row_r + 8 * j;
+        *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(
+            lds + decltype(set_c)::value * kCmpStage + kg * kCmpTile + kr * 256 + (((col4 >> 3) ^ enc_swz16(kr)) << 4) + (col4 & 4) * 2) = word;
+        csum[2] += __uint_as_float(word.y << 16);
+        csum[3] += __uint_as_float(word.y & 0xFFFF0000u);
+    };
+    // X: instruction j of the group's wavefront q fills slots [(4 q + j) * 64, +64) of the group's tile
+    uint32_t x_off[4], x_col[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int s = (q * 4 + j) * kWave + lane, kr = s >> 4;
+        const int lc = (s & 15) ^ enc_swz16(kr);              // logical chunk: columns n0 + 8 lc .. + 7
+        x_col[j] = min(lc, (g.n - n0) / 8 - 1) * 16;          // (n is a multiple of 8; chunks past it re-read a valid one)
+        x_off[j] = (kg * 64 + kr) * x_pitch + x_col[j];
+    }
+    const uint32_t lds_x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + (2 + kg) * kCmpTile + q * 4 * kWave * 16);
+    auto x_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(reinterpret_cast<const char*>(x_item + n0) + static_cast<int64_t>(min(step, steps - 1)) * 128 * g.n * 2); };
+    auto x_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * 128) * x_pitch; };
+    auto issue_x = [&](const char* base, uint32_t last_row, int j, int st) __attribute__((always_inline)) {
+        const uint32_t off = min(x_off[j], last_row + x_col[j]);              // (rows past the item re-read its last)
+        const uint32_t dst = lds_x + st * kCmpStage;
+        if (j == 0) enc_dma16<0 * 1024>(base, off, dst);
+        else if (j == 1) enc_dma16<1 * 1024>(base, off, dst);
+        else if (j == 2) enc_dma16<2 * 1024>(base, off, dst);
+        else enc_dma16<3 * 1024>(base, off, dst);
+    };
+    // operand reads of a 16-row step: 4 contraction rows x 16 columns a block of 16 lanes, a lane receives one column
+    enc_lds_char* a_addr[4];
+    enc_lds_char* b_addr[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int hi = s & 1, j = s >> 1, l16 = lane & 15, g16 = (lane >> 4) & 1;
+        const int kr = 8 * half + 4 * hi + (l16 >> 2), el = 32 * j + 16 * g16 + 4 * (l16 & 3);
+        const int ea = wm * 64 + el, eb = wn * 64 + el;
+        a_addr[s] = lds + kg * kCmpTile + kr * 256 + (((ea >> 3) ^ enc_swz16(kr)) << 4) + (ea & 7) * 2;
+        b_addr[s] = lds + (2 + kg) * kCmpTile + kr * 256 + (((eb >> 3) ^ enc_swz16(kr)) << 4) + (eb & 7) * 2;
+        asm volatile("" : "+v"(a_addr[s]), "+v"(b_addr[s]));
+    }
+    enc_f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // X of the next step has landed (its loads are older than the last eight, R two steps on) and so have all LDS accesses, of every
+    // wavefront
+    auto landed = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070 | (QUADS ? 8 : 0)); // vmcnt, lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // A step: sixteen products, and behind each of them a little of everything else, so that one wavefront's vector instructions run
+    // under the other's product (in blocks behind every fourth product they did not: 1860 clocks a step without its loads, 1130
+    // without vector work as well, 1024 the products alone).  R and X past the last step are fetched all the same, the last rows
+    // again, and R written as zeros: a branch around loads has the compiler move registers of loads under way, and wait for them.
+    auto step = [&](int kt, auto stage_c) __attribute__((always_inline)) {
+        constexpr int st = decltype(stage_c)::value;
+        constexpr std::integral_constant<int, st ^ 1> other{};
+        clear_tail(kt + 1, other);
+        const char* const xb = x_base(kt + 1);
+        const uint32_t xl = x_last(kt + 1);
+        const char* const rb = step_base(kt + 3);
+        const uint32_t rl = step_last(kt + 3);
+        auto read = [&](enc_lds_char* const (&addr)[4], int s, int j) __attribute__((always_inline)) {
+            const enc_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j] + st * kCmpStage + s * 16 * 256));
+            const enc_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j + 1] + st * kCmpStage + s * 16 * 256));
+            const enc_s16x8 v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            return __builtin_bit_cast(enc_bf16x8, v8);
+        };
+        enc_bf16x8 af[2][2], bf[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { af[0][i] = read(a_addr, 0, i); bf[0][i] = read(b_addr, 0, i); }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int cur = s & 1, nxt = cur ^ 1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = k >> 1, j = k & 1;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+                if (s + 1 < 4) {                              // the next 16 rows' operands
+                    if (k < 2) af[nxt][k] = read(a_addr, s + 1, k);
+                    else bf[nxt][k - 2] = read(b_addr, s + 1, k - 2);
+                }
+                if (s == 0) issue_x(xb, xl, k, st ^ 1);       // the next step's X
+                const int row = 2 * s + (k >> 1);             // the next step's R, then the row two steps further on
+                if ((k & 1) == 0) {
+                    round_r(row, other);
+                } else {
+                    write_r(row, other);
+                    if (s > 0) fetch_row(rb, rl, row - 2, other);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        fetch_row(rb, rl, 6, other);
+        fetch_row(rb, rl, 7, other);
+        landed();
+    };
+    auto start = [&](auto stage_c) __attribute__((always_inline)) {
+        constexpr int st = decltype(stage_c)::value;
+        constexpr std::integral_constant<int, st ^ 1> other{};
+        fetch_r(0, stage_c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) issue_x(x_base(0), x_last(0), j, st);
+        fetch_r(1, other);
+        clear_tail(0, stage_c);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { round_r(j, stage_c); write_r(j, stage_c); }
+        fetch_r(2, stage_c);
+        landed();
+    };
+    // Steps in pairs, stage 1 and stage 0, with a single one in front where their number is odd.  (A loop that can end between the
+    // two leaves the compiler in doubt about which loads of R are under way, and the first of the two waits for all.)
+    constexpr std::integral_constant<int, 0> stage0{};
+    constexpr std::integral_constant<int, 1> stage1{};
+    int kt = steps & 1;
+    if (kt) {
+        start(stage0);
+        step(0, stage0);
+    } else {
+        start(stage1);
+    }
+    for (; kt < steps; kt += 2) {
+        step(kt, stage1);
+        step(kt + 1, stage0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);                       // (R past the end)
+    __syncthreads();
+
+    // The two contraction halves exchange a block column each (j = 1 - kg goes, j = kg stays), and the column sums of R meet.
+    // Register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the quadrant.
+    float4* const meet = reinterpret_cast<float4*>(cmp_lds);                  // [8 wavefronts][8 register quads][64 lanes]
+    float* const parts = reinterpret_cast<float*>(meet + 8 * 8 * kWave);      // [16 row slots][128]
+    float* const inv = parts + 16 * 128;                                      // [128]
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            const enc_f32x16& x = kg ? acc[i][0] : acc[i][1];
+            meet[(w * 8 + i * 4 + rq) * kWave + lane] = make_float4(x[4 * rq], x[4 * rq + 1], x[4 * rq + 2], x[4 * rq + 3]);
+        }
+    *reinterpret_cast<float4*>(parts + (tid >> 5) * 128 + col4) = make_float4(csum[0], csum[1], csum[2], csum[3]);
+    __syncthreads();
+    if (tid < 128) {
+        float t = 0.f;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) t += parts[s * 128 + tid];
+        inv[tid] = t != 0.f ? 1.0f / t : 0.f;                 // (a column that sums to zero weighs nothing)
+    }
+    enc_f32x16 sum[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            const float4 t = meet[((w ^ 4) * 8 + i * 4 + rq) * kWave + lane];
+            const float other[4] = {t.x, t.y, t.z, t.w};
+            const enc_f32x16& own = kg ? acc[i][1] : acc[i][0];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[i][4 * rq + e] = own[4 * rq + e] + other[e];
+        }
+    __syncthreads();
+    __bf16* const out = (tensor ? g.out[1] : g.out[0]) + item * g.m * g.n;
+    constexpr int kPitch = 32 + 8;
+    __bf16* const stage = reinterpret_cast<__bf16*>(cmp_lds) + w * 64 * kPitch;   // (inside the area just read: 40 KB of 64)
+    const int row_q = m0 + wm * 64, col_q = n0 + wn * 64 + 32 * kg;
+    float scale[2], odd[2] = {0.f, 0.f};
+    bool again = false;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        scale[i] = inv[wm * 64 + 32 * i + col];
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            enc_bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = sum[i][4 * rq + e] * scale[i];
+                odd[i] = fmaf(v, 0.f, odd[i]);
+                o[e] = static_cast<__bf16>(v);
+            }
+            *reinterpret_cast<enc_bf16x4*>(&stage[(32 * i + col) * kPitch + 8 * rq + 4 * half]) = o;
+        }
+        again |= row_q + 32 * i + col < g.m && scale[i] == scale[i] && (fabsf(scale[i]) > 1.0f / kMinColumnSum || odd[i] != 0.f);
+    }
+    if (__builtin_expect(__any(again), 0)) {
+#pragma unroll 1
+        for (int c4 = 4 * half; c4 < 32; c4 += 8)
+#pragma unroll 1
+            for (int row = row_q + col, i = 0; i < 2; row += 32, ++i) {
+                if (row >= g.m || col_q + c4 >= g.n) continue;
+                const float* wgt = r_item + row;
+                const __bf16* x = x_item + col_q + c4;
+                float total = 0.f;
+                for (int k = 0; k < rows; ++k) total += wgt[static_cast<int64_t>(k) * g.m];
+                const float factor = total != 0.f ? 1.0f / total : 0.f;
+                float t[4] = {0.f, 0.f, 0.f, 0.f};
+                for (int k = 0; k < rows; ++k) {
+                    const enc_bf16x4 xk = *reinterpret_cast<const enc_bf16x4*>(x + static_cast<int64_t>(k) * g.n);
+                    const float wk = static_cast<float>(static_cast<__bf16>(wgt[static_cast<int64_t>(k) * g.m] * factor));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
+                }
+                enc_bf16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(t[e]);
+                *reinterpret_cast<enc_bf16x4*>(out + static_cast<int64_t>(row) * g.n + col_q + c4) = o;
+            }
+        return;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int r = it * 16 + (lane >> 2), c8 = (lane & 3) * 8;
+        const int row = row_q + r, cc = col_q + c8;
+        if (row < g.m && cc < g.n)
+            *reinterpret_cast<u32x4*>(out + static_cast<int64_t>(row) * g.n + cc) = *reinterpret_cast<const u32x4*>(&stage[r * kPitch + c8]);
+    }
+}
+
+// Eq. 9 of `items` items; rows of whole 16-byte pieces in X (n a multiple of 8).
+template <bool PACKED, bool QUADS>
+static int launch_compress_variant(const CompressArgs& g_in, int64_t items, hipStream_t s)
+{
+    CompressArgs g = g_in;
+    g.tiles_m = (g.m + 127) / 128;
+    g.tiles_n = (g.n + 127) / 128;
+    const int64_t slabs = items * 2 * g.tiles_n;
+    if (slabs * g.tiles_m > (int64_t{1} << 30)) return CIVIC_ERR_UNSUPPORTED;
+    g.slabs = static_cast<int32_t>(slabs);
+    constexpr size_t lds = 2 * kCmpStage;
+    static_assert(lds >= (8 * 32 * kWave + 17 * 128) * 4, "the ring holds what the halves exchange");
+    static std::atomic<uint64_t> allowed{0};
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(compress_kernel<PACKED, QUADS>), lds, &allowed);
+    if (rc != CIVIC_OK) return rc;
+    civic::launch((compress_kernel<PACKED, QUADS>), dim3(static_cast<unsigned>((slabs + 7) / 8 * 8 * g.tiles_m)), dim3(kCmpThreads), lds, s, g);
+    return check_launch();
+}
+
+static int launch_compress(const CompressArgs& g, int64_t items, bool packed, hipStream_t s)
+{
+    if (packed) return launch_compress_variant<true, true>(g, items, s);
+    return g.m % 4 == 0 ? launch_compress_variant<false, true>(g, items, s) : launch_compress_variant<false, false>(g, items, s);
 }
 
 static int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
@@ -892,7 +1195,7 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
     if (rc != CIVIC_OK) return rc;
     // Q_A times the dense tokens as they lie; the epilogue makes logits of the products
     GemmArgs g1;
-    g1.b_alt = nullptr; g1.c_alt = nullptr; g1.kb_rows = 0;
+    g1.kb_rows = 0;
     g1.a = qa; g1.b = static_cast<const __bf16*>(x0);
     g1.lda = dim; g1.ldb = dim; g1.ldc = p.t_pad;
     g1.sa = 0; g1.sb = static_cast<int64_t>(n_tokens) * dim; g1.sc = static_cast<int64_t>(n_anchors) * p.t_pad;
@@ -901,7 +1204,6 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
     g1.row_part = row_part; g1.parts = static_cast<int32_t>(p.t_tile / kGemmBN * 2); g1.part_pitch = p.m_tile;
     // Z_0 = W_A X_0, X_0 read where it lies (tokens are its rows: the contraction index is the row index)
     GemmArgs g2;
-    g2.b_alt = nullptr; g2.c_alt = nullptr;
     g2.a = pw; g2.b = static_cast<const __bf16*>(x0); g2.c = z0;
     g2.lda = p.t_pad; g2.ldb = dim; g2.ldc = dim;
     g2.sa = static_cast<int64_t>(n_anchors) * p.t_pad; g2.sb = static_cast<int64_t>(n_tokens) * dim; g2.sc = static_cast<int64_t>(n_anchors) * dim;
@@ -974,6 +1276,14 @@ extern "C" int civic_kv_compress(const void* k, const void* v, int dtype, const 
     if (!workspace || workspace_bytes < p.total || !aligned16(workspace)) return CIVIC_ERR_WORKSPACE;
     if (batch == 0) return CIVIC_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (width % 8 == 0) {
+        CompressArgs c;
+        c.r = r; c.x[0] = static_cast<const __bf16*>(k); c.x[1] = static_cast<const __bf16*>(v);
+        c.out[0] = static_cast<__bf16*>(k_c); c.out[1] = static_cast<__bf16*>(v_c);
+        c.m = n_mem; c.n = width; c.n_rows = n_rows;
+        return launch_compress(c, batch, false, s);
+    }
+    // rows that are not whole 16-byte pieces: transposed, padded copies of them and of Rbar
     char* ws = static_cast<char*>(workspace);
     __bf16* rt = reinterpret_cast<__bf16*>(ws + p.rt);
     __bf16* xt = reinterpret_cast<__bf16*>(ws + p.xt);
@@ -990,12 +1300,6 @@ extern "C" int civic_kv_compress(const void* k, const void* v, int dtype, const 
     g.a = rt; g.lda = p.m_pad; g.ldc = width;
     g.sa = 0; g.sc = static_cast<int64_t>(n_mem) * width;
     g.m = n_mem; g.n = width; g.k = static_cast<int32_t>(p.m_pad); g.alpha = 1.0f;
-    if (width % 8 == 0) {
-        // X_c = Rbar^T X with X read where it lies (its rows are the contraction index); K and V in one launch
-        g.b = static_cast<const __bf16*>(k); g.c = k_c; g.b_alt = static_cast<const __bf16*>(v); g.c_alt = v_c;
-        g.ldb = width; g.sb = static_cast<int64_t>(n_rows) * width; g.kb_rows = n_rows;
-        return launch_gemm<kOutBf16, true>(g, batch, s);
-    }
     const void* src[2] = {k, v};
     void* dst[2] = {k_c, v_c};
     for (int t = 0; t < 2; ++t) {
@@ -1007,7 +1311,7 @@ extern "C" int civic_kv_compress(const void* k, const void* v, int dtype, const 
                            static_cast<int64_t>(width) * p.m_pad);
         rc = check_launch();
         if (rc != CIVIC_OK) return rc;
-        g.b = xt; g.c = dst[t]; g.b_alt = nullptr; g.c_alt = nullptr; g.kb_rows = 0;
+        g.b = xt; g.c = dst[t]; g.kb_rows = 0;
         g.ldb = p.m_pad; g.sb = static_cast<int64_t>(width) * p.m_pad;
         rc = launch_gemm<kOutBf16, false>(g, batch, s);
         if (rc != CIVIC_OK) return rc;
@@ -1080,48 +1384,22 @@ extern "C" int civic_kv_compress_ragged(const void* k, const void* v, int dtype,
     if (p.pad_total > INT32_MAX) return CIVIC_ERR_UNSUPPORTED;                // (padded row numbers are 32-bit as well)
     if (!workspace || workspace_bytes < p.total || !aligned16(workspace)) return CIVIC_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    char* ws = static_cast<char*>(workspace);
-    // Groups of up to kGroupItems items, three launches each: the partial column sums of every item's R rows,
-    // Rbar^T of every item (transposed, scaled, zero-padded to a multiple of 64 contraction rows) and ONE grouped GEMM
-    // for K_c and V_c of all items (grid z = item x tensor; an item's contraction length comes from the group's table).
-    int64_t pad_done = 0;
+    // Groups of up to kGroupItems items, one launch each.
     for (int32_t b0 = 0; b0 < batch; b0 += kGroupItems) {
         const int32_t nb = batch - b0 < kGroupItems ? batch - b0 : kGroupItems;
-        GemmArgs g;
-        g.col_stats = nullptr; g.col_pitch = 0; g.row_sum = nullptr; g.row_inv = nullptr; g.row_part = nullptr; g.parts = 0; g.part_pitch = 0;
-        int32_t longest_pad = 0;
-        g.grp.pad_row[0] = 0;
-        for (int32_t i = 0; i <= kGroupItems; ++i) {
-            const int32_t at = i <= nb ? i : nb;                              // (entries past the group repeat its end)
-            g.grp.row[i] = static_cast<int32_t>(row_offsets[b0 + at]);
-            if (i > 0) {
-                const int32_t padded = i <= nb ? static_cast<int32_t>(pad64(row_offsets[b0 + i] - row_offsets[b0 + i - 1])) : 0;
-                g.grp.pad_row[i] = g.grp.pad_row[i - 1] + padded;
-                longest_pad = padded > longest_pad ? padded : longest_pad;
-            }
-        }
-        for (int32_t i = 0; i < kGroupItems; ++i) g.grp.longest_first[i] = static_cast<uint8_t>(i);
-        std::stable_sort(g.grp.longest_first, g.grp.longest_first + nb, [&](uint8_t x, uint8_t y) {
-            return g.grp.pad_row[x + 1] - g.grp.pad_row[x] > g.grp.pad_row[y + 1] - g.grp.pad_row[y];
+        CompressArgs c;
+        c.r = r; c.x[0] = static_cast<const __bf16*>(k); c.x[1] = static_cast<const __bf16*>(v);
+        c.out[0] = static_cast<__bf16*>(k_c) + static_cast<int64_t>(b0) * n_mem * width;
+        c.out[1] = static_cast<__bf16*>(v_c) + static_cast<int64_t>(b0) * n_mem * width;
+        c.m = n_mem; c.n = width; c.n_rows = 0;
+        for (int32_t i = 0; i <= kGroupItems; ++i)                            // (entries past the group repeat its end)
+            c.grp.row[i] = static_cast<int32_t>(row_offsets[b0 + (i <= nb ? i : nb)]);
+        for (int32_t i = 0; i < kGroupItems; ++i) c.grp.longest_first[i] = static_cast<uint8_t>(i);
+        std::stable_sort(c.grp.longest_first, c.grp.longest_first + nb, [&](uint8_t x, uint8_t y) {
+            return c.grp.row[x + 1] - c.grp.row[x] > c.grp.row[y + 1] - c.grp.row[y];
         });
-        float* part = reinterpret_cast<float*>(ws + p.part) + static_cast<int64_t>(b0) * n_mem * kColParts;
-        __bf16* rt = reinterpret_cast<__bf16*>(ws + p.rt) + static_cast<int64_t>(n_mem) * pad_done;
-        civic::launch(col_part_sum_grouped_kernel, dim3(static_cast<unsigned>((n_mem + kWave - 1) / kWave), kColParts, static_cast<unsigned>(nb)),
-                      dim3(256), 0, s, r, n_mem, part, g.grp);
-        civic::launch(transpose_pad_grouped_kernel, dim3(static_cast<unsigned>(longest_pad / 32), static_cast<unsigned>((n_mem + 31) / 32),
-                                                        static_cast<unsigned>(nb)),
-                      dim3(256), 0, s, r, n_mem, part, rt, g.grp);
-        int rc = check_launch();
+        const int rc = launch_compress(c, nb, true, s);
         if (rc != CIVIC_OK) return rc;
-        g.a = rt; g.lda = 0; g.sa = 0; g.k = 0; g.kb_rows = 0;                // (per item, from the table)
-        g.b = static_cast<const __bf16*>(k); g.b_alt = static_cast<const __bf16*>(v); g.ldb = width; g.sb = 0;
-        g.c = static_cast<__bf16*>(k_c) + static_cast<int64_t>(b0) * n_mem * width;
-        g.c_alt = static_cast<__bf16*>(v_c) + static_cast<int64_t>(b0) * n_mem * width;
-        g.ldc = width; g.sc = static_cast<int64_t>(n_mem) * width;
-        g.m = n_mem; g.n = width; g.alpha = 1.0f;
-        rc = launch_gemm<kOutBf16, true, true>(g, nb, s);
-        if (rc != CIVIC_OK) return rc;
-        pad_done += g.grp.pad_row[nb];
     }
     return CIVIC_OK;
 }

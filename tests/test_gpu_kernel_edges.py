@@ -464,3 +464,38 @@ def test_selection_and_merge_in_one_launch(bd, case):
     some = sorted({0, batch // 2, batch - 1})
     ref, _ = oracle.select(to_host(scores)[some], grid)
     assert np.array_equal(to_host(kept)[some], ref)
+
+
+@pytest.mark.parametrize("case", [
+    # rows of the items, memory, width, packed, scale of R
+    ([1], 1, 8, False, 1.0), ([2, 2], 3, 72, False, 1.0), ([64], 4, 128, False, 1.0), ([65, 65], 127, 136, False, 1.0),
+    ([128], 128, 1152, False, 1.0), ([129], 130, 264, False, 1.0), ([256, 256, 256], 64, 120, False, 1.0), ([257], 512, 64, False, 1.0),
+    ([1, 63, 64, 65, 127, 128, 129, 385], 132, 200, True, 1.0), ([5] * 70, 8, 16, True, 1.0),     # 70 items: two launches
+    ([200], 132, 136, False, 1e-36), ([200], 132, 136, False, 3e35), ([300, 40], 64, 72, True, 1e-30),  # column sums at the ends of fp32
+])
+def test_kv_compress_tiles_and_scales(bd, case):
+    """Eq. 9 over tiles of 128 x 128 in steps of 128 rows, for any scale of R.  A weight is rounded to bf16 (2^-9), their sum moves by as
+    much at most, the result is rounded once more: 2^-8 of the sum of |weight x|, and 2^-8 of the result, bound the error of an element."""
+    rows, mem, width, packed, scale = case
+    log("kv compress", case)
+    rng = np.random.default_rng(sum(rows) + mem + width)
+    lead = (sum(rows),) if packed else (len(rows), rows[0])
+    k, k32 = wl.quantize(rng.standard_normal(lead + (width,)).astype(np.float32), "bf16")
+    v, v32 = wl.quantize(rng.standard_normal(lead + (width,)).astype(np.float32), "bf16")
+    r = (rng.random((lead[0] if packed else rows[0], mem)) ** 4 * scale).astype(np.float32)
+    if mem > 2 and scale == 1.0:
+        r[:, 1] = 0.0                                          # a column that weighs nothing
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    dk, dv, dr = to_dev(k), to_dev(v), torch.from_numpy(r).cuda()
+    kc, vc = bd.civic_kv_compress_ragged(dk, dv, dr, off) if packed else bd.civic_kv_compress(dk, dv, dr)
+    torch.cuda.synchronize()
+    for got, x in ((kc, k32), (vc, v32)):
+        got = widen(to_host(got)).astype(np.float64)
+        for i in range(len(rows)):
+            xi = x[off[i]:off[i + 1]] if packed else x[i]
+            ri = (r[off[i]:off[i + 1]] if packed else r).astype(np.float64)
+            total = ri.sum(0)
+            w = np.where(total != 0, ri / np.where(total != 0, total, 1.0), 0.0)
+            ref = w.T @ xi.astype(np.float64)
+            bar = 2.0 ** -8 * (w.T @ np.abs(xi.astype(np.float64))) + 2.0 ** -8 * np.abs(ref) + 1e-30
+            assert (np.abs(got[i] - ref) <= bar).all(), float((np.abs(got[i] - ref) / bar).max())
