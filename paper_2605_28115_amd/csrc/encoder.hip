@@ -738,9 +738,10 @@ __global__ __launch_bounds__(256) void col_part_sum_kernel(const float* __restri
 // X_c = Rbar^T X for X = K and V, Rbar the columns of R over their sums: the product is taken with R as it lies and every row of
 // the result divided by its column's sum, so neither the sums nor a transposed, scaled copy of R have to be there first.  (Three
 // launches before: partial sums 5.0 us, transposed copy 5.8, product 17.8 on eight items of 85 to 1365 rows, 256 x 1152 out.)
-//   - 128 x 128 outputs per workgroup of eight wavefronts: four quadrants of 64 x 64, twice, once for the even and once for the
-//     odd 64 contraction rows of a step of 128; the two halves meet in LDS at the end.  The longest item's chain of steps is
-//     what these few hundred workgroups wait for, and a unit has room for one workgroup: eight wavefronts halve the chain.
+//   - 128 x 128 outputs per workgroup, a quadrant of 64 x 64 per wavefront, in two sums, over the even and over the odd 64 contraction
+//     rows.  KG = 2: eight wavefronts, each half takes one of the sums in steps of 128 rows, and they meet in LDS: for launches that
+//     wait for their longest item's chain of steps, with one workgroup to a unit.  KG = 1: four wavefronts that take both sums in turn
+//     in steps of 64 rows, two workgroups to a unit: for launches of many or short workgroups.  The same bits either way.
 //   - R goes through registers (fp32 to bf16, and its column sums in fp32 on the way), one step ahead, into tiles [64 rows x 128
 //     columns] like those of X, which go straight into LDS; both operands are read with the transposing LDS read.
 //   - one barrier a step: at its head a wavefront writes the next step's R, asks for the R after that and for the next X, and
@@ -759,18 +760,19 @@ struct CompressArgs {
     int32_t n_rows;                       // of every item; PACKED: from grp
     Group grp;
 };
-constexpr int kCmpThreads = 512, kCmpTile = 64 * 128 * 2;     // bytes of one operand tile of 64 contraction rows
-constexpr int kCmpStage = 4 * kCmpTile;                       // R and X, two groups
+constexpr int kCmpTile = 64 * 128 * 2;                        // bytes of one operand tile of 64 contraction rows
 constexpr float kMinColumnSum = 9.094947e-13f;                // 2^-40
 
 // QUADS: m a multiple of 4, so that rows of R are aligned to 16 bytes and made of whole quads of columns.
-template <bool PACKED, bool QUADS>
-__global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g)
+template <bool PACKED, bool QUADS, int KG>
+__global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
 {
+    constexpr int kStep = 64 * KG, kCmpStage = 2 * KG * kCmpTile;
+    constexpr int kSets = KG;                                 // steps whose R is held in registers or on its way there
     extern __shared__ __attribute__((aligned(16))) char cmp_lds[];
     enc_lds_char* const lds = (enc_lds_char*)cmp_lds;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = w >> 2, q = w & 3;   // contraction half, quadrant
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KG == 2 ? w >> 2 : 0, q = w & 3;   // contraction half, quadrant
     const int col = lane & 31, half = lane >> 5, wm = q >> 1, wn = q & 1;
     // Column slabs (one tile column of an item and tensor, all its tile rows) go to the XCDs in turn, the longest items' first: an
     // XCD's L2 holds the slab of X for its tile rows, and no XCD works on alone.
@@ -788,7 +790,7 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
     }
     const float* const r_item = g.r + r_first * g.m;
     const __bf16* const x_item = (tensor ? g.x[1] : g.x[0]) + x_first * g.n;
-    const int steps = (rows + 127) / 128;
+    const int steps = (rows + kStep - 1) / kStep;
 
     // R: thread -> four columns of rows row_r, row_r + 8, ... of its group's 64
     const int t256 = tid & 255, col4 = (t256 & 31) * 4, row_r = t256 >> 5;
@@ -796,14 +798,16 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
     uint32_t r_off[8];                                        // bytes from the step's first row
 #pragma unroll
     for (int j = 0; j < 8; ++j) r_off[j] = static_cast<uint32_t>(kg * 64 + row_r + 8 * j);
-    enc_f32x4 rv[2][8];                                        // R of an even and of an odd step
-    float csum[4] = {0.f, 0.f, 0.f, 0.f};
+    enc_f32x4 rv[kSets][8];
+    // accumulators and column sums of the even and the odd 64 rows: of two groups of wavefronts, or of one group in turn
+    constexpr int kOwn = KG == 2 ? 1 : 2;
+    float csum[kOwn][4] = {};
     const uint32_t r_col = static_cast<uint32_t>(QUADS ? min(col4, g.m - 4 - m0) : 0) * 4u;
 #pragma unroll
     for (int j = 0; j < 8; ++j) r_off[j] = r_off[j] * r_pitch + r_col;
     // row j of the thread's eight of a step whose first row is at `base` and whose last row is at `last_row`
     auto fetch_row = [&](const char* base, uint32_t last_row, int j, auto set_c) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value;
+        constexpr int set = decltype(set_c)::value % kSets;
         // (global by type: a pointer put together from scalars is a generic one, whose loads count as LDS accesses as well)
         const auto p = (const __attribute__((address_space(1))) char*)base + min(r_off[j], last_row);
         if constexpr (QUADS) {
@@ -815,17 +819,17 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         }
     };
     // (steps, rows and columns past the end re-read the last one)
-    auto step_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(r_item + m0 + static_cast<int64_t>(min(step, steps - 1)) * 128 * g.m); };
-    auto step_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * 128) * r_pitch + r_col; };
+    auto step_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(r_item + m0 + static_cast<int64_t>(min(step, steps - 1)) * kStep * g.m); };
+    auto step_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * kStep) * r_pitch + r_col; };
     auto fetch_r = [&](int step, auto set_c) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) fetch_row(step_base(step), step_last(step), j, set_c);
     };
     // rows of `step` past the item become zeros (only the last step has any)
     auto clear_tail = [&](int step, auto set_c) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value;
-        if (__builtin_expect((step + 1) * 128 > rows, 0)) {
-            const int live = rows - (step * 128 + kg * 64 + row_r);
+        constexpr int set = decltype(set_c)::value % kSets;
+        if (__builtin_expect((step + 1) * kStep > rows, 0)) {
+            const int live = rows - (step * kStep + kg * 64 + row_r);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool in = 8 * j < live;
@@ -835,21 +839,22 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         }
     };
     // Row j of the thread's eight, rounded, into the stage of its step's parity and into its columns' sums.  (Sums of what is
-    // multiplied: the weights of a column add up to one whatever the rounding did, and a single row's weight is exact.)
+    // multiplied: the weights of a column add up to one whatever the rounding did, and a single row's weight is exact.  Packed dot
+    // products with (1, 0) and (0, 1) for the sums, an instruction less each, were 2 % slower.)
     u32x2 word;
     auto round_r = [&](int j, auto set_c) __attribute__((always_inline)) {
-        const enc_f32x4 v = rv[decltype(set_c)::value][j];
+        const enc_f32x4 v = rv[decltype(set_c)::value % kSets][j];
         const enc_bf16x2 lo = {static_cast<__bf16>(v.x), static_cast<__bf16>(v.y)}, hi = {static_cast<__bf16>(v.z), static_cast<__bf16>(v.w)};
         word = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-        csum[0] += __uint_as_float(word.x << 16);
-        csum[1] += __uint_as_float(word.x & 0xFFFF0000u);
+        csum[decltype(set_c)::value % kOwn][0] += __uint_as_float(word.x << 16);
+        csum[decltype(set_c)::value % kOwn][1] += __uint_as_float(word.x & 0xFFFF0000u);
     };
     auto write_r = [&](int j, auto set_c) __attribute__((always_inline)) {
         const int kr = row_r + 8 * j;
         *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(
             lds + decltype(set_c)::value * kCmpStage + kg * kCmpTile + kr * 256 + (((col4 >> 3) ^ enc_swz16(kr)) << 4) + (col4 & 4) * 2) = word;
-        csum[2] += __uint_as_float(word.y << 16);
-        csum[3] += __uint_as_float(word.y & 0xFFFF0000u);
+        csum[decltype(set_c)::value % kOwn][2] += __uint_as_float(word.y << 16);
+        csum[decltype(set_c)::value % kOwn][3] += __uint_as_float(word.y & 0xFFFF0000u);
     };
     // X: instruction j of the group's wavefront q fills slots [(4 q + j) * 64, +64) of the group's tile
     uint32_t x_off[4], x_col[4];
@@ -860,9 +865,9 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         x_col[j] = min(lc, (g.n - n0) / 8 - 1) * 16;          // (n is a multiple of 8; chunks past it re-read a valid one)
         x_off[j] = (kg * 64 + kr) * x_pitch + x_col[j];
     }
-    const uint32_t lds_x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + (2 + kg) * kCmpTile + q * 4 * kWave * 16);
-    auto x_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(reinterpret_cast<const char*>(x_item + n0) + static_cast<int64_t>(min(step, steps - 1)) * 128 * g.n * 2); };
-    auto x_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * 128) * x_pitch; };
+    const uint32_t lds_x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + (KG + kg) * kCmpTile + q * 4 * kWave * 16);
+    auto x_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(reinterpret_cast<const char*>(x_item + n0) + static_cast<int64_t>(min(step, steps - 1)) * kStep * g.n * 2); };
+    auto x_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * kStep) * x_pitch; };
     auto issue_x = [&](const char* base, uint32_t last_row, int j, int st) __attribute__((always_inline)) {
         const uint32_t off = min(x_off[j], last_row + x_col[j]);              // (rows past the item re-read its last)
         const uint32_t dst = lds_x + st * kCmpStage;
@@ -880,16 +885,18 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         const int kr = 8 * half + 4 * hi + (l16 >> 2), el = 32 * j + 16 * g16 + 4 * (l16 & 3);
         const int ea = wm * 64 + el, eb = wn * 64 + el;
         a_addr[s] = lds + kg * kCmpTile + kr * 256 + (((ea >> 3) ^ enc_swz16(kr)) << 4) + (ea & 7) * 2;
-        b_addr[s] = lds + (2 + kg) * kCmpTile + kr * 256 + (((eb >> 3) ^ enc_swz16(kr)) << 4) + (eb & 7) * 2;
+        b_addr[s] = lds + (KG + kg) * kCmpTile + kr * 256 + (((eb >> 3) ^ enc_swz16(kr)) << 4) + (eb & 7) * 2;
         asm volatile("" : "+v"(a_addr[s]), "+v"(b_addr[s]));
     }
-    enc_f32x16 acc[2][2];
+    enc_f32x16 acc[kOwn][2][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int o = 0; o < kOwn; ++o)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[o][i][j][r] = 0.f;
 
     // X of the next step has landed (its loads are older than the last eight, R two steps on) and so have all LDS accesses, of every
     // wavefront
@@ -909,8 +916,8 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         clear_tail(kt + 1, other);
         const char* const xb = x_base(kt + 1);
         const uint32_t xl = x_last(kt + 1);
-        const char* const rb = step_base(kt + 3);
-        const uint32_t rl = step_last(kt + 3);
+        const char* const rb = step_base(kt + 1 + kSets);
+        const uint32_t rl = step_last(kt + 1 + kSets);
         auto read = [&](enc_lds_char* const (&addr)[4], int s, int j) __attribute__((always_inline)) {
             const enc_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j] + st * kCmpStage + s * 16 * 256));
             const enc_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j + 1] + st * kCmpStage + s * 16 * 256));
@@ -926,7 +933,7 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = k >> 1, j = k & 1;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+                acc[st % kOwn][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[st % kOwn][i][j], 0, 0, 0);
                 if (s + 1 < 4) {                              // the next 16 rows' operands
                     if (k < 2) af[nxt][k] = read(a_addr, s + 1, k);
                     else bf[nxt][k - 2] = read(b_addr, s + 1, k - 2);
@@ -952,11 +959,11 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         fetch_r(0, stage_c);
 #pragma unroll
         for (int j = 0; j < 4; ++j) issue_x(x_base(0), x_last(0), j, st);
-        fetch_r(1, other);
+        if constexpr (KG == 2) fetch_r(1, other);
         clear_tail(0, stage_c);
 #pragma unroll
         for (int j = 0; j < 8; ++j) { round_r(j, stage_c); write_r(j, stage_c); }
-        fetch_r(2, stage_c);
+        fetch_r(kSets, stage_c);
         landed();
     };
     // Steps in pairs, stage 1 and stage 0, with a single one in front where their number is odd.  (A loop that can end between the
@@ -977,19 +984,27 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
     __builtin_amdgcn_s_waitcnt(0x0070);                       // (R past the end)
     __syncthreads();
 
-    // The two contraction halves exchange a block column each (j = 1 - kg goes, j = kg stays), and the column sums of R meet.
+    // The even and the odd rows meet: two groups exchange a block column each (j = 1 - kg goes, j = kg stays).  So do the column
+    // sums of R: 8 row slots of the even rows, 8 of the odd ones.
     // Register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the quadrant.
-    float4* const meet = reinterpret_cast<float4*>(cmp_lds);                  // [8 wavefronts][8 register quads][64 lanes]
-    float* const parts = reinterpret_cast<float*>(meet + 8 * 8 * kWave);      // [16 row slots][128]
+    float4* const meet = reinterpret_cast<float4*>(cmp_lds);                  // KG == 2: [8 wavefronts][8 register quads][64 lanes]
+    float* const parts = reinterpret_cast<float*>(meet + (KG == 2 ? 8 * 8 * kWave : 0));   // [16 row slots][128]
     float* const inv = parts + 16 * 128;                                      // [128]
+    __bf16* const stages = KG == 2 ? reinterpret_cast<__bf16*>(cmp_lds) : reinterpret_cast<__bf16*>(inv + 128);
+    if constexpr (KG == 2) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const enc_f32x16& x = kg ? acc[i][0] : acc[i][1];
-            meet[(w * 8 + i * 4 + rq) * kWave + lane] = make_float4(x[4 * rq], x[4 * rq + 1], x[4 * rq + 2], x[4 * rq + 3]);
-        }
-    *reinterpret_cast<float4*>(parts + (tid >> 5) * 128 + col4) = make_float4(csum[0], csum[1], csum[2], csum[3]);
+            for (int rq = 0; rq < 4; ++rq) {
+                const enc_f32x16& x = kg ? acc[0][i][0] : acc[0][i][1];
+                meet[(w * 8 + i * 4 + rq) * kWave + lane] = make_float4(x[4 * rq], x[4 * rq + 1], x[4 * rq + 2], x[4 * rq + 3]);
+            }
+    }
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+        const int odd_rows = KG == 2 ? kg : o ^ (~steps & 1); // (the last of an even number of steps is in stage 0)
+        *reinterpret_cast<float4*>(parts + (odd_rows * 8 + row_r) * 128 + col4) = make_float4(csum[o][0], csum[o][1], csum[o][2], csum[o][3]);
+    }
     __syncthreads();
     if (tid < 128) {
         float t = 0.f;
@@ -998,98 +1013,133 @@ __global__ __launch_bounds__(kCmpThreads, 2) void compress_kernel(CompressArgs g
         inv[tid] = t != 0.f ? 1.0f / t : 0.f;                 // (a column that sums to zero weighs nothing)
     }
     enc_f32x16 sum[2];
+    if constexpr (KG == 2) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const float4 t = meet[((w ^ 4) * 8 + i * 4 + rq) * kWave + lane];
-            const float other[4] = {t.x, t.y, t.z, t.w};
-            const enc_f32x16& own = kg ? acc[i][1] : acc[i][0];
+            for (int rq = 0; rq < 4; ++rq) {
+                const float4 t = meet[((w ^ 4) * 8 + i * 4 + rq) * kWave + lane];
+                const float other[4] = {t.x, t.y, t.z, t.w};
+                const enc_f32x16& own = kg ? acc[0][i][1] : acc[0][i][0];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[i][4 * rq + e] = own[4 * rq + e] + other[e];
-        }
+                for (int e = 0; e < 4; ++e) sum[i][4 * rq + e] = own[4 * rq + e] + other[e];
+            }
+    }
     __syncthreads();
     __bf16* const out = (tensor ? g.out[1] : g.out[0]) + item * g.m * g.n;
     constexpr int kPitch = 32 + 8;
-    __bf16* const stage = reinterpret_cast<__bf16*>(cmp_lds) + w * 64 * kPitch;   // (inside the area just read: 40 KB of 64)
-    const int row_q = m0 + wm * 64, col_q = n0 + wn * 64 + 32 * kg;
-    float scale[2], odd[2] = {0.f, 0.f};
-    bool again = false;
+    __bf16* const stage = stages + w * 64 * kPitch;
+    const int row_q = m0 + wm * 64;
+    float scale[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        scale[i] = inv[wm * 64 + 32 * i + col];
+    for (int i = 0; i < 2; ++i) scale[i] = inv[wm * 64 + 32 * i + col];
+    auto emit = [&](int col_q) __attribute__((always_inline)) {               // a block column of the quadrant, from `sum`
+        float odd[2] = {0.f, 0.f};
+        bool again = false;
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            enc_bf16x4 o;
+        for (int i = 0; i < 2; ++i) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = sum[i][4 * rq + e] * scale[i];
-                odd[i] = fmaf(v, 0.f, odd[i]);
-                o[e] = static_cast<__bf16>(v);
-            }
-            *reinterpret_cast<enc_bf16x4*>(&stage[(32 * i + col) * kPitch + 8 * rq + 4 * half]) = o;
-        }
-        again |= row_q + 32 * i + col < g.m && scale[i] == scale[i] && (fabsf(scale[i]) > 1.0f / kMinColumnSum || odd[i] != 0.f);
-    }
-    if (__builtin_expect(__any(again), 0)) {
-#pragma unroll 1
-        for (int c4 = 4 * half; c4 < 32; c4 += 8)
-#pragma unroll 1
-            for (int row = row_q + col, i = 0; i < 2; row += 32, ++i) {
-                if (row >= g.m || col_q + c4 >= g.n) continue;
-                const float* wgt = r_item + row;
-                const __bf16* x = x_item + col_q + c4;
-                float total = 0.f;
-                for (int k = 0; k < rows; ++k) total += wgt[static_cast<int64_t>(k) * g.m];
-                const float factor = total != 0.f ? 1.0f / total : 0.f;
-                float t[4] = {0.f, 0.f, 0.f, 0.f};
-                for (int k = 0; k < rows; ++k) {
-                    const enc_bf16x4 xk = *reinterpret_cast<const enc_bf16x4*>(x + static_cast<int64_t>(k) * g.n);
-                    const float wk = static_cast<float>(static_cast<__bf16>(wgt[static_cast<int64_t>(k) * g.m] * factor));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
-                }
+            for (int rq = 0; rq < 4; ++rq) {
                 enc_bf16x4 o;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(t[e]);
-                *reinterpret_cast<enc_bf16x4*>(out + static_cast<int64_t>(row) * g.n + col_q + c4) = o;
+                for (int e = 0; e < 4; ++e) {
+                    const float v = sum[i][4 * rq + e] * scale[i];
+                    odd[i] = fmaf(v, 0.f, odd[i]);
+                    o[e] = static_cast<__bf16>(v);
+                }
+                *reinterpret_cast<enc_bf16x4*>(&stage[(32 * i + col) * kPitch + 8 * rq + 4 * half]) = o;
             }
-        return;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+            again |= row_q + 32 * i + col < g.m && scale[i] == scale[i] && (fabsf(scale[i]) > 1.0f / kMinColumnSum || odd[i] != 0.f);
+        }
+        if (__builtin_expect(__any(again), 0)) {
+#pragma unroll 1
+            for (int c4 = 4 * half; c4 < 32; c4 += 8)
+#pragma unroll 1
+                for (int row = row_q + col, i = 0; i < 2; row += 32, ++i) {
+                    if (row >= g.m || col_q + c4 >= g.n) continue;
+                    const float* wgt = r_item + row;
+                    const __bf16* x = x_item + col_q + c4;
+                    float total = 0.f;
+                    for (int k = 0; k < rows; ++k) total += wgt[static_cast<int64_t>(k) * g.m];
+                    const float factor = total != 0.f ? 1.0f / total : 0.f;
+                    float t[4] = {0.f, 0.f, 0.f, 0.f};
+                    for (int k = 0; k < rows; ++k) {
+                        const enc_bf16x4 xk = *reinterpret_cast<const enc_bf16x4*>(x + static_cast<int64_t>(k) * g.n);
+                        const float wk = static_cast<float>(static_cast<__bf16>(wgt[static_cast<int64_t>(k) * g.m] * factor));
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int r = it * 16 + (lane >> 2), c8 = (lane & 3) * 8;
-        const int row = row_q + r, cc = col_q + c8;
-        if (row < g.m && cc < g.n)
-            *reinterpret_cast<u32x4*>(out + static_cast<int64_t>(row) * g.n + cc) = *reinterpret_cast<const u32x4*>(&stage[r * kPitch + c8]);
+                        for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
+                    }
+                    enc_bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(t[e]);
+                    *reinterpret_cast<enc_bf16x4*>(out + static_cast<int64_t>(row) * g.n + col_q + c4) = o;
+                }
+            return;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int r = it * 16 + (lane >> 2), c8 = (lane & 3) * 8;
+            const int row = row_q + r, cc = col_q + c8;
+            if (row < g.m && cc < g.n)
+                *reinterpret_cast<u32x4*>(out + static_cast<int64_t>(row) * g.n + cc) = *reinterpret_cast<const u32x4*>(&stage[r * kPitch + c8]);
+        }
+    };
+    if constexpr (KG == 2) {
+        emit(n0 + wn * 64 + 32 * kg);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[i][r] = acc[0][i][j][r] + acc[1][i][j][r];
+            emit(n0 + wn * 64 + 32 * j);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();                  // (read before the area is written again)
+        }
     }
 }
 
 // Eq. 9 of `items` items; rows of whole 16-byte pieces in X (n a multiple of 8).
-template <bool PACKED, bool QUADS>
-static int launch_compress_variant(const CompressArgs& g_in, int64_t items, hipStream_t s)
+template <bool PACKED, bool QUADS, int KG>
+static int launch_compress_variant(const CompressArgs& g, hipStream_t s)
+{
+    constexpr size_t lds = 2 * 2 * KG * kCmpTile;
+    static_assert(lds >= ((KG == 2 ? 8 * 32 * kWave : 4 * 64 * 40 / 2) + 17 * 128) * 4, "the ring holds what is staged at the end");
+    static std::atomic<uint64_t> allowed{0};
+    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(compress_kernel<PACKED, QUADS, KG>), lds, &allowed);
+    if (rc != CIVIC_OK) return rc;
+    civic::launch((compress_kernel<PACKED, QUADS, KG>), dim3(static_cast<unsigned>((g.slabs + 7) / 8 * 8 * g.tiles_m)), dim3(256 * KG), lds, s, g);
+    return check_launch();
+}
+
+// (packed: the items' rows are in g.grp)
+static int launch_compress(const CompressArgs& g_in, int64_t items, bool packed, hipStream_t s)
 {
     CompressArgs g = g_in;
+    int64_t longest = (g.n_rows + 127) / 128, all_steps = longest * items;
+    if (packed) {
+        for (int64_t i = 0; i < items; ++i) {
+            const int64_t steps = (g.grp.row[i + 1] - g.grp.row[i] + 127) / 128;
+            all_steps += steps;
+            longest = std::max(longest, steps);
+        }
+    }
     g.tiles_m = (g.m + 127) / 128;
     g.tiles_n = (g.n + 127) / 128;
     const int64_t slabs = items * 2 * g.tiles_n;
     if (slabs * g.tiles_m > (int64_t{1} << 30)) return CIVIC_ERR_UNSUPPORTED;
     g.slabs = static_cast<int32_t>(slabs);
-    constexpr size_t lds = 2 * kCmpStage;
-    static_assert(lds >= (8 * 32 * kWave + 17 * 128) * 4, "the ring holds what the halves exchange");
-    static std::atomic<uint64_t> allowed{0};
-    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(compress_kernel<PACKED, QUADS>), lds, &allowed);
-    if (rc != CIVIC_OK) return rc;
-    civic::launch((compress_kernel<PACKED, QUADS>), dim3(static_cast<unsigned>((slabs + 7) / 8 * 8 * g.tiles_m)), dim3(kCmpThreads), lds, s, g);
-    return check_launch();
-}
-
-static int launch_compress(const CompressArgs& g, int64_t items, bool packed, hipStream_t s)
-{
-    if (packed) return launch_compress_variant<true, true>(g, items, s);
-    return g.m % 4 == 0 ? launch_compress_variant<false, true>(g, items, s) : launch_compress_variant<false, false>(g, items, s);
+    // Two groups of wavefronts where the launch waits for its longest chain of steps: one that is long (8 steps of 128 rows), while
+    // all steps together would keep the units busy for less.  Else one group, whose smaller workgroups run two to a unit.  (us, two
+    // groups and one: 4 x 2048 rows, 512 x 1024 out 28.5 and 31.2; 6 x 1024, 256 x 1152 16.9 and 18.5; 8 x 1024 30.1 and 24.1; eight
+    // items of 85..1365 23.4 and 24.9; 16 x 700, 128 x 768 19.5 and 18.1; 24 x 24, 512 x 1280 52.2 and 26.8.)
+    const bool one = longest < 8 || all_steps * 2 * g.tiles_n * g.tiles_m > 256 * longest;
+    if (packed) return one ? launch_compress_variant<true, true, 1>(g, s) : launch_compress_variant<true, true, 2>(g, s);
+    if (g.m % 4) return launch_compress_variant<false, false, 1>(g, s);
+    return one ? launch_compress_variant<false, true, 1>(g, s) : launch_compress_variant<false, true, 2>(g, s);
 }
 
 static int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }

@@ -499,3 +499,21 @@ def test_kv_compress_tiles_and_scales(bd, case):
             ref = w.T @ xi.astype(np.float64)
             bar = 2.0 ** -8 * (w.T @ np.abs(xi.astype(np.float64))) + 2.0 ** -8 * np.abs(ref) + 1e-30
             assert (np.abs(got[i] - ref) <= bar).all(), float((np.abs(got[i] - ref) / bar).max())
+
+
+@pytest.mark.parametrize("items,rows", [(1, 1025), (1, 2048), (17, 1025), (6, 897), (3, 64), (40, 64), (30, 200), (1, 200)])
+def test_kv_compress_of_a_batch_is_that_of_its_items(bd, items, rows):
+    """A launch takes the kernel whose workgroups are one or two groups of wavefronts by its size: the same bits from both, in batches
+    and for items of their own among longer ones."""
+    log("kv compress batch", items, rows)
+    g = torch.Generator(device="cuda").manual_seed(items + rows)
+    k = torch.randn((items, rows, 264), generator=g, device="cuda").bfloat16()
+    v = torch.randn((items, rows, 264), generator=g, device="cuda").bfloat16()
+    r = torch.rand((rows, 132), generator=g, device="cuda") ** 4
+    kc, vc = bd.civic_kv_compress(k, v, r)
+    one = bd.civic_kv_compress(k[-1:].contiguous(), v[-1:].contiguous(), r)
+    long = torch.randn((1500, 264), generator=g, device="cuda").bfloat16()
+    packed = torch.cat([long, k[-1]])
+    kp, _ = bd.civic_kv_compress_ragged(packed, packed, torch.cat([torch.rand((1500, 132), generator=g, device="cuda"), r]), [0, 1500, 1500 + rows])
+    torch.cuda.synchronize()
+    assert torch.equal(one[0][0], kc[-1]) and torch.equal(one[1][0], vc[-1]) and torch.equal(kp[1], kc[-1])
