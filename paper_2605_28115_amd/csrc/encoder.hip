@@ -177,20 +177,22 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
         }
     }
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + w * 4 * kWave * 16);
-    auto issue = [&](int kt, auto stage_c) {
-        constexpr int st = decltype(stage_c)::value;
-        const char* ab = enc_uniform(a_base + static_cast<int64_t>(kt) * kGemmBK * 2);
-        const char* bb = B_KROWS ? enc_uniform(b_base + static_cast<int64_t>(kt) * kGemmBK * g.ldb * 2)
-                                 : enc_uniform(b_base + static_cast<int64_t>(kt) * kGemmBK * 2);
-        const bool tail = B_KROWS && kt == last_tile;
-        enc_dma16<st * kGemmTileBytes + 0 * 1024>(ab, a_off[0], lds_wave);
-        enc_dma16<st * kGemmTileBytes + 1 * 1024>(ab, a_off[1], lds_wave);
-        enc_dma16<st * kGemmTileBytes + 2 * 1024>(ab, a_off[2], lds_wave);
-        enc_dma16<st * kGemmTileBytes + 3 * 1024>(ab, a_off[3], lds_wave);
-        enc_dma16<(STAGES + st) * kGemmTileBytes + 0 * 1024>(bb, tail ? b_off_tail[0] : b_off[0], lds_wave);
-        enc_dma16<(STAGES + st) * kGemmTileBytes + 1 * 1024>(bb, tail ? b_off_tail[1] : b_off[1], lds_wave);
-        enc_dma16<(STAGES + st) * kGemmTileBytes + 2 * 1024>(bb, tail ? b_off_tail[2] : b_off[2], lds_wave);
-        enc_dma16<(STAGES + st) * kGemmTileBytes + 3 * 1024>(bb, tail ? b_off_tail[3] : b_off[3], lds_wave);
+    // Load j of the eight of a tile into the stage's A and B areas.  (Tiles past the last: the last one again.)
+    auto tile_a = [&](int kt) __attribute__((always_inline)) { return enc_uniform(a_base + static_cast<int64_t>(min(kt, last_tile)) * kGemmBK * 2); };
+    auto tile_b = [&](int kt) __attribute__((always_inline)) {
+        return enc_uniform(b_base + static_cast<int64_t>(min(kt, last_tile)) * kGemmBK * 2 * (B_KROWS ? g.ldb : 1));
+    };
+    auto issue = [&](const char* ab, const char* bb, bool tail, int j, auto stage_c) __attribute__((always_inline)) {
+        constexpr int at = decltype(stage_c)::value * kGemmTileBytes, bt = (STAGES + decltype(stage_c)::value) * kGemmTileBytes;
+        const uint32_t off = j < 4 ? a_off[j & 3] : tail ? b_off_tail[j & 3] : b_off[j & 3];
+        if (j == 0) enc_dma16<at + 0 * 1024>(ab, off, lds_wave);
+        else if (j == 1) enc_dma16<at + 1 * 1024>(ab, off, lds_wave);
+        else if (j == 2) enc_dma16<at + 2 * 1024>(ab, off, lds_wave);
+        else if (j == 3) enc_dma16<at + 3 * 1024>(ab, off, lds_wave);
+        else if (j == 4) enc_dma16<bt + 0 * 1024>(bb, off, lds_wave);
+        else if (j == 5) enc_dma16<bt + 1 * 1024>(bb, off, lds_wave);
+        else if (j == 6) enc_dma16<bt + 2 * 1024>(bb, off, lds_wave);
+        else enc_dma16<bt + 3 * 1024>(bb, off, lds_wave);
     };
 
     // A reads: row (quadrant row 32 i + col), logical chunk 2 s + half; the swizzle depends on row bits 1..3 only, so the
@@ -223,25 +225,31 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     const int n_tiles = k_len / kGemmBK;
+    auto issue_all = [&](int kt, auto stage_c) __attribute__((always_inline)) {
+        const char* const ab = tile_a(kt);
+        const char* const bb = tile_b(kt);
 #pragma unroll
-    for (int t = 0; t < STAGES - 1; ++t)
-        if (t == 0) issue(0, std::integral_constant<int, 0>{});
-        else if (t == 1) { if (n_tiles > 1) issue(1, std::integral_constant<int, 1>{}); }
-        else { if (n_tiles > 2) issue(2, std::integral_constant<int, 2>{}); }
-    // Loads retire in order, 8 per tile and wavefront: tile kt has landed once at most 8 * (tiles issued after it)
-    // loads are outstanding.
-    auto wait_landed = [&](int younger) {
-        if (younger >= 2) __builtin_amdgcn_s_waitcnt(0x4F70);            // vmcnt(16): the count's bits 5:4 sit in bits 15:14
-        else if (younger == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);   // vmcnt(8)
-        else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+        for (int j = 0; j < 8; ++j) issue(ab, bb, B_KROWS && kt >= last_tile, j, stage_c);
     };
+    issue_all(0, std::integral_constant<int, 0>{});
+    if constexpr (STAGES == 4) {
+        issue_all(1, std::integral_constant<int, 1>{});
+        issue_all(2, std::integral_constant<int, 2>{});
+    }
     auto step = [&](int kt, auto stage_c) __attribute__((always_inline)) {
         constexpr int st = decltype(stage_c)::value;
-        wait_landed(min(n_tiles - 1 - kt, STAGES - 2));
+        constexpr std::integral_constant<int, (st + STAGES - 1) % STAGES> fill{};
+        // Loads retire in order, 8 per tile and wavefront: tile kt has landed once at most those of the two tiles after it are
+        // outstanding (four stages; loads past the last tile are issued all the same, so that the count holds to the end) or none.
+        if constexpr (STAGES == 4) __builtin_amdgcn_s_waitcnt(0x4F70);       // vmcnt(16): the count's bits 5:4 sit in bits 15:14
+        else __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();                         // landed for every wavefront; the stage of tile kt - 1 is free
         asm volatile("" ::: "memory");
-        if (kt + STAGES - 1 < n_tiles) issue(kt + STAGES - 1, std::integral_constant<int, (st + STAGES - 1) % STAGES>{});
+        const char* const ab = tile_a(kt + STAGES - 1);
+        const char* const bb = tile_b(kt + STAGES - 1);
+        const bool tail = B_KROWS && kt + STAGES - 1 >= last_tile;
+        if (STAGES == 2 && kt + 1 < n_tiles) issue_all(kt + 1, fill);
         // operand fragments of k-step s + 1 are read while the MFMAs of step s run (in the order written)
         auto read_a = [&](int s, int i) __attribute__((always_inline)) {
             return *reinterpret_cast<const __attribute__((address_space(3))) enc_bf16x8*>(a_addr[s] + st * kGemmTileBytes + i * 32 * 128);
@@ -263,12 +271,25 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int cur = s & 1, nxt = cur ^ 1;
-            if (s + 1 < 4) { af[nxt][0] = read_a(s + 1, 0); af[nxt][1] = read_a(s + 1, 1); bf[nxt][0] = read_b(s + 1, 0); bf[nxt][1] = read_b(s + 1, 1); }
+            // Four stages, one wavefront to a SIMD: behind each product one operand read of the next 16 contraction elements and one
+            // load of a tile to come, where the wavefront would only wait for the product.  (All of them ahead of the four products of
+            // a k-step: 41 us on 1365 x 4096 weights times 4096 x 1152 tokens, two items; one by one, spread over the step, 31.  A tile's
+            // first operands read in the step before it as well: no gain.  Eight wavefronts, each half with half of a tile's
+            // contraction: 38.)  Two stages, two workgroups to a unit: the other one's products run meanwhile.
+            if (STAGES == 2 && s + 1 < 4) { af[nxt][0] = read_a(s + 1, 0); af[nxt][1] = read_a(s + 1, 1); bf[nxt][0] = read_b(s + 1, 0); bf[nxt][1] = read_b(s + 1, 1); }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+            for (int k = 0; k < 4; ++k) {
+                const int i = k >> 1, j = k & 1;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+                if constexpr (STAGES == 4) {
+                    if (s + 1 < 4) {
+                        if (k < 2) af[nxt][k] = read_a(s + 1, k);
+                        else bf[nxt][k - 2] = read_b(s + 1, k - 2);
+                    }
+                    if (k & 1) issue(ab, bb, tail, 2 * s + (k >> 1), fill);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -280,6 +301,8 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
             if (kt + 3 < n_tiles) step(kt + 3, std::integral_constant<int, 3>{});
         }
     }
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);                       // (the loads past the last tile, before the ring is written to)
 
     // register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the wavefront's quadrant
     const int row_q = m0 + wm * 64, col_q = n0 + wn * 64;
