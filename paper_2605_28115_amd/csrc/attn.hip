@@ -86,7 +86,7 @@ struct AttnArgs {
 // lie there: channels 16 t + 4 (lane / 16) .. + 3 of key lane % 16 serve four consecutive MFMAs, channels 64 T + 4 (lane % 16) ..
 // + 3 of one key are four rows of V^T.  S^T leaves a lane with four consecutive keys of one query, which is the B operand of
 // O^T += V^T P^T as it stands.  L1 delivers 16 KB per 16 x 16 tile and wavefront, 32 bytes a clock and unit at full MFMA rate.
-// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), 28.8 us here.
+// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), 24.7 us here.
 template <bool BF16>
 __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 {
@@ -104,9 +104,12 @@ static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * (kF32Wave
 
 // NT: head_dim rounded up to 64, over 64.  SUB: sub-tiles of 16 keys a tile (launch_f32_for says which).  TAIL: head_dim ends inside
 // a step of 16 channels (as a check in the loop it cost 0.4 of 43 us on 469 rows with 16 / 8 heads of 128, which have no tail).
-template <bool BF16, int NT, int SUB, bool TAIL>
+// FULL: head_dim is 64 NT.  Its steps are known then, and the loop has no branches around them: loads and products of different steps
+// mix, and a tile's first products do not wait for all of its K rows.
+template <bool BF16, int NT, int SUB, bool TAIL, bool FULL>
 __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_kernel(AttnArgs a)
 {
+    static_assert(!(TAIL && FULL), "a full head has no tail");
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
     constexpr int KEYS = 16 * SUB;                             // SUB sub-tiles of 16 keys a tile
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
     const int l16 = lane & 15, kq = lane >> 4;
     const int row_tile = gridDim.x - 1 - blockIdx.x;           // the heaviest causal tiles first
     const int h = blockIdx.y, b = blockIdx.z, group = a.n_q_heads / a.n_kv_heads;
-    const int g = h / group, d = a.head_dim, i0 = row_tile * kF32Rows;
+    const int g = h / group, d = FULL ? 64 * NT : a.head_dim, i0 = row_tile * kF32Rows;
     const int rows = min(kF32Rows, a.seq - i0);
     const int64_t kv_off = b * a.ks[0] + g * a.ks[2];
 
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
     }
 }
 
-template <bool BF16, int NT, int SUB, bool TAIL>
+template <bool BF16, int NT, int SUB, bool TAIL, bool FULL>
 static int launch_f32_tail(const AttnArgs& a, hipStream_t s)
 {
     const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(a.seq) + kF32Rows - 1) / kF32Rows), static_cast<unsigned>(a.n_q_heads),
@@ -328,29 +331,34 @@ static int launch_f32_tail(const AttnArgs& a, hipStream_t s)
     constexpr size_t lds = f32_lds_bytes(NT);
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
-        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<BF16, NT, SUB, TAIL>), lds, &allowed);
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(attn_f32_kernel<BF16, NT, SUB, TAIL, FULL>), lds, &allowed);
         if (rc != CIVIC_OK) return rc;
     }
-    civic::launch((attn_f32_kernel<BF16, NT, SUB, TAIL>), grid, dim3(kF32Waves * kWave), lds, s, a);
+    civic::launch((attn_f32_kernel<BF16, NT, SUB, TAIL, FULL>), grid, dim3(kF32Waves * kWave), lds, s, a);
     return check_launch();
 }
 
 template <bool BF16, int NT, int SUB>
 static int launch_f32(const AttnArgs& a, hipStream_t s)
 {
-    return a.head_dim % 16 ? launch_f32_tail<BF16, NT, SUB, true>(a, s) : launch_f32_tail<BF16, NT, SUB, false>(a, s);
+    if (a.head_dim == 64 * NT) return launch_f32_tail<BF16, NT, SUB, false, true>(a, s);
+    return a.head_dim % 16 ? launch_f32_tail<BF16, NT, SUB, true, false>(a, s) : launch_f32_tail<BF16, NT, SUB, false, false>(a, s);
 }
 
 template <bool BF16>
 static int launch_f32_for(const AttnArgs& a, hipStream_t s)
 {
-    // 32 keys a tile for long contexts, but 16
+    // 16 keys a tile
     //   - up to 64 keys, one tile for each wavefront, where the instructions of the longer tile are most of the time (17 rows,
     //     4 / 2 fp32 heads of 64 / 128: 4.4 / 6.0 us, 5.3 / 7.7 in tiles of 32, 4.2 / 5.8 with one row per wavefront on the vector
     //     units; 32 x 64 rows, 16 / 8 heads of 128: 33.1, 41.2 and 172.8)
+    //   - for fp32 heads of 64 and 128, whose loop has no branches, and between them up to 1024 keys: more wavefronts fit a unit (us in
+    //     tiles of 32 and 16: 469 rows, 16 / 8 heads of 128 26.2 and 24.7; 8 x 100, 32 / 8 of 128 36.0 and 28.2; 4 x 300, 16 / 16 of 64
+    //     25.1 and 22.1; 3 x 400, 16 / 16 of 96 48.5 and 43.5, but 1500, 8 / 8 of 96 83.3 and 86.5, 469, 16 / 8 of 40 14.4 and 15.1)
     //   - for heads wider than 128, where two workgroups then fit a unit (up to 192) and nothing is spilled (beyond): 469
     //     rows, 16 / 8 fp32 heads of 192 / 256: 36.0 / 72.4 us, 56.6 / 120.7 in tiles of 32; bf16 45.8 / 102, 69.7 / 144
-    const bool few = a.kv_seq <= 64;
+    // and 32 elsewhere.
+    const bool few = a.kv_seq <= 64 || (!BF16 && (a.head_dim == 64 || a.head_dim == 128 || (a.head_dim > 64 && a.kv_seq <= 1024)));
     if (a.head_dim <= 64) return few ? launch_f32<BF16, 1, 1>(a, s) : launch_f32<BF16, 1, 2>(a, s);
     if (a.head_dim <= 128) return few ? launch_f32<BF16, 2, 1>(a, s) : launch_f32<BF16, 2, 2>(a, s);
     if (a.head_dim <= 192) return launch_f32<BF16, 3, 1>(a, s);

@@ -517,3 +517,17 @@ def test_kv_compress_of_a_batch_is_that_of_its_items(bd, items, rows):
     kp, _ = bd.civic_kv_compress_ragged(packed, packed, torch.cat([torch.rand((1500, 132), generator=g, device="cuda"), r]), [0, 1500, 1500 + rows])
     torch.cuda.synchronize()
     assert torch.equal(one[0][0], kc[-1]) and torch.equal(one[1][0], vc[-1]) and torch.equal(kp[1], kc[-1])
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 56, 96, 120])
+@pytest.mark.parametrize("seq", [15, 64, 65, 81, 130, 1023, 1025])
+def test_f32_attention_whole_heads_and_tiles_of_keys(bd, d, seq):
+    """fp32 attention at the tile lengths its launch chooses between (64 and 1024 keys), for heads that fill their steps of 64 channels
+    and heads that do not.  Sums of up to 1025 products in another order: 1e-5, as large as the repository's fp32 tolerance."""
+    log("fp32 attention tiles", d, seq)
+    rng = np.random.default_rng(d + seq)
+    q, k, v = (rng.standard_normal((1, seq, h, d)).astype(np.float32) for h in (4, 2, 2))
+    for causal in (True, False):
+        out = to_host(bd.civic_prefill_attn(to_dev(q), to_dev(k), to_dev(v), causal))
+        ref = oracle.attention(q, k, v, causal)
+        assert np.abs(out.astype(np.float64) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
