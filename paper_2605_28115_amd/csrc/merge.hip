@@ -162,11 +162,11 @@ __global__ __launch_bounds__(T, T / 128) void merge_kernel(MAP, MergeTensors)
     }
     int32_t* const kept_idx = a.kept_idx + place * a.kept;
 
-    for (int32_t j0 = first; j0 < last; j0 += kMergeRows) {
-        const int32_t nrows = min(kMergeRows, last - j0);
+    for (int32_t j0 = first, nrows; j0 < last; j0 += nrows) {          // (nrows at most last - j0: j0 stays in range)
+        nrows = min(kMergeRows, last - j0);
         const int32_t slot0 = text_only ? j0 : j0 + it.head;           // compact row of the run's first row
         // text of both ends: rows from `split` on lie behind the rows in between
-        const int32_t split = text_only ? max(it.head - j0, 0) : nrows;
+        const int32_t split = text_only ? min(max(it.head - j0, 0), nrows) : nrows;
         const int32_t gap = text_only ? it.seq_c - it.head - it.tail : 0;
         if (j0 != first) __syncthreads();                              // the sources of the run before are still read
         if (text_only) {
