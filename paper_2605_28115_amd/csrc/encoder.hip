@@ -771,7 +771,8 @@ __global__ __launch_bounds__(256) void col_part_sum_kernel(const float* __restri
 //     waits for both when the step's products are done.
 // R may have any scale: a wavefront whose results are not finite, or whose column sums are below 2^-40, makes its results again from
 // weights that are normalised before they are rounded, one fp32 multiply-add each.
-// The rounded columns are divided by sums of the same rounded values; against 64 bits the error is 0.67 to 1.00 of that of weights
+// The rounded columns are divided by sums of the same rounded values (of the unrounded ones where a workgroup's columns hold a
+// negative entry and a sum may cancel); against 64 bits the error is 0.67 to 1.00 of that of weights
 // normalised first and rounded after (60 sizes of 1 to 2048 rows, four distributions of R).
 // One step takes 2270 clocks: 64 KB of R in fp32 and 32 KB of X at the 64 bytes a clock that a unit can load are 1536.  Kernel times:
 // eight items of 85 to 1365 rows, 256 x 1152 out, 21 us.
@@ -786,7 +787,8 @@ struct CompressArgs {
 constexpr int kCmpTile = 64 * 128 * 2;                        // bytes of one operand tile of 64 contraction rows
 constexpr float kMinColumnSum = 9.094947e-13f;                // 2^-40
 
-// QUADS: m a multiple of 4, so that rows of R are aligned to 16 bytes and made of whole quads of columns.
+// QUADS: m a multiple of 4, so that rows of R are aligned to 16 bytes and made of whole quads of columns, and below 2^24, so that 64
+// rows are below 2^32 bytes (128 rows as well where KG = 2 is taken: launches of 897 rows or more have at most 2^22 columns).
 template <bool PACKED, bool QUADS, int KG>
 __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
 {
@@ -817,8 +819,9 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
 
     // R: thread -> four columns of rows row_r, row_r + 8, ... of its group's 64
     const int t256 = tid & 255, col4 = (t256 & 31) * 4, row_r = t256 >> 5;
-    const uint32_t r_pitch = static_cast<uint32_t>(g.m) * 4u, x_pitch = static_cast<uint32_t>(g.n) * 2u;
-    uint32_t r_off[8];                                        // bytes from the step's first row
+    // bytes of a row of R; elements where rows are not whole quads or 64 of them take more than 32 bits of bytes
+    const uint32_t r_pitch = static_cast<uint32_t>(g.m) * (QUADS ? 4u : 1u), x_pitch = static_cast<uint32_t>(g.n) * 2u;
+    uint32_t r_off[8];                                        // from the step's first row
 #pragma unroll
     for (int j = 0; j < 8; ++j) r_off[j] = static_cast<uint32_t>(kg * 64 + row_r + 8 * j);
     enc_f32x4 rv[kSets][8];
@@ -832,7 +835,7 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     auto fetch_row = [&](const char* base, uint32_t last_row, int j, auto set_c) __attribute__((always_inline)) {
         constexpr int set = decltype(set_c)::value % kSets;
         // (global by type: a pointer put together from scalars is a generic one, whose loads count as LDS accesses as well)
-        const auto p = (const __attribute__((address_space(1))) char*)base + min(r_off[j], last_row);
+        const auto p = (const __attribute__((address_space(1))) char*)base + static_cast<uint64_t>(min(r_off[j], last_row)) * (QUADS ? 1u : 4u);
         if constexpr (QUADS) {
             rv[set][j] = *(const __attribute__((address_space(1))) enc_f32x4*)p;
         } else {
@@ -843,7 +846,9 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     };
     // (steps, rows and columns past the end re-read the last one)
     auto step_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(r_item + m0 + static_cast<int64_t>(min(step, steps - 1)) * kStep * g.m); };
-    auto step_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * kStep) * r_pitch + r_col; };
+    auto step_last = [&](int step) __attribute__((always_inline)) {
+        return static_cast<uint32_t>(min(rows - 1 - min(step, steps - 1) * kStep, kStep - 1)) * r_pitch + r_col;
+    };
     auto fetch_r = [&](int step, auto set_c) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) fetch_row(step_base(step), step_last(step), j, set_c);
@@ -865,6 +870,7 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     // multiplied: the weights of a column add up to one whatever the rounding did, and a single row's weight is exact.  Packed dot
     // products with (1, 0) and (0, 1) for the sums, an instruction less each, were 2 % slower.)
     u32x2 word;
+    uint32_t signs = 0;
     auto round_r = [&](int j, auto set_c) __attribute__((always_inline)) {
         const enc_f32x4 v = rv[decltype(set_c)::value % kSets][j];
         const enc_bf16x2 lo = {static_cast<__bf16>(v.x), static_cast<__bf16>(v.y)}, hi = {static_cast<__bf16>(v.z), static_cast<__bf16>(v.w)};
@@ -878,6 +884,7 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
             lds + decltype(set_c)::value * kCmpStage + kg * kCmpTile + kr * 256 + (((col4 >> 3) ^ enc_swz16(kr)) << 4) + (col4 & 4) * 2) = word;
         csum[decltype(set_c)::value % kOwn][2] += __uint_as_float(word.y << 16);
         csum[decltype(set_c)::value % kOwn][3] += __uint_as_float(word.y & 0xFFFF0000u);
+        signs |= word.x | word.y;
     };
     // X: instruction j of the group's wavefront q fills slots [(4 q + j) * 64, +64) of the group's tile
     uint32_t x_off[4], x_col[4];
@@ -1013,7 +1020,8 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     float4* const meet = reinterpret_cast<float4*>(cmp_lds);                  // KG == 2: [8 wavefronts][8 register quads][64 lanes]
     float* const parts = reinterpret_cast<float*>(meet + (KG == 2 ? 8 * 8 * kWave : 0));   // [16 row slots][128]
     float* const inv = parts + 16 * 128;                                      // [128]
-    __bf16* const stages = KG == 2 ? reinterpret_cast<__bf16*>(cmp_lds) : reinterpret_cast<__bf16*>(inv + 128);
+    int* const negative = reinterpret_cast<int*>(inv + 128);                  // [8 wavefronts]
+    __bf16* const stages = KG == 2 ? reinterpret_cast<__bf16*>(cmp_lds) : reinterpret_cast<__bf16*>(negative + 8);
     if constexpr (KG == 2) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -1028,7 +1036,39 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
         const int odd_rows = KG == 2 ? kg : o ^ (~steps & 1); // (the last of an even number of steps is in stage 0)
         *reinterpret_cast<float4*>(parts + (odd_rows * 8 + row_r) * 128 + col4) = make_float4(csum[o][0], csum[o][1], csum[o][2], csum[o][3]);
     }
+    const bool some_negative = __any((signs & 0x80008000u) != 0);
+    if (lane == 0) negative[w] = some_negative;
     __syncthreads();
+    int any_negative = 0;
+#pragma unroll
+    for (int x = 0; x < 4 * KG; ++x) any_negative |= negative[x];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any_negative), 0)) {
+        // R with negative entries: a sum can be far smaller than its terms, and what rounding does to them would be most of it.
+        // The columns are summed once more as they lie, eight row slots of 32 quads of columns.
+        if (tid < 256) {
+            float t[4] = {0.f, 0.f, 0.f, 0.f};
+            const float* const first = r_item + m0;
+            const int last = g.m - 1 - m0;
+            constexpr int kAhead = QUADS ? 8 : 4;
+            for (int64_t k = row_r; k < rows; k += 8 * kAhead) {
+                enc_f32x4 v[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const float* const f = first + (k + 8 * u < rows ? k + 8 * u : rows - 1) * static_cast<int64_t>(g.m);
+                    if constexpr (QUADS) v[u] = *reinterpret_cast<const enc_f32x4*>(f + min(col4, last - 3));
+                    else v[u] = enc_f32x4{f[min(col4, last)], f[min(col4 + 1, last)], f[min(col4 + 2, last)], f[min(col4 + 3, last)]};
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const bool in = k + 8 * u < rows;
+                    t[0] += in ? v[u].x : 0.f; t[1] += in ? v[u].y : 0.f; t[2] += in ? v[u].z : 0.f; t[3] += in ? v[u].w : 0.f;
+                }
+            }
+            *reinterpret_cast<float4*>(parts + row_r * 128 + col4) = make_float4(t[0], t[1], t[2], t[3]);
+            *reinterpret_cast<float4*>(parts + (8 + row_r) * 128 + col4) = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        __syncthreads();
+    }
     if (tid < 128) {
         float t = 0.f;
 #pragma unroll
@@ -1130,7 +1170,7 @@ template <bool PACKED, bool QUADS, int KG>
 static int launch_compress_variant(const CompressArgs& g, hipStream_t s)
 {
     constexpr size_t lds = 2 * 2 * KG * kCmpTile;
-    static_assert(lds >= ((KG == 2 ? 8 * 32 * kWave : 4 * 64 * 40 / 2) + 17 * 128) * 4, "the ring holds what is staged at the end");
+    static_assert(lds >= ((KG == 2 ? 8 * 32 * kWave : 4 * 64 * 40 / 2) + 17 * 128 + 8) * 4, "the ring holds what is staged at the end");
     static std::atomic<uint64_t> allowed{0};
     const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(compress_kernel<PACKED, QUADS, KG>), lds, &allowed);
     if (rc != CIVIC_OK) return rc;
@@ -1160,8 +1200,8 @@ static int launch_compress(const CompressArgs& g_in, int64_t items, bool packed,
     // groups and one: 4 x 2048 rows, 512 x 1024 out 28.5 and 31.2; 6 x 1024, 256 x 1152 16.9 and 18.5; 8 x 1024 30.1 and 24.1; eight
     // items of 85..1365 23.4 and 24.9; 16 x 700, 128 x 768 19.5 and 18.1; 24 x 24, 512 x 1280 52.2 and 26.8.)
     const bool one = longest < 8 || all_steps * 2 * g.tiles_n * g.tiles_m > 256 * longest;
+    if (g.m % 4 || g.m >= (1 << 24)) return packed ? launch_compress_variant<true, false, 1>(g, s) : launch_compress_variant<false, false, 1>(g, s);
     if (packed) return one ? launch_compress_variant<true, true, 1>(g, s) : launch_compress_variant<true, true, 2>(g, s);
-    if (g.m % 4) return launch_compress_variant<false, false, 1>(g, s);
     return one ? launch_compress_variant<false, true, 1>(g, s) : launch_compress_variant<false, true, 2>(g, s);
 }
 

@@ -519,6 +519,36 @@ def test_kv_compress_of_a_batch_is_that_of_its_items(bd, items, rows):
     assert torch.equal(one[0][0], kc[-1]) and torch.equal(one[1][0], vc[-1]) and torch.equal(kp[1], kc[-1])
 
 
+@pytest.mark.parametrize("rows,mem,width", [(2, 4, 8), (65, 127, 136), (200, 130, 72), (390, 132, 64), (1025, 132, 64)])
+def test_kv_compress_of_signed_assignments(bd, rows, mem, width):
+    """R with negative entries, some of whose column sums nearly cancel: the error stays that of weights rounded to bf16, 2^-8 of the sum
+    of |weight x| and of the result, and of an fp32 sum (chains of at most 129 + 8 terms, below 2^-16 of the sum of |weight|).  A batch,
+    an item of its own and an item among longer ones give the same bits."""
+    log("kv compress signed", rows, mem, width)
+    rng = np.random.default_rng(rows + mem + width)
+    k, k32 = wl.quantize(rng.standard_normal((3, rows, width)).astype(np.float32) + 1, "bf16")
+    r = rng.standard_normal((rows, mem)).astype(np.float32)
+    r[:, 3] = np.abs(r[:, 3])
+    r[-1, :2] = -r[:-1, :2].astype(np.float64).sum(0) + np.asarray([0.01, -0.5]) * (1 if rows > 2 else 0.1)
+    dk, dr = to_dev(k), torch.from_numpy(r).cuda()
+    kc, vc = bd.civic_kv_compress(dk, dk, dr)
+    w = r.astype(np.float64) / r.astype(np.float64).sum(0)
+    for b in range(3):
+        x = k32[b].astype(np.float64)
+        ref = w.T @ x
+        bar = 2.0 ** -8 * (np.abs(w).T @ np.abs(x)) + (2.0 ** -8 + 2.0 ** -16 * np.abs(w).sum(0)[:, None]) * np.abs(ref) + 1e-30
+        for got in (kc, vc):
+            err = np.abs(widen(to_host(got[b])).astype(np.float64) - ref)
+            assert (err <= bar).all(), float((err / bar).max())
+    one, _ = bd.civic_kv_compress(dk[2:].contiguous(), dk[2:].contiguous(), dr)
+    assert torch.equal(one[0], kc[2])
+    if mem % 4 == 0:
+        long = torch.ones((1500, width), device="cuda").bfloat16()
+        packed = torch.cat([long, dk[2]])
+        kp, _ = bd.civic_kv_compress_ragged(packed, packed, torch.cat([torch.rand((1500, mem), device="cuda"), dr]), [0, 1500, 1500 + rows])
+        assert torch.equal(kp[1], kc[2])
+
+
 @pytest.mark.parametrize("d", [64, 128, 192, 256, 56, 96, 120])
 @pytest.mark.parametrize("seq", [15, 64, 65, 81, 130, 1023, 1025])
 def test_f32_attention_whole_heads_and_tiles_of_keys(bd, d, seq):
