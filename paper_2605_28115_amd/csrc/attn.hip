@@ -399,13 +399,14 @@ typedef __attribute__((address_space(3))) char lds_char;
 // tracks these loads with explicit s_waitcnt vmcnt(N), and an LDS read the compiler could see racing
 // with an asynchronous LDS write would make it drain the whole load queue first.  m0 is written and not
 // declared: the register is reserved (the compiler rejects it as a clobber), never allocated, and set by the
-// compiler only directly in front of an instruction that reads it, of which this file has none.
+// compiler only directly in front of an instruction that reads it, of which this file has none.  (A load into LDS may read m0 one
+// wait state after a scalar instruction wrote it.)
 template <int LDS_IMM>
 __device__ __forceinline__ void dma16(const void* base, uint32_t byte_off, uint32_t lds_addr)
 {
     // (the LDS address is lds_addr + LDS_IMM, added here so that one scalar register serves every instruction
     // of a tile instead of one register per instruction)
-    asm volatile("s_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(byte_off), "s"(base), "n"(LDS_IMM) : "memory", "scc");
 }
 
@@ -866,7 +867,10 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
             mx = fmaxf(fmaxf(mx, max3(x[12], x[13], x[14])), x[15]);
             mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
             const float m_new = fmaxf(mx, m_run);
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * sl2);
+            float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * sl2);
+            // (The compiler counts no wait states into or out of an asm statement: an exponential's result may be read one instruction
+            // later at the earliest, a product may read what a vector instruction wrote two later.)
+            asm volatile("s_nop 1" : "+v"(alpha));
             l_run[0] *= alpha; l_run[1] *= alpha;
             // (in place, tied operands: the accumulators stay in the registers they have on the common path)
 #pragma unroll
@@ -874,7 +878,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     float y = acc_o[t][r];
-                    asm volatile("v_mul_f32 %0, %0, %1" : "+v"(y) : "v"(alpha));
+                    asm volatile("v_mul_f32 %0, %0, %1\n\ts_nop 1" : "+v"(y) : "v"(alpha));
                     acc_o[t][r] = y;
                 }
             m_run = m_new;

@@ -68,7 +68,7 @@ template <int LDS_IMM>
 __device__ __forceinline__ void enc_dma16(const void* base, uint32_t byte_off, uint32_t lds_addr)
 {
     // 16 bytes per lane from base + byte_off (scalar base, per-lane offset) into LDS at lds_addr + LDS_IMM + lane * 16
-    asm volatile("s_add_u32 m0, %0, %3\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(byte_off), "s"(base), "n"(LDS_IMM) : "memory", "scc");
 }
 
