@@ -463,11 +463,15 @@ struct AttnTile {
     static constexpr int TLOADS = 2 * NI;                  // ... per tile (K and V)
     static constexpr int VBASE = STAGES * TILEB;           // byte offset of the V stages
     static constexpr int OROW = DP + 8;                    // elements per staged output row (padded against bank conflicts)
-    // behind the rings every wavefront owns an area that first stages its Q tile (32 rows in the K tile layout)
-    // and later its 32 x DP output tile
+    // Every wavefront has an area that first stages its Q tile (32 rows in the K tile layout) and later its 32 x DP output tile.  With
+    // 8 wavefronts it lies behind the rings, since a second row tile's Q arrives while they are in use.  With 4 wavefronts there is one
+    // row tile, and the rings themselves serve: the four Q tiles fill stage 1 of K and V, which the first key tile does not touch, and
+    // the output comes when all keys are done.  64 KB instead of 99 at 128 channels: two workgroups fit a unit.
     static constexpr int QW = 32 * PITCHB;
     static constexpr int WAREA = QW > 32 * OROW * 2 ? QW : 32 * OROW * 2;
-    static constexpr int LDS_BYTES = 2 * STAGES * TILEB + WAVES * WAREA;
+    static constexpr bool IN_RINGS = WAVES == 4;
+    static constexpr int LDS_BYTES = 2 * STAGES * TILEB + (IN_RINGS ? 0 : WAVES * WAREA);
+    static_assert(!IN_RINGS || (2 * QW == TILEB && WAVES * WAREA <= 2 * STAGES * TILEB), "the rings hold four Q tiles in stage 1, four output tiles");
     static_assert(WAVES == 4 || WAVES == 8, "block shapes are 4 or 8 wavefronts");
     static_assert(STAGES == 2, "every wait below is for all outstanding loads, which fits a ring of two");
 };
@@ -507,7 +511,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     // first K/V tile are fetched under the first one's last tiles and output stores.
     auto div_magic = [](uint32_t n, uint32_t magic) { return magic ? __umulhi(n, magic) : n; };
     int rt = a.row_tiles - 1 - static_cast<int>(blockIdx.y);
-    int rt_next = a.paired ? static_cast<int>(blockIdx.y) - (a.row_tiles & 1) : -1;
+    int rt_next = !T::IN_RINGS && a.paired ? static_cast<int>(blockIdx.y) - (a.row_tiles & 1) : -1;
     const uint32_t bid = blockIdx.x;
     const uint32_t bid_hb = div_magic(bid, a.magic_head_blocks);      // = kv head + n_kv_heads * batch
     const int hb = static_cast<int>(bid - bid_hb * head_blocks);
@@ -552,9 +556,9 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
 
     // Q first: its loads are the longest wait of the prologue, everything else is set up in their shadow.
     // Q goes through LDS as well (same swizzled layout as a K tile, 32 rows per wavefront, in the wavefront's
-    // own area behind the rings), so that the main loop holds no register-destination global load: the
+    // own area), so that the main loop holds no register-destination global load: the
     // compiler then never emits a vmcnt wait of its own there.
-    const uint32_t q_lds = 2 * VBASE + w * T::WAREA;
+    const uint32_t q_lds = T::IN_RINGS ? (w & 1) * T::QW + TILEB + (w >> 1) * VBASE : 2 * VBASE + w * T::WAREA;
     const char* qb = reinterpret_cast<const char*>(static_cast<const __bf16*>(a.q) + q_first + h * a.qs[2]);
     const uint64_t qb_bits = reinterpret_cast<uint64_t>(qb);
     // (the builtin returns a signed int: widen each half as unsigned)
@@ -969,7 +973,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     constexpr int CPR = DP / 8;
     constexpr int kKvJ = (DP / 8 + 7) / 8;                     // pieces per thread, row and tensor
     constexpr int kKvRows = WAVES * kWave / 8;                 // rows per pass of the workgroup (64 with 8 wavefronts)
-    __bf16* const o_s = reinterpret_cast<__bf16*>(smem) + q_lds / 2;   // the wavefront's area, now its output tile
+    __bf16* const o_s = reinterpret_cast<__bf16*>(smem) + (T::IN_RINGS ? w * T::WAREA : q_lds) / 2;   // the wavefront's area, now its output tile
 
     for (;;) {
 #pragma unroll
@@ -977,7 +981,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc_o[t][r] = 0.f;
         m_run = 0.f; l_run[0] = 0.f; l_run[1] = 0.f;
-        const bool has_next = rt_next >= 0;
+        const bool has_next = !T::IN_RINGS && rt_next >= 0;
         q_issue = has_next ? max(n_tiles - 3, 0) : -1;
         next_row0 = rt_next * RB * 32 + wrow;
 
@@ -1179,6 +1183,39 @@ static bool choose_paired(const AttnArgs& a, int64_t per_rt, int rows_per_block)
     return paired;
 }
 
+// Whether the launch takes workgroups of 8 wavefronts (256 query rows x heads); `a` holds their geometry.  Workgroups of 4 wavefronts,
+// two to a unit, do not wait for each other at every key tile, start and end under each other's products and leave less idle at the
+// end of a launch; those of 8 bring half as many K/V tiles into LDS and can pair causal row tiles.  8 is faster only for long rows of
+// keys where its workgroups fill the units (us, 8 and 4 wavefronts; bf16 heads of 128 unless said):
+//   - up to 128 workgroups of 8: 4.  1 x 469 rows causal, 16 / 8 heads 14.9, 11.2; 3 x 550, 16 / 8 17.9, 13.7
+//   - no mask, one generation of 8: 8 from 8 key tiles on.  2 x 1365, 16 / 16 of 72 33.1, 35.2; three items of 700 to 1100 rows over
+//     512 keys, 16 / 16 of 72 15.9, 16.6; but two of 656 and 1637 rows over 64 keys, 16 / 16 7.9, 7.4
+//   - no mask, more: 8 for wide heads from 24 key tiles on where the last generation is full.  8 x 4096, 32 / 8 1986, 2077; 3 x 2323,
+//     16 / 8 138, 143; but 4 x 1618, 32 / 8 192, 182; eight items of 85 to 1365 rows over 256 keys, 16 / 16 of 72 23.3, 21.2;
+//     2 x 4096, 16 / 16 of 64 152, 144
+//   - causal: 8 for wide heads where pairs of row tiles fill their generations.  4 x 938, 32 / 8 38.5, 40.0; 1 x 3584, 32 / 8 105.5,
+//     109.6; but 4 x 600, 32 / 8 22.8, 21.1; 8 x 900, 16 / 16 of 64 30.0, 26.8
+//   - causal, not paired (items of different length never are): 8 beyond 44 key tiles and one generation.  Eight items of 3000 rows,
+//     28 / 4 544, 615 and 32 / 8 563, 573; but eight of 101 to 938, 32 / 8 39.8, 35.9; four of 300 to 2700, 32 / 8 178, 169
+static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
+{
+    const int rows_per_block = 32 * (8 / a.heads_per_block);
+    int64_t blocks = per_rt * a.row_tiles;
+    if (ragged) {
+        blocks = 0;
+        for (int i = 0; i < a.batch; ++i)
+            blocks += (static_cast<int64_t>(a.item_row[i + 1]) - a.item_row[i] + rows_per_block - 1) / rows_per_block * (per_rt / a.batch);
+    }
+    const bool paired = !ragged && choose_paired(a, per_rt, rows_per_block);
+    if (a.causal && !paired) return a.head_dim > 64 && blocks > kComputeUnits && a.seq > 44 * kBN;
+    if (paired) blocks = per_rt * ((a.row_tiles + 1) / 2);
+    const int64_t generations = (blocks + kComputeUnits - 1) / kComputeUnits;
+    const bool full = 100 * blocks >= 85 * generations * kComputeUnits;
+    if (a.causal) return a.head_dim > 64 && full;
+    if (generations == 1) return 2 * blocks > kComputeUnits && a.kv_seq > 7 * kBN;
+    return a.head_dim > 64 && full && a.kv_seq > 23 * kBN;
+}
+
 template <int DP, int WAVES, int STAGES, bool RAGGED>
 static int launch_mfma(AttnArgs& a, hipStream_t s)
 {
@@ -1188,7 +1225,7 @@ static int launch_mfma(AttnArgs& a, hipStream_t s)
     auto magic = [](int64_t d) { return d <= 1 ? 0u : static_cast<uint32_t>(((int64_t{1} << 32) + d - 1) / d); };
     a.magic_head_blocks = magic(a.head_blocks);
     a.magic_kv_heads = magic(a.n_kv_heads);
-    a.paired = !RAGGED && choose_paired(a, per_rt, 32 * (WAVES / a.heads_per_block)) ? 1 : 0;   // (pairs assume one length)
+    a.paired = !RAGGED && WAVES == 8 && choose_paired(a, per_rt, 32 * (WAVES / a.heads_per_block)) ? 1 : 0;   // (pairs assume one length)
     const unsigned grid_y = static_cast<unsigned>(a.paired ? (a.row_tiles + 1) / 2 : a.row_tiles);
     constexpr size_t lds = T::LDS_BYTES;
     if (lds > 64 * 1024) {
@@ -1270,17 +1307,13 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
 
     // the MFMA path addresses a K/V tile, and a head's Q rows, with 32-bit per-lane byte offsets, and its grid
     // has limits of its own; whatever falls outside takes the plain kernel
-    // Workgroups of 8 wavefronts (256 query rows x heads) share each K/V tile the most; when they would
-    // leave at least half of the compute units without work, workgroups of 4 wavefronts spread it over twice
-    // as many (measured: 32 workgroups of 8 wavefronts 15.4 us, 64 of 4 12.2 us; but 192 of 8 37.9 us against
-    // 384 of 4, two per unit, 39.7 us).
     int64_t per_rt = 0;
     // (with a rotary table the MFMA kernel needs an unpadded head whose halves are whole k-step pairs)
     const bool rope_fits = !q_cos_sin || head_dim == 64 || head_dim == 96 || head_dim == 128;
     if (dtype == CIVIC_BF16 && head_dim <= 128 && rope_fits && kv_strides[1] * 2 < (1 << 25) &&
         static_cast<int64_t>(seq) * q_strides[1] * 2 < (int64_t{1} << 32) && mfma_geometry<8>(a, &per_rt)) {
         if (dry_run) return CIVIC_OK;
-        const bool eight = 2 * per_rt * a.row_tiles > kComputeUnits || !mfma_geometry<4>(a, &per_rt);
+        const bool eight = eight_wavefronts(a, per_rt, item_row != nullptr) || !mfma_geometry<4>(a, &per_rt);
         if (item_row) return eight ? launch_mfma_for<8, true>(a, s) : launch_mfma_for<4, true>(a, s);
         return eight ? launch_mfma_for<8, false>(a, s) : launch_mfma_for<4, false>(a, s);
     }

@@ -561,3 +561,38 @@ def test_f32_attention_whole_heads_and_tiles_of_keys(bd, d, seq):
         out = to_host(bd.civic_prefill_attn(to_dev(q), to_dev(k), to_dev(v), causal))
         ref = oracle.attention(q, k, v, causal)
         assert np.abs(out.astype(np.float64) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("case", [
+    # batch, rows, query heads, KV heads, width, causal, rotary: the batch in workgroups of 8 wavefronts, a single sample in those of 4
+    (4, 938, 32, 8, 128, True, False), (4, 938, 32, 8, 128, True, True), (3, 1440, 16, 4, 96, True, True), (2, 1365, 16, 16, 72, False, False),
+    (2, 1153, 8, 8, 128, False, False), (12, 1537, 4, 4, 64, False, False),
+    # both in those of 4, around the ends of their row and key tiles
+    (3, 1, 4, 2, 64, True, False), (2, 65, 4, 4, 96, True, True), (5, 129, 4, 1, 128, True, True), (2, 161, 6, 2, 80, False, False), (9, 767, 8, 8, 128, False, False),
+])
+def test_attention_of_a_batch_is_that_of_its_samples(bd, case):
+    """Attention, with and without rotary positions and the fused cache write, of a batch and of its samples one by one and as a ragged
+    batch: launches choose workgroups of 4 or 8 wavefronts by their size, and the bits are the same.  One sample against the oracle at
+    the repository's tolerance for bf16."""
+    batch, seq, hq, hkv, d, causal, rope = case
+    log("attention by workgroup", case)
+    g = torch.Generator(device="cuda").manual_seed(seq + d)
+    q, k, v = (torch.randn((batch, seq, h, d), generator=g, device="cuda").bfloat16() for h in (hq, hkv, hkv))
+    table = torch.rand((batch, seq, d // 2, 2), generator=g, device="cuda") if rope else None
+
+    def attend(lo, hi):
+        if rope:
+            return (bd.civic_prefill_attn_rope(q[lo:hi], k[lo:hi], v[lo:hi], table[lo:hi], causal),)
+        kc, vc = (torch.zeros((hi - lo, hkv, seq + 3, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        return bd.civic_prefill_attn_kv(q[lo:hi], k[lo:hi], v[lo:hi], kc, vc, 3, causal), kc, vc
+
+    whole = attend(0, batch)
+    for b in {0, batch - 1}:
+        for x, y in zip(whole, attend(b, b + 1)):
+            assert torch.equal(x[b], y[0]), b
+    if not rope:
+        packed = bd.civic_prefill_attn_ragged(q.flatten(0, 1), k.flatten(0, 1), v.flatten(0, 1), [seq * i for i in range(batch + 1)], causal)
+        assert torch.equal(packed.view_as(q), whole[0])
+        ref = oracle.attention(*(t[:1].float().cpu().numpy() for t in (q, k, v)), causal)
+        err = np.abs(whole[0][:1].float().cpu().numpy() - ref).max()
+        assert err <= 2e-2 * max(1.0, np.abs(ref).max()), err
