@@ -368,8 +368,7 @@ int civic_anchor_aggregate(const void* x0, const void* anchors, int dtype, int32
  *   r         device [n_rows, n_mem] fp32, shared by the batch
  *   k_c, v_c  device [batch, n_mem, width] bf16
  *   workspace device, 16-byte aligned, civic_kv_compress_workspace_bytes(same sizes) bytes
- * R is rounded to bf16 for the contraction (bf16 MFMA, fp32 accumulation) and every row of the result divided by its
- * column's sum.  dtype must be CIVIC_BF16. */
+ * Rbar is rounded to bf16 for the contraction (bf16 MFMA, fp32 accumulation).  dtype must be CIVIC_BF16. */
 size_t civic_kv_compress_workspace_bytes(int32_t batch, int32_t n_rows, int32_t n_mem, int32_t width);
 int civic_kv_compress(const void* k, const void* v, int dtype, const float* r, int32_t batch, int32_t n_rows,
                       int32_t n_mem, int32_t width, void* k_c, void* v_c, void* workspace, size_t workspace_bytes,
@@ -387,7 +386,7 @@ int civic_cross_attn(const void* q, const void* k, const void* v, void* out, int
  * packed back to back, item b owning rows [row_offsets[b], row_offsets[b+1]) of k, v and of its own assignment rows in
  * r; every item is compressed and attended by itself, and the results equal civic_kv_compress / civic_cross_attn on
  * that item alone, bit for bit.  Items travel in groups of up to 64 whose row numbers are passed with the launch: the
- * compression is ONE launch per group, the attention ONE launch per group (fp32 or head_dim > 128: one launch per item).
+ * compression is two launches per group (column sums, product), the attention ONE launch per group (fp32 or head_dim > 128: one launch per item).
  *   k, v         device [total_rows, width] bf16;  r  device [total_rows, n_mem] fp32
  *   row_offsets  host [batch + 1] int64, row_offsets[0] = 0, strictly increasing (no empty item)
  *   k_c, v_c     device [batch, n_mem, width] bf16

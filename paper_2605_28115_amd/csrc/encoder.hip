@@ -4,7 +4,7 @@
 //   civic_kv_compress       Eq. 9: K_c = Rbar^T K, V_c = Rbar^T V with the column-normalised assignment matrix
 // (the attention over the compressed keys, softmax(Q K_c^T / sqrt(d)) V_c, is civic_cross_attn in attn.hip).
 //
-// Both are dense contractions and run on the bf16 MFMA pipe.  Eq. 9 has a kernel of its own (compress_kernel, one launch); the
+// Both are dense contractions and run on the bf16 MFMA pipe.  Eq. 9 has a kernel of its own (compress_kernel); the
 // products of Eq. 8 go through one kernel, C = alpha * A B^T, whose B operand may be stored either way round: like A, with the
 // contraction index contiguous (the products Q_A X_0^T behind the logits), or with the contraction index as the row index, which is
 // how X_0 lies in Z_0 = W_A X_0; it is read where it is (transposing LDS reads), no transposed copy is made.  A is always
@@ -735,17 +735,24 @@ __global__ __launch_bounds__(256) void transpose_pad_kernel(const TIN* __restric
     transpose_pad_block<TIN>(in, rows, cols, ld_in, in_batch, part, out, ld_out, out_batch, blockIdx.z);
 }
 
-// Column sums of r [rows, cols], first step: block (x, y) adds the rows y, y + gridDim.y, ... of 64 columns (its four
-// wavefronts four rows apart, coalesced 256-byte reads, meeting in LDS) into part[y, c]; the transposing kernel above
-// adds a column's kColParts partial sums and inverts the total.
+// Column sums of r [rows, cols], first step: block (x, y) adds the rows 4 y .. 4 y + 3 of every 4 kColParts of 64 columns (a row of
+// the four for each wavefront, coalesced 256-byte reads, four in flight, meeting in LDS) into part[y, c]; whoever divides by a column's
+// sum adds its kColParts partial sums in order.
 __device__ __forceinline__ void col_part_sum_block(const float* __restrict__ r, int32_t rows, int32_t cols, float* __restrict__ part)
 {
     __shared__ float lds_part[4][kWave];
+    constexpr int kAhead = 4, kStride = 4 * kColParts;
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
     const int c = blockIdx.x * kWave + lane;
     float acc = 0.f;
     if (c < cols)
-        for (int m = blockIdx.y * 4 + wv; m < rows; m += 4 * kColParts) acc += r[static_cast<int64_t>(m) * cols + c];
+        for (int64_t m = blockIdx.y * 4 + wv; m < rows; m += kAhead * kStride) {
+            float v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = r[(m + u * kStride < rows ? m + u * kStride : m) * cols + c];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) acc = m + u * kStride < rows ? acc + v[u] : acc;
+        }
     lds_part[wv][lane] = acc;
     __syncthreads();
     if (wv == 0 && c < cols)
@@ -757,27 +764,33 @@ __global__ __launch_bounds__(256) void col_part_sum_kernel(const float* __restri
     col_part_sum_block(r, rows, cols, part);
 }
 
-// ------------------------------------------------------------------------------------------ Eq. 9 in one launch
-// X_c = Rbar^T X for X = K and V, Rbar the columns of R over their sums: the product is taken with R as it lies and every row of
-// the result divided by its column's sum, so neither the sums nor a transposed, scaled copy of R have to be there first.  (Three
-// launches before: partial sums 5.0 us, transposed copy 5.8, product 17.8 on eight items of 85 to 1365 rows, 256 x 1152 out.)
-//   - 128 x 128 outputs per workgroup, a quadrant of 64 x 64 per wavefront, in two sums, over the even and over the odd 64 contraction
-//     rows.  KG = 2: eight wavefronts, each half takes one of the sums in steps of 128 rows, and they meet in LDS: for launches that
-//     wait for their longest item's chain of steps, with one workgroup to a unit.  KG = 1: four wavefronts that take both sums in turn
-//     in steps of 64 rows, two workgroups to a unit: for launches of many or short workgroups.  The same bits either way.
-//   - R goes through registers (fp32 to bf16, and its column sums in fp32 on the way), one step ahead, into tiles [64 rows x 128
-//     columns] like those of X, which go straight into LDS; both operands are read with the transposing LDS read.
-//   - one barrier a step: at its head a wavefront writes the next step's R, asks for the R after that and for the next X, and
-//     waits for both when the step's products are done.
-// R may have any scale: a wavefront whose results are not finite, or whose column sums are below 2^-40, makes its results again from
-// weights that are normalised before they are rounded, one fp32 multiply-add each.
-// The rounded columns are divided by sums of the same rounded values (of the unrounded ones where a workgroup's columns hold a
-// negative entry and a sum may cancel); against 64 bits the error is 0.67 to 1.00 of that of weights
-// normalised first and rounded after (60 sizes of 1 to 2048 rows, four distributions of R).
-// One step takes 2270 clocks: 64 KB of R in fp32 and 32 KB of X at the 64 bytes a clock that a unit can load are 1536.  Kernel times:
-// eight items of 85 to 1365 rows, 256 x 1152 out, 21 us.
+// The same for the items of a group (grid z): every item its own rows, its own kColParts x cols partial sums.
+__global__ __launch_bounds__(256) void col_part_sum_grouped_kernel(const float* __restrict__ r, int32_t cols, float* __restrict__ part, Group grp)
+{
+    const int i = blockIdx.z;
+    const int64_t r0 = grp.row[i];
+    col_part_sum_block(r + r0 * cols, grp.row[i + 1] - grp.row[i], cols, part + static_cast<int64_t>(i) * kColParts * cols);
+}
+
+// ------------------------------------------------------------------------------------------ Eq. 9
+// X_c = Rbar^T X for X = K and V, Rbar the columns of R over their sums, rounded to bf16, in two launches: partial column sums of R
+// (col_part_sum_kernel), then the product, which takes R as it lies, divides by its columns' sums and rounds on the way into LDS: no
+// transposed copy of Rbar in memory.  (Rounding R first and dividing the result instead needs no sums ahead of the product, but a
+// column whose sum is far from the entries' size or that nearly cancels then needs a route of its own, and results change.)
+//   - 128 x 128 outputs per workgroup of four wavefronts, a quadrant of 64 x 64 each, in steps of 64 contraction rows, two workgroups
+//     to a unit; one sum per output over all rows in order, whatever the launch holds besides: items of a batch, packed or not, come
+//     out the same bits
+//   - R goes through registers one step ahead, into tiles [64 rows x 128 columns] like those of X, which go straight into LDS; both
+//     operands are read with the transposing LDS read
+//   - one barrier a step: a wavefront writes the next step's R, asks for the R after that and for the next X, and waits for X when
+//     the step's products are done
+// Both launches (us): eight items of 85 to 1365 rows, 256 x 1152 out 25.1; 4 x 2048 rows, 512 x 1024 out 32.3; 6 x 1024, 256 x 1152
+// 19.2; 16 x 700, 128 x 768 19.8; 24 x 24, 512 x 1280 31.1; 1 x 85, 256 x 1152 11.8.  With a transposed copy of Rbar made between
+// the two: 29.8, 35.0, 22.6, 24.4, 30.6, 19.3.  (The R of two steps in registers instead of one's: the same within 2 %, but 33.0 for
+// 24 x 24.)
 struct CompressArgs {
     const float* r;                       // [rows x m], shared by all items or packed like them
+    const float* part;                    // [kColParts x m] partial column sums; PACKED: of every item, one after the other
     const __bf16* x[2];                   // K, V [rows x n]
     __bf16* out[2];                       // [items x m x n]
     int32_t m, n, tiles_m, tiles_n, slabs;
@@ -785,20 +798,18 @@ struct CompressArgs {
     Group grp;
 };
 constexpr int kCmpTile = 64 * 128 * 2;                        // bytes of one operand tile of 64 contraction rows
-constexpr float kMinColumnSum = 9.094947e-13f;                // 2^-40
 
 // QUADS: m a multiple of 4, so that rows of R are aligned to 16 bytes and made of whole quads of columns, and below 2^24, so that 64
-// rows are below 2^32 bytes (128 rows as well where KG = 2 is taken: launches of 897 rows or more have at most 2^22 columns).
-template <bool PACKED, bool QUADS, int KG>
-__global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
+// rows are below 2^32 bytes.
+template <bool PACKED, bool QUADS>
+__global__ __launch_bounds__(256, 2) void compress_kernel(CompressArgs g)
 {
-    constexpr int kStep = 64 * KG, kCmpStage = 2 * KG * kCmpTile;
-    constexpr int kSets = KG;                                 // steps whose R is held in registers or on its way there
+    constexpr int kStep = 64, kCmpStage = 2 * kCmpTile;
     extern __shared__ __attribute__((aligned(16))) char cmp_lds[];
     enc_lds_char* const lds = (enc_lds_char*)cmp_lds;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KG == 2 ? w >> 2 : 0, q = w & 3;   // contraction half, quadrant
-    const int col = lane & 31, half = lane >> 5, wm = q >> 1, wn = q & 1;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // the wavefront's quadrant
+    const int col = lane & 31, half = lane >> 5, wm = w >> 1, wn = w & 1;
     // Column slabs (one tile column of an item and tensor, all its tile rows) go to the XCDs in turn, the longest items' first: an
     // XCD's L2 holds the slab of X for its tile rows, and no XCD works on alone.
     const uint32_t slot = blockIdx.x >> 3, per_item = static_cast<uint32_t>(g.tiles_n) * 2u;
@@ -817,31 +828,25 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     const __bf16* const x_item = (tensor ? g.x[1] : g.x[0]) + x_first * g.n;
     const int steps = (rows + kStep - 1) / kStep;
 
-    // R: thread -> four columns of rows row_r, row_r + 8, ... of its group's 64
-    const int t256 = tid & 255, col4 = (t256 & 31) * 4, row_r = t256 >> 5;
+    // R: thread -> four columns of rows row_r, row_r + 8, ... of the step's 64
+    const int col4 = (tid & 31) * 4, row_r = tid >> 5;
     // bytes of a row of R; elements where rows are not whole quads or 64 of them take more than 32 bits of bytes
     const uint32_t r_pitch = static_cast<uint32_t>(g.m) * (QUADS ? 4u : 1u), x_pitch = static_cast<uint32_t>(g.n) * 2u;
+    const uint32_t r_col = static_cast<uint32_t>(QUADS ? min(col4, g.m - 4 - m0) : 0) * 4u;
     uint32_t r_off[8];                                        // from the step's first row
 #pragma unroll
-    for (int j = 0; j < 8; ++j) r_off[j] = static_cast<uint32_t>(kg * 64 + row_r + 8 * j);
-    enc_f32x4 rv[kSets][8];
-    // accumulators and column sums of the even and the odd 64 rows: of two groups of wavefronts, or of one group in turn
-    constexpr int kOwn = KG == 2 ? 1 : 2;
-    float csum[kOwn][4] = {};
-    const uint32_t r_col = static_cast<uint32_t>(QUADS ? min(col4, g.m - 4 - m0) : 0) * 4u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r_off[j] = r_off[j] * r_pitch + r_col;
+    for (int j = 0; j < 8; ++j) r_off[j] = static_cast<uint32_t>(row_r + 8 * j) * r_pitch + r_col;
+    enc_f32x4 rv[8];                                          // the next step's R, or on its way there
     // row j of the thread's eight of a step whose first row is at `base` and whose last row is at `last_row`
-    auto fetch_row = [&](const char* base, uint32_t last_row, int j, auto set_c) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value % kSets;
+    auto fetch_row = [&](const char* base, uint32_t last_row, int j) __attribute__((always_inline)) {
         // (global by type: a pointer put together from scalars is a generic one, whose loads count as LDS accesses as well)
         const auto p = (const __attribute__((address_space(1))) char*)base + static_cast<uint64_t>(min(r_off[j], last_row)) * (QUADS ? 1u : 4u);
         if constexpr (QUADS) {
-            rv[set][j] = *(const __attribute__((address_space(1))) enc_f32x4*)p;
+            rv[j] = *(const __attribute__((address_space(1))) enc_f32x4*)p;
         } else {
             const int last = g.m - 1 - m0;
             const auto f = (const __attribute__((address_space(1))) float*)p;
-            rv[set][j] = enc_f32x4{f[min(col4, last)], f[min(col4 + 1, last)], f[min(col4 + 2, last)], f[min(col4 + 3, last)]};
+            rv[j] = enc_f32x4{f[min(col4, last)], f[min(col4 + 1, last)], f[min(col4 + 2, last)], f[min(col4 + 3, last)]};
         }
     };
     // (steps, rows and columns past the end re-read the last one)
@@ -849,53 +854,46 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
     auto step_last = [&](int step) __attribute__((always_inline)) {
         return static_cast<uint32_t>(min(rows - 1 - min(step, steps - 1) * kStep, kStep - 1)) * r_pitch + r_col;
     };
-    auto fetch_r = [&](int step, auto set_c) __attribute__((always_inline)) {
+    auto fetch_r = [&](int step) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) fetch_row(step_base(step), step_last(step), j, set_c);
+        for (int j = 0; j < 8; ++j) fetch_row(step_base(step), step_last(step), j);
     };
     // rows of `step` past the item become zeros (only the last step has any)
-    auto clear_tail = [&](int step, auto set_c) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value % kSets;
+    auto clear_tail = [&](int step) __attribute__((always_inline)) {
         if (__builtin_expect((step + 1) * kStep > rows, 0)) {
-            const int live = rows - (step * kStep + kg * 64 + row_r);
+            const int live = rows - (step * kStep + row_r);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool in = 8 * j < live;
-                rv[set][j].x = in ? rv[set][j].x : 0.f; rv[set][j].y = in ? rv[set][j].y : 0.f;
-                rv[set][j].z = in ? rv[set][j].z : 0.f; rv[set][j].w = in ? rv[set][j].w : 0.f;
+                rv[j].x = in ? rv[j].x : 0.f; rv[j].y = in ? rv[j].y : 0.f;
+                rv[j].z = in ? rv[j].z : 0.f; rv[j].w = in ? rv[j].w : 0.f;
             }
         }
     };
-    // Row j of the thread's eight, rounded, into the stage of its step's parity and into its columns' sums.  (Sums of what is
-    // multiplied: the weights of a column add up to one whatever the rounding did, and a single row's weight is exact.  Packed dot
-    // products with (1, 0) and (0, 1) for the sums, an instruction less each, were 2 % slower.)
+    // Row j of the thread's eight, over its columns' sums and rounded, into the stage of its step's parity.
+    float4 inv;
     u32x2 word;
-    uint32_t signs = 0;
-    auto round_r = [&](int j, auto set_c) __attribute__((always_inline)) {
-        const enc_f32x4 v = rv[decltype(set_c)::value % kSets][j];
-        const enc_bf16x2 lo = {static_cast<__bf16>(v.x), static_cast<__bf16>(v.y)}, hi = {static_cast<__bf16>(v.z), static_cast<__bf16>(v.w)};
+    auto round_r = [&](int j) __attribute__((always_inline)) {
+        const enc_f32x4 v = rv[j];
+        const enc_bf16x2 lo = {static_cast<__bf16>(v.x * inv.x), static_cast<__bf16>(v.y * inv.y)};
+        const enc_bf16x2 hi = {static_cast<__bf16>(v.z * inv.z), static_cast<__bf16>(v.w * inv.w)};
         word = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-        csum[decltype(set_c)::value % kOwn][0] += __uint_as_float(word.x << 16);
-        csum[decltype(set_c)::value % kOwn][1] += __uint_as_float(word.x & 0xFFFF0000u);
     };
-    auto write_r = [&](int j, auto set_c) __attribute__((always_inline)) {
+    auto write_r = [&](int j, auto stage_c) __attribute__((always_inline)) {
         const int kr = row_r + 8 * j;
         *reinterpret_cast<__attribute__((address_space(3))) u32x2*>(
-            lds + decltype(set_c)::value * kCmpStage + kg * kCmpTile + kr * 256 + (((col4 >> 3) ^ enc_swz16(kr)) << 4) + (col4 & 4) * 2) = word;
-        csum[decltype(set_c)::value % kOwn][2] += __uint_as_float(word.y << 16);
-        csum[decltype(set_c)::value % kOwn][3] += __uint_as_float(word.y & 0xFFFF0000u);
-        signs |= word.x | word.y;
+            lds + decltype(stage_c)::value * kCmpStage + kr * 256 + (((col4 >> 3) ^ enc_swz16(kr)) << 4) + (col4 & 4) * 2) = word;
     };
-    // X: instruction j of the group's wavefront q fills slots [(4 q + j) * 64, +64) of the group's tile
+    // X: instruction j of wavefront w fills slots [(4 w + j) * 64, +64) of the tile
     uint32_t x_off[4], x_col[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int s = (q * 4 + j) * kWave + lane, kr = s >> 4;
+        const int s = (w * 4 + j) * kWave + lane, kr = s >> 4;
         const int lc = (s & 15) ^ enc_swz16(kr);              // logical chunk: columns n0 + 8 lc .. + 7
         x_col[j] = min(lc, (g.n - n0) / 8 - 1) * 16;          // (n is a multiple of 8; chunks past it re-read a valid one)
-        x_off[j] = (kg * 64 + kr) * x_pitch + x_col[j];
+        x_off[j] = kr * x_pitch + x_col[j];
     }
-    const uint32_t lds_x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + (KG + kg) * kCmpTile + q * 4 * kWave * 16);
+    const uint32_t lds_x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + kCmpTile + w * 4 * kWave * 16);
     auto x_base = [&](int step) __attribute__((always_inline)) { return enc_uniform(reinterpret_cast<const char*>(x_item + n0) + static_cast<int64_t>(min(step, steps - 1)) * kStep * g.n * 2); };
     auto x_last = [&](int step) __attribute__((always_inline)) { return static_cast<uint32_t>(rows - 1 - min(step, steps - 1) * kStep) * x_pitch; };
     auto issue_x = [&](const char* base, uint32_t last_row, int j, int st) __attribute__((always_inline)) {
@@ -914,22 +912,19 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
         const int hi = s & 1, j = s >> 1, l16 = lane & 15, g16 = (lane >> 4) & 1;
         const int kr = 8 * half + 4 * hi + (l16 >> 2), el = 32 * j + 16 * g16 + 4 * (l16 & 3);
         const int ea = wm * 64 + el, eb = wn * 64 + el;
-        a_addr[s] = lds + kg * kCmpTile + kr * 256 + (((ea >> 3) ^ enc_swz16(kr)) << 4) + (ea & 7) * 2;
-        b_addr[s] = lds + (KG + kg) * kCmpTile + kr * 256 + (((eb >> 3) ^ enc_swz16(kr)) << 4) + (eb & 7) * 2;
+        a_addr[s] = lds + kr * 256 + (((ea >> 3) ^ enc_swz16(kr)) << 4) + (ea & 7) * 2;
+        b_addr[s] = lds + kCmpTile + kr * 256 + (((eb >> 3) ^ enc_swz16(kr)) << 4) + (eb & 7) * 2;
         asm volatile("" : "+v"(a_addr[s]), "+v"(b_addr[s]));
     }
-    enc_f32x16 acc[kOwn][2][2];
+    enc_f32x16 acc[2][2];
 #pragma unroll
-    for (int o = 0; o < kOwn; ++o)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[o][i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // X of the next step has landed (its loads are older than the last eight, R two steps on) and so have all LDS accesses, of every
-    // wavefront
+    // X of the next step has landed (its loads are older than the last eight, of R) and so have all LDS accesses, of every wavefront
     auto landed = [&]() __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0x0070 | (QUADS ? 8 : 0)); // vmcnt, lgkmcnt(0)
@@ -937,17 +932,16 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
         asm volatile("" ::: "memory");
     };
     // A step: sixteen products, and behind each of them a little of everything else, so that one wavefront's vector instructions run
-    // under the other's product (in blocks behind every fourth product they did not: 1860 clocks a step without its loads, 1130
-    // without vector work as well, 1024 the products alone).  R and X past the last step are fetched all the same, the last rows
-    // again, and R written as zeros: a branch around loads has the compiler move registers of loads under way, and wait for them.
+    // under the other's product.  R and X past the last step are fetched all the same, the last rows again, and R written as zeros: a
+    // branch around loads has the compiler move registers of loads under way, and wait for them.
     auto step = [&](int kt, auto stage_c) __attribute__((always_inline)) {
         constexpr int st = decltype(stage_c)::value;
         constexpr std::integral_constant<int, st ^ 1> other{};
-        clear_tail(kt + 1, other);
+        clear_tail(kt + 1);
         const char* const xb = x_base(kt + 1);
         const uint32_t xl = x_last(kt + 1);
-        const char* const rb = step_base(kt + 1 + kSets);
-        const uint32_t rl = step_last(kt + 1 + kSets);
+        const char* const rb = step_base(kt + 2);
+        const uint32_t rl = step_last(kt + 2);
         auto read = [&](enc_lds_char* const (&addr)[4], int s, int j) __attribute__((always_inline)) {
             const enc_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j] + st * kCmpStage + s * 16 * 256));
             const enc_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) enc_s16x4*)(addr[2 * j + 1] + st * kCmpStage + s * 16 * 256));
@@ -963,37 +957,50 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = k >> 1, j = k & 1;
-                acc[st % kOwn][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[st % kOwn][i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
                 if (s + 1 < 4) {                              // the next 16 rows' operands
                     if (k < 2) af[nxt][k] = read(a_addr, s + 1, k);
                     else bf[nxt][k - 2] = read(b_addr, s + 1, k - 2);
                 }
                 if (s == 0) issue_x(xb, xl, k, st ^ 1);       // the next step's X
-                const int row = 2 * s + (k >> 1);             // the next step's R, then the row two steps further on
+                const int row = 2 * s + (k >> 1);             // the next step's R, then the row to take its registers
                 if ((k & 1) == 0) {
-                    round_r(row, other);
+                    round_r(row);
                 } else {
                     write_r(row, other);
-                    if (s > 0) fetch_row(rb, rl, row - 2, other);
+                    if (s > 0) fetch_row(rb, rl, row - 2);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        fetch_row(rb, rl, 6, other);
-        fetch_row(rb, rl, 7, other);
+        fetch_row(rb, rl, 6);
+        fetch_row(rb, rl, 7);
         landed();
     };
     auto start = [&](auto stage_c) __attribute__((always_inline)) {
         constexpr int st = decltype(stage_c)::value;
-        constexpr std::integral_constant<int, st ^ 1> other{};
-        fetch_r(0, stage_c);
+        float p[kColParts];
+        if (tid < 128) {
+            const float* const sums = g.part + (PACKED ? item * kColParts * g.m : 0) + min(m0 + tid, g.m - 1);
+#pragma unroll
+            for (int i = 0; i < kColParts; ++i) p[i] = sums[static_cast<int64_t>(i) * g.m];
+        }
+        fetch_r(0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) issue_x(x_base(0), x_last(0), j, st);
-        if constexpr (KG == 2) fetch_r(1, other);
-        clear_tail(0, stage_c);
+        float* const inv_s = reinterpret_cast<float*>(cmp_lds + (st ^ 1) * kCmpStage);   // (written to from the first step on, behind another barrier)
+        if (tid < 128) {
+            float t = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { round_r(j, stage_c); write_r(j, stage_c); }
-        fetch_r(kSets, stage_c);
+            for (int i = 0; i < kColParts; ++i) t += p[i];
+            inv_s[tid] = t != 0.f ? 1.0f / t : 0.f;           // (a column that sums to zero weighs nothing)
+        }
+        __syncthreads();
+        inv = *reinterpret_cast<const float4*>(inv_s + col4);
+        clear_tail(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { round_r(j); write_r(j, stage_c); }
+        fetch_r(1);
         landed();
     };
     // Steps in pairs, stage 1 and stage 0, with a single one in front where their number is odd.  (A loop that can end between the
@@ -1012,169 +1019,42 @@ __global__ __launch_bounds__(256 * KG, 2) void compress_kernel(CompressArgs g)
         step(kt + 1, stage0);
     }
     __builtin_amdgcn_s_waitcnt(0x0070);                       // (R past the end)
-    __syncthreads();
+    __syncthreads();                                          // the ring is free
 
-    // The even and the odd rows meet: two groups exchange a block column each (j = 1 - kg goes, j = kg stays).  So do the column
-    // sums of R: 8 row slots of the even rows, 8 of the odd ones.
-    // Register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the quadrant.
-    float4* const meet = reinterpret_cast<float4*>(cmp_lds);                  // KG == 2: [8 wavefronts][8 register quads][64 lanes]
-    float* const parts = reinterpret_cast<float*>(meet + (KG == 2 ? 8 * 8 * kWave : 0));   // [16 row slots][128]
-    float* const inv = parts + 16 * 128;                                      // [128]
-    int* const negative = reinterpret_cast<int*>(inv + 128);                  // [8 wavefronts]
-    __bf16* const stages = KG == 2 ? reinterpret_cast<__bf16*>(cmp_lds) : reinterpret_cast<__bf16*>(negative + 8);
-    if constexpr (KG == 2) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const enc_f32x16& x = kg ? acc[0][i][0] : acc[0][i][1];
-                meet[(w * 8 + i * 4 + rq) * kWave + lane] = make_float4(x[4 * rq], x[4 * rq + 1], x[4 * rq + 2], x[4 * rq + 3]);
-            }
-    }
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o) {
-        const int odd_rows = KG == 2 ? kg : o ^ (~steps & 1); // (the last of an even number of steps is in stage 0)
-        *reinterpret_cast<float4*>(parts + (odd_rows * 8 + row_r) * 128 + col4) = make_float4(csum[o][0], csum[o][1], csum[o][2], csum[o][3]);
-    }
-    const bool some_negative = __any((signs & 0x80008000u) != 0);
-    if (lane == 0) negative[w] = some_negative;
-    __syncthreads();
-    int any_negative = 0;
-#pragma unroll
-    for (int x = 0; x < 4 * KG; ++x) any_negative |= negative[x];
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any_negative), 0)) {
-        // R with negative entries: a sum can be far smaller than its terms, and what rounding does to them would be most of it.
-        // The columns are summed once more as they lie, eight row slots of 32 quads of columns.
-        if (tid < 256) {
-            float t[4] = {0.f, 0.f, 0.f, 0.f};
-            const float* const first = r_item + m0;
-            const int last = g.m - 1 - m0;
-            constexpr int kAhead = QUADS ? 8 : 4;
-            for (int64_t k = row_r; k < rows; k += 8 * kAhead) {
-                enc_f32x4 v[kAhead];
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const float* const f = first + (k + 8 * u < rows ? k + 8 * u : rows - 1) * static_cast<int64_t>(g.m);
-                    if constexpr (QUADS) v[u] = *reinterpret_cast<const enc_f32x4*>(f + min(col4, last - 3));
-                    else v[u] = enc_f32x4{f[min(col4, last)], f[min(col4 + 1, last)], f[min(col4 + 2, last)], f[min(col4 + 3, last)]};
-                }
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const bool in = k + 8 * u < rows;
-                    t[0] += in ? v[u].x : 0.f; t[1] += in ? v[u].y : 0.f; t[2] += in ? v[u].z : 0.f; t[3] += in ? v[u].w : 0.f;
-                }
-            }
-            *reinterpret_cast<float4*>(parts + row_r * 128 + col4) = make_float4(t[0], t[1], t[2], t[3]);
-            *reinterpret_cast<float4*>(parts + (8 + row_r) * 128 + col4) = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-    }
-    if (tid < 128) {
-        float t = 0.f;
-#pragma unroll
-        for (int s = 0; s < 16; ++s) t += parts[s * 128 + tid];
-        inv[tid] = t != 0.f ? 1.0f / t : 0.f;                 // (a column that sums to zero weighs nothing)
-    }
-    enc_f32x16 sum[2];
-    if constexpr (KG == 2) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const float4 t = meet[((w ^ 4) * 8 + i * 4 + rq) * kWave + lane];
-                const float other[4] = {t.x, t.y, t.z, t.w};
-                const enc_f32x16& own = kg ? acc[0][i][1] : acc[0][i][0];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sum[i][4 * rq + e] = own[4 * rq + e] + other[e];
-            }
-    }
-    __syncthreads();
+    // Register r of block (i, j): row 32 i + col, column 32 j + 8 (r / 4) + 4 half + r % 4 of the quadrant; through LDS into whole
+    // 16-byte pieces of rows.
+    constexpr int kPitch = 64 + 8;
+    __bf16* const stage = reinterpret_cast<__bf16*>(cmp_lds) + w * 64 * kPitch;
     __bf16* const out = (tensor ? g.out[1] : g.out[0]) + item * g.m * g.n;
-    constexpr int kPitch = 32 + 8;
-    __bf16* const stage = stages + w * 64 * kPitch;
-    const int row_q = m0 + wm * 64;
-    float scale[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) scale[i] = inv[wm * 64 + 32 * i + col];
-    auto emit = [&](int col_q) __attribute__((always_inline)) {               // a block column of the quadrant, from `sum`
-        float odd[2] = {0.f, 0.f};
-        bool again = false;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
                 enc_bf16x4 o;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float v = sum[i][4 * rq + e] * scale[i];
-                    odd[i] = fmaf(v, 0.f, odd[i]);
-                    o[e] = static_cast<__bf16>(v);
-                }
-                *reinterpret_cast<enc_bf16x4*>(&stage[(32 * i + col) * kPitch + 8 * rq + 4 * half]) = o;
+                for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(acc[i][j][4 * rq + e]);
+                *reinterpret_cast<enc_bf16x4*>(&stage[(32 * i + col) * kPitch + 32 * j + 8 * rq + 4 * half]) = o;
             }
-            again |= row_q + 32 * i + col < g.m && scale[i] == scale[i] && (fabsf(scale[i]) > 1.0f / kMinColumnSum || odd[i] != 0.f);
-        }
-        if (__builtin_expect(__any(again), 0)) {
-#pragma unroll 1
-            for (int c4 = 4 * half; c4 < 32; c4 += 8)
-#pragma unroll 1
-                for (int row = row_q + col, i = 0; i < 2; row += 32, ++i) {
-                    if (row >= g.m || col_q + c4 >= g.n) continue;
-                    const float* wgt = r_item + row;
-                    const __bf16* x = x_item + col_q + c4;
-                    float total = 0.f;
-                    for (int k = 0; k < rows; ++k) total += wgt[static_cast<int64_t>(k) * g.m];
-                    const float factor = total != 0.f ? 1.0f / total : 0.f;
-                    float t[4] = {0.f, 0.f, 0.f, 0.f};
-                    for (int k = 0; k < rows; ++k) {
-                        const enc_bf16x4 xk = *reinterpret_cast<const enc_bf16x4*>(x + static_cast<int64_t>(k) * g.n);
-                        const float wk = static_cast<float>(static_cast<__bf16>(wgt[static_cast<int64_t>(k) * g.m] * factor));
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) t[e] = fmaf(wk, static_cast<float>(xk[e]), t[e]);
-                    }
-                    enc_bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = static_cast<__bf16>(t[e]);
-                    *reinterpret_cast<enc_bf16x4*>(out + static_cast<int64_t>(row) * g.n + col_q + c4) = o;
-                }
-            return;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int r = it * 16 + (lane >> 2), c8 = (lane & 3) * 8;
-            const int row = row_q + r, cc = col_q + c8;
-            if (row < g.m && cc < g.n)
-                *reinterpret_cast<u32x4*>(out + static_cast<int64_t>(row) * g.n + cc) = *reinterpret_cast<const u32x4*>(&stage[r * kPitch + c8]);
-        }
-    };
-    if constexpr (KG == 2) {
-        emit(n0 + wn * 64 + 32 * kg);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sum[i][r] = acc[0][i][j][r] + acc[1][i][j][r];
-            emit(n0 + wn * 64 + 32 * j);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();                  // (read before the area is written again)
-        }
+    for (int it = 0; it < 8; ++it) {
+        const int r = it * 8 + (lane >> 3), c8 = (lane & 7) * 8;
+        const int row = m0 + wm * 64 + r, cc = n0 + wn * 64 + c8;
+        if (row < g.m && cc < g.n)
+            *reinterpret_cast<u32x4*>(out + static_cast<int64_t>(row) * g.n + cc) = *reinterpret_cast<const u32x4*>(&stage[r * kPitch + c8]);
     }
 }
 
-// Eq. 9 of `items` items; rows of whole 16-byte pieces in X (n a multiple of 8).
-template <bool PACKED, bool QUADS, int KG>
+// Eq. 9 of `items` items whose partial column sums are there; rows of whole 16-byte pieces in X (n a multiple of 8).
+template <bool PACKED, bool QUADS>
 static int launch_compress_variant(const CompressArgs& g, hipStream_t s)
 {
-    constexpr size_t lds = 2 * 2 * KG * kCmpTile;
-    static_assert(lds >= ((KG == 2 ? 8 * 32 * kWave : 4 * 64 * 40 / 2) + 17 * 128 + 8) * 4, "the ring holds what is staged at the end");
-    static std::atomic<uint64_t> allowed{0};
-    const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(compress_kernel<PACKED, QUADS, KG>), lds, &allowed);
-    if (rc != CIVIC_OK) return rc;
-    civic::launch((compress_kernel<PACKED, QUADS, KG>), dim3(static_cast<unsigned>((g.slabs + 7) / 8 * 8 * g.tiles_m)), dim3(256 * KG), lds, s, g);
+    constexpr size_t lds = 2 * 2 * kCmpTile;
+    static_assert(lds >= 4 * 64 * (64 + 8) * 2, "the ring holds the staged output");
+    civic::launch((compress_kernel<PACKED, QUADS>), dim3(static_cast<unsigned>((g.slabs + 7) / 8 * 8 * g.tiles_m)), dim3(256), lds, s, g);
     return check_launch();
 }
 
@@ -1182,27 +1062,14 @@ static int launch_compress_variant(const CompressArgs& g, hipStream_t s)
 static int launch_compress(const CompressArgs& g_in, int64_t items, bool packed, hipStream_t s)
 {
     CompressArgs g = g_in;
-    int64_t longest = (g.n_rows + 127) / 128, all_steps = longest * items;
-    if (packed) {
-        for (int64_t i = 0; i < items; ++i) {
-            const int64_t steps = (g.grp.row[i + 1] - g.grp.row[i] + 127) / 128;
-            all_steps += steps;
-            longest = std::max(longest, steps);
-        }
-    }
     g.tiles_m = (g.m + 127) / 128;
     g.tiles_n = (g.n + 127) / 128;
     const int64_t slabs = items * 2 * g.tiles_n;
     if (slabs * g.tiles_m > (int64_t{1} << 30)) return CIVIC_ERR_UNSUPPORTED;
     g.slabs = static_cast<int32_t>(slabs);
-    // Two groups of wavefronts where the launch waits for its longest chain of steps: one that is long (8 steps of 128 rows), while
-    // all steps together would keep the units busy for less.  Else one group, whose smaller workgroups run two to a unit.  (us, two
-    // groups and one: 4 x 2048 rows, 512 x 1024 out 28.5 and 31.2; 6 x 1024, 256 x 1152 16.9 and 18.5; 8 x 1024 30.1 and 24.1; eight
-    // items of 85..1365 23.4 and 24.9; 16 x 700, 128 x 768 19.5 and 18.1; 24 x 24, 512 x 1280 52.2 and 26.8.)
-    const bool one = longest < 8 || all_steps * 2 * g.tiles_n * g.tiles_m > 256 * longest;
-    if (g.m % 4 || g.m >= (1 << 24)) return packed ? launch_compress_variant<true, false, 1>(g, s) : launch_compress_variant<false, false, 1>(g, s);
-    if (packed) return one ? launch_compress_variant<true, true, 1>(g, s) : launch_compress_variant<true, true, 2>(g, s);
-    return one ? launch_compress_variant<false, true, 1>(g, s) : launch_compress_variant<false, true, 2>(g, s);
+    const bool quads = g.m % 4 == 0 && g.m < (1 << 24);
+    if (packed) return quads ? launch_compress_variant<true, true>(g, s) : launch_compress_variant<true, false>(g, s);
+    return quads ? launch_compress_variant<false, true>(g, s) : launch_compress_variant<false, false>(g, s);
 }
 
 static int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
@@ -1232,7 +1099,7 @@ static void agg_plan(int32_t batch, int32_t n_tokens, int32_t n_anchors, int32_t
 
 struct CompressPlan {                    // byte offsets into the workspace of civic_kv_compress
     int64_t m_pad;
-    size_t part, rt, xt, total;
+    size_t part, rt, xt, total;          // (rt and xt are written for widths of no whole 16-byte pieces only)
 };
 
 static void compress_plan(int32_t batch, int32_t n_rows, int32_t n_mem, int32_t width, CompressPlan* p)
@@ -1389,24 +1256,26 @@ extern "C" int civic_kv_compress(const void* k, const void* v, int dtype, const 
     if (!workspace || workspace_bytes < p.total || !aligned16(workspace)) return CIVIC_ERR_WORKSPACE;
     if (batch == 0) return CIVIC_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    char* ws = static_cast<char*>(workspace);
+    float* part = reinterpret_cast<float*>(ws + p.part);
+    civic::launch(col_part_sum_kernel, dim3(static_cast<unsigned>((n_mem + kWave - 1) / kWave), kColParts), dim3(256), 0, s, r, n_rows,
+                       n_mem, part);
+    int rc = check_launch();
+    if (rc != CIVIC_OK) return rc;
     if (width % 8 == 0) {
         CompressArgs c;
-        c.r = r; c.x[0] = static_cast<const __bf16*>(k); c.x[1] = static_cast<const __bf16*>(v);
+        c.r = r; c.part = part; c.x[0] = static_cast<const __bf16*>(k); c.x[1] = static_cast<const __bf16*>(v);
         c.out[0] = static_cast<__bf16*>(k_c); c.out[1] = static_cast<__bf16*>(v_c);
         c.m = n_mem; c.n = width; c.n_rows = n_rows;
         return launch_compress(c, batch, false, s);
     }
     // rows that are not whole 16-byte pieces: transposed, padded copies of them and of Rbar
-    char* ws = static_cast<char*>(workspace);
     __bf16* rt = reinterpret_cast<__bf16*>(ws + p.rt);
     __bf16* xt = reinterpret_cast<__bf16*>(ws + p.xt);
     // Rbar^T [n_mem x m_pad]: every column of R over its sum, transposed, zero beyond n_rows
-    float* part = reinterpret_cast<float*>(ws + p.part);
-    civic::launch(col_part_sum_kernel, dim3(static_cast<unsigned>((n_mem + kWave - 1) / kWave), kColParts), dim3(256), 0, s, r, n_rows,
-                       n_mem, part);
     civic::launch((transpose_pad_kernel<float>), dim3(static_cast<unsigned>(p.m_pad / 32), static_cast<unsigned>((n_mem + 31) / 32), 1u),
                        dim3(256), 0, s, r, n_rows, n_mem, static_cast<int64_t>(n_mem), int64_t{0}, part, rt, p.m_pad, int64_t{0});
-    int rc = check_launch();
+    rc = check_launch();
     if (rc != CIVIC_OK) return rc;
     GemmArgs g;
     g.col_stats = nullptr; g.col_pitch = 0; g.row_sum = nullptr; g.row_inv = nullptr; g.row_part = nullptr; g.parts = 0; g.part_pitch = 0;
@@ -1448,19 +1317,14 @@ static bool offsets_ok(const int64_t* off, int32_t batch)
 
 namespace civic {
 
-struct RaggedPlan {                      // byte offsets into the workspace of civic_kv_compress_ragged
-    int64_t pad_total;                   // sum of the items' row counts, each rounded up to 64
-    size_t part, rt, total;
-};
-
-static void ragged_plan(int32_t batch, const int64_t* off, int32_t n_mem, RaggedPlan* p)
+// Bytes of the workspace of civic_kv_compress_ragged: every item's partial column sums, and room for a transposed, rounded copy of
+// Rbar in whole steps of 64 rows, which is not written (the product makes it on the way into LDS): the size is part of what callers
+// rely on.  Sets *pad_total to the items' rows in such steps.
+static size_t ragged_workspace(int32_t batch, const int64_t* off, int32_t n_mem, int64_t* pad_total)
 {
-    p->pad_total = 0;
-    for (int32_t b = 0; b < batch; ++b) p->pad_total += pad64(off[b + 1] - off[b]);
-    size_t at = 0;
-    p->part = at; at += align256(static_cast<size_t>(batch) * n_mem * 4 * kColParts);
-    p->rt = at;   at += align256(static_cast<size_t>(n_mem) * p->pad_total * 2);
-    p->total = at;
+    *pad_total = 0;
+    for (int32_t b = 0; b < batch; ++b) *pad_total += pad64(off[b + 1] - off[b]);
+    return align256(static_cast<size_t>(batch) * n_mem * 4 * kColParts) + align256(static_cast<size_t>(n_mem) * *pad_total * 2);
 }
 
 }  // namespace civic
@@ -1468,9 +1332,8 @@ static void ragged_plan(int32_t batch, const int64_t* off, int32_t n_mem, Ragged
 extern "C" size_t civic_kv_compress_ragged_workspace_bytes(int32_t batch, const int64_t* row_offsets, int32_t n_mem, int32_t width)
 {
     if (batch <= 0 || n_mem <= 0 || width <= 0 || !civic::offsets_ok(row_offsets, batch)) return 0;
-    civic::RaggedPlan p;                                      // every item keeps its own column sums and its own Rbar^T
-    civic::ragged_plan(batch, row_offsets, n_mem, &p);
-    return p.total;
+    int64_t pad_total;
+    return civic::ragged_workspace(batch, row_offsets, n_mem, &pad_total);
 }
 
 extern "C" int civic_kv_compress_ragged(const void* k, const void* v, int dtype, const float* r, int32_t batch,
@@ -1492,12 +1355,12 @@ extern "C" int civic_kv_compress_ragged(const void* k, const void* v, int dtype,
         const int64_t padded = pad64(row_offsets[b + 1] - row_offsets[b]);
         if (padded * width * 2 >= (int64_t{1} << 32) || padded * n_mem * 2 >= (int64_t{1} << 32)) return CIVIC_ERR_UNSUPPORTED;
     }
-    RaggedPlan p;
-    ragged_plan(batch, row_offsets, n_mem, &p);
-    if (p.pad_total > INT32_MAX) return CIVIC_ERR_UNSUPPORTED;                // (padded row numbers are 32-bit as well)
-    if (!workspace || workspace_bytes < p.total || !aligned16(workspace)) return CIVIC_ERR_WORKSPACE;
+    int64_t pad_total;
+    const size_t need = ragged_workspace(batch, row_offsets, n_mem, &pad_total);
+    if (pad_total > INT32_MAX) return CIVIC_ERR_UNSUPPORTED;
+    if (!workspace || workspace_bytes < need || !aligned16(workspace)) return CIVIC_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Groups of up to kGroupItems items, one launch each.
+    // Groups of up to kGroupItems items, two launches each.
     for (int32_t b0 = 0; b0 < batch; b0 += kGroupItems) {
         const int32_t nb = batch - b0 < kGroupItems ? batch - b0 : kGroupItems;
         CompressArgs c;
@@ -1511,7 +1374,13 @@ extern "C" int civic_kv_compress_ragged(const void* k, const void* v, int dtype,
         std::stable_sort(c.grp.longest_first, c.grp.longest_first + nb, [&](uint8_t x, uint8_t y) {
             return c.grp.row[x + 1] - c.grp.row[x] > c.grp.row[y + 1] - c.grp.row[y];
         });
-        const int rc = launch_compress(c, nb, true, s);
+        float* part = static_cast<float*>(workspace) + static_cast<int64_t>(b0) * n_mem * kColParts;
+        c.part = part;
+        civic::launch(col_part_sum_grouped_kernel, dim3(static_cast<unsigned>((n_mem + kWave - 1) / kWave), kColParts, static_cast<unsigned>(nb)),
+                      dim3(256), 0, s, r, n_mem, part, c.grp);
+        int rc = check_launch();
+        if (rc != CIVIC_OK) return rc;
+        rc = launch_compress(c, nb, true, s);
         if (rc != CIVIC_OK) return rc;
     }
     return CIVIC_OK;

@@ -474,7 +474,7 @@ def test_selection_and_merge_in_one_launch(bd, case):
     ([200], 132, 136, False, 1e-36), ([200], 132, 136, False, 3e35), ([300, 40], 64, 72, True, 1e-30),  # column sums at the ends of fp32
 ])
 def test_kv_compress_tiles_and_scales(bd, case):
-    """Eq. 9 over tiles of 128 x 128 in steps of 128 rows, for any scale of R.  A weight is rounded to bf16 (2^-9), their sum moves by as
+    """Eq. 9 over tiles of 128 x 128 in steps of 64 rows, for any scale of R.  A weight is rounded to bf16 (2^-9), their sum moves by as
     much at most, the result is rounded once more: 2^-8 of the sum of |weight x|, and 2^-8 of the result, bound the error of an element."""
     rows, mem, width, packed, scale = case
     log("kv compress", case)
@@ -503,8 +503,7 @@ def test_kv_compress_tiles_and_scales(bd, case):
 
 @pytest.mark.parametrize("items,rows", [(1, 1025), (1, 2048), (17, 1025), (6, 897), (3, 64), (40, 64), (30, 200), (1, 200)])
 def test_kv_compress_of_a_batch_is_that_of_its_items(bd, items, rows):
-    """A launch takes the kernel whose workgroups are one or two groups of wavefronts by its size: the same bits from both, in batches
-    and for items of their own among longer ones."""
+    """Every item's sums run over its rows in order: the same bits in a batch, alone and packed among longer ones."""
     log("kv compress batch", items, rows)
     g = torch.Generator(device="cuda").manual_seed(items + rows)
     k = torch.randn((items, rows, 264), generator=g, device="cuda").bfloat16()
@@ -522,7 +521,7 @@ def test_kv_compress_of_a_batch_is_that_of_its_items(bd, items, rows):
 @pytest.mark.parametrize("rows,mem,width", [(2, 4, 8), (65, 127, 136), (200, 130, 72), (390, 132, 64), (1025, 132, 64)])
 def test_kv_compress_of_signed_assignments(bd, rows, mem, width):
     """R with negative entries, some of whose column sums nearly cancel: the error stays that of weights rounded to bf16, 2^-8 of the sum
-    of |weight x| and of the result, and of an fp32 sum (chains of at most 129 + 8 terms, below 2^-16 of the sum of |weight|).  A batch,
+    of |weight x| and of the result, and of an fp32 sum (chains of at most 9 + 2 + 32 terms, below 2^-16 of the sum of |weight|).  A batch,
     an item of its own and an item among longer ones give the same bits."""
     log("kv compress signed", rows, mem, width)
     rng = np.random.default_rng(rows + mem + width)
@@ -547,6 +546,57 @@ def test_kv_compress_of_signed_assignments(bd, rows, mem, width):
         packed = torch.cat([long, dk[2]])
         kp, _ = bd.civic_kv_compress_ragged(packed, packed, torch.cat([torch.rand((1500, mem), device="cuda"), dr]), [0, 1500, 1500 + rows])
         assert torch.equal(kp[1], kc[2])
+
+
+@pytest.mark.parametrize("spread", [0, 99])
+@pytest.mark.parametrize("rows,mem,width,packed", [([1], 4, 8, False), ([65], 127, 136, False), ([300, 64, 129], 64, 304, True), ([1025], 132, 1032, False), ([1088, 1088], 128, 72, False)])
+def test_kv_compress_weights_are_normalised_and_then_rounded(bd, rows, mem, width, packed, spread):
+    """Rbar itself, bit for bit: a column of X that is 1 in one row and 0 elsewhere brings that row's weights out, each the fp32 quotient
+    rounded to bf16 once.  R holds whole numbers, of both signs in every second column, whose sums (below 2^24) are exact in any order,
+    times a power of two per column: sums from 2^-99 to 2^109 and entries far from their sum cost no bit."""
+    log("kv compress weights", rows, mem, width, packed, spread)
+    rng = np.random.default_rng(sum(rows) + mem)
+    total = sum(rows) if packed else rows[0]
+    whole = rng.integers(1, 1 << 12, (total, mem))
+    whole[:, 1::2] -= 2000
+    whole[:, 2] = 0
+    r = (whole * 2.0 ** rng.integers(-spread, spread - 11 if spread else 1, mem)).astype(np.float32)
+    lead = (total,) if packed else (len(rows), total)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    x = np.zeros(lead + (width,), dtype=np.float32)
+    at = [rng.integers(0, n, width) for n in rows]
+    for i, rows_of in enumerate(at):
+        if packed:
+            x[off[i] + rows_of, np.arange(width)] = 1.0
+        else:
+            x[i, rows_of, np.arange(width)] = 1.0
+    dx, dr = torch.from_numpy(x).cuda().bfloat16(), torch.from_numpy(r).cuda()
+    kc, vc = bd.civic_kv_compress_ragged(dx, dx, dr, off) if packed else bd.civic_kv_compress(dx, dx, dr)
+    for i in range(len(rows)):
+        ri = r[off[i]:off[i + 1]] if packed else r
+        t = ri.astype(np.float64).sum(0).astype(np.float32)
+        inv = np.where(t != 0, np.float32(1) / np.where(t != 0, t, np.float32(1)), np.float32(0))
+        ref = torch.from_numpy((ri * inv)[at[i]].T.copy()).bfloat16()
+        for got in (kc, vc):
+            assert torch.equal(got[i].cpu(), ref)
+
+
+@pytest.mark.parametrize("rows,mem", [(64, 1 << 24), (1030, 1100000)])
+def test_kv_compress_of_r_of_four_gigabytes(bd, rows, mem):
+    """R of 4 GB and more, whose row offsets pass 32 bits of bytes within one step (2^24 columns) or over all rows: sampled columns
+    against float64, with the bound of the test of tiles and scales."""
+    log("kv compress, large R", rows, mem)
+    width = 8
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randn((1, rows, width), generator=g, device="cuda").bfloat16()
+    r = torch.rand((rows, mem), generator=g, device="cuda")
+    kc, _ = bd.civic_kv_compress(x, x, r)
+    at = torch.cat([torch.arange(0, 130, device="cuda"), torch.arange(mem - 130, mem, device="cuda"), torch.arange(0, mem, mem // 1000, device="cuda")])
+    w = r[:, at].double()
+    w /= w.sum(0)
+    ref = w.T @ x[0].double()
+    bar = 2.0 ** -8 * (w.T @ x[0].double().abs()) + 2.0 ** -8 * ref.abs() + 1e-30
+    assert ((kc[0, at].double() - ref).abs() <= bar).all()
 
 
 @pytest.mark.parametrize("d", [64, 128, 192, 256, 56, 96, 120])
