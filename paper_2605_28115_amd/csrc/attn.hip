@@ -399,8 +399,9 @@ typedef __attribute__((address_space(3))) char lds_char;
 // tracks these loads with explicit s_waitcnt vmcnt(N), and an LDS read the compiler could see racing
 // with an asynchronous LDS write would make it drain the whole load queue first.  m0 is written and not
 // declared: the register is reserved (the compiler rejects it as a clobber), never allocated, and set by the
-// compiler only directly in front of an instruction that reads it, of which this file has none.  (A load into LDS may read m0 one
-// wait state after a scalar instruction wrote it.)
+// compiler only directly in front of an instruction that reads it, of which this file has none.
+// The compiler counts no wait states into an asm statement.  A load into LDS may read m0 one wait state after a scalar instruction wrote
+// it; `base` comes from uniform_ptr, which sees to the ones that it needs.
 template <int LDS_IMM>
 __device__ __forceinline__ void dma16(const void* base, uint32_t byte_off, uint32_t lds_addr)
 {
@@ -431,14 +432,20 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
 }
 
-// The same pointer with both halves forced into scalar registers (the value must be wave-uniform).
+// The same pointer with both halves forced into scalar registers (the value must be wave-uniform), written by a scalar instruction at
+// the place of the call.  A load reads its base five wait states after a vector instruction wrote that at the earliest
+// (v_readfirstlane, or v_readlane of a spilled pair), which the compiler does not see to for a load inside an asm statement; a scalar
+// instruction waits for the vector one in hardware, and what it wrote may be read at once.  (Five states in front of every load
+// instead: 0.5 to 1 % of a launch.)
 __device__ __forceinline__ const char* uniform_ptr(const void* p)
 {
     const uint64_t bits = reinterpret_cast<uint64_t>(p);
     // the builtin returns a signed int: widen each half as unsigned
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits)));
-    return reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+    uint64_t copy;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
+    return reinterpret_cast<const char*>(copy);
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt()
@@ -560,11 +567,6 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     // compiler then never emits a vmcnt wait of its own there.
     const uint32_t q_lds = T::IN_RINGS ? (w & 1) * T::QW + TILEB + (w >> 1) * VBASE : 2 * VBASE + w * T::WAREA;
     const char* qb = reinterpret_cast<const char*>(static_cast<const __bf16*>(a.q) + q_first + h * a.qs[2]);
-    const uint64_t qb_bits = reinterpret_cast<uint64_t>(qb);
-    // (the builtin returns a signed int: widen each half as unsigned)
-    const uint32_t qb_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(qb_bits >> 32)));
-    const uint32_t qb_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(qb_bits)));
-    const uint64_t qb_uni = (static_cast<uint64_t>(qb_hi) << 32) | qb_lo;
     const uint32_t q_row_bytes = static_cast<uint32_t>(a.qs[1]) * 2u;
     const uint32_t q_lds_uni = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + q_lds);
     // Slot -> (row, physical chunk) as for a K tile: instruction j covers rows 4j .. 4j+3 when a row has 16
@@ -579,9 +581,10 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
         return static_cast<uint32_t>(r) * q_row_bytes + cb;
     };
     auto issue_q = [&](int first_row) {                       // any row tile: rows past the sequence re-read its last row
+        const char* base = uniform_ptr(qb);
 #pragma unroll
         for (int j = 0; j < PITCH / 2; ++j)
-            dma16_at(reinterpret_cast<const void*>(qb_uni), q_slot_off(j, first_row, true), q_lds_uni, std::integral_constant<int, 0>{}, j);
+            dma16_at(base, q_slot_off(j, first_row, true), q_lds_uni, std::integral_constant<int, 0>{}, j);
     };
     // The Q rows of a workgroup's second row tile, which is never the last of the sequence (no clamping): the
     // offsets of the first 16 rows stay in registers, the tile's first row enters through the scalar base.
@@ -590,7 +593,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
 #pragma unroll
     for (int j = 0; j < QJ; ++j) q_voff[j] = q_slot_off(j, 0, false);
     auto issue_q_next = [&](int first_row) {
-        const char* base0 = uniform_ptr(reinterpret_cast<const char*>(qb_uni) + static_cast<int64_t>(first_row) * q_row_bytes);
+        const char* base0 = uniform_ptr(qb + static_cast<int64_t>(first_row) * q_row_bytes);
         const char* base1 = uniform_ptr(base0 + 16 * static_cast<int64_t>(q_row_bytes));
 #pragma unroll
         for (int j = 0; j < PITCH / 2; ++j)
@@ -873,8 +876,11 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
             const float m_new = fmaxf(mx, m_run);
             float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * sl2);
             // (The compiler counts no wait states into or out of an asm statement: an exponential's result may be read one instruction
-            // later at the earliest, a product may read what a vector instruction wrote two later.)
-            asm volatile("s_nop 1" : "+v"(alpha));
+            // later at the earliest, a product may read what a vector instruction wrote two later, and a vector instruction what a
+            // product of 8 passes wrote 12 later.  The products into acc_o were issued before the sums that led here, which took longer;
+            // these 24 states, all products being in front of them, do not rely on it.)
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15\n\ts_nop 7" : "+v"(alpha));
             l_run[0] *= alpha; l_run[1] *= alpha;
             // (in place, tied operands: the accumulators stay in the registers they have on the common path)
 #pragma unroll

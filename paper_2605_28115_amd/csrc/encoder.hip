@@ -67,17 +67,22 @@ struct GemmArgs {
 template <int LDS_IMM>
 __device__ __forceinline__ void enc_dma16(const void* base, uint32_t byte_off, uint32_t lds_addr)
 {
-    // 16 bytes per lane from base + byte_off (scalar base, per-lane offset) into LDS at lds_addr + LDS_IMM + lane * 16
+    // 16 bytes per lane from base + byte_off (scalar base, per-lane offset) into LDS at lds_addr + LDS_IMM + lane * 16.  (The compiler
+    // counts no wait states into an asm statement: the load may read m0 one state after the scalar write; `base` is enc_uniform's.)
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(byte_off), "s"(base), "n"(LDS_IMM) : "memory", "scc");
 }
 
+// The same pointer in scalar registers, written by a scalar instruction, so that a load inside an asm statement may read it at once:
+// from a vector instruction's write five wait states would have to lie in between, which the compiler does not count there.
 __device__ __forceinline__ const char* enc_uniform(const void* p)
 {
     const uint64_t bits = reinterpret_cast<uint64_t>(p);
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits)));
-    return reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+    uint64_t copy;
+    asm volatile("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
+    return reinterpret_cast<const char*>(copy);
 }
 
 // physical chunk = logical chunk ^ swz(row): rows 0..31 of a 128-byte-pitch tile, same logical chunk -> 32 banks groups
