@@ -180,8 +180,8 @@ int civic_compact(const void* hidden, int dtype, int32_t dim, const int32_t* pos
 
 /* The front of the path in one call: civic_score_visual (Eq. 8), civic_select (budget and
  * floors) and civic_compact (Eq. 13) on `stream`, with n_kept = civic_kept_count(grid).  The
- * results are those of the three calls, bit for bit; selection and merge are one launch, and
- * there is one crossing from the caller's language instead of three.
+ * results are those of the three calls, bit for bit; selection and merge are one launch (a
+ * launch each beyond 2^19 visual tokens in samples of more than 2048), and there is one crossing from the caller's language instead of three.
  * Arguments as in the three calls; scores [batch, N_v] and kept_idx [batch, K] are outputs
  * here (intermediate results the caller may want).  Every check of every stage runs before
  * the first launch. */

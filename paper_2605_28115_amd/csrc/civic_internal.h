@@ -80,6 +80,9 @@ int compact_check(const void* hidden, int dtype, int32_t dim, const int32_t* pos
 int score_slices_launch(const void* hidden, int dtype, int32_t dim, const float* anchor_q, float inv_tau, float* scores,
                         const int32_t* first, const int32_t* count, const int32_t* out, int32_t n_slices, int32_t longest, void* stream);
 
+// Whether selection and compact merge of `batch` samples of `nv` visual tokens are faster in one launch than in two.
+bool merge_in_one_launch(int32_t batch, int64_t nv);
+
 // Selection and compact merge in one launch (merge.hip), arguments checked by the caller.  pos_axis_in / pos_axis_out: element
 // distances between the three id axes of pos_ids and of pos_c.
 int merge_batch_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, int32_t batch, int64_t seq_len,

@@ -1,6 +1,6 @@
 // civic_compact_prefill: the front of the path in one call - anchor scores of the visual rows (Eq. 8), token
 // selection under the budget and the floors, compact merge (Eq. 13) - in two launches on the caller's stream: the
-// scores, then selection and merge (merge.hip).  One crossing of the language boundary and two launches are most of what
+// scores, then selection and merge (merge.hip; a launch each for large batches of large grids).  One crossing of the language boundary and two launches are most of what
 // the call costs on shapes whose kernels take a few microseconds each.
 #include "civic_internal.h"
 
@@ -26,7 +26,13 @@ extern "C" int civic_compact_prefill(const void* hidden, int dtype, int32_t batc
 
     rc = civic_score_visual(hidden, dtype, batch, seq_len, dim, grid, frame_start, anchor_q, inv_tau, scores, stream);
     if (rc != CIVIC_OK) return rc;
-    const int64_t seq_c = seq_len - static_cast<int64_t>(grid->frames) * grid->height * grid->width + n_kept;
+    const int64_t nv = static_cast<int64_t>(grid->frames) * grid->height * grid->width, seq_c = seq_len - nv + n_kept;
+    if (!merge_in_one_launch(batch, nv)) {
+        rc = civic_select(scores, batch, grid, kept_idx, nullptr, workspace, workspace_bytes, stream);
+        if (rc != CIVIC_OK) return rc;
+        return civic_compact(hidden, dtype, dim, pos_ids, batch, seq_len, grid, frame_start, kept_idx, n_kept, hidden_c, pos_c, src_idx,
+                             workspace, workspace_bytes, stream);
+    }
     return merge_batch_launch(hidden, dtype, dim, pos_ids, batch, seq_len, grid, frame_start, scores, kept_idx, hidden_c, pos_c, src_idx,
                               batch * seq_len, batch * seq_c, stream);
 }

@@ -20,9 +20,10 @@
 namespace civic {
 
 constexpr int kMergeRows = 2048;                 // rows whose sources are held in LDS at a time
-constexpr int kMergeUnits = 256;                 // workgroups that select, per launch
+constexpr int kMergeUnits = 256;                 // compute units
 constexpr int kMergeGroupBytes = 8 * 1024;       // a workgroup of 512 threads moves at least this much: one load per thread
 constexpr int kMergeTextBytes = 64 * 1024;       // moved by a workgroup that only copies text
+constexpr int kMergeLongBytes = 128 * 1024;      // moved by a workgroup of a large batch of long samples
 
 struct MergeItem {
     SelArgs sel;
@@ -271,6 +272,18 @@ static MergeItem merge_item(const float* scores, int32_t* kept_idx, const civic_
 // Rows that selecting workgroups move.
 static int64_t placed_rows(const MergeItem& it, bool text_apart) { return it.seq_c - (text_apart ? it.head + it.tail : 0); }
 
+// Selecting workgroups of each of `batch` samples with `bytes` of rows to move.  Up to half as many samples as units: one workgroup to
+// a unit.  More samples: workgroups that fill the units twice over, two for each sample at least, and for long samples one for every
+// 128 KB up to eight times over: what a selection costs is small beside their rows, and many small workgroups end together.  (us,
+// front, one workgroup to a unit and so: 129 samples of 16 x 16, 1024 channels 39.0, 36.8, 300 of them 83.4, 78.8; 129 of 32 x 32, 2048
+// channels 205, 181, 300 of them 535, 485; 300 of 64 x 64, 1152 channels 1242, 1154.)
+static int64_t merge_share(int32_t batch, int64_t bytes)
+{
+    if (batch <= kMergeUnits / 2) return kMergeUnits / batch;
+    const int64_t least = std::max(2 * kMergeUnits / batch, 2), most = (8 * kMergeUnits + batch - 1) / batch;
+    return std::max(least, std::min(most, bytes / kMergeLongBytes));
+}
+
 // How many workgroups move an item's rows when `units` of the launch's selecting workgroups are its share.
 static void merge_groups(MergeItem* it, int64_t units, int64_t row_bytes, bool text_apart)
 {
@@ -312,6 +325,12 @@ static int merge_launch(const MAP& map, const MergeTensors& t, int32_t widest, b
 // Text gets workgroups of its own where two workgroups fit a unit's LDS, and for launches whose samples take several each.
 constexpr size_t kMergePairLds = 80 * 1024;
 
+// Beyond 2^19 visual tokens in samples of more than 2048 the selection as a launch of its own is the faster one: there are samples for
+// enough units then, and a sample's selection takes too long to be made by all its workgroups.  (us, front, in one launch and in two: 64
+// samples of 64 x 64, 1152 channels 177, 182; 64 of 8 x 32 x 32, 512 channels 225, 225; 32 of 128 x 128 218, 218; 64 of 96 x 96 247, 243,
+// 128 of them 523, 506; 64 of 180 x 180 895, 877.)
+bool merge_in_one_launch(int32_t batch, int64_t nv) { return nv <= kSelSmallTokens || batch * nv <= (int64_t{1} << 19); }
+
 int merge_batch_launch(const void* hidden, int dtype, int32_t dim, const int32_t* pos_ids, int32_t batch, int64_t seq_len,
                        const civic_grid* grid, const int64_t* frame_start, const float* scores, int32_t* kept_idx, void* hidden_c,
                        int32_t* pos_c, int32_t* src_idx, int64_t pos_axis_in, int64_t pos_axis_out, void* stream)
@@ -323,7 +342,8 @@ int merge_batch_launch(const void* hidden, int dtype, int32_t dim, const int32_t
     for (int32_t f = 0; f < CIVIC_MAX_FRAMES; ++f) map.start[f] = 0;
     map.it = merge_item(scores, kept_idx, grid, frame_start, seq_len, map.start, &lds);
     map.n = batch;
-    merge_groups(&map.it, kMergeUnits / batch, row_bytes, lds <= kMergePairLds && batch <= kMergeUnits / 2);
+    const bool text_apart = lds <= kMergePairLds && batch <= kMergeUnits / 2;
+    merge_groups(&map.it, merge_share(batch, placed_rows(map.it, text_apart) * row_bytes), row_bytes, text_apart);
     const MergeTensors t = merge_tensors(hidden, row_bytes, pos_ids, hidden_c, pos_c, src_idx, pos_axis_in, pos_axis_out);
     const int32_t widest = std::max(map.it.sel_groups, map.it.text_groups);
     const bool text = map.it.text_groups > 0;

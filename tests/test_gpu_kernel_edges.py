@@ -426,7 +426,12 @@ def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
     (1, (2, 8, 8, 4, 4, 0, 0, 1), 0, 6, 0, 64, "random"),         # one kept token among text
     (128, (1, 8, 8, 4, 4, 1, 0, 20), 3, 0, 2, 64, "random"),      # the last batch with text workgroups, the first without
     (129, (1, 8, 8, 4, 4, 1, 0, 20), 3, 0, 2, 64, "random"),
-    (300, (1, 40, 60, 4, 4, 1, 0, 2300), 9, 0, 100, 8, "random"),  # more samples than units: 2409 rows a workgroup, in two runs
+    (300, (1, 40, 60, 4, 4, 1, 0, 2300), 9, 0, 100, 8, "random"),  # more than 2^19 tokens in samples of more than 2048: two launches
+    (128, (1, 64, 64, 4, 4, 1, 0, 1365), 9, 0, 100, 8, "random"),  # 2^19 tokens: one launch
+    (256, (1, 32, 64, 4, 4, 1, 0, 1900), 9, 0, 2500, 8, "random"),  # two workgroups a sample: 2204 rows each, in two runs
+    (257, (1, 8, 8, 4, 4, 1, 0, 20), 3, 0, 2, 64, "random"),      # more samples than units
+    (130, (1, 32, 32, 4, 4, 1, 0, 341), 64, 0, 64, 512, "random"),  # three workgroups a sample by number, one for every 128 KB
+    (130, (1, 32, 32, 4, 4, 1, 0, 341), 64, 0, 64, 2048, "random"),
     (1, (1, 32, 64, 4, 4, 1, 0, 700), 3, 0, 5, 64, "equal"),      # every score 0: ties by index
     (1, (1, 64, 64, 4, 4, 1, 9, 1500), 3, 0, 5, 64, "few"),       # eight distinct scores
     (1, (1, 32, 64, 4, 4, 2, 0, 700), 3, 0, 5, 64, "outlier"),    # all but two scores in one bucket
