@@ -63,20 +63,24 @@ struct MergeTensors {
     uint32_t magic_vpr;                          // ceil(2^32 / vpr), 0 for vpr = 1
 };
 
-// What a kernel of the signature (MAP, MergeTensors) was launched with, read from the argument segment again: values that were
-// read before the selection and are needed after it would fill the scalar registers across it (60 of them spilled).
+// What the kernel is launched with, as its one argument: it lies at the front of the argument segment as it lies on the host.  The kernel
+// reads it there, and again after the selection: values that were read before and are needed after it would fill the scalar registers
+// across it (60 of them spilled).
 template <typename MAP>
 struct MergeArgs { MAP map; MergeTensors t; };
 template <typename MAP>
 __device__ __forceinline__ const MergeArgs<MAP>& merge_args()
 {
+    static_assert(std::is_trivially_copyable<MergeArgs<MAP>>::value && std::is_standard_layout<MergeArgs<MAP>>::value &&
+                      alignof(MergeArgs<MAP>) <= 16 && sizeof(MergeArgs<MAP>) <= 4096,
+                  "passed byte for byte, where the segment begins");
     auto p = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *(const MergeArgs<MAP>*)p;
 }
 
 template <typename MAP, int T>
-__global__ __launch_bounds__(T, T / 128) void merge_kernel(MAP, MergeTensors)
+__global__ __launch_bounds__(T, T / 128) void merge_kernel(MergeArgs<MAP>)
 {
     constexpr int kSelThreads = T, kSelWaves = T / kWave;
     constexpr int kMergeUnroll = T == kSelMaxThreads ? 6 : 10;         // 16-byte loads in flight per thread (in 64 and in 128 registers)
@@ -318,7 +322,7 @@ static int merge_launch(const MAP& map, const MergeTensors& t, int32_t widest, b
         if (rc != CIVIC_OK) return rc;
     }
     const dim3 grid(static_cast<unsigned>(widest), static_cast<unsigned>(text ? 2 * map.n : map.n));
-    civic::launch((merge_kernel<MAP, T>), grid, dim3(T), lds, static_cast<hipStream_t>(stream), map, t);
+    civic::launch((merge_kernel<MAP, T>), grid, dim3(T), lds, static_cast<hipStream_t>(stream), MergeArgs<MAP>{map, t});
     return check_launch();
 }
 
