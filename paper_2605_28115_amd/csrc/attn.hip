@@ -432,8 +432,8 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
 }
 
-// The same pointer with both halves forced into scalar registers (the value must be wave-uniform), written by a scalar instruction at
-// the place of the call.  A load reads its base five wait states after a vector instruction wrote that at the earliest
+// The same pointer with both halves forced into scalar registers (the value must be wave-uniform), written by a scalar instruction.
+// A load reads its base five wait states after a vector instruction wrote that at the earliest
 // (v_readfirstlane, or v_readlane of a spilled pair), which the compiler does not see to for a load inside an asm statement; a scalar
 // instruction waits for the vector one in hardware, and what it wrote may be read at once.  (Five states in front of every load
 // instead: 0.5 to 1 % of a launch.)
@@ -444,7 +444,7 @@ __device__ __forceinline__ const char* uniform_ptr(const void* p)
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits)));
     uint64_t copy;
-    asm volatile("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
+    asm("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
     return reinterpret_cast<const char*>(copy);
 }
 

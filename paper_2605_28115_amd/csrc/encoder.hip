@@ -81,7 +81,7 @@ __device__ __forceinline__ const char* enc_uniform(const void* p)
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits)));
     uint64_t copy;
-    asm volatile("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
+    asm("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
     return reinterpret_cast<const char*>(copy);
 }
 

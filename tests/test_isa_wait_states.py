@@ -60,6 +60,8 @@ def states_before(code, index, before):
         if op.startswith("v_") and any(scalar_registers(a) & base for a in args[:2 if "_co_" in op else 1]):
             best = waited
             continue
+        if op.startswith("s_") and args and base <= scalar_registers(args[0]):
+            continue                                          # a scalar instruction waits for the vector one by itself
         todo += [(q, waited + (int(args[0], 0) + 1 if op == "s_nop" else 1)) for q in before[p]]
     return best
 
