@@ -1222,6 +1222,14 @@ static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
     return a.head_dim > 64 && full && a.kv_seq > 23 * kBN;
 }
 
+// The choice of a launch whose geometry with 8 wavefronts fits; `a` holds it.
+static bool takes_eight(const AttnArgs& a, int64_t per_rt, bool ragged)
+{
+    AttnArgs four = a;
+    int64_t per_rt4 = 0;
+    return eight_wavefronts(a, per_rt, ragged) || !mfma_geometry<4>(four, &per_rt4);
+}
+
 template <int DP, int WAVES, int STAGES, bool RAGGED>
 static int launch_mfma(AttnArgs& a, hipStream_t s)
 {
@@ -1319,7 +1327,7 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
     if (dtype == CIVIC_BF16 && head_dim <= 128 && rope_fits && kv_strides[1] * 2 < (1 << 25) &&
         static_cast<int64_t>(seq) * q_strides[1] * 2 < (int64_t{1} << 32) && mfma_geometry<8>(a, &per_rt)) {
         if (dry_run) return CIVIC_OK;
-        const bool eight = eight_wavefronts(a, per_rt, item_row != nullptr) || !mfma_geometry<4>(a, &per_rt);
+        const bool eight = takes_eight(a, per_rt, item_row != nullptr);
         if (item_row) return eight ? launch_mfma_for<8, true>(a, s) : launch_mfma_for<4, true>(a, s);
         return eight ? launch_mfma_for<8, false>(a, s) : launch_mfma_for<4, false>(a, s);
     }
@@ -1348,6 +1356,22 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
 }
 
 }  // namespace civic
+
+// For tests, on the host alone (no part of civic.h): how a launch of bf16 attention of these sizes, one length for all samples, is
+// taken.  4 or 8: wavefronts of a workgroup of the MFMA kernel; 9: of 8, with two row tiles each; 0: another kernel.
+extern "C" int civic_attn_workgroup(int32_t batch, int32_t seq, int32_t kv_seq, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                    int32_t causal)
+{
+    using namespace civic;
+    if (batch <= 0 || seq <= 0 || kv_seq <= 0 || n_kv_heads <= 0 || n_q_heads % n_kv_heads || head_dim > 128) return 0;
+    AttnArgs a = {};
+    a.batch = batch; a.seq = seq; a.kv_seq = kv_seq; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
+    a.causal = causal ? 1 : 0;
+    int64_t per_rt = 0;
+    if (!mfma_geometry<8>(a, &per_rt)) return 0;
+    if (!takes_eight(a, per_rt, false)) return 4;
+    return choose_paired(a, per_rt, 32 * (8 / a.heads_per_block)) ? 9 : 8;
+}
 
 extern "C" int civic_prefill_attn(const void* q, const void* k, const void* v, void* out, int dtype, int32_t batch,
                                   int32_t seq, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,

@@ -383,3 +383,14 @@ def test_a_single_number_is_an_array_of_one_entry(bd):
             bd.civic_decode_attn_ragged(q, cache, cache, kind(3))
     with pytest.raises(ValueError, match="one entry per frame"):
         bd.civic_score_visual(hidden, (1, 4, 4, 2, 2, 1, 0, 5), np.zeros((1, 1), dtype=np.int64), torch.zeros(8), 1.0)
+
+
+def test_attention_sizes_reach_the_kernel_they_are_chosen_for(bd):
+    """The GPU tests' sizes against the host's choice of a launch: workgroups of 8 wavefronts with two row tiles each (9), of 8 or 4."""
+    from test_gpu_parity import TWO_ROW_TILES
+    for b, s, hq, hkv, d in TWO_ROW_TILES:
+        assert bd.lib.civic_attn_workgroup(b, s, s, hq, hkv, d, 1) == 9, (b, s, hq, hkv, d)
+    tiles = [(-(-s // (256 // hpb)), s % (256 // hpb) == 0, hpb, d) for b, s, hq, hkv, d in TWO_ROW_TILES
+             for hpb in [4 if hq // hkv % 4 == 0 else 2 if hq // hkv % 2 == 0 else 1]]
+    assert {(n % 2, full) for n, full, _, _ in tiles} == {(0, True), (0, False), (1, True), (1, False)}
+    assert {hpb for _, _, hpb, _ in tiles} == {1, 2, 4} and {d for *_, d in tiles} == {72, 96, 128}

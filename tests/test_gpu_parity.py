@@ -393,16 +393,7 @@ def peaked_qkv(rng, b, s, hq, hkv, d, causal, sharp=3.0):
     return (wl.quantize(x, "bf16")[0] for x in (q, k, v))
 
 
-# The first four shapes are the sizes that matter (the 8B-shaped workload, 4096 and 20000 tokens, the encoder's
-# head size); the others are causal launches with more workgroups than compute units, where a workgroup walks two
-# row tiles (a heavy and a light one): odd and even numbers of row tiles, a full and a ragged last tile, 2 and 4
-# heads per workgroup, padded heads, and the KV-cache copy in the same launch.
-@pytest.mark.parametrize("shape,row_step", [((4, 938, 32, 8, 128), 1), ((1, 4096, 8, 2, 128), 1), ((1, 1365, 4, 4, 72), 1),
-                                            ((1, 20000, 4, 2, 128), 41), ((4, 896, 32, 8, 128), 1), ((5, 961, 32, 8, 128), 1),
-                                            ((8, 700, 16, 8, 128), 1), ((16, 1100, 12, 4, 96), 1), ((20, 1000, 8, 8, 64), 1),
-                                            ((40, 130, 32, 8, 128), 1), ((3, 2049, 16, 4, 72), 1)])
-@pytest.mark.parametrize("causal", [True, False])
-def test_attention_one_key_per_query(bd, shape, row_step, causal):
+def check_one_key_per_query(bd, shape, row_step, causal):
     b, s, hq, hkv, d = shape
     log("attention, one key per query", shape, "causal", causal)
     q, k, v = peaked_qkv(np.random.default_rng(s + d), b, s, hq, hkv, d, causal)
@@ -420,6 +411,28 @@ def test_attention_one_key_per_query(bd, shape, row_step, causal):
     log("   max abs err", err, "tol", attn_tol(ref, "bf16"), "mean |ref|", float(np.abs(ref).mean()))
     assert np.abs(ref).mean() > 0.5                          # the outputs really are single V rows, not averages
     assert np.isfinite(got).all() and err <= attn_tol(ref, "bf16")
+
+
+# The first four shapes are the sizes that matter (the 8B-shaped workload, 4096 and 20000 tokens, the encoder's
+# head size); the others are launches of more than one generation of workgroups, of 4 wavefronts all of them.
+@pytest.mark.parametrize("shape,row_step", [((4, 938, 32, 8, 128), 1), ((1, 4096, 8, 2, 128), 1), ((1, 1365, 4, 4, 72), 1),
+                                            ((1, 20000, 4, 2, 128), 41), ((4, 896, 32, 8, 128), 1), ((5, 961, 32, 8, 128), 1),
+                                            ((8, 700, 16, 8, 128), 1), ((16, 1100, 12, 4, 96), 1), ((20, 1000, 8, 8, 64), 1),
+                                            ((40, 130, 32, 8, 128), 1), ((3, 2049, 16, 4, 72), 1)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_one_key_per_query(bd, shape, row_step, causal):
+    check_one_key_per_query(bd, shape, row_step, causal)
+
+
+# Causal launches of workgroups of 8 wavefronts that walk two row tiles, a heavy and a light one: odd and even numbers of row tiles, a
+# full and a ragged last tile, 1, 2 and 4 heads per workgroup, padded heads, and the KV-cache copy in the same launch.
+TWO_ROW_TILES = [(8, 1024, 16, 16, 72), (5, 1200, 16, 16, 128), (5, 1280, 16, 16, 96), (10, 768, 16, 8, 96), (6, 1100, 16, 8, 128),
+                 (10, 700, 16, 8, 72), (16, 1000, 8, 2, 72), (4, 960, 32, 8, 96), (4, 1024, 32, 8, 128)]
+
+
+@pytest.mark.parametrize("shape", TWO_ROW_TILES)
+def test_attention_two_row_tiles_a_workgroup(bd, shape):
+    check_one_key_per_query(bd, shape, 7, True)
 
 
 @pytest.mark.parametrize("shape", [
