@@ -394,3 +394,10 @@ def test_attention_sizes_reach_the_kernel_they_are_chosen_for(bd):
              for hpb in [4 if hq // hkv % 4 == 0 else 2 if hq // hkv % 2 == 0 else 1]]
     assert {(n % 2, full) for n, full, _, _ in tiles} == {(0, True), (0, False), (1, True), (1, False)}
     assert {hpb for _, _, hpb, _ in tiles} == {1, 2, 4} and {d for *_, d in tiles} == {72, 96, 128}
+    from test_gpu_kernel_edges import EIGHT_AND_FOUR, FOUR_AND_FOUR
+
+    def wavefronts(batch, case):
+        _, s, hq, hkv, d, causal, _ = case
+        return bd.lib.civic_attn_workgroup(batch, s, s, hq, hkv, d, int(causal))
+    assert [wavefronts(c[0], c) for c in EIGHT_AND_FOUR] == [9] * 4 + [8] * 7 and [wavefronts(1, c) for c in EIGHT_AND_FOUR] == [4] * 11
+    assert {wavefronts(b, c) for c in FOUR_AND_FOUR for b in (1, c[0])} == {4}

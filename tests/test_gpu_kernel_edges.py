@@ -618,13 +618,21 @@ def test_f32_attention_whole_heads_and_tiles_of_keys(bd, d, seq):
         assert np.abs(out.astype(np.float64) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
 
 
-@pytest.mark.parametrize("case", [
-    # batch, rows, query heads, KV heads, width, causal, rotary: the batch in workgroups of 8 wavefronts, a single sample in those of 4
-    (4, 938, 32, 8, 128, True, False), (4, 938, 32, 8, 128, True, True), (3, 1440, 16, 4, 96, True, True), (2, 1365, 16, 16, 72, False, False),
-    (2, 1153, 8, 8, 128, False, False), (12, 1537, 4, 4, 64, False, False),
-    # both in those of 4, around the ends of their row and key tiles
-    (3, 1, 4, 2, 64, True, False), (2, 65, 4, 4, 96, True, True), (5, 129, 4, 1, 128, True, True), (2, 161, 6, 2, 80, False, False), (9, 767, 8, 8, 128, False, False),
-])
+# batch, rows, query heads, KV heads, width, causal, rotary: the batch in workgroups of 8 wavefronts, with two row tiles each where marked,
+# a single sample in those of 4
+EIGHT_AND_FOUR = [
+    (4, 938, 32, 8, 128, True, False), (4, 938, 32, 8, 128, True, True), (3, 960, 40, 10, 96, True, True), (6, 1100, 16, 8, 72, True, False),   # two
+    (6, 2817, 4, 2, 128, True, False), (2, 1365, 16, 16, 72, False, False), (4, 1153, 8, 8, 128, False, False), (8, 1200, 4, 4, 64, False, False),
+    (24, 1537, 4, 4, 128, False, False), (8, 1537, 8, 8, 96, False, False), (9, 767, 8, 8, 128, False, False),
+]
+# both in those of 4, two and more to a unit, and around the ends of their row and key tiles
+FOUR_AND_FOUR = [
+    (3, 1440, 16, 4, 96, True, True), (2, 1153, 8, 8, 128, False, False), (12, 1537, 4, 4, 64, False, False),
+    (3, 1, 4, 2, 64, True, False), (2, 65, 4, 4, 96, True, True), (5, 129, 4, 1, 128, True, True), (2, 161, 6, 2, 80, False, False),
+]
+
+
+@pytest.mark.parametrize("case", EIGHT_AND_FOUR + FOUR_AND_FOUR)
 def test_attention_of_a_batch_is_that_of_its_samples(bd, case):
     """Attention, with and without rotary positions and the fused cache write, of a batch and of its samples one by one and as a ragged
     batch: launches choose workgroups of 4 or 8 wavefronts by their size, and the bits are the same.  One sample against the oracle at
