@@ -1199,12 +1199,13 @@ static bool choose_paired(const AttnArgs& a, int64_t per_rt, int rows_per_block)
 //   - no mask, more: 8 for wide heads from 24 key tiles on where the last generation is full.  8 x 4096, 32 / 8 1986, 2077; 3 x 2323,
 //     16 / 8 138, 143; but 4 x 1618, 32 / 8 192, 182; eight items of 85 to 1365 rows over 256 keys, 16 / 16 of 72 23.3, 21.2;
 //     2 x 4096, 16 / 16 of 64 152, 144
-//   - causal: 8 for wide heads where pairs of row tiles fill their generations.  4 x 938, 32 / 8 38.5, 40.0; 1 x 3584, 32 / 8 105.5,
+//   - causal: 8 for heads wider than 64 where pairs of row tiles fill their generations.  4 x 938, 32 / 8 38.5, 40.0; 1 x 3584, 32 / 8 105.5,
 //     109.6; but 4 x 600, 32 / 8 22.8, 21.1; 8 x 900, 16 / 16 of 64 30.0, 26.8
 //   - causal, not paired (items of different length never are): 8 beyond 44 key tiles and one generation.  Eight items of 3000 rows,
 //     28 / 4 544, 615 and 32 / 8 563, 573; but eight of 101 to 938, 32 / 8 39.8, 35.9; four of 300 to 2700, 32 / 8 178, 169
 static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
 {
+    if (a.causal && a.head_dim <= 64) return false;           // (before the model of a launch that is not taken)
     const int rows_per_block = 32 * (8 / a.heads_per_block);
     int64_t blocks = per_rt * a.row_tiles;
     if (ragged) {
@@ -1213,11 +1214,11 @@ static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
             blocks += (static_cast<int64_t>(a.item_row[i + 1]) - a.item_row[i] + rows_per_block - 1) / rows_per_block * (per_rt / a.batch);
     }
     const bool paired = !ragged && choose_paired(a, per_rt, rows_per_block);
-    if (a.causal && !paired) return a.head_dim > 64 && blocks > kComputeUnits && a.seq > 44 * kBN;
+    if (a.causal && !paired) return blocks > kComputeUnits && a.seq > 44 * kBN;
     if (paired) blocks = per_rt * ((a.row_tiles + 1) / 2);
     const int64_t generations = (blocks + kComputeUnits - 1) / kComputeUnits;
     const bool full = 100 * blocks >= 85 * generations * kComputeUnits;
-    if (a.causal) return a.head_dim > 64 && full;
+    if (a.causal) return full;
     if (generations == 1) return 2 * blocks > kComputeUnits && a.kv_seq > 7 * kBN;
     return a.head_dim > 64 && full && a.kv_seq > 23 * kBN;
 }

@@ -401,3 +401,19 @@ def test_attention_sizes_reach_the_kernel_they_are_chosen_for(bd):
         return bd.lib.civic_attn_workgroup(batch, s, s, hq, hkv, d, int(causal))
     assert [wavefronts(c[0], c) for c in EIGHT_AND_FOUR] == [9] * 4 + [8] * 7 and [wavefronts(1, c) for c in EIGHT_AND_FOUR] == [4] * 11
     assert {wavefronts(b, c) for c in FOUR_AND_FOUR for b in (1, c[0])} == {4}
+
+
+def test_attention_launch_of_narrow_causal_heads_is_not_modelled(bd):
+    """Causal heads of up to 64 channels take workgroups of 4 wavefronts whatever the size: a new prompt length costs no model of the
+    launch on the host, which wider heads need (tens of microseconds, forty times as much)."""
+    import time
+    rng = np.random.default_rng(3)
+    sizes = [(int(b), int(s)) for b, s in zip(rng.integers(1, 40, 300), rng.integers(100, 4000, 300))]
+
+    def pass_over(d):
+        t = time.perf_counter()
+        got = {bd.lib.civic_attn_workgroup(b, s, s, 32, 8, d, 1) for b, s in sizes}
+        return time.perf_counter() - t, got
+    narrow, wide = min(pass_over(64) for _ in range(3)), min(pass_over(128) for _ in range(3))
+    assert narrow[1] == {4} and wide[1] == {4, 8, 9}
+    assert narrow[0] < wide[0] / 4
