@@ -8,8 +8,8 @@ civic_score_visual (the visual rows scored where they lie in the dense sequence)
 the scores just written) -> civic_compact -> civic_prefill_attn_kv (attention and the KV-cache write
 of the same K/V as one call; --unfused runs civic_prefill_attn -> civic_kv_write instead), back to
 back on one stream, for one transformer layer.  The timed step issues the first three through
-civic_compact_prefill, the library's one-call front (the same three kernels, one crossing from Python;
---separate-calls issues them one by one).  Buffers rotate over R independent sets so that
+civic_compact_prefill, the library's one-call front (the score kernel, then selection and merge in one
+kernel; one crossing from Python; --separate-calls issues the three calls, a kernel each, one by one).  Buffers rotate over R independent sets so that
 consecutive steps do not find their inputs in the last-level cache.
 
 Order of a run: an untimed pre-warm of full steps for --prewarm-ms of wall time (the chip's clock
@@ -26,7 +26,8 @@ kernel's duration inside the step (`us_kernel_in_step`, the figure a kernel trac
 duration.  A third pass times every stage alone as a GPU number: a
 spin kernel holds the stream while --stage-launches launches of the stage are queued behind it, and
 two events bracket them, so the figure under `stages` (`us`) is the kernels' own back-to-back time
-and carries no host launch cost.  `decode` reports the decode-step attention
+and carries no host launch cost.  `select` and `compact` there are the separate calls; `front` is the one
+call, and `merge` what it takes beyond the scores: the kernel that a step runs for both.  `decode` reports the decode-step attention
 over the cache the step has just written (one query per sequence, HBM-bound).  `cpu_baseline` times
 the CPU oracle, as it stands, on a bounded sample of the same workload on this machine's host cores.
 Prints one JSON line.
@@ -239,8 +240,8 @@ def main() -> int:
     STAGES = STAGES_UNFUSED if args.unfused else STAGES_FUSED
     order = [calls[s] for s in STAGES]
 
-    # the timed step: the front of the path as one library call (the same three kernels; one crossing from Python
-    # instead of three), then attention and the KV write
+    # the timed step: the front of the path as one library call (the scores in one kernel, selection and merge in
+    # another; one crossing from Python instead of three), then attention and the KV write
     step_calls = order if args.separate_calls else [calls["front"]] + order[3:]
 
     def step(i):
@@ -338,6 +339,8 @@ def main() -> int:
             continue
         stage_us[name]["alone"] = alone(calls[name])
     select_dist_us = alone(calls["select_dist"])
+    front_us = alone(calls["front"])
+    merge_us = front_us - stage_us["score"]["alone"]
 
     work = algorithmic_work(w)
     stages = {}
@@ -358,8 +361,12 @@ def main() -> int:
             entry.update(gbs=round(gbs, 1), frac_hbm_peak=round(gbs / HBM_PEAK_GBS, 4))
         stages[name] = entry
     stages["select"]["us_on_workload_scores"] = round(select_dist_us, 2)   # the configuration's own score distribution
-    sg = (work["select"] + work["compact"]) / ((stage_us["select"]["alone"] + stage_us["compact"]["alone"]) * 1e-6) / 1e9
-    stages["select+compact"] = {"gbs": round(sg, 1), "frac_hbm_peak": round(sg / HBM_PEAK_GBS, 4)}
+    stages["front"] = {"us": round(front_us, 2)}
+    sc_bytes = work["select"] + work["compact"]
+    stages["merge"] = {"us": round(merge_us, 2), "gbs": round(sc_bytes / merge_us / 1e3, 1), "frac_hbm_peak": round(sc_bytes / merge_us / 1e3 / HBM_PEAK_GBS, 4)}
+    # selection and merge as the step runs them: in one kernel, or as two calls
+    sc_us = stage_us["select"]["alone"] + stage_us["compact"]["alone"] if args.separate_calls else merge_us
+    stages["select+compact"] = {"us": round(sc_us, 2), "gbs": round(sc_bytes / sc_us / 1e3, 1), "frac_hbm_peak": round(sc_bytes / sc_us / 1e3 / HBM_PEAK_GBS, 4)}
 
     attn_name = "attn" if args.unfused else "attn_kv"
     attn_us = stage_us[attn_name]["kernel"]          # the events ride on the kernel's own dispatch, inside the step
@@ -370,7 +377,7 @@ def main() -> int:
                     "traffic": measured_traffic(w.name, attn_name) if w.batch == wl.WORKLOADS[w.name].batch else None, "launch_us": round(attn_us, 2),
                     "launch_us_between_events": round(stage_us[attn_name]["mean"], 2), "flops_per_launch": work["attn_flops"]}
     else:
-        roofline = {"bound": "alu", "kernel": f"attn_plain_kernel (civic_prefill_{attn_name})", "achieved": round(attn_tf, 3),
+        roofline = {"bound": "alu", "kernel": f"attn_f32_kernel (civic_prefill_{attn_name})", "achieved": round(attn_tf, 3),
                     "peak": 157.3, "unit": "TFLOP/s", "frac": round(attn_tf / 157.3, 5), "traffic": None,
                     "launch_us": round(attn_us, 2), "flops_per_launch": work["attn_flops"]}
 
@@ -468,8 +475,8 @@ def main() -> int:
                                   "frac_hbm_peak": round(q_bytes / t_apply / 1e3 / HBM_PEAK_GBS, 4)}}
 
     # The path on a ragged batch (images of different grid sizes in one batch, packed along the token axis), on the
-    # 8b-shaped workload's widths: eight samples from one 16 x 16 image to two 32 x 32 images.  The front runs its three
-    # kernels sample by sample; the attention (with the KV write) is one launch, timed against one call per sample.
+    # 8b-shaped workload's widths: eight samples from one 16 x 16 image to two 32 x 32 images.  The front is a launch for
+    # all scores and one for all selections and merges; the attention (with the KV write) is one launch, timed against one call per sample.
     ragged = None
     if not args.path_only and w.name == "8b":
         from paper_2605_28115_amd import workloads as wl_
@@ -506,8 +513,8 @@ def main() -> int:
         f_r = sum(4.0 * w.n_q_heads * w.head_dim * (n_ * (n_ + 1) / 2) for n_ in np.diff(rcomp))
         ragged = {"samples": len(rgrids), "dense_rows": int(rseq[-1]), "compact_rows": tc,
                   "compact_prefill_ragged_us": round(t_front, 2),
-                  # scores 64 frame spans per launch, selection 16 samples per launch, merge 24 samples per launch (all have few frames)
-                  "launches_front": -(-sum(g_[0] for g_ in rgrids) // 64) + -(-len(rgrids) // 16) + -(-len(rgrids) // 24),
+                  # scores 64 frame spans per launch, selection and merge 16 samples per launch (all have few frames)
+                  "launches_front": -(-sum(g_[0] for g_ in rgrids) // 64) + -(-len(rgrids) // 16),
                   "prefill_attn_ragged": {"us": round(t_rattn, 2), "us_one_call_per_sample": round(t_rattn_items, 2), "flops": f_r,
                                           "tflops": round(f_r / t_rattn / 1e6, 1)},
                   "decode_attn_ragged_us": round(t_rdec, 2)}
