@@ -432,20 +432,25 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
 }
 
-// The same pointer with both halves forced into scalar registers (the value must be wave-uniform), written by a scalar instruction.
-// A load reads its base five wait states after a vector instruction wrote that at the earliest
-// (v_readfirstlane, or v_readlane of a spilled pair), which the compiler does not see to for a load inside an asm statement; a scalar
-// instruction waits for the vector one in hardware, and what it wrote may be read at once.  (Five states in front of every load
-// instead: 0.5 to 1 % of a launch.)
+// The same pointer, written by a scalar instruction.  A load reads its base five wait states after a vector instruction wrote that at
+// the earliest (v_readfirstlane, or v_readlane of a spilled pair), which the compiler does not see to for a load inside an asm
+// statement; a scalar instruction waits for the vector one in hardware, and what it wrote may be read at once.  (Five states in front
+// of every load instead: 0.5 to 1 % of a launch.)
+__device__ __forceinline__ const char* scalar_copy(const char* p)
+{
+    uint64_t copy;
+    asm("s_mov_b64 %0, %1" : "=s"(copy) : "s"(p));
+    return reinterpret_cast<const char*>(copy);
+}
+
+// A wave-uniform pointer with both halves forced into scalar registers, for loads.
 __device__ __forceinline__ const char* uniform_ptr(const void* p)
 {
     const uint64_t bits = reinterpret_cast<uint64_t>(p);
     // the builtin returns a signed int: widen each half as unsigned
     const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits >> 32)));
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bits)));
-    uint64_t copy;
-    asm("s_mov_b64 %0, %1" : "=s"(copy) : "s"((static_cast<uint64_t>(hi) << 32) | lo));
-    return reinterpret_cast<const char*>(copy);
+    return scalar_copy(reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt()
@@ -566,7 +571,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     // own area), so that the main loop holds no register-destination global load: the
     // compiler then never emits a vmcnt wait of its own there.
     const uint32_t q_lds = T::IN_RINGS ? (w & 1) * T::QW + TILEB + (w >> 1) * VBASE : 2 * VBASE + w * T::WAREA;
-    const char* qb = reinterpret_cast<const char*>(static_cast<const __bf16*>(a.q) + q_first + h * a.qs[2]);
+    const char* const qb = uniform_ptr(static_cast<const __bf16*>(a.q) + q_first + h * a.qs[2]);
     const uint32_t q_row_bytes = static_cast<uint32_t>(a.qs[1]) * 2u;
     const uint32_t q_lds_uni = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + q_lds);
     // Slot -> (row, physical chunk) as for a K tile: instruction j covers rows 4j .. 4j+3 when a row has 16
@@ -581,7 +586,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
         return static_cast<uint32_t>(r) * q_row_bytes + cb;
     };
     auto issue_q = [&](int first_row) {                       // any row tile: rows past the sequence re-read its last row
-        const char* base = uniform_ptr(qb);
+        const char* base = scalar_copy(qb);
 #pragma unroll
         for (int j = 0; j < PITCH / 2; ++j)
             dma16_at(base, q_slot_off(j, first_row, true), q_lds_uni, std::integral_constant<int, 0>{}, j);
