@@ -181,7 +181,8 @@ int civic_compact(const void* hidden, int dtype, int32_t dim, const int32_t* pos
 /* The front of the path in one call: civic_score_visual (Eq. 8), civic_select (budget and
  * floors) and civic_compact (Eq. 13) on `stream`, with n_kept = civic_kept_count(grid).  The
  * results are those of the three calls, bit for bit; selection and merge are one launch (a
- * launch each beyond 2^19 visual tokens in samples of more than 2048), and there is one crossing from the caller's language instead of three.
+ * launch each beyond 2^19 visual tokens in samples of more than 2048), and there is one
+ * crossing from the caller's language instead of three.
  * Arguments as in the three calls; scores [batch, N_v] and kept_idx [batch, K] are outputs
  * here (intermediate results the caller may want).  Every check of every stage runs before
  * the first launch. */
@@ -386,7 +387,8 @@ int civic_cross_attn(const void* q, const void* k, const void* v, void* out, int
  * packed back to back, item b owning rows [row_offsets[b], row_offsets[b+1]) of k, v and of its own assignment rows in
  * r; every item is compressed and attended by itself, and the results equal civic_kv_compress / civic_cross_attn on
  * that item alone, bit for bit.  Items travel in groups of up to 64 whose row numbers are passed with the launch: the
- * compression is two launches per group (column sums, product), the attention ONE launch per group (fp32 or head_dim > 128: one launch per item).
+ * compression is two launches per group (column sums, product), the attention ONE launch per group (fp32 or
+ * head_dim > 128: one launch per item).
  *   k, v         device [total_rows, width] bf16;  r  device [total_rows, n_mem] fp32
  *   row_offsets  host [batch + 1] int64, row_offsets[0] = 0, strictly increasing (no empty item)
  *   k_c, v_c     device [batch, n_mem, width] bf16

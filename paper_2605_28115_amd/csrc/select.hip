@@ -1,18 +1,18 @@
 // civic_select: exact constrained top-k (cell floors, frame floors, global budget) with ascending,
 // order-preserving output.  Latency-bound: a sample's scores are 8-128 KB.
 //
-// One 1024-thread workgroup per sample keeps everything in LDS: a 32-bit sort key per token and one
-// mark bit per token.  The strict order "higher score first, equal scores to the lower index" becomes
+// One workgroup per sample (1024 threads, 512 up to 2048 tokens) keeps everything in LDS: a 32-bit sort key per
+// token and one mark bit per token.  The strict order "higher score first, equal scores to the lower index" becomes
 // (key ascending, index ascending) after mapping the float bits to an unsigned key (with -0 folded
 // onto +0).
-//   cells   small cells: one thread per cell picks the cell's best remaining member cell_floor times
-//           (members scanned in index order, strict key comparison = the tie rule).
+//   cells   small cells: one thread per cell (from registers up to 4 x 4), or a team of 16 lanes, picks the
+//           cell's best remaining member cell_floor times (smallest key, then smallest index = the tie rule).
 //           large cells: one wavefront per cell runs the select below.
 //   frames  one wavefront per frame: the select below over the frame's unmarked tokens (256 bins).
-//   budget  the same select run by the whole workgroup over the unmarked tokens of the sample (2048
-//           bins).
-//   select  one histogram pass over buckets that are linear in the score, a scan for the bucket that
-//           holds the m-th token, one marking pass; the few tokens of that bucket are ranked against
+//   budget  the same select run by the whole workgroup over the unmarked tokens of the sample (512 to
+//           2048 bins, by the tokens).
+//   select  one histogram pass over buckets that are linear in the score, a search for the bucket that
+//           holds the m-th token (by every wavefront for itself), one marking pass; the few tokens of that bucket are ranked against
 //           each other directly.  Degenerate score distributions fall back to an exact radix select
 //           over the key digits (see select_first).
 //   output  popcounts of the 64-bit mark words -> LDS prefix scan -> every set bit writes its index
