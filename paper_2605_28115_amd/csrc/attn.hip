@@ -59,9 +59,10 @@ struct AttnArgs {
     int32_t batch, seq, n_q_heads, n_kv_heads, head_dim, causal;
     int32_t kv_seq;                       // keys per sample (= seq except for civic_cross_attn, which has no mask)
     float scale;                          // softmax scale (natural-exponent domain)
-    int32_t heads_per_block, row_tiles;   // MFMA path: block shape and number of 32*rows_per_block tiles
+    int32_t heads_per_block, row_tiles;   // MFMA path: block shape and number of 32*rows_per_block tiles; fp32 path: tiles of 16 rows
+    int32_t pass_tiles;                   // fp32 path: row tiles of a pass over the units (f32_grid)
     int32_t paired;                       // MFMA path: a workgroup walks two row tiles, a heavy and a light one
-    // MFMA path, block index -> (head block, kv head, batch) without integer division: q heads per kv head,
+    // block index -> (head block, kv head, batch) without integer division: q heads per kv head,
     // head blocks per kv head, log2(heads_per_block), ceil(2^32 / d) for d = head blocks, kv heads (0 for d = 1)
     int32_t group, head_blocks, hb_shift;
     uint32_t magic_head_blocks, magic_kv_heads;
@@ -86,7 +87,7 @@ struct AttnArgs {
 // lie there: channels 16 t + 4 (lane / 16) .. + 3 of key lane % 16 serve four consecutive MFMAs, channels 64 T + 4 (lane % 16) ..
 // + 3 of one key are four rows of V^T.  S^T leaves a lane with four consecutive keys of one query, which is the B operand of
 // O^T += V^T P^T as it stands.  L1 delivers 16 KB per 16 x 16 tile and wavefront, 32 bytes a clock and unit at full MFMA rate.
-// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), 24.7 us here.
+// 469 rows, 16 / 8 heads of 128, causal: 175 us on the vector units (one row per wavefront), 20.7 us here.
 template <bool BF16>
 __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 {
@@ -100,6 +101,7 @@ __device__ __forceinline__ float4 load_quad(const void* p, int64_t i)
 }
 
 constexpr int kF32Rows = 16, kF32Waves = 4;
+constexpr int kMaxGridZ = 65535;
 static constexpr size_t f32_lds_bytes(int nt) { return sizeof(float) * (kF32Waves * kF32Rows * (64 * nt + 4 + 2) + kF32Waves); }
 
 // NT: head_dim rounded up to 64, over 64.  SUB: sub-tiles of 16 keys a tile (launch_f32_for says which).  TAIL: head_dim ends inside
@@ -117,9 +119,18 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
     float* const st_m = f32_lds + kF32Waves * kF32Rows * PITCH, * const st_l = st_m + kF32Waves * kF32Rows, * const st_odd = st_l + kF32Waves * kF32Rows;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int l16 = lane & 15, kq = lane >> 4;
-    const int row_tile = gridDim.x - 1 - blockIdx.x;           // the heaviest causal tiles first
-    const int h = blockIdx.y, b = blockIdx.z, group = a.n_q_heads / a.n_kv_heads;
-    const int g = h / group, d = FULL ? 64 * NT : a.head_dim, i0 = row_tile * kF32Rows;
+    // Grid x: the query heads, those of KV head g at g, g + n_kv_heads, ...; y: the samples; z: the row tiles, f32_grid has the order.
+    const int group = a.group, hg = a.magic_kv_heads ? static_cast<int>(__umulhi(blockIdx.x, a.magic_kv_heads)) : static_cast<int>(blockIdx.x);
+    const int g = static_cast<int>(blockIdx.x) - hg * a.n_kv_heads, h = g * group + hg;
+    int b = blockIdx.y, y = blockIdx.z;
+    if (b >= a.batch) { const int up = b / a.batch; b -= up * a.batch; y += up * kMaxGridZ; }
+    if (y >= a.row_tiles) return;
+    if (a.pass_tiles < a.row_tiles) {
+        const int pass = y / a.pass_tiles, first = pass * a.pass_tiles;
+        if (pass & 1) y = first + min(first + a.pass_tiles, a.row_tiles) - 1 - y;
+    }
+    const int row_tile = a.row_tiles - 1 - y;                  // the heaviest causal tiles first
+    const int d = FULL ? 64 * NT : a.head_dim, i0 = row_tile * kF32Rows;
     const int rows = min(kF32Rows, a.seq - i0);
     const int64_t kv_off = b * a.ks[0] + g * a.ks[2];
 
@@ -323,11 +334,30 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
     }
 }
 
-template <bool BF16, int NT, int SUB, bool TAIL, bool FULL>
-static int launch_f32_tail(const AttnArgs& a, hipStream_t s)
+// Grid and order of the workgroups.  The hardware hands consecutive workgroups to the eight XCDs in turn: with the heads innermost, the
+// query heads of a KV head and all their row tiles land on the same few, and its K and V in those L2s (2 x 1024 rows, 8 heads of 256
+// 188 -> 130 us, 1 x 1500, 8 of 96 85 -> 68; the row tiles innermost brought all K and V to every XCD).
+// Under the causal mask row tiles go out by falling weight.  Up to four workgroups to a unit they go in passes of one workgroup to a
+// unit, every other pass in reverse, so that the unit with the heaviest first takes the lightest second: all start at once or nearly
+// so, and nothing evens out the units later (1 x 469, 16 / 8 heads of 128 23.5 -> 20.9 us, 1 x 1024, 8 / 8 40.0 -> 31.8, 1 x 700, 16 / 8
+// 38.4 -> 33.9).  More workgroups than that even out by themselves (4 x 200, 32 / 8 33.7 and 34.3 in passes, 8 x 117, 16 / 8 19.3, 19.9).
+static dim3 f32_grid(AttnArgs& a)
 {
-    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(a.seq) + kF32Rows - 1) / kF32Rows), static_cast<unsigned>(a.n_q_heads),
-                    static_cast<unsigned>(a.batch));
+    constexpr int64_t kUnits = 256;                            // compute units
+    a.row_tiles = static_cast<int32_t>((static_cast<int64_t>(a.seq) + kF32Rows - 1) / kF32Rows);
+    const int64_t per_rt = static_cast<int64_t>(a.n_q_heads) * a.batch;
+    a.pass_tiles = a.causal && per_rt <= kUnits && per_rt * a.row_tiles <= 4 * kUnits ? static_cast<int32_t>(kUnits / per_rt) : a.row_tiles;
+    a.magic_kv_heads = a.n_kv_heads <= 1 ? 0u : static_cast<uint32_t>(((int64_t{1} << 32) + a.n_kv_heads - 1) / a.n_kv_heads);
+    // (row tiles past what a grid has in z continue behind the samples in y)
+    return dim3(static_cast<unsigned>(a.n_q_heads), static_cast<unsigned>(a.batch * ((a.row_tiles + kMaxGridZ - 1) / kMaxGridZ)),
+                static_cast<unsigned>(std::min(a.row_tiles, kMaxGridZ)));
+}
+
+template <bool BF16, int NT, int SUB, bool TAIL, bool FULL>
+static int launch_f32_tail(const AttnArgs& a_in, hipStream_t s)
+{
+    AttnArgs a = a_in;
+    const dim3 grid = f32_grid(a);
     constexpr size_t lds = f32_lds_bytes(NT);
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
@@ -1317,7 +1347,7 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
     a.batch = batch; a.seq = seq; a.kv_seq = kv_seq; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
     a.causal = causal ? 1 : 0;
     a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt(static_cast<float>(head_dim));
-    a.heads_per_block = 1; a.row_tiles = 0; a.paired = 0;
+    a.heads_per_block = 1; a.row_tiles = 0; a.pass_tiles = 0; a.paired = 0;
     a.group = n_q_heads / n_kv_heads; a.head_blocks = 0; a.hb_shift = 0; a.magic_head_blocks = 0; a.magic_kv_heads = 0;
     a.k_cache = k_cache; a.v_cache = v_cache; a.s_max = s_max; a.pos0 = pos0;
     a.q_cs = reinterpret_cast<const float2*>(q_cos_sin);

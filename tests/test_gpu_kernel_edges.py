@@ -184,6 +184,39 @@ def test_fp32_attention_tile_lengths(bd, n_kv, dtype, head_dim):
     assert np.abs(out - ref).max() <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(np.abs(ref).max()))
 
 
+@pytest.mark.parametrize("batch,seq,q_heads,kv_heads", [
+    (1, 513, 16, 8), (1, 130, 28, 4), (3, 97, 7, 7), (2, 255, 9, 1), (1, 1000, 8, 8), (1, 17, 200, 4), (1, 2000, 5, 1),
+    (4, 257, 16, 8), (1, 40, 300, 3)])
+def test_fp32_attention_order_of_row_tiles(bd, batch, seq, q_heads, kv_heads):
+    """Every row tile of every head and sample is computed once, whatever the passes over the units: one and several of them, whole
+    and not, units that do not divide by the heads, and launches that take none.  fp32 bar of the parity tests."""
+    log("fp32 attention, order", batch, seq, q_heads, kv_heads)
+    g = torch.Generator().manual_seed(seq + q_heads)
+    q, k, v = (torch.randn((batch, seq, n, 64), generator=g) for n in (q_heads, kv_heads, kv_heads))
+    out = torch.full(q.shape, float("nan"), device="cuda")
+    bd.civic_prefill_attn(q.cuda(), k.cuda(), v.cuda(), True, out=out)
+    qq, kk, vv = (x.double().transpose(1, 2) for x in (q, k, v))
+    kk, vv = (x.repeat_interleave(q_heads // kv_heads, 1) for x in (kk, vv))
+    z = torch.matmul(qq, kk.transpose(2, 3)) / 8.0
+    z.masked_fill_(torch.ones(seq, seq, dtype=torch.bool).triu(1), float("-inf"))
+    ref = torch.matmul(torch.softmax(z, -1), vv).transpose(1, 2)
+    assert (out.cpu().double() - ref).abs().max().item() <= 1e-5 * max(1.0, ref.abs().max().item())
+
+
+def test_fp32_attention_more_row_tiles_than_a_grid_has(bd):
+    """65535 row tiles of 16 rows and some more, two samples: weights over three keys, fp32 bar of the parity tests."""
+    n = 65535 * 16 + 21
+    log("fp32 attention, rows", n)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn((2, n, 2, 8), generator=g, device="cuda")
+    k, v = (torch.randn((2, 3, 1, 8), generator=g, device="cuda") for _ in range(2))
+    out = torch.full(q.shape, float("nan"), device="cuda")
+    bd.civic_cross_attn(q, k, v, out=out)
+    z = (q[:, :, :, None] * k[:, None, None, :, 0]).sum(-1) / 8 ** 0.5
+    ref = (torch.softmax(z, -1)[..., None] * v[:, None, None, :, 0]).sum(-2)
+    assert (out - ref).abs().max().item() <= 1e-5 * max(1.0, ref.abs().max().item())
+
+
 @pytest.mark.parametrize("seq,at", [(17, 16), (40, 33), (64, 50), (150, 149)])
 @pytest.mark.parametrize("head_dim", [64, 72, 256])
 def test_fp32_attention_hidden_rows_hold_anything(bd, seq, at, head_dim):
