@@ -417,6 +417,7 @@ template <int PITCH>
 __device__ __forceinline__ int swz(int row)
 {
     if constexpr (PITCH == 16) return ((row & 3) << 2) | ((row >> 2) & 3);
+    else if constexpr (PITCH == 12) return (row >> 2) & 3;   // (rows 12 chunks apart start in 4 different quarters of the 16 by themselves)
     else return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
 }
 
@@ -491,24 +492,27 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// DP: head_dim rounded up to a multiple of 32; WAVES: wavefronts per workgroup (4 or 8); STAGES: K/V
+// DP: head_dim rounded up to 64, 80, 96 or 128; WAVES: wavefronts per workgroup (4 or 8); STAGES: K/V
 // tiles in flight in LDS.
 template <int DP, int WAVES, int STAGES>
 struct AttnTile {
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int KSTEPS = DP / 16;      // MFMA k-steps of Q K^T
-    static constexpr int DT = DP / 32;          // 32-row tiles of O^T
-    static constexpr int PITCH = DP == 64 ? 8 : 16;        // 16-byte chunks per LDS row
+    static constexpr int DT = (DP + 31) / 32;   // 32-row tiles of O^T
+    static constexpr int PITCH = DP == 64 ? 8 : DP <= 96 && WAVES == 4 ? 12 : 16;   // 16-byte chunks per LDS row
     static constexpr int PITCHB = PITCH * 16;              // ... in bytes
     static constexpr int TILEB = kBN * PITCHB;             // bytes per K (or V) tile
     static constexpr int NI = kBN * PITCH / THREADS;       // global->LDS instructions per wavefront, tile and tensor
     static constexpr int TLOADS = 2 * NI;                  // ... per tile (K and V)
     static constexpr int VBASE = STAGES * TILEB;           // byte offset of the V stages
-    static constexpr int OROW = DP + 8;                    // elements per staged output row (padded against bank conflicts)
-    // Every wavefront has an area that first stages its Q tile (32 rows in the K tile layout) and later its 32 x DP output tile.  With
+    static constexpr int OROW = 32 * DT + 8;               // elements per staged output row (padded against bank conflicts)
+    // Every wavefront has an area that first stages its Q tile (32 rows in the K tile layout) and later its output tile.  With
     // 8 wavefronts it lies behind the rings, since a second row tile's Q arrives while they are in use.  With 4 wavefronts there is one
     // row tile, and the rings themselves serve: the four Q tiles fill stage 1 of K and V, which the first key tile does not touch, and
     // the output comes when all keys are done.  64 KB instead of 99 at 128 channels: two workgroups fit a unit.
+    // 65 to 96 channels in workgroups of 4 wavefronts: rows of 12 pieces, 48 KB, three workgroups a unit (items of 24..1600 rows over
+    // 512 keys, 16 heads of 72 34.7 us in rows of 16 pieces, 32.6 so; a ragged batch of 50..2700 rows, 16 / 8 89.4, 75.0).
+    // Up to 80 channels are five k-steps of Q K^T instead of six (the two 31.1 and 73.2 then; 8 x 4096, 16 heads of 72 831, 808).
     static constexpr int QW = 32 * PITCHB;
     static constexpr int WAREA = QW > 32 * OROW * 2 ? QW : 32 * OROW * 2;
     static constexpr bool IN_RINGS = WAVES == 4;
@@ -687,7 +691,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
         }
         // in registers before the area is written again
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (a.q_cs != nullptr) {
+        if (DP % 32 == 0 && a.q_cs != nullptr) {
             // Rotary embedding of the query row in registers: the lane holds elements 16 s + 8 half + j, and with
             // head_dim a multiple of 32 the partner of an element, head_dim / 2 further on, sits KSTEPS / 2
             // k-steps later in the same lane.  (cos, sin) of the row's 8 consecutive pairs come as four 16-byte loads.
@@ -1295,6 +1299,7 @@ template <int WAVES, bool RAGGED>
 static int launch_mfma_for(AttnArgs& a, hipStream_t s)
 {
     if (a.head_dim <= 64) return launch_mfma<64, WAVES, CIVIC_ATTN_STAGES, RAGGED>(a, s);
+    if (a.head_dim <= 80) return launch_mfma<80, WAVES, CIVIC_ATTN_STAGES, RAGGED>(a, s);
     if (a.head_dim <= 96) return launch_mfma<96, WAVES, CIVIC_ATTN_STAGES, RAGGED>(a, s);
     return launch_mfma<128, WAVES, CIVIC_ATTN_STAGES, RAGGED>(a, s);
 }

@@ -692,3 +692,29 @@ def test_attention_of_a_batch_is_that_of_its_samples(bd, case):
         ref = oracle.attention(*(t[:1].float().cpu().numpy() for t in (q, k, v)), causal)
         err = np.abs(whole[0][:1].float().cpu().numpy() - ref).max()
         assert err <= 2e-2 * max(1.0, np.abs(ref).max()), err
+
+
+@pytest.mark.parametrize("head_dim", [72, 80, 88, 96])
+@pytest.mark.parametrize("batch,n_q,n_kv,causal", [(1, 1, 1, True), (2, 33, 33, True), (1, 129, 129, True), (2, 40, 63, False), (3, 130, 65, False),
+                                                   (4, 700, 520, False)])
+def test_attention_heads_of_72_to_96(bd, head_dim, batch, n_q, n_kv, causal):
+    """Heads that are padded to 80 and to 96, in workgroups of 4 wavefronts (12 pieces a row in LDS) and of 8 (the last): nothing but
+    the head's own channels is read, as the rows lie in buffers of NaN, and every row is right.  Weights and output are rounded to
+    bf16, 2^-9 each, the row sums are of the rounded weights: 2^-7 of the largest value covers them."""
+    log("attention, heads of 72 to 96", head_dim, batch, n_q, n_kv, causal)
+    g = torch.Generator(device="cuda").manual_seed(head_dim + n_q)
+
+    def rows(n, heads):
+        x = torch.full((batch, n, heads, head_dim + 8), float("nan"), dtype=torch.bfloat16, device="cuda")[..., :head_dim]
+        return x.copy_(torch.randn(x.shape, generator=g, device="cuda"))
+
+    q, k, v = rows(n_q, 16), rows(n_kv, 16), rows(n_kv, 16)
+    out = bd.civic_prefill_attn(q, k, v, True) if causal else bd.civic_cross_attn(q, k, v)
+    if batch == 4:
+        assert bd.lib.civic_attn_workgroup(batch, n_q, n_kv, 16, 16, head_dim, 0) == 8
+    qq, kk, vv = (x.double().transpose(1, 2).contiguous() for x in (q, k, v))
+    z = torch.matmul(qq, kk.transpose(2, 3).contiguous()) / head_dim ** 0.5
+    if causal:
+        z.masked_fill_(torch.ones(n_q, n_kv, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    ref = torch.matmul(torch.softmax(z, -1), vv).transpose(1, 2)
+    assert (out.double() - ref).abs().max().item() <= 2.0 ** -7 * ref.abs().max().item()
