@@ -14,7 +14,7 @@
 //     summed over the row's lanes; every lane of the row then holds the row's logits.
 //   - Each (wavefront, row slot) runs its own online softmax over the rows it meets: no barrier and no LDS in
 //     the loop.  The lane keeps the 8 output channels of its chunk for every head in fp32.
-//   - At the end the 4 * 64 / LPR partial states of the workgroup meet, in registers and LDS; it writes the final
+//   - At the end the partial states of the workgroup's 4, 8 or 16 wavefronts meet, in registers and LDS; it writes the final
 //     rows (one split) or its (max, sum, unnormalised output) into the workspace, which a second small launch
 //     combines.
 #include <algorithm>
@@ -108,18 +108,19 @@ template <int LPR> __device__ __forceinline__ float slots_max(float v) { return 
 // States of the vector kernel's workgroup that meet in LDS: one per wavefront where a wavefront holds 8 row slots, one per slot
 // elsewhere.  Sums in registers take two lane swaps a value and halving of the slots, LDS one round trip a slot (21 x 16 rows, 8 / 8
 // bf16 heads of 64, 8 slots: 3.7 us in registers, 4.1 in LDS; 85 x 23 rows, 28 / 4 fp32 heads of 64, 4 slots: 7.7 and 6.9).
-constexpr int decode_states(int lpr) { return lpr == 8 ? kDecWaves : kDecWaves * (kWave / lpr); }
+constexpr int decode_states(int lpr, int waves) { return lpr == 8 || waves > kDecWaves ? waves : waves * (kWave / lpr); }
 
-template <bool BF16, int HG, int LPR, typename TABLE>
-__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs a, TABLE t)
+// WAVES: wavefronts of a workgroup (kDecWaves, or what decode_plan calls wide)
+template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
+__global__ __launch_bounds__(WAVES * kWave) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
     constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
     constexpr int E = BF16 ? 8 : 4;       // elements per 16-byte chunk
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int RPS = kWave / LPR;      // cache rows per wavefront instruction
-    constexpr int SLOTS = kDecWaves * RPS;   // independent softmax streams per workgroup
+    constexpr int SLOTS = WAVES * RPS;   // independent softmax streams per workgroup
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
-    constexpr int STATES = decode_states(LPR);
+    constexpr int STATES = decode_states(LPR, WAVES);
     // of every state that meets in LDS: [HG][d] outputs, [HG] maxima, [HG] sums
     float* sm_o = dec_lds;
     float* sm_m = dec_lds + STATES * HG * a.head_dim;
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
     const bool chunk_live = c < a.cpr;
-    const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
+    const int hb = blockIdx.y / a.n_kv_heads, g = blockIdx.y - hb * a.n_kv_heads;   // (passes over the same rows: on one XCD for 8 KV heads)
     const int d = a.head_dim;
     const int b = blockIdx.z, split = blockIdx.x;
     int n_ctx = a.n_ctx, n_splits = a.splits;
@@ -162,13 +163,13 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         for (int e = 0; e < E; ++e) acc[hh][e] = 0.f;
     }
 
-    // Round: the workgroup's next SLOTS * U rows; slot (w, r) takes rows key0 + (u * kDecWaves + w) * RPS + r.  The
+    // Round: the workgroup's next SLOTS * U rows; slot (w, r) takes rows key0 + (u * WAVES + w) * RPS + r.  The
     // loads of the next round are issued before the current one is computed.
     u32x4 kq[kDecU], vq[kDecU], kn[kDecU], vn[kDecU];
     auto fetch = [&](int key0, u32x4* kd, u32x4* vd) {
 #pragma unroll
         for (int u = 0; u < kDecU; ++u) {
-            const int key = key0 + (u * kDecWaves + w) * RPS + r;
+            const int key = key0 + (u * WAVES + w) * RPS + r;
             kd[u] = u32x4{0u, 0u, 0u, 0u};
             vd[u] = u32x4{0u, 0u, 0u, 0u};
             if (key < k1 && chunk_live) {
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         float s[kDecU][HG];
 #pragma unroll
         for (int u = 0; u < kDecU; ++u) {
-            const int key = key0 + (u * kDecWaves + w) * RPS + r;
+            const int key = key0 + (u * WAVES + w) * RPS + r;
 #pragma unroll
             for (int hh = 0; hh < HG; ++hh) {
                 float part = 0.f;
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 
     int state = w * RPS + r;
     bool writes = true;
-    if constexpr (STATES == kDecWaves) {                       // a wavefront's slots meet in registers first
+    if constexpr (STATES == WAVES) {                           // a wavefront's slots meet in registers first
 #pragma unroll
         for (int hh = 0; hh < HG; ++hh) {
             const float mw = slots_max<LPR>(m[hh]);
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
     // the workgroup's states meet in LDS
 #pragma unroll
     for (int hh = 0; hh < HG; ++hh) {
-        if constexpr (STATES == kDecWaves) writes = hh % RPS == r;   // (every slot holds the sums: slot r writes heads r, r + RPS, ...)
+        if constexpr (STATES == WAVES) writes = hh % RPS == r;   // (every slot holds the sums: slot r writes heads r, r + RPS, ...)
         if (writes && c == 0) { sm_m[state * HG + hh] = m[hh]; sm_l[state * HG + hh] = l[hh]; }
         if (writes && chunk_live) {
             float4* dst = reinterpret_cast<float4*>(sm_o + (state * HG + hh) * d + c * E);
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
         }
     }
     __syncthreads();
-    for (int i = tid; i < HG * d; i += kDecThreads) {
+    for (int i = tid; i < HG * d; i += WAVES * kWave) {
         const int hh = i / d, ch = i - hh * d;
         const int hg = hb * HG + hh;
         if (hg >= a.group) continue;
@@ -301,11 +302,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(DecodeArgs 
 // 10.6 -> 9.0; 16 x 2000 with 64 / 8 heads 43.8 -> 27.7, 32 x 2000 with 32 / 2 43.8 -> 19.6.  With one or two heads the vector
 // work is less than the gathering here (32 x 1000, 16 / 16 heads of 64: 22.5 there, 26.0 here; 8 x 1280, 16 / 8 heads 12.8, 13.8),
 // so those stay there.
-template <typename TABLE>
-__global__ __launch_bounds__(kDecThreads, 2) void decode_mfma_kernel(DecodeArgs a, TABLE tab)
+template <int WAVES, typename TABLE>
+__global__ __launch_bounds__(WAVES * kWave, 2) void decode_mfma_kernel(DecodeArgs a, TABLE tab)
 {
     constexpr bool RAGGED = std::is_same<TABLE, DecodeTable>::value;
-    constexpr int WAVES = kDecWaves, THREADS = kDecThreads, KT = 4;      // K chunks of 32 channels
+    constexpr int THREADS = WAVES * kWave, KT = 4;             // K chunks of 32 channels
     extern __shared__ __attribute__((aligned(16))) float dec_lds[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform for the compiler: loads take scalar base addresses)
@@ -622,6 +623,8 @@ __global__ __launch_bounds__(THREADS) void decode_merge_kernel(const float* __re
 struct DecodePlan {
     bool mfma;
     int hg, lpr, head_blocks, round_keys;
+    int waves;                           // of a workgroup: kDecWaves, or a wide one's
+    bool wide_heads, wide_short, wide_full;   // where wide workgroups are the faster way: one for each query head, contexts short or even
     int whole_keys;                      // contexts up to this are not cut
     // pieces of different contexts: whole samples from ragged_units pairs on; else no more than ragged_groups, or of ragged_keys rows
     int ragged_units, ragged_keys, ragged_groups;
@@ -629,6 +632,23 @@ struct DecodePlan {
     int32_t max_splits;                  // per sample, at most: what the workspace is sized for
     size_t ws_bytes, lds_bytes;
 };
+
+// Wavefronts of a wide workgroup: as many as the registers of a unit hold.
+static int decode_wide_waves(const DecodePlan& p) { return !p.mfma && p.hg <= 2 ? 16 : 8; }
+
+static size_t decode_lds(const DecodePlan& p, int32_t head_dim)
+{
+    return sizeof(float) * (p.mfma ? p.waves : decode_states(p.lpr, p.waves)) * static_cast<size_t>(p.hg) * (head_dim + 2);
+}
+
+static void go_wide(DecodePlan* p, int32_t longest, int32_t head_dim, int group)
+{
+    if (p->wide_heads) { p->mfma = false; p->hg = 1; p->head_blocks = group; }
+    p->waves = decode_wide_waves(*p);
+    p->splits = 1;
+    p->keys_per_split = longest;
+    p->lds_bytes = decode_lds(*p, head_dim);
+}
 
 static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int64_t n_ctx,
                        DecodePlan* p, bool ragged = false)
@@ -694,7 +714,23 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
         wanted = std::min<int64_t>(busy, (1024 + room_units - 1) / room_units);
     cut(wanted, round_keys, &p->splits, &p->keys_per_split);
     p->ws_bytes = p->max_splits > 1 ? sizeof(float) * static_cast<size_t>(batch) * n_q_heads * p->max_splits * (head_dim + 2) : 0;
-    p->lds_bytes = sizeof(float) * (p->mfma ? kDecWaves : decode_states(p->lpr)) * static_cast<size_t>(p->hg) * (head_dim + 2);
+    p->waves = kDecWaves;
+    p->lds_bytes = decode_lds(*p, head_dim);
+    // Wide workgroups and one split, where contexts would be cut (us, as it was and so):
+    //   - up to 256 query heads with three rounds of 16 wavefronts or less: a workgroup for each of them, which is bound by its
+    //     instructions and through before a second launch would have started; the group's reads meet in an L2 (1 x 469 rows, 16 / 8
+    //     heads of 128 10.6, 8.1; 4 x 700, 28 / 4 10.7, 8.7; 8 x 300, 32 / 8 of 64 in fp32 10.6, 7.4; but 1 x 1000, 32 / 8 10.4, 9.7 and
+    //     8 x 1000 11.5, 12.6).  With 4 or 8 heads on the vector units contexts need not be cut for that (1 x 130, 32 / 4 fp32 heads 11.9, 7.1).
+    //   - matrix cores, up to 128 pairs with 5 / 4 rounds of 8 wavefronts (16 x 300, 32 / 8 10.2, 8.5; 8 x 400 9.2, 10.2)
+    //   - 192 to 256 pairs up to 3072 rows: one such workgroup to a unit reads at its rate and nothing is left to combine (24 x 600 rows,
+    //     32 / 8 heads of 128 19.5, 14.4; 60 x 1200, 28 / 4 30.8, 26.7; 28 x 2400, 16 / 8 fp32 of 64 45.3, 43.2; 32 x 2400, 16 / 8 of 128
+    //     53.1, 51.1, but of 4000 85, 90; 160 pairs: 20 x 1200, 16 / 8 19.7, 20.7)
+    const bool cut_up = n_ctx > whole_keys;
+    p->wide_heads = static_cast<int64_t>(batch) * n_q_heads <= 256 && (cut_up || (p->hg > 2 && !p->mfma && n_ctx > round_keys)) &&
+                    n_ctx <= 3 * 16 * (kWave / p->lpr) * kDecU;
+    p->wide_short = p->wide_heads || (p->mfma && cut_up && units <= 128 && n_ctx <= 5 * 32 * 8 / 4);
+    p->wide_full = cut_up && units >= 192 && units <= 256 && n_ctx <= 3072;
+    if (!ragged && (p->wide_short || p->wide_full)) go_wide(p, static_cast<int32_t>(n_ctx), head_dim, group);
     return CIVIC_OK;
 }
 
@@ -710,11 +746,12 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
 //     10.1, 11.2), but no more than 512 of a single round of 32 rows.  (With 8 heads a pass 512 as well, and whole samples from
 //     384 pairs on only: 80 of 694..1388, 32 / 4 fp32 heads of 64 58 us, 69 in 1024 or whole.)
 // Never more pieces per sample than the workspace holds, max_splits.
-static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, DecodePlan* p)
+static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, int32_t head_dim, int group, DecodePlan* p)
 {
     int64_t rows = 0;
     int32_t longest = 0;
     for (int32_t i = 0; i < batch; ++i) { rows += ctx_of[i]; longest = std::max(longest, ctx_of[i]); }
+    if (p->wide_short || (p->wide_full && longest - rows / batch <= kDecTailKeys)) return go_wide(p, longest, head_dim, group);
     const int64_t per_sample = units / batch;
     int64_t kps = p->round_keys;
     if (longest <= p->whole_keys || (units >= p->ragged_units && longest - rows / batch <= kDecTailKeys)) kps = longest;
@@ -729,17 +766,26 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, Deco
     p->splits = static_cast<int32_t>((longest + kps - 1) / kps);
 }
 
-template <bool BF16, int HG, int LPR, typename TABLE>
-static int launch_decode_kernel(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
+template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
+static int launch_decode_waves(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
     const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
     if (p.lds_bytes > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
-        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(decode_partial_kernel<BF16, HG, LPR, TABLE>), p.lds_bytes, &allowed);
+        // (of the widest rows: the limit is set once for all launches of the instance)
+        constexpr size_t most = sizeof(float) * decode_states(LPR, WAVES) * HG * (LPR * (BF16 ? 8 : 4) + 2);
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(decode_partial_kernel<BF16, HG, LPR, WAVES, TABLE>), most, &allowed);
         if (rc != CIVIC_OK) return rc;
     }
-    civic::launch((decode_partial_kernel<BF16, HG, LPR, TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
+    civic::launch((decode_partial_kernel<BF16, HG, LPR, WAVES, TABLE>), grid, dim3(WAVES * kWave), p.lds_bytes, s, a, t);
     return check_launch();
+}
+
+template <bool BF16, int HG, int LPR, typename TABLE>
+static int launch_decode_kernel(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
+{
+    return p.waves == kDecWaves ? launch_decode_waves<BF16, HG, LPR, kDecWaves>(a, t, p, s)
+                                : launch_decode_waves<BF16, HG, LPR, HG <= 2 ? 16 : 8>(a, t, p, s);   // (decode_wide_waves)
 }
 
 template <bool BF16, int HG, typename TABLE>
@@ -761,9 +807,18 @@ static int launch_decode(const DecodeArgs& a, const TABLE& t, const DecodePlan& 
 {
     int rc;
     if (p.mfma) {
-        static_assert(sizeof(float) * kDecWaves * 16 * (128 + 2) <= 64 * 1024, "no launch needs more LDS than every launch may have");
         const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
-        civic::launch((decode_mfma_kernel<TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
+        if (p.waves == kDecWaves) {
+            static_assert(sizeof(float) * kDecWaves * 16 * (128 + 2) <= 64 * 1024, "no launch needs more LDS than every launch may have");
+            civic::launch((decode_mfma_kernel<kDecWaves, TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
+        } else {
+            if (p.lds_bytes > 64 * 1024) {
+                static std::atomic<uint64_t> allowed{0};
+                rc = allow_dynamic_lds(reinterpret_cast<const void*>(decode_mfma_kernel<8, TABLE>), sizeof(float) * 8 * 16 * (128 + 2), &allowed);
+                if (rc != CIVIC_OK) return rc;
+            }
+            civic::launch((decode_mfma_kernel<8, TABLE>), grid, dim3(8 * kWave), p.lds_bytes, s, a, t);
+        }
         rc = check_launch();
     } else switch (p.hg) {
         case 1: rc = launch_decode_lpr<BF16, 1>(a, t, p, s); break;
@@ -799,7 +854,8 @@ static int decode_attn(const void* q, const void* k_cache, const void* v_cache, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!ctx_of) return dtype == CIVIC_BF16 ? launch_decode<true>(a, NoTable{}, p, s) : launch_decode<false>(a, NoTable{}, p, s);
     DecodePlan pr = p;
-    cut_ragged(ctx_of, batch, static_cast<int64_t>(batch) * n_kv_heads * p.head_blocks, &pr);
+    cut_ragged(ctx_of, batch, static_cast<int64_t>(batch) * n_kv_heads * p.head_blocks, head_dim, a.group, &pr);
+    a.head_blocks = pr.head_blocks;
     a.keys_per_split = pr.keys_per_split;
     a.splits = pr.splits;
     DecodeTable t;

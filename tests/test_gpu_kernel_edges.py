@@ -445,6 +445,24 @@ def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
         assert err <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(ref.abs().max())), err
 
 
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", [
+    (1, 16, 8, 128, [257], "bf16"), (1, 16, 8, 128, [768], "bf16"), (1, 16, 8, 128, [769], "bf16"),         # three rounds of 16 wavefronts
+    (8, 32, 8, 128, [300], "bf16"), (9, 32, 8, 128, [300], "bf16"), (1, 9, 1, 128, [20, ], "fp32"), (1, 9, 1, 128, [33], "fp32"),  # 256 heads
+    (3, 6, 6, 72, [300, 257, 1], "bf16"), (2, 2, 1, 64, [900, 1024], "bf16"), (1, 2, 1, 256, [200], "bf16"), (2, 2, 2, 512, [100, 64], "bf16"),
+    (2, 8, 4, 128, [256], "fp32"), (2, 8, 4, 128, [257, 129], "fp32"), (2, 3, 3, 32, [1000, 513], "fp32"),   # eight lanes a row
+    (2, 8, 2, 64, [250, 256], "fp32"), (2, 9, 1, 64, [255], "fp32"), (1, 16, 2, 256, [63], "fp32"),           # 8 wavefronts, 4 and 8 heads
+    (2, 16, 1, 512, [33, 20], "bf16"), (1, 4, 1, 200, [120], "bf16"),
+    (4, 28, 4, 128, [300, 320, 257, 1], "bf16"), (1, 32, 2, 128, [320], "bf16"), (1, 17, 1, 64, [257], "bf16"), (1, 32, 8, 96, [321], "bf16"),
+    (96, 2, 1, 64, [600], "bf16"), (97, 2, 1, 64, [600], "bf16"), (24, 16, 4, 64, [300], "bf16"), (25, 16, 4, 64, [300], "bf16"),  # 96 pairs
+    (24, 32, 8, 64, [600], "bf16"), (32, 16, 8, 64, [700], "bf16"), (33, 16, 8, 64, [700], "bf16"), (191, 4, 1, 64, [300], "bf16"),   # 192 to 256
+    (28, 16, 8, 64, [3072], "fp32"), (28, 16, 8, 64, [3073], "fp32"), (48, 8, 4, 64, [600 + 9 * i for i in range(48)], "bf16"),
+    (48, 8, 4, 64, [60 + 25 * i for i in range(48)], "bf16"), (60, 16, 4, 128, [300], "fp32")])
+def test_decode_wide_workgroups(bd, batch, hq, hkv, d, ctx, dtype):
+    """Workgroups of 8 and of 16 wavefronts and the rule that takes them, on both sides of its edges, one length for all samples and one
+    each.  Checks and bars of test_decode_cuts_of_either_kernel."""
+    test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx * batch if len(ctx) == 1 else ctx, dtype)
+
+
 @pytest.mark.parametrize("case", [
     # batch, grid (frames, height, width, cell, cell, cell floor, frame floor, budget), text before / between / behind, dim, rows
     (1, (1, 1, 1, 4, 4, 1, 0, 1), 0, 0, 0, 8, "random"),          # one token, one vector a row
