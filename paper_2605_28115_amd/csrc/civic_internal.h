@@ -110,6 +110,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename T>
 __device__ __forceinline__ T load_streaming(const T* p) { return __builtin_nontemporal_load(p); }
+template <typename T>
+__device__ __forceinline__ void store_streaming(T* p, const T& v) { __builtin_nontemporal_store(v, p); }
 
 // Sum over the 64 lanes of a wavefront, returned in every lane.  Data-parallel-primitive (DPP) adds:
 // an inclusive scan inside each row of 16 lanes (row_shr 1, 2, 4, 8), then the row totals are carried
