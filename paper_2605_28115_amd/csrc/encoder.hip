@@ -62,6 +62,8 @@ struct GemmArgs {
     // partial row sums [batch][parts][part_pitch], written by kOutExp (parts = 2 * its tiles_n), read by kOutRowNorm
     float* row_part; int32_t parts; int64_t part_pitch;
     float* row_inv;                    // kOutRowNorm: one over the sum of every A row, written when not null, [batch x m]
+    // kOutRowNorm: workgroups behind the tiles' that make the token weights, each `sum_chunks` times 64 columns of a batch item (0: none)
+    float* col_sum; int32_t sum_groups, sum_chunks;
 };
 
 template <int LDS_IMM>
@@ -117,6 +119,105 @@ constexpr float kExpShift = 15.3f, kMaxDirectInvTau = 60.0f;
 // 2^-40 then; never at inv_tau <= 17, and above only for an anchor that every token points away from).
 constexpr float kMaxRowFactor = 1.0995116e12f;
 
+// Token weights by workgroups of the second product's launch, on units that its tiles leave idle: column j's sum over the rows i of
+// w(i, j) / sum_i, for `sum_chunks` times 64 columns.  The rows' factors first, from the partial sums as the tiles take them; then the
+// columns, in the order of col_sum_kernel (128 row slots, of which a thread has every 32nd here): the same bits as from that kernel.
+// (2 x 4096 tokens, 1365 anchors: a launch of 6.8 us behind the product's 33 on 198 units; here under it.)
+// Sum over the eight lanes 8 apart: x + x of lane ^ 8, ^ 16, ^ 32, one after the other (a sum does not depend on whose comes first).
+__device__ __forceinline__ float over_row_slots(float v)
+{
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+constexpr int kSumGroupRows = 24 * 1024;                      // (a multiple of 4) rows whose factors fit beside the rest of the LDS
+__device__ __forceinline__ void col_sum_group(const GemmArgs& g, uint32_t group, char* smem)
+{
+    constexpr int kVirtual = 16, kCols = 64, kSlots = 128, kMine = 4;
+    float* const inv = reinterpret_cast<float*>(smem);
+    float* const part = inv + kSumGroupRows;                  // [kVirtual][kCols]
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
+    const int32_t chunks = (g.kb_rows + kCols - 1) / kCols, per_item = (chunks + g.sum_chunks - 1) / g.sum_chunks;
+    const int64_t b = group / static_cast<uint32_t>(per_item);
+    const int32_t first = static_cast<int32_t>(group - b * per_item) * g.sum_chunks, last = min(first + g.sum_chunks, chunks);
+    for (int r = 4 * tid; r < g.m; r += 4 * kGemmThreads) {   // (rows up to whole tiles are there: m <= part_pitch, a multiple of 128)
+        const enc_f32x4* const src = reinterpret_cast<const enc_f32x4*>(g.row_part + b * g.parts * g.part_pitch + r);
+        enc_f32x4 t[2] = {enc_f32x4{0.f, 0.f, 0.f, 0.f}, enc_f32x4{0.f, 0.f, 0.f, 0.f}};
+        const int64_t pitch = g.part_pitch / 4;
+        constexpr int kAhead = 16;                            // pairs of parts in flight
+        for (int x0 = 0; x0 < g.parts; x0 += 2 * kAhead) {    // (an even number of parts; past the last the last pair again, not added)
+            enc_f32x4 v[2 * kAhead];
+#pragma unroll
+            for (int x = 0; x < 2 * kAhead; ++x) v[x] = src[min(x0 + x, g.parts - 2 + (x & 1)) * pitch];
+#pragma unroll
+            for (int x = 0; x < 2 * kAhead; ++x)
+                if (x0 + x < g.parts) t[x & 1] += v[x];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inv[r + e] = 1.0f / (t[0][e] + t[1][e]);
+    }
+    __syncthreads();
+    const int c = tid & 7, slot = tid >> 3;
+    for (int32_t chunk = first; chunk < last; ++chunk) {
+        const char* const src = reinterpret_cast<const char*>(g.a + b * g.sa + chunk * kCols + 8 * c);
+        float acc[kMine][8];
+#pragma unroll
+        for (int u = 0; u < kMine; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[u][e] = 0.f;
+        auto add = [&](int u, const u32x4& v, float f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[u][2 * e] = fmaf(__uint_as_float(v[e] << 16), f, acc[u][2 * e]);
+                acc[u][2 * e + 1] = fmaf(__uint_as_float(v[e] & 0xFFFF0000u), f, acc[u][2 * e + 1]);
+            }
+        };
+        constexpr int kDeep = 6;                              // rows of a slot in flight: 24 loads of 16 bytes a lane
+        int r0 = slot;
+        for (; r0 - slot + kDeep * kSlots <= g.m; r0 += kDeep * kSlots) {
+            u32x4 v[kDeep][kMine];
+#pragma unroll
+            for (int x = 0; x < kDeep; ++x)
+#pragma unroll
+                for (int u = 0; u < kMine; ++u) v[x][u] = *reinterpret_cast<const u32x4*>(src + (r0 + x * kSlots + 32 * u) * g.lda * 2);
+#pragma unroll
+            for (int x = 0; x < kDeep; ++x)
+#pragma unroll
+                for (int u = 0; u < kMine; ++u) add(u, v[x][u], inv[r0 + x * kSlots + 32 * u]);
+        }
+        if (r0 - slot < g.m) {                                // fewer are left: a row past the last re-reads it and is not added
+            u32x4 v[kDeep][kMine];
+#pragma unroll
+            for (int x = 0; x < kDeep; ++x)
+#pragma unroll
+                for (int u = 0; u < kMine; ++u) v[x][u] = *reinterpret_cast<const u32x4*>(src + min(r0 + x * kSlots + 32 * u, g.m - 1) * g.lda * 2);
+#pragma unroll
+            for (int x = 0; x < kDeep; ++x)
+#pragma unroll
+                for (int u = 0; u < kMine; ++u)
+                    if (r0 + x * kSlots + 32 * u < g.m) add(u, v[x][u], inv[r0 + x * kSlots + 32 * u]);
+        }
+        __syncthreads();                                      // the sums of the chunk before have been read
+#pragma unroll
+        for (int u = 0; u < kMine; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                acc[u][e] = over_row_slots(acc[u][e]);
+                if (lane < 8) part[(w + 4 * u) * kCols + 8 * lane + e] = acc[u][e];
+            }
+        __syncthreads();
+        const int j = chunk * kCols + tid;
+        if (tid < kCols && j < g.kb_rows) {
+            float t = 0.f;
+#pragma unroll
+            for (int x = 0; x < kVirtual; ++x) t += part[x * kCols + tid];
+            g.col_sum[b * g.kb_rows + j] = t;
+        }
+    }
+}
+
 // C = A B^T in the form OUT.  A is stored [m x k] (contraction index contiguous).  B_KROWS = false: B stored [n x k], the same
 // way.  B_KROWS = true: B stored [k x n], contraction index as the row index - the layout of X_0 in Z_0 = W_A X_0 and of
 // K, V in Eq. 9; its tiles (64 contraction rows x 128 columns, 256-byte pitch) are read with the transposing LDS read,
@@ -140,7 +241,11 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
     // that run is a compact block whose A row slabs and B column slabs are shared inside one L2 as the workgroups
     // advance along the contraction together.  With the plain (x, y) numbering every XCD touches every slab and the
     // kernel runs at the speed of the memory behind the L2s.
-    const uint32_t per_xcd = gridDim.x >> 3;
+    const uint32_t tile_blocks = gridDim.x - static_cast<uint32_t>(OUT == kOutRowNorm ? g.sum_groups : 0);
+    if constexpr (OUT == kOutRowNorm) {
+        if (blockIdx.x >= tile_blocks) { col_sum_group(g, blockIdx.x - tile_blocks, gemm_lds); return; }
+    }
+    const uint32_t per_xcd = tile_blocks >> 3;
     const uint32_t tile = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (tile >= static_cast<uint32_t>(g.total_tiles)) return;        // (the grid is padded to a multiple of 8)
     const uint32_t per_mat = static_cast<uint32_t>(g.tiles_m) * g.tiles_n;
@@ -471,7 +576,7 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
 template <int OUT, bool B_KROWS, int STAGES>
 static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s)
 {
-    const dim3 grid(blocks);
+    const dim3 grid(blocks + static_cast<unsigned>(OUT == kOutRowNorm ? g.sum_groups : 0));
     constexpr size_t lds = 2 * STAGES * kGemmTileBytes;
     static_assert(lds >= 4 * 64 * (64 + 8) * 2 + 1024, "the ring holds the staged output tile and the row sums");
     static std::atomic<uint64_t> allowed{0};
@@ -479,6 +584,24 @@ static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s
     if (rc != CIVIC_OK) return rc;
     civic::launch((gemm_kernel<OUT, B_KROWS, STAGES>), grid, dim3(kGemmThreads), lds, s, g);
     return check_launch();
+}
+
+// Whether the token weights go into the second product's launch, and their share of it: its tiles run one to a unit and leave units
+// idle (in their only generation or in the second), and those are through with the columns when the tiles are with their rows, or
+// nearly so.  In us, as measured: 0.52 for 64 tokens of a tile, 60 KB of partial row sums and 50 of weights read by a unit.
+static bool sums_fit(GemmArgs* g, int64_t batch)
+{
+    const int64_t total = batch * ((g->m + kGemmBM - 1) / kGemmBM) * ((g->n + kGemmBN - 1) / kGemmBN);
+    const int64_t idle = (total <= 256 ? 256 : 512) - (total + 7) / 8 * 8, chunks = (g->kb_rows + 63) / 64;
+    if (idle <= 0 || g->m > kSumGroupRows) return false;
+    int64_t each = std::max<int64_t>((chunks * batch + idle - 1) / idle, 1);
+    while ((chunks + each - 1) / each * batch > idle && each < chunks) ++each;
+    const int64_t groups = (chunks + each - 1) / each * batch, rounds = (groups + idle - 1) / idle;
+    const double rows = 1.5 + g->m * static_cast<double>(g->parts) * 4.0 / 60e3, columns = 1.0 + g->m * 128.0 / 50e3;
+    if (static_cast<double>(rounds) * (rows + static_cast<double>(each) * columns) > 0.52 * (g->k / 64) + 6.0) return false;
+    g->sum_chunks = static_cast<int32_t>(each);
+    g->sum_groups = static_cast<int32_t>(groups);
+    return true;
 }
 
 // `batch` batch items.  B_KROWS: B is stored [k x n].
@@ -1186,6 +1309,7 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
     g1.sa = 0; g1.sb = static_cast<int64_t>(n_tokens) * dim; g1.sc = static_cast<int64_t>(n_anchors) * p.t_pad;
     g1.m = n_anchors; g1.n = n_tokens; g1.k = dim; g1.alpha = inv_tau;
     g1.col_stats = stats; g1.col_pitch = p.t_tile; g1.row_sum = qa_sum; g1.row_inv = nullptr;
+    g1.col_sum = nullptr; g1.sum_groups = 0; g1.sum_chunks = 0;
     g1.row_part = row_part; g1.parts = static_cast<int32_t>(p.t_tile / kGemmBN * 2); g1.part_pitch = p.m_tile;
     // Z_0 = W_A X_0, X_0 read where it lies (tokens are its rows: the contraction index is the row index)
     GemmArgs g2;
@@ -1194,6 +1318,7 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
     g2.sa = static_cast<int64_t>(n_anchors) * p.t_pad; g2.sb = static_cast<int64_t>(n_tokens) * dim; g2.sc = static_cast<int64_t>(n_anchors) * dim;
     g2.m = n_anchors; g2.n = dim; g2.k = static_cast<int32_t>(p.t_pad); g2.kb_rows = n_tokens; g2.alpha = 1.0f;
     g2.col_stats = nullptr; g2.col_pitch = 0; g2.row_sum = nullptr; g2.row_inv = nullptr;
+    g2.col_sum = nullptr; g2.sum_groups = 0; g2.sum_chunks = 0;
     g2.row_part = row_part; g2.parts = g1.parts; g2.part_pitch = g1.part_pitch;
     auto token_weights = [&](const float* row_scale) {
         civic::launch(col_sum_kernel, dim3(static_cast<unsigned>((n_tokens + kColSumCols - 1) / kColSumCols), static_cast<unsigned>(batch)),
@@ -1207,9 +1332,11 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
         g1.c = pw;
         rc = launch_gemm<kOutExp, false>(g1, batch, s);
         if (rc != CIVIC_OK) return rc;
-        g2.row_inv = token_weight ? row_inv : nullptr;
+        const bool with_sums = token_weight && sums_fit(&g2, batch);
+        g2.col_sum = with_sums ? token_weight : nullptr;
+        g2.row_inv = token_weight && !with_sums ? row_inv : nullptr;
         rc = launch_gemm<kOutRowNorm, true>(g2, batch, s);
-        if (rc != CIVIC_OK || !token_weight) return rc;
+        if (rc != CIVIC_OK || !token_weight || with_sums) return rc;
         return token_weights(row_inv);
     }
     // Colder softmaxes need their row's maximum: logits in fp32, a softmax over their rows into bf16 weights (zero in the
@@ -1283,7 +1410,7 @@ extern "C" int civic_kv_compress(const void* k, const void* v, int dtype, const 
     rc = check_launch();
     if (rc != CIVIC_OK) return rc;
     GemmArgs g;
-    g.col_stats = nullptr; g.col_pitch = 0; g.row_sum = nullptr; g.row_inv = nullptr; g.row_part = nullptr; g.parts = 0; g.part_pitch = 0;
+    g.col_stats = nullptr; g.col_pitch = 0; g.row_sum = nullptr; g.row_inv = nullptr; g.row_part = nullptr; g.parts = 0; g.part_pitch = 0; g.col_sum = nullptr; g.sum_groups = 0; g.sum_chunks = 0;
     g.a = rt; g.lda = p.m_pad; g.ldc = width;
     g.sa = 0; g.sc = static_cast<int64_t>(n_mem) * width;
     g.m = n_mem; g.n = width; g.k = static_cast<int32_t>(p.m_pad); g.alpha = 1.0f;

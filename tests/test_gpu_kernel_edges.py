@@ -142,6 +142,29 @@ def test_anchor_aggregate_over_the_range_of_the_tokens(bd, tokens, anchors, dim,
     assert (np.abs(to_host(tw).astype(np.float64) - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all()
 
 
+@pytest.mark.parametrize("tokens,anchors", [(1, 1), (64, 5), (65, 127), (700, 129), (193, 767), (300, 768), (129, 769), (2500, 100), (130, 1665), (4100, 40)])
+def test_token_weights_under_the_second_product(bd, tokens, anchors):
+    """Token weights made by workgroups of the second product's launch (one item) and by a launch of their own (so many items that the
+    product fills the chip twice): the same bits, and the sums of the weights of a 64-bit softmax.  Weights are rounded to bf16 (2^-9
+    each, sums of them as rounded) and logits carry the rounding of the normalised anchors, 2^-9 of at most 14: 2^-5 covers them."""
+    log("token weights", tokens, anchors)
+    dim = 128
+    items = 512 // (-(-anchors // 128) * (dim // 128)) + 1
+    g = torch.Generator(device="cuda").manual_seed(tokens + anchors)
+    x0 = torch.randn((1, tokens, dim), generator=g, device="cuda").bfloat16()
+    a = torch.randn((anchors, dim), generator=g, device="cuda").bfloat16()
+    z1, w1 = bd.civic_anchor_aggregate(x0, a, 14.0, True)
+    zn, wn = bd.civic_anchor_aggregate(x0.expand(items, tokens, dim).contiguous(), a, 14.0, True)
+    assert torch.equal(zn[items - 1], z1[0]) and torch.equal(wn[items - 1], w1[0]) and torch.equal(wn[0], w1[0])
+
+    def norm(x):
+        x = x.double() - x.double().mean(-1, keepdim=True)
+        return x / x.norm(dim=-1, keepdim=True)
+
+    ref = torch.softmax(14.0 * norm(a) @ norm(x0[0]).T.contiguous(), -1).sum(0)
+    assert (w1[0].double() - ref).abs().max().item() <= 2.0 ** -5 * ref.max().item()
+
+
 @pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 161])
 @pytest.mark.parametrize("dtype,head_dim", [("fp32", 8), ("fp32", 64), ("fp32", 72), ("fp32", 128), ("fp32", 136), ("fp32", 192),
                                             ("fp32", 256), ("bf16", 136), ("bf16", 192), ("bf16", 256)])
