@@ -40,6 +40,7 @@ struct DecodeArgs {
     int64_t s_max;
     int32_t batch, n_q_heads, n_kv_heads, head_dim, group, head_blocks;
     int32_t n_ctx, splits, keys_per_split;
+    int32_t heads_first;                  // grid order (decode_grid)
     int32_t cpr;                          // 16-byte chunks per cache row
     float scale_log2;                     // softmax scale * log2(e)
 };
@@ -111,6 +112,21 @@ template <int LPR> __device__ __forceinline__ float slots_max(float v) { return 
 constexpr int decode_states(int lpr, int waves) { return lpr == 8 || waves > kDecWaves ? waves : waves * (kWave / lpr); }
 
 // WAVES: wavefronts of a workgroup (kDecWaves, or what decode_plan calls wide)
+// A workgroup's place: block of query heads, KV head, sample, split.
+struct DecodePlace { int hb, g, b, split; };
+__device__ __forceinline__ DecodePlace decode_place(const DecodeArgs& a)
+{
+    DecodePlace p;
+    if (a.heads_first) {
+        p.hb = blockIdx.x / a.n_kv_heads; p.g = blockIdx.x - p.hb * a.n_kv_heads;
+        p.b = blockIdx.y; p.split = blockIdx.z;
+    } else {
+        p.hb = blockIdx.y / a.n_kv_heads; p.g = blockIdx.y - p.hb * a.n_kv_heads;
+        p.b = blockIdx.z; p.split = blockIdx.x;
+    }
+    return p;
+}
+
 template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
 __global__ __launch_bounds__(WAVES * kWave) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
@@ -129,9 +145,10 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_partial_kernel(DecodeArg
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
     const bool chunk_live = c < a.cpr;
-    const int hb = blockIdx.y / a.n_kv_heads, g = blockIdx.y - hb * a.n_kv_heads;   // (passes over the same rows: on one XCD for 8 KV heads)
+    const DecodePlace at = decode_place(a);
+    const int hb = at.hb, g = at.g;
     const int d = a.head_dim;
-    const int b = blockIdx.z, split = blockIdx.x;
+    const int b = at.b, split = at.split;
     int n_ctx = a.n_ctx, n_splits = a.splits;
     if constexpr (RAGGED) {
         n_ctx = t.ctx[b];
@@ -311,8 +328,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void decode_mfma_kernel(DecodeArg
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform for the compiler: loads take scalar base addresses)
     const int l16 = lane & 15, kq = lane >> 4;
-    const int g = blockIdx.y / a.head_blocks, hb = blockIdx.y - g * a.head_blocks;
-    const int b = blockIdx.z, split = blockIdx.x, d = a.head_dim;
+    const DecodePlace place = decode_place(a);
+    const int hb = place.hb, g = place.g, b = place.b, split = place.split, d = a.head_dim;
     int n_ctx = a.n_ctx, n_splits = a.splits;
     if constexpr (RAGGED) {
         n_ctx = tab.ctx[b];
@@ -703,7 +720,7 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     p->whole_keys = static_cast<int>(whole_keys);
     // The vector kernel with 4 or 8 heads a pass is bound by its instructions and takes more workgroups per unit: 4 splits (74 x 968
     // rows, 16 / 4 fp32 heads of 96: 63 us in one, 49 in four; 22 x 392, 32 / 8 of 128: 22.5 in two, 21.3 in four), or 8 where
-    // several passes read the same rows, which then run on one XCD (grid x a multiple of 8) and share its L2 (24 x 2500, 28 / 4
+    // several passes read the same rows, which then run on one XCD (decode_heads_first) and share its L2 (24 x 2500, 28 / 4
     // of 128: 93 us in two, 65 in eight).  As long as a split is two rounds, and the workspace has the room.
     int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
     // The same 4 where the matrix cores would run one workgroup on most units and two on some through a long context (80 x 2918
@@ -766,10 +783,24 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, int3
     p->splits = static_cast<int32_t>((longest + kps - 1) / kps);
 }
 
+// Order of the workgroups.  The hardware hands consecutive ones to the eight XCDs in turn.  With the splits innermost a power of two of
+// them puts every sample's last pieces on the same XCDs, and of samples of different length these are the ones that are not there: the
+// other XCDs get more of the work (24 samples of 100..2000 rows, 32 / 8 heads of 128 38.9 us, 27.5 with the heads innermost; 80 of
+// 60..4000, 28 / 4 99.7, 69.8; 24 of 100..2000, 16 / 8 fp32 51.9, 39.2; 64 of 117..3584, 32 / 8 91.7, 90.1).  Where several passes read the
+// same rows the splits stay innermost: a power of two of them keeps the passes on one XCD, where they share its L2 (40 x 1000, 28 / 4
+// fp32 heads of 128 52.0, 68.9 with the heads innermost; 40 of 500..1500 55.2, 63.5).
+static bool decode_heads_first(const DecodePlan& p) { return p.head_blocks == 1 && p.splits > 1; }
+
+static dim3 decode_grid(const DecodeArgs& a, const DecodePlan& p)
+{
+    const unsigned heads = static_cast<unsigned>(a.n_kv_heads * p.head_blocks), batch = static_cast<unsigned>(a.batch), splits = static_cast<unsigned>(p.splits);
+    return a.heads_first ? dim3(heads, batch, splits) : dim3(splits, heads, batch);
+}
+
 template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
 static int launch_decode_waves(const DecodeArgs& a, const TABLE& t, const DecodePlan& p, hipStream_t s)
 {
-    const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
+    const dim3 grid = decode_grid(a, p);
     if (p.lds_bytes > 64 * 1024) {
         static std::atomic<uint64_t> allowed{0};
         // (of the widest rows: the limit is set once for all launches of the instance)
@@ -807,7 +838,7 @@ static int launch_decode(const DecodeArgs& a, const TABLE& t, const DecodePlan& 
 {
     int rc;
     if (p.mfma) {
-        const dim3 grid(static_cast<unsigned>(p.splits), static_cast<unsigned>(a.n_kv_heads * p.head_blocks), static_cast<unsigned>(a.batch));
+        const dim3 grid = decode_grid(a, p);
         if (p.waves == kDecWaves) {
             static_assert(sizeof(float) * kDecWaves * 16 * (128 + 2) <= 64 * 1024, "no launch needs more LDS than every launch may have");
             civic::launch((decode_mfma_kernel<kDecWaves, TABLE>), grid, dim3(kDecThreads), p.lds_bytes, s, a, t);
@@ -852,10 +883,12 @@ static int decode_attn(const void* q, const void* k_cache, const void* v_cache, 
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt(static_cast<float>(head_dim));
     a.scale_log2 = scale * 1.4426950408889634f;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    a.heads_first = decode_heads_first(p);
     if (!ctx_of) return dtype == CIVIC_BF16 ? launch_decode<true>(a, NoTable{}, p, s) : launch_decode<false>(a, NoTable{}, p, s);
     DecodePlan pr = p;
     cut_ragged(ctx_of, batch, static_cast<int64_t>(batch) * n_kv_heads * p.head_blocks, head_dim, a.group, &pr);
     a.head_blocks = pr.head_blocks;
+    a.heads_first = decode_heads_first(pr);
     a.keys_per_split = pr.keys_per_split;
     a.splits = pr.splits;
     DecodeTable t;

@@ -478,6 +478,7 @@ def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
     (4, 28, 4, 128, [300, 320, 257, 1], "bf16"), (1, 32, 2, 128, [320], "bf16"), (1, 17, 1, 64, [257], "bf16"), (1, 32, 8, 96, [321], "bf16"),
     (96, 2, 1, 64, [600], "bf16"), (97, 2, 1, 64, [600], "bf16"), (24, 16, 4, 64, [300], "bf16"), (25, 16, 4, 64, [300], "bf16"),  # 96 pairs
     (24, 32, 8, 64, [600], "bf16"), (32, 16, 8, 64, [700], "bf16"), (33, 16, 8, 64, [700], "bf16"), (191, 4, 1, 64, [300], "bf16"),   # 192 to 256
+    (5, 32, 8, 64, [40, 2000, 700, 1, 1024], "bf16"), (3, 40, 2, 64, [900, 1, 513], "bf16"), (4, 28, 4, 64, [1500, 800, 3, 40], "fp32"),  # cut: order
     (28, 16, 8, 64, [3072], "fp32"), (28, 16, 8, 64, [3073], "fp32"), (48, 8, 4, 64, [600 + 9 * i for i in range(48)], "bf16"),
     (48, 8, 4, 64, [60 + 25 * i for i in range(48)], "bf16"), (60, 16, 4, 128, [300], "fp32")])
 def test_decode_wide_workgroups(bd, batch, hq, hkv, d, ctx, dtype):
