@@ -114,12 +114,15 @@ constexpr int decode_states(int lpr, int waves) { return lpr == 8 || waves > kDe
 // WAVES: wavefronts of a workgroup (kDecWaves, or what decode_plan calls wide)
 // A workgroup's place: block of query heads, KV head, sample, split.
 struct DecodePlace { int hb, g, b, split; };
+template <bool RAGGED>
 __device__ __forceinline__ DecodePlace decode_place(const DecodeArgs& a)
 {
     DecodePlace p;
     if (a.heads_first) {
         p.hb = blockIdx.x / a.n_kv_heads; p.g = blockIdx.x - p.hb * a.n_kv_heads;
-        p.b = blockIdx.y; p.split = blockIdx.z;
+        p.b = blockIdx.z; p.split = blockIdx.y;
+        if constexpr (RAGGED)
+            if ((a.splits & 1) == 0) p.split = (p.split + p.b + (p.b >> 2) + (p.b >> 3)) % a.splits;
     } else {
         p.hb = blockIdx.y / a.n_kv_heads; p.g = blockIdx.y - p.hb * a.n_kv_heads;
         p.b = blockIdx.z; p.split = blockIdx.x;
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(WAVES * kWave) void decode_partial_kernel(DecodeArg
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int r = lane / LPR, c = lane % LPR;
     const bool chunk_live = c < a.cpr;
-    const DecodePlace at = decode_place(a);
+    const DecodePlace at = decode_place<RAGGED>(a);
     const int hb = at.hb, g = at.g;
     const int d = a.head_dim;
     const int b = at.b, split = at.split;
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void decode_mfma_kernel(DecodeArg
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform for the compiler: loads take scalar base addresses)
     const int l16 = lane & 15, kq = lane >> 4;
-    const DecodePlace place = decode_place(a);
+    const DecodePlace place = decode_place<RAGGED>(a);
     const int hb = place.hb, g = place.g, b = place.b, split = place.split, d = a.head_dim;
     int n_ctx = a.n_ctx, n_splits = a.splits;
     if constexpr (RAGGED) {
@@ -783,18 +786,22 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, int3
     p->splits = static_cast<int32_t>((longest + kps - 1) / kps);
 }
 
-// Order of the workgroups.  The hardware hands consecutive ones to the eight XCDs in turn.  With the splits innermost a power of two of
-// them puts every sample's last pieces on the same XCDs, and of samples of different length these are the ones that are not there: the
-// other XCDs get more of the work (24 samples of 100..2000 rows, 32 / 8 heads of 128 38.9 us, 27.5 with the heads innermost; 80 of
-// 60..4000, 28 / 4 99.7, 69.8; 24 of 100..2000, 16 / 8 fp32 51.9, 39.2; 64 of 117..3584, 32 / 8 91.7, 90.1).  Where several passes read the
-// same rows the splits stay innermost: a power of two of them keeps the passes on one XCD, where they share its L2 (40 x 1000, 28 / 4
-// fp32 heads of 128 52.0, 68.9 with the heads innermost; 40 of 500..1500 55.2, 63.5).
+// Order of the workgroups.  The hardware hands consecutive ones to the eight XCDs in turn, and an XCD's to its units.  With the splits
+// innermost an even number of them puts the last pieces of all samples on the same XCDs, and of samples of different length these are
+// the ones that do not exist: the other XCDs have more of the work.  So the heads are innermost, then the splits; and since 32 units
+// would see the same split of every few samples where their number is even, each sample begins with another one then (us, splits
+// innermost, heads innermost, and with a split of its own: 24 samples of 100..2000 rows, 32 / 8 heads of 128 38.9, 38.0, 27.2; 80 of
+// 60..4000, 28 / 4 99.8, 96.9, 71.0; 24 of 100..2000, 16 / 8 fp32 51.5, 41.2, 39.2; five splits, 40 of 85..2500 48.0, 47.3, 50.5; seven, 64 of
+// 117..3584 91.6, 89.1, 90.6).  The samples outermost: with the splits there a first pass over caches that were not touched before took
+// 132 us instead of 119 (64 of 117..3584).
+// Where several passes read the same rows the splits stay innermost: a power of two of them keeps the passes on one XCD, where they
+// share its L2 (40 x 1000, 28 / 4 fp32 heads of 128 52.0, 68.9 with the heads innermost; 40 of 500..1500 55.2, 63.5).
 static bool decode_heads_first(const DecodePlan& p) { return p.head_blocks == 1 && p.splits > 1; }
 
 static dim3 decode_grid(const DecodeArgs& a, const DecodePlan& p)
 {
     const unsigned heads = static_cast<unsigned>(a.n_kv_heads * p.head_blocks), batch = static_cast<unsigned>(a.batch), splits = static_cast<unsigned>(p.splits);
-    return a.heads_first ? dim3(heads, batch, splits) : dim3(splits, heads, batch);
+    return a.heads_first ? dim3(heads, splits, batch) : dim3(splits, heads, batch);
 }
 
 template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
