@@ -561,8 +561,14 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     const uint32_t bid = blockIdx.x;
     const uint32_t bid_hb = div_magic(bid, a.magic_head_blocks);      // = kv head + n_kv_heads * batch
     const int hb = static_cast<int>(bid - bid_hb * head_blocks);
-    const int b = static_cast<int>(div_magic(bid_hb, a.magic_kv_heads));
-    const int g = static_cast<int>(bid_hb) - b * a.n_kv_heads;
+    int item = static_cast<int>(div_magic(bid_hb, a.magic_kv_heads));
+    const int g = static_cast<int>(bid_hb) - item * a.n_kv_heads;
+    // Items of different length: the row tiles of a long one, whose neighbours in x have none there, would go to the same few units of an
+    // XCD again and again (every item's x a fixed distance apart, 32 units), two of the heaviest to a unit.  Every fourth row tile begins
+    // with the next item instead.  (us, without and so: 60..2700 rows, 16 / 8 heads of 128 101, 67; eight of 117 to 938, 32 / 8 40.8, 36.0;
+    // 50..2700, 16 / 8 of 72 71, 58; eight of 85 to 1365 over 256 keys, 16 / 16 of 72 20.4, 18.3; equal lengths the same.)
+    if constexpr (RAGGED) item = (item + static_cast<int>(blockIdx.y >> 2)) % a.batch;
+    const int b = item;
 
     const int h = g * group + hb * HB + (w & (HB - 1));
     const int wrow = (w >> a.hb_shift) * 32;                  // this wavefront's first query row inside a row tile
