@@ -378,7 +378,7 @@ static int launch_f32(const AttnArgs& a, hipStream_t s)
 template <bool BF16>
 static int launch_f32_for(const AttnArgs& a, hipStream_t s)
 {
-    // 16 keys a tile
+    // 16 keys a tile (times with the row tiles innermost in the grid; f32_grid's order takes up to a third off both sides)
     //   - up to 64 keys, one tile for each wavefront, where the instructions of the longer tile are most of the time (17 rows,
     //     4 / 2 fp32 heads of 64 / 128: 4.4 / 6.0 us, 5.3 / 7.7 in tiles of 32, 4.2 / 5.8 with one row per wavefront on the vector
     //     units; 32 x 64 rows, 16 / 8 heads of 128: 33.1, 41.2 and 172.8)
