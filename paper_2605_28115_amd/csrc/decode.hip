@@ -661,6 +661,27 @@ static size_t decode_lds(const DecodePlan& p, int32_t head_dim)
     return sizeof(float) * (p.mfma ? p.waves : decode_states(p.lpr, p.waves)) * static_cast<size_t>(p.hg) * (head_dim + 2);
 }
 
+// Where 192 to 256 workgroups that take a whole context each are not the faster way after all; p->splits is what the contexts would be
+// cut into otherwise (us, cut and whole).
+//   - one or two heads a pass, samples of different length, as many pairs as units: these are not cut anyway, and narrow workgroups
+//     are the better ones (32 samples, 16 / 8 heads of 128: of 300..600 rows 14.2, 15.1, of 1000..1300 27.8, 30.2; 28 samples 28.0, 27.0)
+//   - 4 and more heads a pass on the vector units are bound by their instructions, and 192 workgroups leave a quarter of the units
+//     without any: with one length from some length on (48 x 2000 rows, 32 / 4 fp32 heads 98, 108; 48 x 800 50.9, 47.4, but 51 x 2500
+//     143, 135; 24 x 2500, 32 / 8 bf16 heads of 256 89, 95; 24 x 1500 fp32 of 128 53.5, 51.0; 12 x 1500, 56 / 8 45.2, 48.0; 48 of
+//     300..600, 32 / 4 of 128 35.6, 37.6, but of 64 23.3, 19.9, and 24 of 300..600, 32 / 8 25.0, 24.1)
+//   - two passes over the same rows, n_kv_heads times the splits apart in the grid (decode_place): cut they may meet on an XCD, whole
+//     they do only if n_kv_heads is a multiple of 8 (24 x 2500, 28 / 4 fp32 heads 76, 85 and 32 x 2500 86, 103, in 6 and 4 splits; 28 x 2500
+//     103, 90, in 5; 24 x 800 33.1, 30.3, but 31 x 500 23.4, 24.7; samples of different length 26 of 600..900 36.9, 32.9, of 1600..2000 59.9, 66.9)
+static bool wide_full_pays(const DecodePlan& p, int64_t units, int64_t n_ctx, int32_t n_kv_heads, bool ragged)
+{
+    if (p.mfma) return true;
+    if (p.hg <= 2) return !ragged || units < kDecRaggedUnits;
+    if (ragged) return (units >= 200 || p.hg == 4 || p.lpr <= 16) && (p.head_blocks == 1 || n_ctx <= 900);
+    if (p.hg == 4 && p.head_blocks > 1 && n_kv_heads % 8 != 0)
+        return static_cast<int64_t>(n_kv_heads) * p.splits % 8 != 0 || (n_ctx <= 800 && units <= 240);
+    return units >= 200 || n_ctx <= (p.hg > 4 ? 800 : p.head_blocks == 1 ? 1500 : 700);
+}
+
 static void go_wide(DecodePlan* p, int32_t longest, int32_t head_dim, int group)
 {
     if (p->wide_heads) { p->mfma = false; p->hg = 1; p->head_blocks = group; }
@@ -723,8 +744,8 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     p->whole_keys = static_cast<int>(whole_keys);
     // The vector kernel with 4 or 8 heads a pass is bound by its instructions and takes more workgroups per unit: 4 splits (74 x 968
     // rows, 16 / 4 fp32 heads of 96: 63 us in one, 49 in four; 22 x 392, 32 / 8 of 128: 22.5 in two, 21.3 in four), or 8 where
-    // several passes read the same rows, which then run on one XCD (decode_heads_first) and share its L2 (24 x 2500, 28 / 4
-    // of 128: 93 us in two, 65 in eight).  As long as a split is two rounds, and the workspace has the room.
+    // several passes read the same rows, which then run on one XCD (decode_place) and share its L2 (24 x 2500, 28 / 4
+    // of 128: 93 us in two, 65 in eight).  As long as a split is two rounds, and the workspace has the room (there 6, 75 us).
     int64_t wanted = units >= kDecFullUnits || n_ctx <= whole_keys ? 1 : std::max(std::min<int64_t>(512 / units, 8), 256 / units);
     // The same 4 where the matrix cores would run one workgroup on most units and two on some through a long context (80 x 2918
     // rows, 16 / 4 heads of 72, 320 pairs: 87 us in one, 74 in four).
@@ -742,14 +763,15 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     //     heads of 128 10.6, 8.1; 4 x 700, 28 / 4 10.7, 8.7; 8 x 300, 32 / 8 of 64 in fp32 10.6, 7.4; but 1 x 1000, 32 / 8 10.4, 9.7 and
     //     8 x 1000 11.5, 12.6).  With 4 or 8 heads on the vector units contexts need not be cut for that (1 x 130, 32 / 4 fp32 heads 11.9, 7.1).
     //   - matrix cores, up to 128 pairs with 5 / 4 rounds of 8 wavefronts (16 x 300, 32 / 8 10.2, 8.5; 8 x 400 9.2, 10.2)
-    //   - 192 to 256 pairs up to 3072 rows: one such workgroup to a unit reads at its rate and nothing is left to combine (24 x 600 rows,
-    //     32 / 8 heads of 128 19.5, 14.4; 60 x 1200, 28 / 4 30.8, 26.7; 28 x 2400, 16 / 8 fp32 of 64 45.3, 43.2; 32 x 2400, 16 / 8 of 128
-    //     53.1, 51.1, but of 4000 85, 90; 160 pairs: 20 x 1200, 16 / 8 19.7, 20.7)
+    //   - 192 to 256 pairs (of them and passes) up to 3072 rows: one such workgroup to a unit reads at its rate and nothing is left to
+    //     combine (24 x 600 rows, 32 / 8 heads of 128 19.5, 14.4; 60 x 1200, 28 / 4 30.8, 26.7; 28 x 2400, 16 / 8 fp32 of 64 45.3, 43.2;
+    //     32 x 2400, 16 / 8 of 128 53.1, 51.1, but of 4000 85, 90; 160 pairs: 20 x 1200, 16 / 8 19.7, 20.7)
+    // (wide_full_pays has where the third does not hold)
     const bool cut_up = n_ctx > whole_keys;
     p->wide_heads = static_cast<int64_t>(batch) * n_q_heads <= 256 && (cut_up || (p->hg > 2 && !p->mfma && n_ctx > round_keys)) &&
                     n_ctx <= 3 * 16 * (kWave / p->lpr) * kDecU;
     p->wide_short = p->wide_heads || (p->mfma && cut_up && units <= 128 && n_ctx <= 5 * 32 * 8 / 4);
-    p->wide_full = cut_up && units >= 192 && units <= 256 && n_ctx <= 3072;
+    p->wide_full = cut_up && units >= 192 && units <= 256 && n_ctx <= 3072 && wide_full_pays(*p, units, n_ctx, n_kv_heads, ragged);
     if (!ragged && (p->wide_short || p->wide_full)) go_wide(p, static_cast<int32_t>(n_ctx), head_dim, group);
     return CIVIC_OK;
 }
@@ -920,6 +942,26 @@ static int decode_check(const void* q, const void* k_cache, const void* v_cache,
     if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(out)) return CIVIC_ERR_INVALID_ARG;
     return CIVIC_OK;
 }
+
+}  // namespace civic
+
+// For tests, on the host alone (no part of civic.h): how a launch is taken, of one context length n_ctx[0] for all samples or, `ragged`,
+// of n_ctx[i] each.  shape: wavefronts of a workgroup, query heads a pass, passes, splits, whether on the matrix cores.
+extern "C" int civic_decode_shape(int dtype, int32_t batch, const int32_t* n_ctx, int32_t ragged, int32_t n_q_heads, int32_t n_kv_heads,
+                                  int32_t head_dim, int32_t* shape)
+{
+    using namespace civic;
+    if (batch < 1 || batch > kDecRaggedItems || !n_ctx || !shape) return CIVIC_ERR_INVALID_ARG;
+    DecodePlan p;
+    const int32_t longest = ragged ? *std::max_element(n_ctx, n_ctx + batch) : n_ctx[0];
+    const int rc = decode_plan(dtype, batch, n_q_heads, n_kv_heads, head_dim, longest, &p, ragged != 0);
+    if (rc != CIVIC_OK) return rc;
+    if (ragged) cut_ragged(n_ctx, batch, static_cast<int64_t>(batch) * n_kv_heads * p.head_blocks, head_dim, n_q_heads / n_kv_heads, &p);
+    shape[0] = p.waves; shape[1] = p.hg; shape[2] = p.head_blocks; shape[3] = p.splits; shape[4] = p.mfma ? 1 : 0;
+    return CIVIC_OK;
+}
+
+namespace civic {
 
 // ------------------------------------------------------------------------------ no allocation at all
 // civic_decode_attn_noalloc keeps the partial results of the splits in a buffer that belongs to the library's

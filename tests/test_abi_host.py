@@ -417,3 +417,39 @@ def test_attention_launch_of_narrow_causal_heads_is_not_modelled(bd):
     narrow, wide = min(pass_over(64) for _ in range(3)), min(pass_over(128) for _ in range(3))
     assert narrow[1] == {4} and wide[1] == {4, 8, 9}
     assert narrow[0] < wide[0] / 4
+
+
+def decode_shape(bd, dtype, batch, hq, hkv, d, ctx):
+    """(wavefronts of a workgroup, query heads a pass, passes, splits, matrix cores); ctx: one length, or (lowest, highest) of samples
+    that each have their own."""
+    ragged = isinstance(ctx, tuple)
+    n = np.linspace(ctx[0], ctx[1], batch).round().astype(np.int32) if ragged else np.array([ctx], dtype=np.int32)
+    shape = (C.c_int32 * 5)()
+    assert bd.lib.civic_decode_shape(bd.CIVIC_F32 if dtype == "fp32" else bd.CIVIC_BF16, batch, n.ctypes.data_as(C.c_void_p), int(ragged),
+                                     hq, hkv, d, shape) == 0
+    return tuple(shape)
+
+
+@pytest.mark.parametrize("dtype,batch,hq,hkv,d,ctx,whole", [
+    # as many pairs as units, or nearly: one wide workgroup for each
+    ("bf16", 24, 32, 8, 128, 600, True), ("bf16", 32, 16, 8, 128, 2400, True), ("bf16", 24, 32, 8, 128, (1000, 1300), True),
+    ("fp32", 28, 32, 8, 128, 2500, True), ("fp32", 51, 32, 4, 128, 2500, True), ("fp32", 24, 32, 8, 128, 1500, True),
+    ("fp32", 28, 28, 4, 128, 2500, True), ("fp32", 14, 56, 8, 128, 2500, True), ("fp32", 24, 28, 4, 128, 800, True),
+    ("fp32", 26, 28, 4, 128, (600, 900), True), ("fp32", 48, 32, 4, 64, (1600, 2000), True), ("bf16", 28, 16, 8, 128, (1000, 1300), True),
+    ("fp32", 48, 32, 4, 128, (300, 600), False), ("fp32", 24, 64, 4, 128, (300, 600), False), ("fp32", 24, 32, 8, 128, (300, 600), True),
+    # 192 workgroups with 4 or 8 heads a pass leave a quarter of the units idle for long
+    ("fp32", 48, 32, 4, 128, 2000, False), ("bf16", 24, 32, 8, 256, 2000, False), ("fp32", 24, 32, 8, 128, 2000, False),
+    ("fp32", 12, 56, 8, 128, 1500, False),
+    # passes that share an XCD's L2 only where the contexts are cut
+    ("fp32", 24, 28, 4, 128, 2500, False), ("fp32", 24, 28, 4, 64, 3000, False), ("fp32", 32, 28, 4, 128, 1000, False),
+    ("fp32", 31, 28, 4, 128, 500, False), ("fp32", 26, 28, 4, 128, (1600, 2000), False)])
+def test_decode_of_whole_contexts_in_wide_workgroups(bd, dtype, batch, hq, hkv, d, ctx, whole):
+    """192 to 256 (sample, KV head, pass) workgroups: contexts whole in wide ones, but not where cut contexts were measured faster."""
+    waves, _, _, splits, _ = decode_shape(bd, dtype, batch, hq, hkv, d, ctx)
+    assert (waves > 4 and splits == 1) if whole else (waves == 4 and splits > 1)
+
+
+def test_decode_of_different_lengths_whole_in_narrow_workgroups(bd):
+    """One or two heads a pass and as many pairs as units: contexts within a few hundred rows of each other are whole, and narrow."""
+    assert decode_shape(bd, "bf16", 32, 16, 8, 128, (300, 600))[::3] == (4, 1)
+    assert decode_shape(bd, "fp32", 32, 16, 8, 64, (1000, 1300))[::3] == (4, 1)
