@@ -644,7 +644,9 @@ struct DecodePlan {
     bool mfma;
     int hg, lpr, head_blocks, round_keys;
     int waves;                           // of a workgroup: kDecWaves, or a wide one's
-    bool wide_heads, wide_short, wide_full;   // where wide workgroups are the faster way: one for each query head, contexts short or even
+    bool wide_short, wide_full;          // where wide workgroups are the faster way: contexts short or even
+    bool wide_heads;                     // the same with one for each query head, where wide_heads_pay as well
+    int64_t heads_row_bytes, heads_most; // bytes that these read of a context row into all L2s, and what they may read (wide_heads_pay)
     int whole_keys;                      // contexts up to this are not cut
     // pieces of different contexts: whole samples from ragged_units pairs on; else no more than ragged_groups, or of ragged_keys rows
     int ragged_units, ragged_keys, ragged_groups;
@@ -682,9 +684,18 @@ static bool wide_full_pays(const DecodePlan& p, int64_t units, int64_t n_ctx, in
     return units >= 200 || n_ctx <= (p.hg > 4 ? 800 : p.head_blocks == 1 ? 1500 : 700);
 }
 
-static void go_wide(DecodePlan* p, int32_t longest, int32_t head_dim, int group)
+// Workgroups of one query head each read their KV head's rows as often as there are heads.  A group's workgroups lie n_kv_heads apart in
+// the grid, so they are on one XCD, and all but the first read from its L2, only where n_kv_heads is a multiple of 8; else every
+// XCD of the 8 / gcd(n_kv_heads, 8) that have some of them fetches the rows, and above a number of bytes that costs more than a launch
+// saves (us, first for caches that the passes find in the last-level cache, then for such as they do not; cut and so: 16 x 300 rows, 16 / 1
+// bf16 heads 10.1 / 10.5, 8.4 / 10.0, 8 x 512, 8 / 1 9.2 / 9.5, 8.8 / 11.0, but 16 x 420 9.8 / 10.5, 8.9 / 11.7 and 32 x 300, 8 / 1 9.4 / 9.6, 9.8 / 12.0; in fp32 16 x 270, 16 / 4
+// 11.8 / 12.7, 9.4 / 11.2, but 16 x 384 12.0 / 13.4, 12.4 / 13.8 and 64 x 270, 4 / 1 11.9 / 12.7, 12.9 / 15.6; samples of different
+// length, which take longer cut: 16 of 100..500, 16 / 1 12.3 / 13.1, 10.1 / 11.8, but of 500..768 12.3 / 13.3, 14.0 / 15.7, and 8 of 500..768, 32 / 4 10.2 / 10.5, 10.8 / 12.2).
+static bool wide_heads_pay(const DecodePlan& p, int64_t rows) { return p.wide_heads && rows * p.heads_row_bytes <= p.heads_most; }
+
+static void go_wide(DecodePlan* p, bool heads, int32_t longest, int32_t head_dim, int group)
 {
-    if (p->wide_heads) { p->mfma = false; p->hg = 1; p->head_blocks = group; }
+    if (heads) { p->mfma = false; p->hg = 1; p->head_blocks = group; }
     p->waves = decode_wide_waves(*p);
     p->splits = 1;
     p->keys_per_split = longest;
@@ -759,20 +770,29 @@ static int decode_plan(int dtype, int32_t batch, int32_t n_q_heads, int32_t n_kv
     p->lds_bytes = decode_lds(*p, head_dim);
     // Wide workgroups and one split, where contexts would be cut (us, as it was and so):
     //   - up to 256 query heads with three rounds of 16 wavefronts or less: a workgroup for each of them, which is bound by its
-    //     instructions and through before a second launch would have started; the group's reads meet in an L2 (1 x 469 rows, 16 / 8
-    //     heads of 128 10.6, 8.1; 4 x 700, 28 / 4 10.7, 8.7; 8 x 300, 32 / 8 of 64 in fp32 10.6, 7.4; but 1 x 1000, 32 / 8 10.4, 9.7 and
-    //     8 x 1000 11.5, 12.6).  With 4 or 8 heads on the vector units contexts need not be cut for that (1 x 130, 32 / 4 fp32 heads 11.9, 7.1).
+    //     instructions and through before a second launch would have started (1 x 469 rows, 16 / 8 heads of 128 8.9, 6.4, and 9.5, 8.1 for
+    //     caches that no pass has touched before; 8 x 300, 32 / 8 of 64 in fp32 10.6, 7.4).  Two rounds where matrix cores would take contexts
+    //     of one length (8 x 512, 32 / 8 9.0, 7.9 and untouched 9.8, 9.5, but 8 x 768 10.4, 9.8 and 11.9, 13.1; 8 of 500..768 12.2, 10.1 and
+    //     13.1, 12.3), and where one pass over the rows would do for a single KV head's 4 or 8 heads (8 x 384, 8 / 1 in fp32 12.1, 12.7
+    //     and untouched 12.6, 14.3).  With 4 or 8 heads on the vector units contexts need not be cut for that (1 x 130, 32 / 4 fp32 heads 11.9, 7.1).
     //   - matrix cores, up to 128 pairs with 5 / 4 rounds of 8 wavefronts (16 x 300, 32 / 8 10.2, 8.5; 8 x 400 9.2, 10.2)
     //   - 192 to 256 pairs (of them and passes) up to 3072 rows: one such workgroup to a unit reads at its rate and nothing is left to
     //     combine (24 x 600 rows, 32 / 8 heads of 128 19.5, 14.4; 60 x 1200, 28 / 4 30.8, 26.7; 28 x 2400, 16 / 8 fp32 of 64 45.3, 43.2;
     //     32 x 2400, 16 / 8 of 128 53.1, 51.1, but of 4000 85, 90; 160 pairs: 20 x 1200, 16 / 8 19.7, 20.7)
     // (wide_full_pays has where the third does not hold)
     const bool cut_up = n_ctx > whole_keys;
+    const int spread = std::min(group, n_kv_heads % 8 == 0 ? 1 : n_kv_heads % 4 == 0 ? 2 : n_kv_heads % 2 == 0 ? 4 : 8);
+    p->heads_row_bytes = static_cast<int64_t>(2) * n_kv_heads * head_dim * esz * spread;
+    const int64_t rounds = (n_ctx + 16 * (kWave / p->lpr) * kDecU - 1) / (16 * (kWave / p->lpr) * kDecU);
+    p->heads_most = spread == 1 ? INT64_MAX : !p->mfma ? 44000000 : !ragged ? 20000000 : rounds <= 2 ? 24000000 : 12000000;
     p->wide_heads = static_cast<int64_t>(batch) * n_q_heads <= 256 && (cut_up || (p->hg > 2 && !p->mfma && n_ctx > round_keys)) &&
-                    n_ctx <= 3 * 16 * (kWave / p->lpr) * kDecU;
-    p->wide_short = p->wide_heads || (p->mfma && cut_up && units <= 128 && n_ctx <= 5 * 32 * 8 / 4);
+                    rounds <= ((p->mfma ? !ragged : spread == 8 && p->head_blocks == 1) ? 2 : 3);
+    p->wide_short = p->mfma && cut_up && units <= 128 && n_ctx <= 5 * 32 * 8 / 4;
     p->wide_full = cut_up && units >= 192 && units <= 256 && n_ctx <= 3072 && wide_full_pays(*p, units, n_ctx, n_kv_heads, ragged);
-    if (!ragged && (p->wide_short || p->wide_full)) go_wide(p, static_cast<int32_t>(n_ctx), head_dim, group);
+    if (!ragged) {
+        const bool heads = wide_heads_pay(*p, static_cast<int64_t>(batch) * n_ctx);
+        if (heads || p->wide_short || p->wide_full) go_wide(p, heads, static_cast<int32_t>(n_ctx), head_dim, group);
+    }
     return CIVIC_OK;
 }
 
@@ -793,7 +813,8 @@ static void cut_ragged(const int32_t* ctx_of, int32_t batch, int64_t units, int3
     int64_t rows = 0;
     int32_t longest = 0;
     for (int32_t i = 0; i < batch; ++i) { rows += ctx_of[i]; longest = std::max(longest, ctx_of[i]); }
-    if (p->wide_short || (p->wide_full && longest - rows / batch <= kDecTailKeys)) return go_wide(p, longest, head_dim, group);
+    const bool heads = wide_heads_pay(*p, rows);
+    if (heads || p->wide_short || (p->wide_full && longest - rows / batch <= kDecTailKeys)) return go_wide(p, heads, longest, head_dim, group);
     const int64_t per_sample = units / batch;
     int64_t kps = p->round_keys;
     if (longest <= p->whole_keys || (units >= p->ragged_units && longest - rows / batch <= kDecTailKeys)) kps = longest;

@@ -453,3 +453,19 @@ def test_decode_of_different_lengths_whole_in_narrow_workgroups(bd):
     """One or two heads a pass and as many pairs as units: contexts within a few hundred rows of each other are whole, and narrow."""
     assert decode_shape(bd, "bf16", 32, 16, 8, 128, (300, 600))[::3] == (4, 1)
     assert decode_shape(bd, "fp32", 32, 16, 8, 64, (1000, 1300))[::3] == (4, 1)
+
+
+@pytest.mark.parametrize("dtype,batch,hq,hkv,d,ctx,heads", [
+    ("bf16", 1, 16, 8, 128, 469, True), ("bf16", 16, 16, 8, 128, 768, True), ("bf16", 8, 32, 8, 128, 512, True), ("bf16", 8, 32, 8, 128, 513, False),
+    ("bf16", 8, 32, 8, 128, (500, 768), True), ("bf16", 8, 32, 8, 128, (500, 769), False), ("fp32", 8, 32, 1, 128, 384, True),
+    ("fp32", 1, 32, 4, 128, 384, True), ("bf16", 1, 32, 1, 128, 512, True), ("fp32", 16, 16, 4, 128, 270, True),
+    # the group's rows into several L2s, and too many of them
+    ("bf16", 16, 16, 1, 128, 420, False), ("bf16", 32, 8, 1, 128, 400, False), ("bf16", 64, 4, 1, 128, 700, False), ("bf16", 9, 28, 4, 128, 600, False),
+    ("fp32", 16, 16, 4, 128, 384, False), ("fp32", 64, 4, 1, 128, 270, False), ("bf16", 128, 2, 1, 128, 768, False),
+    ("bf16", 16, 16, 1, 128, (100, 500), True), ("bf16", 16, 16, 1, 128, (500, 768), False), ("bf16", 8, 32, 4, 128, (500, 768), False),
+    ("bf16", 4, 64, 4, 128, (500, 768), True), ("fp32", 8, 8, 1, 128, 256, True), ("fp32", 8, 8, 1, 128, 257, False)])
+def test_decode_in_a_workgroup_for_each_query_head(bd, dtype, batch, hq, hkv, d, ctx, heads):
+    """Short contexts of up to 256 query heads: a workgroup of 16 wavefronts for each, but not where the KV heads' rows would be
+    fetched into several XCDs' L2s for more than the second launch costs, nor for long contexts that matrix cores would take."""
+    waves, per_pass, passes, splits, _ = decode_shape(bd, dtype, batch, hq, hkv, d, ctx)
+    assert ((waves, per_pass, passes, splits) == (16, 1, hq // hkv, 1)) == heads
