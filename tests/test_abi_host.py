@@ -469,3 +469,26 @@ def test_decode_in_a_workgroup_for_each_query_head(bd, dtype, batch, hq, hkv, d,
     fetched into several XCDs' L2s for more than the second launch costs, nor for long contexts that matrix cores would take."""
     waves, per_pass, passes, splits, _ = decode_shape(bd, dtype, batch, hq, hkv, d, ctx)
     assert ((waves, per_pass, passes, splits) == (16, 1, hq // hkv, 1)) == heads
+
+
+def test_decode_sizes_reach_the_workgroups_they_are_chosen_for(bd):
+    """The GPU tests' sizes against the host's choice: (wavefronts, query heads a pass, whether on the matrix cores), lanes to a row."""
+    from test_gpu_kernel_edges import DECODE_CUTS, DECODE_WIDE
+
+    def shapes(cases):
+        got = set()
+        for batch, hq, hkv, d, ctx, dtype in cases:
+            n = np.array(ctx * batch if len(ctx) == 1 else ctx, dtype=np.int32)
+            shape = (C.c_int32 * 5)()
+            assert bd.lib.civic_decode_shape(bd.CIVIC_F32 if dtype == "fp32" else bd.CIVIC_BF16, batch, n.ctypes.data_as(C.c_void_p), 1,
+                                             hq, hkv, d, shape) == 0
+            lanes = 8
+            while lanes * 16 < d * (4 if dtype == "fp32" else 2):
+                lanes *= 2
+            got.add((shape[0], shape[1], shape[4], lanes))
+        return got
+    wide, narrow = shapes(DECODE_WIDE), shapes(DECODE_CUTS)
+    assert {s[:3] for s in wide} >= {(16, 1, 0), (16, 2, 0), (8, 4, 0), (8, 8, 0), (8, 4, 1), (4, 4, 1), (4, 8, 1), (4, 4, 0)}
+    assert {s[3] for s in wide if s[0] == 16} == {8, 16, 32, 64}
+    assert {s[:3] for s in narrow if s[0] == 4} >= {(4, 1, 0), (4, 2, 0), (4, 4, 0), (4, 8, 0), (4, 4, 1)}
+    assert {s[3] for s in narrow if s[0] == 4 and s[2] == 0} == {8, 16, 32, 64}

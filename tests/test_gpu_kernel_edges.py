@@ -442,13 +442,19 @@ def test_noalloc_takes_groups_of_five_to_seven_heads(bd, batch, hq, hkv, d, n):
     assert torch.equal(out, bd.civic_decode_attn(q, k, v, n))
 
 
-@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", [
+DECODE_CUTS = [
     (70, 16, 4, 96, [600] * 70, "fp32"), (20, 28, 4, 64, [1100] * 20, "fp32"), (12, 14, 2, 64, [511] * 12, "fp32"),   # 4 and 8 splits, and not
-    (3, 16, 2, 64, [128, 129, 300], "fp32"), (2, 8, 1, 128, [64, 65], "fp32"), (1, 9, 1, 256, [200], "fp32"),         # eight heads a pass
-    (2, 4, 1, 32, [257, 40], "fp32"), (2, 4, 1, 36, [33, 500], "fp32"), (3, 2, 2, 64, [90, 1, 400], "bf16"),          # 8 and 4 row slots
-    (3, 4, 2, 128, [90, 64, 400], "bf16"), (2, 2, 1, 512, [70, 9], "bf16"),                                          # 4 and 1
+    (3, 16, 2, 64, [128, 129, 300], "fp32"), (2, 8, 1, 128, [64, 65], "fp32"), (1, 9, 1, 256, [200], "fp32"),
+    (33, 8, 1, 64, [128, 129, 300] * 11, "fp32"), (34, 8, 1, 128, [64, 65] * 17, "fp32"),                             # eight heads a pass
+    (2, 4, 1, 32, [257, 40], "fp32"), (2, 4, 1, 36, [33, 500], "fp32"), (3, 2, 2, 64, [90, 1, 400], "bf16"),
+    (66, 4, 1, 32, [257, 40] * 33, "fp32"), (66, 4, 1, 36, [33, 500] * 33, "fp32"),                                   # 8 and 4 row slots
+    (3, 4, 2, 128, [90, 64, 400], "bf16"), (2, 2, 1, 512, [70, 9], "bf16"),
+    (66, 4, 2, 128, [90, 64, 400] * 22, "bf16"), (130, 2, 1, 512, [70, 9] * 65, "bf16"),                              # 4 and 1
     (30, 8, 4, 128, [1 + 17 * i for i in range(30)], "fp32"), (64, 8, 4, 64, [250 + 7 * i for i in range(64)], "fp32"),  # pieces, whole
-    (66, 16, 4, 72, [1100] * 66, "bf16"), (33, 32, 8, 64, [200 + i for i in range(33)], "bf16")])
+    (66, 16, 4, 72, [1100] * 66, "bf16"), (33, 32, 8, 64, [200 + i for i in range(33)], "bf16")]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", DECODE_CUTS)
 def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
     """The rules of the cuts that go by the kernel and its heads a pass, and both ways a workgroup's states meet.  Rows past a
     context are NaN.  fp32: bar of the parity tests; bf16 rounds the result once."""
@@ -468,19 +474,25 @@ def test_decode_cuts_of_either_kernel(bd, batch, hq, hkv, d, ctx, dtype):
         assert err <= (1e-5 if dtype == "fp32" else 2.0 ** -8) * max(1.0, float(ref.abs().max())), err
 
 
-@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", [
+DECODE_WIDE = [
     (1, 16, 8, 128, [257], "bf16"), (1, 16, 8, 128, [768], "bf16"), (1, 16, 8, 128, [769], "bf16"),         # three rounds of 16 wavefronts
     (8, 32, 8, 128, [300], "bf16"), (9, 32, 8, 128, [300], "bf16"), (1, 9, 1, 128, [20, ], "fp32"), (1, 9, 1, 128, [33], "fp32"),  # 256 heads
     (3, 6, 6, 72, [300, 257, 1], "bf16"), (2, 2, 1, 64, [900, 1024], "bf16"), (1, 2, 1, 256, [200], "bf16"), (2, 2, 2, 512, [100, 64], "bf16"),
     (2, 8, 4, 128, [256], "fp32"), (2, 8, 4, 128, [257, 129], "fp32"), (2, 3, 3, 32, [1000, 513], "fp32"),   # eight lanes a row
-    (2, 8, 2, 64, [250, 256], "fp32"), (2, 9, 1, 64, [255], "fp32"), (1, 16, 2, 256, [63], "fp32"),           # 8 wavefronts, 4 and 8 heads
+    (2, 8, 2, 64, [250, 256], "fp32"), (2, 9, 1, 64, [255], "fp32"), (1, 16, 2, 256, [63], "fp32"),
+    (28, 32, 8, 64, [257], "fp32"), (25, 64, 8, 64, [129], "fp32"), (28, 28, 4, 64, [300], "fp32"),           # 8 wavefronts, 4 and 8 heads
+    (28, 32, 8, 128, [170 + i for i in range(28)], "fp32"), (52, 32, 4, 128, [70 + i for i in range(52)], "fp32"),
+    (32, 8, 1, 128, [400], "bf16"), (16, 16, 1, 128, [300], "bf16"), (64, 4, 1, 128, [300], "fp32"),          # rows into several L2s
     (2, 16, 1, 512, [33, 20], "bf16"), (1, 4, 1, 200, [120], "bf16"),
     (4, 28, 4, 128, [300, 320, 257, 1], "bf16"), (1, 32, 2, 128, [320], "bf16"), (1, 17, 1, 64, [257], "bf16"), (1, 32, 8, 96, [321], "bf16"),
     (96, 2, 1, 64, [600], "bf16"), (97, 2, 1, 64, [600], "bf16"), (24, 16, 4, 64, [300], "bf16"), (25, 16, 4, 64, [300], "bf16"),  # 96 pairs
     (24, 32, 8, 64, [600], "bf16"), (32, 16, 8, 64, [700], "bf16"), (33, 16, 8, 64, [700], "bf16"), (191, 4, 1, 64, [300], "bf16"),   # 192 to 256
     (5, 32, 8, 64, [40, 2000, 700, 1, 1024], "bf16"), (3, 40, 2, 64, [900, 1, 513], "bf16"), (4, 28, 4, 64, [1500, 800, 3, 40], "fp32"),  # cut: order
     (28, 16, 8, 64, [3072], "fp32"), (28, 16, 8, 64, [3073], "fp32"), (48, 8, 4, 64, [600 + 9 * i for i in range(48)], "bf16"),
-    (48, 8, 4, 64, [60 + 25 * i for i in range(48)], "bf16"), (60, 16, 4, 128, [300], "fp32")])
+    (48, 8, 4, 64, [60 + 25 * i for i in range(48)], "bf16"), (60, 16, 4, 128, [300], "fp32")]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,ctx,dtype", DECODE_WIDE)
 def test_decode_wide_workgroups(bd, batch, hq, hkv, d, ctx, dtype):
     """Workgroups of 8 and of 16 wavefronts and the rule that takes them, on both sides of its edges, one length for all samples and one
     each.  Checks and bars of test_decode_cuts_of_either_kernel."""
