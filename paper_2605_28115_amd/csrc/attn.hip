@@ -62,6 +62,7 @@ struct AttnArgs {
     int32_t heads_per_block, row_tiles;   // MFMA path: block shape and number of 32*rows_per_block tiles; fp32 path: tiles of 16 rows
     int32_t pass_tiles;                   // fp32 path: row tiles of a pass over the units (f32_grid)
     int32_t paired;                       // MFMA path: a workgroup walks two row tiles, a heavy and a light one
+    int32_t item_shift;                   // MFMA path, ragged: every fourth row tile begins with the next item (shift_items)
     // block index -> (head block, kv head, batch) without integer division: q heads per kv head,
     // head blocks per kv head, log2(heads_per_block), ceil(2^32 / d) for d = head blocks, kv heads (0 for d = 1)
     int32_t group, head_blocks, hb_shift;
@@ -563,11 +564,9 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
     const int hb = static_cast<int>(bid - bid_hb * head_blocks);
     int item = static_cast<int>(div_magic(bid_hb, a.magic_kv_heads));
     const int g = static_cast<int>(bid_hb) - item * a.n_kv_heads;
-    // Items of different length: the row tiles of a long one, whose neighbours in x have none there, would go to the same few units of an
-    // XCD again and again (every item's x a fixed distance apart, 32 units), two of the heaviest to a unit.  Every fourth row tile begins
-    // with the next item instead.  (us, without and so: 60..2700 rows, 16 / 8 heads of 128 101, 67; eight of 117 to 938, 32 / 8 40.8, 36.0;
-    // 50..2700, 16 / 8 of 72 71, 58; eight of 85 to 1365 over 256 keys, 16 / 16 of 72 20.4, 18.3; equal lengths the same.)
-    if constexpr (RAGGED) item = (item + static_cast<int>(blockIdx.y >> 2)) % a.batch;
+    // (shift_items; the one integer division here, and only in launches that gain far more by it)
+    if constexpr (RAGGED)
+        if (a.item_shift) item = (item + static_cast<int>(blockIdx.y >> 2)) % a.batch;
     const int b = item;
 
     const int h = g * group + hb * HB + (w & (HB - 1));
@@ -1278,6 +1277,52 @@ static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
     return a.head_dim > 64 && full && a.kv_seq > 23 * kBN;
 }
 
+// Whether every fourth row tile of a ragged launch begins with the next item.  Items of different length leave workgroups without work
+// in the grid, and as the hardware hands workgroup n to unit n mod 256 (to XCD n mod 8, to the XCD's 32 units in turn), the row tiles of
+// a long item, a fixed number of workgroups apart, may meet on a few units again and again, several of the heaviest to a unit.  Shifted
+// items spread them then, and bring them together where the plain order has them on units of their own.  So both orders' loads of the
+// 256 units are counted, 3 for a workgroup and 1 for a key tile, and the items are shifted if that makes the largest load smaller.
+// (us, plain and shifted, and the ratio of the largest loads; heads of 128 unless said: eight items of 60..2700 rows, 16 / 8 105, 63, 0.25,
+// 16 / 4 169, 60, 0.40, 8 / 2 90, 49, 0.62; eight of 117 to 938, 32 / 8 52, 40, 0.66; eight of 85 to 1365 over 256 keys, 16 / 16 of 72 19.9, 18.6, 0.67;
+// but items of 2000, 500 and 200, 16 / 4 38.7, 43.5, 2.08, 36 / 6 of 64 39, 49, 1.39; five of 117..1500, 28 / 4 of 64 31.6, 36.8, 1.66; eight of
+// 60..2700, 12 / 3 of 64 49, 60, 1.98; four of 1400..1600 over 512 keys, 12 / 12 of 64 18.0, 19.2, 1.00: K and V change their XCD.)
+static bool shift_items(const AttnArgs& a, int64_t per_rt, int rows_per_block)
+{
+    if (a.row_tiles <= 4) return false;
+    constexpr uint32_t kUnits = kComputeUnits, kMask = kUnits - 1;
+    static_assert((kUnits & kMask) == 0, "unit numbers are taken by a mask");
+    const uint32_t per_item = static_cast<uint32_t>(per_rt / a.batch);
+    int32_t left = 4096;                                      // tiles to count: a few microseconds on the host; longer launches are shifted
+    int64_t plain[kUnits] = {}, shifted[kUnits] = {};         // differences from unit to unit
+    auto put = [&](int64_t* load, uint32_t y, int at, int64_t cost) {
+        const uint32_t from = (y * static_cast<uint32_t>(per_rt) + static_cast<uint32_t>(at) * per_item) & kMask, to = from + (per_item & kMask);
+        load[from] += cost;
+        if (to < kUnits) load[to] -= cost;
+        else { load[0] += cost; load[to - kUnits] -= cost; }
+    };
+    for (int it = 0; it < a.batch; ++it) {
+        const int64_t rows = static_cast<int64_t>(a.item_row[it + 1]) - a.item_row[it];
+        const int32_t tiles = static_cast<int32_t>((rows + rows_per_block - 1) / rows_per_block);
+        if ((left -= tiles) < 0) return true;
+        uint32_t y = static_cast<uint32_t>(a.row_tiles) - 1;  // of row tile 0
+        int at = it - static_cast<int>((y >> 2) % static_cast<uint32_t>(a.batch));   // the shifted item's place among the items
+        if (at < 0) at += a.batch;
+        for (int32_t rt = 0; rt < tiles; ++rt, --y) {
+            const int64_t keys = a.causal ? std::min((rt + 1) * static_cast<int64_t>(rows_per_block), rows) : a.kv_packed ? rows : a.kv_seq;
+            const int64_t cost = 3 + (keys + kBN - 1) / kBN;
+            put(plain, y, it, cost);
+            put(shifted, y, at, cost);
+            if ((y & 3) == 0 && ++at == a.batch) at = 0;
+        }
+    }
+    int64_t most[2] = {0, 0}, sum[2] = {0, 0};
+    for (uint32_t u = 0; u < kUnits; ++u) {
+        most[0] = std::max(most[0], sum[0] += plain[u]);
+        most[1] = std::max(most[1], sum[1] += shifted[u]);
+    }
+    return 20 * most[1] < 19 * most[0];
+}
+
 // The choice of a launch whose geometry with 8 wavefronts fits; `a` holds it.
 static bool takes_eight(const AttnArgs& a, int64_t per_rt, bool ragged)
 {
@@ -1296,6 +1341,7 @@ static int launch_mfma(AttnArgs& a, hipStream_t s)
     a.magic_head_blocks = magic(a.head_blocks);
     a.magic_kv_heads = magic(a.n_kv_heads);
     a.paired = !RAGGED && WAVES == 8 && choose_paired(a, per_rt, 32 * (WAVES / a.heads_per_block)) ? 1 : 0;   // (pairs assume one length)
+    if constexpr (RAGGED) a.item_shift = shift_items(a, per_rt, 32 * (WAVES / a.heads_per_block)) ? 1 : 0;
     const unsigned grid_y = static_cast<unsigned>(a.paired ? (a.row_tiles + 1) / 2 : a.row_tiles);
     constexpr size_t lds = T::LDS_BYTES;
     if (lds > 64 * 1024) {
@@ -1368,7 +1414,7 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
     a.batch = batch; a.seq = seq; a.kv_seq = kv_seq; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
     a.causal = causal ? 1 : 0;
     a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt(static_cast<float>(head_dim));
-    a.heads_per_block = 1; a.row_tiles = 0; a.pass_tiles = 0; a.paired = 0;
+    a.heads_per_block = 1; a.row_tiles = 0; a.pass_tiles = 0; a.paired = 0; a.item_shift = 0;
     a.group = n_q_heads / n_kv_heads; a.head_blocks = 0; a.hb_shift = 0; a.magic_head_blocks = 0; a.magic_kv_heads = 0;
     a.k_cache = k_cache; a.v_cache = v_cache; a.s_max = s_max; a.pos0 = pos0;
     a.q_cs = reinterpret_cast<const float2*>(q_cos_sin);
@@ -1413,6 +1459,26 @@ static int prefill_attn(const void* q, const void* k, const void* v, void* out, 
 }
 
 }  // namespace civic
+
+// For tests, on the host alone (no part of civic.h): whether a ragged launch of bf16 attention, of up to 64 items with rows
+// [offsets[i], offsets[i + 1]), shifts its items.  kv_seq > 0: over so many keys each; 0: over the item's own rows.
+extern "C" int civic_attn_item_shift(int32_t batch, const int32_t* offsets, int32_t kv_seq, int32_t n_q_heads, int32_t n_kv_heads,
+                                     int32_t head_dim, int32_t causal)
+{
+    using namespace civic;
+    if (batch <= 0 || batch > kRaggedItems || !offsets || n_kv_heads <= 0 || n_q_heads % n_kv_heads || head_dim > 128) return -1;
+    AttnArgs a = {};
+    a.batch = batch; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
+    a.causal = causal ? 1 : 0; a.kv_packed = kv_seq > 0 ? 0 : 1;
+    for (int32_t i = 0; i <= batch; ++i) a.item_row[i] = offsets[i];
+    for (int32_t i = 0; i < batch; ++i) a.seq = std::max(a.seq, offsets[i + 1] - offsets[i]);
+    a.kv_seq = kv_seq > 0 ? kv_seq : a.seq;
+    int64_t per_rt = 0;
+    if (!mfma_geometry<8>(a, &per_rt)) return -1;
+    const bool eight = takes_eight(a, per_rt, true);
+    if (!eight && !mfma_geometry<4>(a, &per_rt)) return -1;
+    return shift_items(a, per_rt, 32 * ((eight ? 8 : 4) / a.heads_per_block)) ? 1 : 0;
+}
 
 // For tests, on the host alone (no part of civic.h): how a launch of bf16 attention of these sizes, one length for all samples, is
 // taken.  4 or 8: wavefronts of a workgroup of the MFMA kernel; 9: of 8, with two row tiles each; 0: another kernel.

@@ -492,3 +492,24 @@ def test_decode_sizes_reach_the_workgroups_they_are_chosen_for(bd):
     assert {s[3] for s in wide if s[0] == 16} == {8, 16, 32, 64}
     assert {s[:3] for s in narrow if s[0] == 4} >= {(4, 1, 0), (4, 2, 0), (4, 4, 0), (4, 8, 0), (4, 4, 1)}
     assert {s[3] for s in narrow if s[0] == 4 and s[2] == 0} == {8, 16, 32, 64}
+
+
+@pytest.mark.parametrize("rows,keys,hq,hkv,d,shifted", [
+    # the row tiles of a long item on few units: every fourth begins with the next item
+    ((500, 61, 2700, 90, 1200, 333, 800, 60), 0, 16, 8, 128, 1), ((500, 61, 2700, 90, 1200, 333, 800, 60), 0, 16, 4, 128, 1),
+    ((938, 117, 117, 938, 500, 300, 200, 800), 0, 32, 8, 128, 1), ((1365, 341, 85, 1024, 600, 341, 1365, 85), 256, 16, 16, 72, 1),
+    # the plain order has them on units of their own
+    ((2000, 500, 200), 0, 16, 4, 128, 0), ((2000, 500, 200), 0, 36, 6, 64, 0), ((938, 117, 300, 650, 1500), 0, 28, 4, 64, 0),
+    ((179, 51, 660, 97, 693, 1420), 512, 16, 16, 64, 0), ((937, 177, 198, 221, 192, 489, 202), 0, 8, 8, 128, 0),
+    ((73, 28, 632, 75, 41, 141, 1103, 748), 256, 12, 12, 64, 0), ((1600, 1500, 1400, 1550), 512, 12, 12, 64, 0), ((400,) * 9, 0, 16, 8, 64, 0)])
+def test_ragged_attention_shifts_items_where_that_spreads_the_load(bd, rows, keys, hq, hkv, d, shifted):
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    assert bd.lib.civic_attn_item_shift(len(rows), off.ctypes.data_as(C.c_void_p), keys, hq, hkv, d, int(keys == 0)) == shifted
+
+
+def test_ragged_attention_sizes_reach_either_order_of_items(bd):
+    from test_gpu_kernel_edges import ITEM_ORDER
+    for rows, keys, hq, hkv, d, causal, shifted in ITEM_ORDER:
+        off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+        got = bd.lib.civic_attn_item_shift(len(rows), off.ctypes.data_as(C.c_void_p), keys, hq, hkv, d, int(causal))
+        assert got == int(shifted), (rows, keys, hq, hkv, d, got)

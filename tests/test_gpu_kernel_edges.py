@@ -772,3 +772,35 @@ def test_attention_heads_of_72_to_96(bd, head_dim, batch, n_q, n_kv, causal):
         z.masked_fill_(torch.ones(n_q, n_kv, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
     ref = torch.matmul(torch.softmax(z, -1), vv).transpose(1, 2)
     assert (out.double() - ref).abs().max().item() <= 2.0 ** -7 * ref.abs().max().item()
+
+
+ITEM_ORDER = [
+    # rows of the items, keys (0: the item's own), query and KV heads, head dim, causal, whether the items are shifted
+    ((700, 20, 33, 25, 20, 10, 30, 21), 0, 16, 4, 64, True, True), ((640, 33, 1, 5), 0, 32, 4, 128, True, True),
+    ((1200, 1, 1, 40), 0, 16, 8, 72, False, True), ((33, 900, 1, 257, 64, 31, 90, 140), 64, 16, 16, 80, False, True),
+    ((520, 257, 1), 0, 16, 4, 128, True, False), ((300, 1, 290, 40, 161), 0, 8, 2, 96, True, False), ((700, 85, 300), 128, 12, 12, 64, False, False)]
+
+
+@pytest.mark.parametrize("case", ITEM_ORDER)
+def test_ragged_attention_order_of_items(bd, case):
+    """Every row tile of every item once, in either order of the items (their shift by row tile also wraps around): the bits of a call
+    for each item alone, and the items' rows in the caches."""
+    rows, keys, q_heads, kv_heads, d, causal, _ = case
+    log("ragged order", *case)
+    g = torch.Generator(device="cuda").manual_seed(sum(rows) + d)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    kv_shape = (len(rows), keys, kv_heads, d) if keys else (int(off[-1]), kv_heads, d)
+    q = torch.randn((int(off[-1]), q_heads, d), generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn(kv_shape, generator=g, device="cuda").bfloat16() for _ in range(2))
+    out = torch.full_like(q, float("nan"))
+    if keys:
+        bd.civic_cross_attn_ragged(q, k, v, off, out=out)
+        alone = [bd.civic_cross_attn(q[a:b][None], k[i:i + 1], v[i:i + 1])[0] for i, (a, b) in enumerate(zip(off[:-1], off[1:]))]
+    else:
+        kc, vc = (torch.full((len(rows), kv_heads, max(rows) + 3, d), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        bd.civic_prefill_attn_ragged(q, k, v, off, causal, 0.0, kc, vc, 2, out=out)
+        alone = [bd.civic_prefill_attn(q[a:b][None], k[a:b][None], v[a:b][None], causal)[0] for a, b in zip(off[:-1], off[1:])]
+        for i, (a, b) in enumerate(zip(off[:-1], off[1:])):
+            for cache, x in ((kc, k), (vc, v)):
+                assert torch.equal(cache[i, :, 2:2 + rows[i]], x[a:b].transpose(0, 1)) and cache[i, :, 2 + rows[i]:].isnan().all()
+    assert torch.equal(out, torch.cat(alone))
