@@ -119,10 +119,6 @@ constexpr float kExpShift = 15.3f, kMaxDirectInvTau = 60.0f;
 // 2^-40 then; never at inv_tau <= 17, and above only for an anchor that every token points away from).
 constexpr float kMaxRowFactor = 1.0995116e12f;
 
-// Token weights by workgroups of the second product's launch, on units that its tiles leave idle: column j's sum over the rows i of
-// w(i, j) / sum_i, for `sum_chunks` times 64 columns.  The rows' factors first, from the partial sums as the tiles take them; then the
-// columns, in the order of col_sum_kernel (128 row slots, of which a thread has every 32nd here): the same bits as from that kernel.
-// (2 x 4096 tokens, 1365 anchors: a launch of 6.8 us behind the product's 33 on 198 units; here under it.)
 // Sum over the eight lanes 8 apart: x + x of lane ^ 8, ^ 16, ^ 32, one after the other (a sum does not depend on whose comes first).
 __device__ __forceinline__ float over_row_slots(float v)
 {
@@ -132,10 +128,17 @@ __device__ __forceinline__ float over_row_slots(float v)
     const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
-constexpr int kSumGroupRows = 24 * 1024;                      // (a multiple of 4) rows whose factors fit beside the rest of the LDS
+// Token weights by workgroups of the second product's launch, on units that its tiles leave idle: column j's sum over the rows i of
+// w(i, j) / sum_i, for `sum_chunks` times 64 columns.  The rows' factors first, from the partial sums as the tiles take them; then the
+// columns, in the order of col_sum_kernel (128 row slots, of which a thread has every 32nd here): the same bits as from that kernel.
+// (2 x 4096 tokens, 1365 anchors, 1152 wide: the product alone 33.5 us on 198 units and a launch of 6.8 behind it; together 37.4, since
+// each of 44 groups reads the partial sums of all rows of its item and their weights past the tiles.)
+constexpr int kSumGroupRows = 24 * 1024;                      // (a multiple of 4) rows whose factors are kept in LDS
+constexpr int kSumGroupParts = 16, kSumGroupCols = 64;
+constexpr size_t kSumGroupBytes = sizeof(float) * (kSumGroupRows + kSumGroupParts * kSumGroupCols);
 __device__ __forceinline__ void col_sum_group(const GemmArgs& g, uint32_t group, char* smem)
 {
-    constexpr int kVirtual = 16, kCols = 64, kSlots = 128, kMine = 4;
+    constexpr int kVirtual = kSumGroupParts, kCols = kSumGroupCols, kSlots = 128, kMine = 4;
     float* const inv = reinterpret_cast<float*>(smem);
     float* const part = inv + kSumGroupRows;                  // [kVirtual][kCols]
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
@@ -241,8 +244,10 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
     // that run is a compact block whose A row slabs and B column slabs are shared inside one L2 as the workgroups
     // advance along the contraction together.  With the plain (x, y) numbering every XCD touches every slab and the
     // kernel runs at the speed of the memory behind the L2s.
-    const uint32_t tile_blocks = gridDim.x - static_cast<uint32_t>(OUT == kOutRowNorm ? g.sum_groups : 0);
-    if constexpr (OUT == kOutRowNorm) {
+    constexpr bool kSums = OUT == kOutRowNorm && STAGES == 4;
+    const uint32_t tile_blocks = gridDim.x - static_cast<uint32_t>(kSums ? g.sum_groups : 0);
+    if constexpr (kSums) {
+        static_assert(kSumGroupBytes <= 2 * STAGES * kGemmTileBytes, "the factors and partial sums of the token weights fit the ring");
         if (blockIdx.x >= tile_blocks) { col_sum_group(g, blockIdx.x - tile_blocks, gemm_lds); return; }
     }
     const uint32_t per_xcd = tile_blocks >> 3;
@@ -576,7 +581,8 @@ __global__ __launch_bounds__(kGemmThreads, STAGES == 2 ? 2 : 1) void gemm_kernel
 template <int OUT, bool B_KROWS, int STAGES>
 static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s)
 {
-    const dim3 grid(blocks + static_cast<unsigned>(OUT == kOutRowNorm ? g.sum_groups : 0));
+    if (g.sum_groups != 0 && !(OUT == kOutRowNorm && STAGES == 4)) return CIVIC_ERR_UNSUPPORTED;   // (sums_fit asks for none there)
+    const dim3 grid(blocks + static_cast<unsigned>(g.sum_groups));
     constexpr size_t lds = 2 * STAGES * kGemmTileBytes;
     static_assert(lds >= 4 * 64 * (64 + 8) * 2 + 1024, "the ring holds the staged output tile and the row sums");
     static std::atomic<uint64_t> allowed{0};
@@ -586,14 +592,18 @@ static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s
     return check_launch();
 }
 
+// Output tiles from which on a launch has a second workgroup for every unit, or nearly, and takes the ring of two stages.
+constexpr int64_t kTwoStageTiles = 2 * 256;
+
 // Whether the token weights go into the second product's launch, and their share of it: its tiles run one to a unit and leave units
 // idle (in their only generation or in the second), and those are through with the columns when the tiles are with their rows, or
 // nearly so.  In us, as measured: 0.52 for 64 tokens of a tile, 60 KB of partial row sums and 50 of weights read by a unit.
 static bool sums_fit(GemmArgs* g, int64_t batch)
 {
     const int64_t total = batch * ((g->m + kGemmBM - 1) / kGemmBM) * ((g->n + kGemmBN - 1) / kGemmBN);
+    if (total >= kTwoStageTiles || g->m > kSumGroupRows) return false;   // (their LDS is that of four stages)
     const int64_t idle = (total <= 256 ? 256 : 512) - (total + 7) / 8 * 8, chunks = (g->kb_rows + 63) / 64;
-    if (idle <= 0 || g->m > kSumGroupRows) return false;
+    if (idle <= 0) return false;
     int64_t each = std::max<int64_t>((chunks * batch + idle - 1) / idle, 1);
     while ((chunks + each - 1) / each * batch > idle && each < chunks) ++each;
     const int64_t groups = (chunks + each - 1) / each * batch, rounds = (groups + idle - 1) / idle;
@@ -620,7 +630,7 @@ static int launch_gemm(const GemmArgs& g_in, int batch, hipStream_t s)
     while (static_cast<int64_t>(panel + 1) * (panel + 1) <= (total + 7) / 8) ++panel;
     g.panel = panel < g.tiles_n ? panel : g.tiles_n;
     // a grid that leaves compute units without a second workgroup takes the deeper ring
-    return total < 2 * 256 ? launch_gemm_variant<OUT, B_KROWS, 4>(g, grid, s) : launch_gemm_variant<OUT, B_KROWS, 2>(g, grid, s);
+    return total < kTwoStageTiles ? launch_gemm_variant<OUT, B_KROWS, 4>(g, grid, s) : launch_gemm_variant<OUT, B_KROWS, 2>(g, grid, s);
 }
 
 // ------------------------------------------------------------------------------------------ row kernels
@@ -1360,6 +1370,20 @@ extern "C" int civic_anchor_aggregate(const void* x0, const void* anchors, int d
     if (rc == CIVIC_OK && token_weight) rc = token_weights(nullptr);
     if (rc != CIVIC_OK) return rc;
     return launch_gemm<kOutBf16, true>(g2, batch, s);
+}
+
+// For tests, on the host alone (no part of civic.h): workgroups that make the token weights inside the second product's launch, and the
+// columns of each over 64 in *chunks; 0 where they are a launch of their own.
+extern "C" int civic_aggregate_sum_groups(int32_t batch, int32_t n_tokens, int32_t n_anchors, int32_t dim, int32_t* chunks)
+{
+    using namespace civic;
+    AggPlan p;
+    agg_plan(batch, n_tokens, n_anchors, dim, &p);
+    GemmArgs g = {};
+    g.m = n_anchors; g.n = dim; g.k = static_cast<int32_t>(p.t_pad); g.kb_rows = n_tokens; g.parts = static_cast<int32_t>(p.t_tile / kGemmBN * 2);
+    const bool with_sums = sums_fit(&g, batch);
+    if (chunks) *chunks = with_sums ? g.sum_chunks : 0;
+    return with_sums ? g.sum_groups : 0;
 }
 
 extern "C" size_t civic_kv_compress_workspace_bytes(int32_t batch, int32_t n_rows, int32_t n_mem, int32_t width)

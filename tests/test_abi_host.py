@@ -513,3 +513,18 @@ def test_ragged_attention_sizes_reach_either_order_of_items(bd):
         off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
         got = bd.lib.civic_attn_item_shift(len(rows), off.ctypes.data_as(C.c_void_p), keys, hq, hkv, d, int(causal))
         assert got == int(shifted), (rows, keys, hq, hkv, d, got)
+
+
+def test_token_weights_stay_out_of_launches_with_little_lds(bd):
+    """Token weights under the second product need the LDS of its four-stage ring: from 512 output tiles on it has two, and they are a
+    launch of their own, whatever else would speak for them; likewise more anchors than have a place for their factors."""
+    from test_gpu_kernel_edges import TOKEN_WEIGHTS
+    each = C.c_int32()
+    for batch, tokens, anchors, dim, chunks in TOKEN_WEIGHTS:
+        groups = bd.lib.civic_aggregate_sum_groups(batch, tokens, anchors, dim, C.byref(each))
+        assert each.value == chunks and groups == -(-(-(-tokens // 64)) // chunks) * batch
+    for batch in range(1, 600):
+        for anchors, dim in ((100, 128), (1365, 1152), (129, 768)):
+            groups = bd.lib.civic_aggregate_sum_groups(batch, 4096, anchors, dim, None)
+            assert groups == 0 or batch * -(-anchors // 128) * (dim // 128) < 512
+    assert bd.lib.civic_aggregate_sum_groups(1, 60000, 24 * 1024 + 1, 128, None) == 0

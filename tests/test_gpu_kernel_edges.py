@@ -1,5 +1,7 @@
 """Sizes at which a kernel's tiling or a rule of its dispatch can go wrong (edges of tiles, remainders, the smallest and the
 largest of a range), against the CPU oracle.  Every tolerance is derived beside its test."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -142,27 +144,36 @@ def test_anchor_aggregate_over_the_range_of_the_tokens(bd, tokens, anchors, dim,
     assert (np.abs(to_host(tw).astype(np.float64) - ref_tw) <= 2 * rel * np.maximum(ref_tw, 1.0)).all()
 
 
-@pytest.mark.parametrize("tokens,anchors", [(1, 1), (64, 5), (65, 127), (700, 129), (193, 767), (300, 768), (129, 769), (2500, 100), (130, 1665), (4100, 40)])
-def test_token_weights_under_the_second_product(bd, tokens, anchors):
-    """Token weights made by workgroups of the second product's launch (one item) and by a launch of their own (so many items that the
+# batch, tokens, anchors, dim, times 64 columns of a workgroup (0: a launch of their own)
+TOKEN_WEIGHTS = [(1, 1, 1, 128, 1), (1, 64, 5, 128, 1), (1, 65, 127, 128, 1), (1, 700, 129, 128, 1), (1, 193, 767, 128, 1), (1, 300, 768, 128, 1),
+                 (1, 129, 769, 128, 1), (1, 2500, 100, 128, 1), (1, 130, 1665, 128, 1), (1, 4100, 40, 128, 1), (2, 4096, 1365, 1152, 3),
+                 (4, 4100, 1000, 768, 5), (1, 20000, 700, 1152, 2)]
+
+
+@pytest.mark.parametrize("batch,tokens,anchors,dim,chunks", TOKEN_WEIGHTS)
+def test_token_weights_under_the_second_product(bd, batch, tokens, anchors, dim, chunks):
+    """Token weights made by workgroups of the second product's launch (a few items) and by a launch of their own (so many items that the
     product fills the chip twice): the same bits, and the sums of the weights of a 64-bit softmax.  Weights are rounded to bf16 (2^-9
     each, sums of them as rounded) and logits carry the rounding of the normalised anchors, 2^-9 of at most 14: 2^-5 covers them."""
-    log("token weights", tokens, anchors)
-    dim = 128
-    items = 512 // (-(-anchors // 128) * (dim // 128)) + 1
+    log("token weights", batch, tokens, anchors, dim)
+    items = 512 // (-(-anchors // 128) * (dim // 128)) // batch * batch + batch
+    each = C.c_int32()
+    assert bd.lib.civic_aggregate_sum_groups(batch, tokens, anchors, dim, C.byref(each)) > 0 and each.value == chunks
+    assert bd.lib.civic_aggregate_sum_groups(items, tokens, anchors, dim, None) == 0
     g = torch.Generator(device="cuda").manual_seed(tokens + anchors)
-    x0 = torch.randn((1, tokens, dim), generator=g, device="cuda").bfloat16()
+    x0 = torch.randn((batch, tokens, dim), generator=g, device="cuda").bfloat16()
     a = torch.randn((anchors, dim), generator=g, device="cuda").bfloat16()
     z1, w1 = bd.civic_anchor_aggregate(x0, a, 14.0, True)
-    zn, wn = bd.civic_anchor_aggregate(x0.expand(items, tokens, dim).contiguous(), a, 14.0, True)
-    assert torch.equal(zn[items - 1], z1[0]) and torch.equal(wn[items - 1], w1[0]) and torch.equal(wn[0], w1[0])
+    zn, wn = bd.civic_anchor_aggregate(x0.repeat(items // batch, 1, 1), a, 14.0, True)
+    assert torch.equal(zn[-batch:], z1) and torch.equal(wn[-batch:], w1) and torch.equal(wn[:batch], w1)
 
     def norm(x):
         x = x.double() - x.double().mean(-1, keepdim=True)
         return x / x.norm(dim=-1, keepdim=True)
 
-    ref = torch.softmax(14.0 * norm(a) @ norm(x0[0]).T.contiguous(), -1).sum(0)
-    assert (w1[0].double() - ref).abs().max().item() <= 2.0 ** -5 * ref.max().item()
+    for x, w in zip(x0, w1):
+        ref = torch.softmax(14.0 * norm(a) @ norm(x).T.contiguous(), -1).sum(0)
+        assert (w.double() - ref).abs().max().item() <= 2.0 ** -5 * ref.max().item()
 
 
 @pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 161])
