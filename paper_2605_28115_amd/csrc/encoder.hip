@@ -596,8 +596,12 @@ static int launch_gemm_variant(const GemmArgs& g, unsigned blocks, hipStream_t s
 constexpr int64_t kTwoStageTiles = 2 * 256;
 
 // Whether the token weights go into the second product's launch, and their share of it: its tiles run one to a unit and leave units
-// idle (in their only generation or in the second), and those are through with the columns when the tiles are with their rows, or
-// nearly so.  In us, as measured: 0.52 for 64 tokens of a tile, 60 KB of partial row sums and 50 of weights read by a unit.
+// idle (in their only generation or in the second), and those are through with the columns well before the tiles are with their rows:
+// a unit reads 60 KB of partial row sums and 50 of weights a microsecond by itself, a tile takes 0.52 for 64 tokens, beside each other
+// both take longer, and a launch of their own costs 4 before its work.  (us, so and as a launch of their own, and what is compared: 2 x 4096
+// tokens, 1365 anchors, 1152 wide 78.7, 80.4, 21 <= 27; 1 x 8192, 2730, 768 112.8, 119.5, 41 <= 47; 4 x 6144, 1536, 1152 215.4, 215.6,
+// 36 <= 37; but 1 x 8192, 2730, 1152 143.8, 139.8, 49 > 47; 3 x 12000, 1333, 768 232, 221, 67 > 65; 1 x 8086, 2695, 1280 160, 149, 56 > 46;
+// 2 x 6144, 3072, 1152 224, 217, 48 > 37.)
 static bool sums_fit(GemmArgs* g, int64_t batch)
 {
     const int64_t total = batch * ((g->m + kGemmBM - 1) / kGemmBM) * ((g->n + kGemmBN - 1) / kGemmBN);
@@ -608,7 +612,7 @@ static bool sums_fit(GemmArgs* g, int64_t batch)
     while ((chunks + each - 1) / each * batch > idle && each < chunks) ++each;
     const int64_t groups = (chunks + each - 1) / each * batch, rounds = (groups + idle - 1) / idle;
     const double rows = 1.5 + g->m * static_cast<double>(g->parts) * 4.0 / 60e3, columns = 1.0 + g->m * 128.0 / 50e3;
-    if (static_cast<double>(rounds) * (rows + static_cast<double>(each) * columns) > 0.52 * (g->k / 64) + 6.0) return false;
+    if (static_cast<double>(rounds) * (rows + static_cast<double>(each) * columns) > 0.31 * (g->k / 64) + 7.0) return false;
     g->sum_chunks = static_cast<int32_t>(each);
     g->sum_groups = static_cast<int32_t>(groups);
     return true;

@@ -528,3 +528,11 @@ def test_token_weights_stay_out_of_launches_with_little_lds(bd):
             groups = bd.lib.civic_aggregate_sum_groups(batch, 4096, anchors, dim, None)
             assert groups == 0 or batch * -(-anchors // 128) * (dim // 128) < 512
     assert bd.lib.civic_aggregate_sum_groups(1, 60000, 24 * 1024 + 1, 128, None) == 0
+
+
+@pytest.mark.parametrize("batch,tokens,anchors,dim,inside", [
+    (2, 4096, 1365, 1152, True), (2, 2048, 1365, 1152, True), (1, 8192, 2730, 768, True), (3, 12000, 1333, 1280, True), (4, 12000, 1333, 1152, True),
+    (1, 4096, 2730, 1152, False), (1, 8192, 2730, 1152, False), (1, 8086, 2695, 1280, False), (2, 6144, 3072, 1152, False),
+    (2, 6144, 4096, 768, False), (3, 8192, 4096, 128, False), (3, 12000, 1333, 768, False)])
+def test_token_weights_under_the_second_product_where_that_is_faster(bd, batch, tokens, anchors, dim, inside):
+    assert (bd.lib.civic_aggregate_sum_groups(batch, tokens, anchors, dim, None) > 0) == inside
