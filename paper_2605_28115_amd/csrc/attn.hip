@@ -1111,11 +1111,12 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
         }
         __bf16* ob = static_cast<__bf16*>(a.out) + o_first + h * a.os[2];
         if (kWave % CPR == 0 && e_row0 + 32 <= seq && a.head_dim == DP) {
-            // whole tile, unpadded head: the lane keeps its column, rows advance by 64 / CPR per store.  The stores are non-temporal, as are
-            // those into the caches: lines that stay behind dirty are written back under the next launches' loads (4 x 938 rows, 32 / 8
-            // heads of 128 with the scores and the merge in front 72.0 -> 67.5 us where inputs change from pass to pass; with an
-            // elementwise pass or a product that reads the output right behind, the same within 1 %).  Not for rows that end inside
-            // a line of 128 bytes (heads of 72: two grids of 64 x 64 54.3 -> 55.9).
+            // whole tile, unpadded head: the lane keeps its column, rows advance by 64 / CPR per store.  The stores are non-temporal: next a
+            // model runs a product over these rows, which takes no longer for it (path, a layer norm over the merged rows and that product,
+            // 4 x 938 rows, 32 / 8 heads of 128 260.0 -> 257.5 us, 8 x 938 455 -> 452, 16 frames 324 -> 323; a layer norm over the output instead
+            // 104.5 -> 105.9), and the path alone is faster where inputs change from pass to pass (72.4 -> 70.5, 153 -> 151).  Non-temporal
+            // stores into the caches changed nothing (72.4).  Not for rows that end inside a line of 128 bytes (heads of 72: two grids of
+            // 64 x 64 54.3 -> 55.9).
             constexpr int RPI = kWave / CPR > 0 ? kWave / CPR : 1;
             const int r0 = lane_late / CPR, dc = lane_late - r0 * CPR;
             __bf16* dst = ob + static_cast<int64_t>(e_row0 + r0) * a.os[1] + dc * 8;
@@ -1138,17 +1139,11 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
             __bf16* const kc = static_cast<__bf16*>(a.k_cache);
             __bf16* const vc = static_cast<__bf16*>(a.v_cache);
             const int64_t d0 = kv_dst_off(kv_r);
-            const bool whole_lines = a.head_dim % 64 == 0;
 #pragma unroll
             for (int j = 0; j < kKvJ; ++j)
                 if (kv_r < kv_rows && kv_c + 8 * j < kv_cpr) {
-                    if (whole_lines) {
-                        store_streaming(reinterpret_cast<u32x4*>(kc + d0 + 64 * j), kv_piece[2 * j]);
-                        store_streaming(reinterpret_cast<u32x4*>(vc + d0 + 64 * j), kv_piece[2 * j + 1]);
-                    } else {
-                        *reinterpret_cast<u32x4*>(kc + d0 + 64 * j) = kv_piece[2 * j];
-                        *reinterpret_cast<u32x4*>(vc + d0 + 64 * j) = kv_piece[2 * j + 1];
-                    }
+                    *reinterpret_cast<u32x4*>(kc + d0 + 64 * j) = kv_piece[2 * j];
+                    *reinterpret_cast<u32x4*>(vc + d0 + 64 * j) = kv_piece[2 * j + 1];
                 }
             for (int r = kv_r + kKvRows; r < kv_rows; r += kKvRows) {   // taller blocks (fewer than 4 heads per block)
                 const int64_t so = kv_src_off(r), dd = kv_dst_off(r);
