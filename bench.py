@@ -433,7 +433,7 @@ def main() -> int:
 
     decode = None
     if not args.path_only and (w.n_kv_heads != w.n_q_heads or w.causal):   # the encoder-side workload keeps no cache
-        decode = {"kernel": "decode_partial_kernel + decode_merge_kernel (civic_decode_attn)", "bound": "hbm",
+        decode = {"kernel": "civic_decode_attn, one launch or two (decode_mfma_kernel or decode_partial_kernel, decode_merge_kernel)", "bound": "hbm",
                   "unit": "GB/s", "peak": HBM_PEAK_GBS, "workload": decode_figures(w.batch), "batch_64": decode_figures(64)}
 
     # Rotary embedding from the carried ids: the table once per prompt; per layer K rotated on its way into the

@@ -340,8 +340,10 @@ __global__ __launch_bounds__(kF32Waves * kWave, NT <= 3 ? 2 : 1) void attn_f32_k
 // 188 -> 130 us, 1 x 1500, 8 of 96 85 -> 68; the row tiles innermost brought all K and V to every XCD).
 // Under the causal mask row tiles go out by falling weight.  Up to four workgroups to a unit they go in passes of one workgroup to a
 // unit, every other pass in reverse, so that the unit with the heaviest first takes the lightest second: all start at once or nearly
-// so, and nothing evens out the units later (1 x 469, 16 / 8 heads of 128 23.5 -> 20.9 us, 1 x 1024, 8 / 8 40.0 -> 31.8, 1 x 700, 16 / 8
-// 38.4 -> 33.9).  More workgroups than that even out by themselves (4 x 200, 32 / 8 33.7 and 34.3 in passes, 8 x 117, 16 / 8 19.3, 19.9).
+// so, and nothing evens out the units later (1 x 469, 16 / 8 heads of 128 23.1 -> 20.7 us, 1 x 1024, 8 / 8 40.0 -> 31.8, 1 x 700, 16 / 8
+// 38.4 -> 33.9).  Around four to a unit either order may be the faster, in passes 2 % on average over 140 sizes (without and in them:
+// 2 x 1050, 4 / 2 of 96 42.2, 36.3, 4 x 450, 8 / 8 of 64 19.6, 18.5, 8 x 128, 16 / 8 19.8, 19.2, but 8 x 117 18.9, 19.6, and the worst
+// 4 x 200, 16 / 8 20.0, 21.1).  More workgroups than that even out by themselves (4 x 200, 32 / 8 33.7 and 34.3 in passes).
 static dim3 f32_grid(AttnArgs& a)
 {
     constexpr int64_t kUnits = 256;                            // compute units
@@ -1243,15 +1245,18 @@ static bool choose_paired(const AttnArgs& a, int64_t per_rt, int rows_per_block)
 // end of a launch; those of 8 bring half as many K/V tiles into LDS and can pair causal row tiles.  8 is faster only for long rows of
 // keys where its workgroups fill the units (us, 8 and 4 wavefronts; bf16 heads of 128 unless said):
 //   - up to 128 workgroups of 8: 4.  1 x 469 rows causal, 16 / 8 heads 14.9, 11.2; 3 x 550, 16 / 8 17.9, 13.7
-//   - no mask, one generation of 8: 8 from 8 key tiles on.  2 x 1365, 16 / 16 of 72 33.1, 35.2; three items of 700 to 1100 rows over
-//     512 keys, 16 / 16 of 72 15.9, 16.6; but two of 656 and 1637 rows over 64 keys, 16 / 16 7.9, 7.4
+//   - no mask, one generation of 8: 8 from 8 key tiles on.  2 x 2048 over 512 and 4096 keys, 16 / 16 of 72 19.3, 20.5 and 98, 102; 1 x 4096
+//     98, 102; 2 x 1365 over 4096 85, 87, over its own 35.9, 34.8; three items of 700 to 1100 rows over 512 keys 17.6, 17.6; but two
+//     of 656 and 1637 rows over 64 keys, 16 / 16 7.9, 7.4
 //   - no mask, more: 8 for wide heads from 24 key tiles on where the last generation is full.  8 x 4096, 32 / 8 1986, 2077; 3 x 2323,
-//     16 / 8 138, 143; but 4 x 1618, 32 / 8 192, 182; eight items of 85 to 1365 rows over 256 keys, 16 / 16 of 72 23.3, 21.2;
-//     2 x 4096, 16 / 16 of 64 152, 144
+//     16 / 8 138, 143; 2 x 4096, 16 / 16 of 72 191, 197, but over 1024 keys 60.1, 58.4; 4 x 1618, 32 / 8 192, 182; eight items of 85 to
+//     1365 rows over 256 keys, 16 / 16 of 72 23.3, 18.3; 2 x 4096, 16 / 16 of 64 152, 144
 //   - causal: 8 for heads wider than 64 where pairs of row tiles fill their generations.  4 x 938, 32 / 8 38.5, 40.0; 1 x 3584, 32 / 8 105.5,
-//     109.6; but 4 x 600, 32 / 8 22.8, 21.1; 8 x 900, 16 / 16 of 64 30.0, 26.8
+//     109.6, of 72 84.0, 86.6; 8 x 900, 16 / 16 of 72 49.8, 51.0; but 4 x 600, 32 / 8 22.8, 21.1; 8 x 3000, 32 / 8 of 72 441, 429; 8 x 900,
+//     16 / 16 of 64 30.0, 26.8
 //   - causal, not paired (items of different length never are): 8 beyond 44 key tiles and one generation.  Eight items of 3000 rows,
-//     28 / 4 544, 615 and 32 / 8 563, 573; but eight of 101 to 938, 32 / 8 39.8, 35.9; four of 300 to 2700, 32 / 8 178, 169
+//     28 / 4 544, 615 and 32 / 8 563, 573, of 72 433, 444, but 32 / 8 of 96 482, 457; eight of 101 to 938, 32 / 8 39.8, 35.9; four of 300
+//     to 2700, 32 / 8 178, 169
 static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
 {
     if (a.causal && a.head_dim <= 64) return false;           // (before the model of a launch that is not taken)

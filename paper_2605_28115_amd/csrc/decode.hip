@@ -108,11 +108,13 @@ template <int LPR> __device__ __forceinline__ float slots_max(float v) { return 
 
 // States of the vector kernel's workgroup that meet in LDS: one per wavefront where a wavefront holds 8 row slots, one per slot
 // elsewhere.  Sums in registers take two lane swaps a value and halving of the slots, LDS one round trip a slot (21 x 16 rows, 8 / 8
-// bf16 heads of 64, 8 slots: 3.7 us in registers, 4.1 in LDS; 85 x 23 rows, 28 / 4 fp32 heads of 64, 4 slots: 7.7 and 6.9).
+// bf16 heads of 64, 8 slots: 3.7 us in registers, 4.1 in LDS; 85 x 23 rows, 28 / 4 fp32 heads of 64, 4 slots: 7.7 and 6.9).  Wide
+// workgroups always meet in registers first: their slots would take up to 133 KB of LDS (8 wavefronts, 8 fp32 heads of 128).
 constexpr int decode_states(int lpr, int waves) { return lpr == 8 || waves > kDecWaves ? waves : waves * (kWave / lpr); }
 
-// WAVES: wavefronts of a workgroup (kDecWaves, or what decode_plan calls wide)
-// A workgroup's place: block of query heads, KV head, sample, split.
+// A workgroup's place: block of query heads, KV head, sample, split (decode_grid has the orders).  Passes over the same rows and the
+// workgroups of a group's query heads lie n_kv_heads times the splits apart: on one XCD where that is a multiple of 8.  (Next to each other
+// they are on different ones: 40 of 500..1500 rows, 28 / 4 fp32 heads 55 us so, 66 then; 8 x 400, 32 / 8 one workgroup a query head 7.6, 9.9.)
 struct DecodePlace { int hb, g, b, split; };
 template <bool RAGGED>
 __device__ __forceinline__ DecodePlace decode_place(const DecodeArgs& a)
@@ -130,6 +132,7 @@ __device__ __forceinline__ DecodePlace decode_place(const DecodeArgs& a)
     return p;
 }
 
+// WAVES: wavefronts of a workgroup (kDecWaves, or a wide one's)
 template <bool BF16, int HG, int LPR, int WAVES, typename TABLE>
 __global__ __launch_bounds__(WAVES * kWave) void decode_partial_kernel(DecodeArgs a, TABLE t)
 {
