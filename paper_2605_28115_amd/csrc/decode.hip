@@ -687,13 +687,14 @@ static bool wide_full_pays(const DecodePlan& p, int64_t units, int64_t n_ctx, in
     return units >= 200 || n_ctx <= (p.hg > 4 ? 800 : p.head_blocks == 1 ? 1500 : 700);
 }
 
-// Workgroups of one query head each read their KV head's rows as often as there are heads.  A group's workgroups lie n_kv_heads apart in
-// the grid, so they are on one XCD, and all but the first read from its L2, only where n_kv_heads is a multiple of 8; else every
-// XCD of the 8 / gcd(n_kv_heads, 8) that have some of them fetches the rows, and above a number of bytes that costs more than a launch
-// saves (us, first for caches that the passes find in the last-level cache, then for such as they do not; cut and so: 16 x 300 rows, 16 / 1
-// bf16 heads 10.1 / 10.5, 8.4 / 10.0, 8 x 512, 8 / 1 9.2 / 9.5, 8.8 / 11.0, but 16 x 420 9.8 / 10.5, 8.9 / 11.7 and 32 x 300, 8 / 1 9.4 / 9.6, 9.8 / 12.0; in fp32 16 x 270, 16 / 4
-// 11.8 / 12.7, 9.4 / 11.2, but 16 x 384 12.0 / 13.4, 12.4 / 13.8 and 64 x 270, 4 / 1 11.9 / 12.7, 12.9 / 15.6; samples of different
-// length, which take longer cut: 16 of 100..500, 16 / 1 12.3 / 13.1, 10.1 / 11.8, but of 500..768 12.3 / 13.3, 14.0 / 15.7, and 8 of 500..768, 32 / 4 10.2 / 10.5, 10.8 / 12.2).
+// Workgroups of one query head each read their KV head's rows as often as there are heads.  A group's workgroups lie n_kv_heads apart
+// in the grid, so they are on one XCD, and all but the first read from its L2, only where n_kv_heads is a multiple of 8; else every XCD
+// of the 8 / gcd(n_kv_heads, 8) that have some of them fetches the rows, and above a number of bytes that costs more than a launch
+// saves (us, first for caches that the passes find in the last-level cache, then for such as they do not; cut and so: 16 x 300 rows, 16
+// / 1 bf16 heads 10.1 / 10.5, 8.4 / 10.0, 8 x 512, 8 / 1 9.2 / 9.5, 8.8 / 11.0, but 16 x 420 9.8 / 10.5, 8.9 / 11.7 and 32 x 300, 8 / 1
+// 9.4 / 9.6, 9.8 / 12.0; in fp32 16 x 270, 16 / 4 11.8 / 12.7, 9.4 / 11.2, but 16 x 384 12.0 / 13.4, 12.4 / 13.8 and 64 x 270, 4 / 1
+// 11.9 / 12.7, 12.9 / 15.6; samples of different length, which take longer cut: 16 of 100..500, 16 / 1 12.3 / 13.1, 10.1 / 11.8, but of
+// 500..768 12.3 / 13.3, 14.0 / 15.7, and 8 of 500..768, 32 / 4 10.2 / 10.5, 10.8 / 12.2).
 static bool wide_heads_pay(const DecodePlan& p, int64_t rows) { return p.wide_heads && rows * p.heads_row_bytes <= p.heads_most; }
 
 static void go_wide(DecodePlan* p, bool heads, int32_t longest, int32_t head_dim, int group)
