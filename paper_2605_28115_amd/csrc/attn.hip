@@ -1116,9 +1116,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
             // whole tile, unpadded head: the lane keeps its column, rows advance by 64 / CPR per store.  The stores are non-temporal: next a
             // model runs a product over these rows, which takes no longer for it (path, a layer norm over the merged rows and that product,
             // 4 x 938 rows, 32 / 8 heads of 128 260.0 -> 257.5 us, 8 x 938 455 -> 452, 16 frames 324 -> 323; a layer norm over the output instead
-            // 104.5 -> 105.9), and the path alone is faster where inputs change from pass to pass (72.4 -> 70.5, 153 -> 151).  Non-temporal
-            // stores into the caches changed nothing (72.4).  Not for rows that end inside a line of 128 bytes (heads of 72: two grids of
-            // 64 x 64 54.3 -> 55.9).
+            // 104.5 -> 105.9), and the path alone is faster where inputs change from pass to pass (72.4 -> 70.5, 153 -> 151).  Not for rows
+            // that end inside a line of 128 bytes (heads of 72: two grids of 64 x 64 54.3 -> 55.9).
             constexpr int RPI = kWave / CPR > 0 ? kWave / CPR : 1;
             const int r0 = lane_late / CPR, dc = lane_late - r0 * CPR;
             __bf16* dst = ob + static_cast<int64_t>(e_row0 + r0) * a.os[1] + dc * 8;
@@ -1141,19 +1140,26 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void attn_mfma_kernel(AttnArgs a)
             __bf16* const kc = static_cast<__bf16*>(a.k_cache);
             __bf16* const vc = static_cast<__bf16*>(a.v_cache);
             const int64_t d0 = kv_dst_off(kv_r);
+            // (whole lines non-temporally: the caches are read in a later step.  Path alone and with the layer norm and the product,
+            // inputs that change: 4 x 938 rows 70.6 -> 69.8, 256.8 -> 255.7 us, eight ragged prompts 73.2 -> 71.5, 247.5 -> 246.2)
+            const bool whole_lines = a.head_dim % 64 == 0;
+            auto put = [&](__bf16* p, const u32x4& x) {
+                if (whole_lines) store_streaming(reinterpret_cast<u32x4*>(p), x);
+                else *reinterpret_cast<u32x4*>(p) = x;
+            };
 #pragma unroll
             for (int j = 0; j < kKvJ; ++j)
                 if (kv_r < kv_rows && kv_c + 8 * j < kv_cpr) {
-                    *reinterpret_cast<u32x4*>(kc + d0 + 64 * j) = kv_piece[2 * j];
-                    *reinterpret_cast<u32x4*>(vc + d0 + 64 * j) = kv_piece[2 * j + 1];
+                    put(kc + d0 + 64 * j, kv_piece[2 * j]);
+                    put(vc + d0 + 64 * j, kv_piece[2 * j + 1]);
                 }
             for (int r = kv_r + kKvRows; r < kv_rows; r += kKvRows) {   // taller blocks (fewer than 4 heads per block)
                 const int64_t so = kv_src_off(r), dd = kv_dst_off(r);
 #pragma unroll
                 for (int j = 0; j < kKvJ; ++j)
                     if (kv_c + 8 * j < kv_cpr) {
-                        *reinterpret_cast<u32x4*>(kc + dd + 64 * j) = *reinterpret_cast<const u32x4*>(kp + so + 64 * j);
-                        *reinterpret_cast<u32x4*>(vc + dd + 64 * j) = *reinterpret_cast<const u32x4*>(vp + so + 64 * j);
+                        put(kc + dd + 64 * j, *reinterpret_cast<const u32x4*>(kp + so + 64 * j));
+                        put(vc + dd + 64 * j, *reinterpret_cast<const u32x4*>(vp + so + 64 * j));
                     }
             }
         }
