@@ -1287,14 +1287,15 @@ static bool eight_wavefronts(const AttnArgs& a, int64_t per_rt, bool ragged)
 // in the grid, and as the hardware hands workgroup n to unit n mod 256 (to XCD n mod 8, to the XCD's 32 units in turn), the row tiles of
 // a long item, a fixed number of workgroups apart, may meet on a few units again and again, several of the heaviest to a unit.  Shifted
 // items spread them then, and bring them together where the plain order has them on units of their own.  So both orders' loads of the
-// 256 units are counted, 3 for a workgroup and 1 for a key tile, and the items are shifted if that makes the largest load smaller.
+// 256 units are counted, 3 for a workgroup and 1 for a key tile, and the items are shifted if that makes the largest load smaller, or an
+// XCD's by 8 % and a unit's by no more than a fifth larger (24 items, 12 / 3 44, 39; 294, 1197, 384 and 157 rows, 16 / 4 of 72 25.2, 24.0).
 // (us, plain and shifted, and the ratio of the largest loads; heads of 128 unless said: eight items of 60..2700 rows, 16 / 8 105, 63, 0.25,
 // 16 / 4 169, 60, 0.40, 8 / 2 90, 49, 0.62; eight of 117 to 938, 32 / 8 52, 40, 0.66; eight of 85 to 1365 over 256 keys, 16 / 16 of 72 19.9, 18.6, 0.67;
 // but items of 2000, 500 and 200, 16 / 4 38.7, 43.5, 2.08, 36 / 6 of 64 39, 49, 1.39; five of 117..1500, 28 / 4 of 64 31.6, 36.8, 1.66; eight of
 // 60..2700, 12 / 3 of 64 49, 60, 1.98; four of 1400..1600 over 512 keys, 12 / 12 of 64 18.0, 19.2, 1.00: K and V change their XCD.)
 static bool shift_items(const AttnArgs& a, int64_t per_rt, int rows_per_block)
 {
-    if (a.row_tiles <= 4) return false;
+    if (a.row_tiles <= 4 || per_rt * a.row_tiles <= kComputeUnits) return false;   // (nothing to shift; a unit for every workgroup)
     constexpr uint32_t kUnits = kComputeUnits, kMask = kUnits - 1;
     static_assert((kUnits & kMask) == 0, "unit numbers are taken by a mask");
     const uint32_t per_item = static_cast<uint32_t>(per_rt / a.batch);
@@ -1321,12 +1322,15 @@ static bool shift_items(const AttnArgs& a, int64_t per_rt, int rows_per_block)
             if ((y & 3) == 0 && ++at == a.batch) at = 0;
         }
     }
-    int64_t most[2] = {0, 0}, sum[2] = {0, 0};
+    int64_t most[2] = {0, 0}, sum[2] = {0, 0}, xcd[2][8] = {};
     for (uint32_t u = 0; u < kUnits; ++u) {
         most[0] = std::max(most[0], sum[0] += plain[u]);
         most[1] = std::max(most[1], sum[1] += shifted[u]);
+        xcd[0][u & 7] += sum[0];
+        xcd[1][u & 7] += sum[1];
     }
-    return 20 * most[1] < 19 * most[0];
+    const int64_t xcd0 = *std::max_element(xcd[0], xcd[0] + 8), xcd1 = *std::max_element(xcd[1], xcd[1] + 8);
+    return most[1] < most[0] || (5 * most[1] <= 6 * most[0] && 100 * xcd1 <= 92 * xcd0);
 }
 
 // The choice of a launch whose geometry with 8 wavefronts fits; `a` holds it.

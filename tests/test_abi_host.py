@@ -498,6 +498,9 @@ def test_decode_sizes_reach_the_workgroups_they_are_chosen_for(bd):
     # the row tiles of a long item on few units: every fourth begins with the next item
     ((500, 61, 2700, 90, 1200, 333, 800, 60), 0, 16, 8, 128, 1), ((500, 61, 2700, 90, 1200, 333, 800, 60), 0, 16, 4, 128, 1),
     ((938, 117, 117, 938, 500, 300, 200, 800), 0, 32, 8, 128, 1), ((1365, 341, 85, 1024, 600, 341, 1365, 85), 256, 16, 16, 72, 1),
+    # few heads and items of different length on some XCDs only
+    ((294, 1197, 384, 157), 0, 16, 4, 72, 1), ((1732, 1357, 1609, 173), 0, 16, 16, 128, 1),
+    ((1242, 274, 1044, 337, 202, 822, 1295, 133, 502, 536, 180, 271, 147, 174, 199, 507, 584, 173, 103, 243, 628, 165, 233, 173), 0, 12, 3, 128, 1),
     # the plain order has them on units of their own
     ((2000, 500, 200), 0, 16, 4, 128, 0), ((2000, 500, 200), 0, 36, 6, 64, 0), ((938, 117, 300, 650, 1500), 0, 28, 4, 64, 0),
     ((179, 51, 660, 97, 693, 1420), 512, 16, 16, 64, 0), ((937, 177, 198, 221, 192, 489, 202), 0, 8, 8, 128, 0),
