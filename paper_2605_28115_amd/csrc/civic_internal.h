@@ -112,6 +112,13 @@ template <typename T>
 __device__ __forceinline__ T load_streaming(const T* p) { return __builtin_nontemporal_load(p); }
 template <typename T>
 __device__ __forceinline__ void store_streaming(T* p, const T& v) { __builtin_nontemporal_store(v, p); }
+// 16 bytes, written through the XCD's L2 at once and kept in the last-level cache: nothing is left to write back when the launch ends,
+// and who reads them next finds them there.  (The compiler counts no wait states out of an asm statement: a vector instruction may
+// overwrite the data of such a store one state later.)
+__device__ __forceinline__ void store_through(u32x4* p, const u32x4& v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+}
 
 // Sum over the 64 lanes of a wavefront, returned in every lane.  Data-parallel-primitive (DPP) adds:
 // an inclusive scan inside each row of 16 lanes (row_shr 1, 2, 4, 8), then the row totals are carried

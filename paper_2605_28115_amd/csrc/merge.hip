@@ -230,13 +230,14 @@ __global__ __launch_bounds__(T, T / 128) void merge_kernel(MergeArgs<MAP>)
                 const int32_t r = div_magic(i, t.magic_vpr), c = i - r * t.vpr;
                 val[u] = load_streaming(in + static_cast<int64_t>(source(r)) * t.vpr + c);
             }
-            // (Cached stores: a model normalises these rows next.  Non-temporal ones made the path alone 2 to 8 % faster where inputs change
-            // from pass to pass, and the path with a layer norm over the rows and a product over the attention's output 1 to 3 % slower:
-            // 4 x 938 rows, 4096 wide, 253.9 -> 258.0 us, 16 / 8 heads 130.2 -> 133.6.)
+            // (A model normalises these rows next.  us for the path alone, and with a layer norm over the rows and a product over the
+            // attention's output, inputs that change from pass to pass; stores cached, non-temporal and written through: 4 x 938 rows of 4096
+            // 71.1, 68.7, 69.9 and 257.8, 259.0, 257.3; eight ragged prompts 73.4, 71.6, 72.0 and 248.0, 251.2, 246.2; heads of 64 55.0, 55.0,
+            // 53.8 and 134.1, 135.7, 131.7; 16 / 8 heads 63.5, 58.1, 62.4 and 137.1, 138.7, 135.8.)
 #pragma unroll
             for (int u = 0; u < kMergeUnroll; ++u) {
                 const int32_t i = i0 + u * kSelThreads + tid;
-                if (i < n_vec) out[i + (i >= split_vec ? gap_vec : 0)] = val[u];
+                if (i < n_vec) store_through(out + i + (i >= split_vec ? gap_vec : 0), val[u]);
             }
         }
         auto put_ids = [&](int32_t r, int32_t src, const int32_t (&p)[3]) {

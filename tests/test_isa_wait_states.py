@@ -1,4 +1,4 @@
-"""Wait states around the loads into LDS that the kernels issue from inline assembly, looked up in the built library's own code.
+"""Wait states around the memory instructions that the kernels issue from inline assembly, looked up in the built library's own code.
 
 A vector memory instruction reads a scalar register five wait states after a vector instruction (v_readfirstlane, v_readlane of a
 spilled register) wrote it at the earliest.  The compiler sees to that for its own instructions and not inside an asm statement, so
@@ -66,14 +66,19 @@ def states_before(code, index, before):
     return best
 
 
-@pytest.mark.skipif(OBJDUMP is None, reason="no llvm-objdump")
-def test_loads_into_lds_wait_for_their_base(tmp_path):
+def listings(tmp_path):
+    """The disassembly of every code object of the built library."""
     lib = tmp_path / "lib.so"
     shutil.copy(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_28115_amd", "libcivic.so"), lib)
     subprocess.run([OBJDUMP, "--offloading", lib.name], cwd=tmp_path, check=True, stdout=subprocess.DEVNULL)
-    loads = 0
     for obj in sorted(tmp_path.glob("*gfx950*")):
-        listing = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(obj)], check=True, stdout=subprocess.PIPE, text=True).stdout
+        yield subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(obj)], check=True, stdout=subprocess.PIPE, text=True).stdout
+
+
+@pytest.mark.skipif(OBJDUMP is None, reason="no llvm-objdump")
+def test_loads_into_lds_wait_for_their_base(tmp_path):
+    loads = 0
+    for listing in listings(tmp_path):
         if LOAD not in listing:
             continue
         for name, code in functions(listing):
@@ -88,3 +93,16 @@ def test_loads_into_lds_wait_for_their_base(tmp_path):
                     loads += 1
                     assert states_before(code, i, before) >= STATES, (name, i)
     assert loads > 100                                        # the listings were read
+
+
+@pytest.mark.skipif(OBJDUMP is None, reason="no llvm-objdump")
+def test_written_through_stores_keep_their_data_for_a_state(tmp_path):
+    """A store of more than 8 bytes reads its data a wait state after it was issued; those written in assembly wait it out themselves."""
+    stores = 0
+    for listing in listings(tmp_path):
+        for name, code in functions(listing) if "sc1" in listing else ():
+            for (op, args, _), (after, _, _) in zip(code, code[1:]):
+                if op == "global_store_dwordx4" and any("sc1" in a for a in args):
+                    stores += 1
+                    assert after == "s_nop", name
+    assert stores >= 10                                       # the merged rows
